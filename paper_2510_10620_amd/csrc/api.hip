@@ -74,7 +74,7 @@ static dcp_status_t check_tensor(const char* name, const void* p, int64_t st, in
 static dcp_status_t pick_impl(const dcp_tensors_t* t, bool* use_mfma) {
   const bool m_ok = mfma_supports(t->dtype, t->d), s_ok = scalar_supports(t->d);
   if (t->impl == DCP_IMPL_MFMA) {
-    if (!m_ok) return fail(DCP_ERR_UNSUPPORTED, "MFMA kernels cover bf16 with head_dim 128 only");
+    if (!m_ok) return fail(DCP_ERR_UNSUPPORTED, "MFMA kernels cover bf16 with head_dim 128 and fp32 with head_dim 32, 64, 128");
     *use_mfma = true;
   } else if (t->impl == DCP_IMPL_SCALAR) {
     if (!s_ok) return fail(DCP_ERR_UNSUPPORTED, "scalar kernels cover head_dim 32, 64, 128");
@@ -101,7 +101,7 @@ static KTensors pack(const dcp_plan_t* plan, const dcp_tensors_t* t) {
   k.do_st = t->do_stride_t; k.do_sh = t->do_stride_h; k.dq_st = t->dq_stride_t; k.dq_sh = t->dq_stride_h;
   k.dk_st = t->dk_stride_t; k.dk_sh = t->dk_stride_h; k.dv_st = t->dv_stride_t; k.dv_sh = t->dv_stride_h;
   k.q_rows = plan->q_rows;
-  k.hq = t->hq; k.hkv = t->hkv; k.d = t->d; k.block_size = plan->block_size;
+  k.hq = t->hq; k.hkv = t->hkv; k.d = t->d; k.dtype = t->dtype; k.block_size = plan->block_size;
   k.scale = t->softmax_scale;
   k.use_slots = plan->use_slots ? 1 : 0;
   return k;
@@ -125,7 +125,7 @@ extern "C" dcp_status_t dcp_plan_prepare(dcp_plan_t* plan, int32_t hq, int32_t h
   const int n_seg = use_mfma ? xcd_segments(hkv) : 1;
   if ((st = plan->group_for(0, use_mfma ? mfma_fwd_tile() : scalar_fwd_tile(), s, &g, 0, true, n_seg)) != DCP_OK) return st;
   if ((st = plan->group_for(1, use_mfma ? mfma_dq_tile() : scalar_bwd_tile(), s, &g, 0, true, n_seg)) != DCP_OK) return st;
-  return plan->group_for(2, use_mfma ? mfma_dkv_tile() : scalar_bwd_tile(), s, &g, use_mfma ? hkv : 0, true, n_seg);
+  return plan->group_for(2, use_mfma ? mfma_dkv_tile() : scalar_bwd_tile(), s, &g, use_mfma && mfma_splits_dkv(dtype, d) ? hkv : 0, true, n_seg);
 }
 
 extern "C" dcp_status_t dcp_block_attn_fwd(dcp_plan_t* plan, const dcp_tensors_t* t, void* stream) {
@@ -199,7 +199,7 @@ static BwdWorkspace bwd_workspace(dcp_plan_t* plan, int32_t hq, int32_t hkv, int
   // range-bound summaries of every 32-row tile (+1 spare entry), only for tables with RANGES or WINDOW rows
   w.n_bounds = (plan->has_ranges || plan->has_window) ? ((size_t)plan->blk_t32.back() + 1) * 8 * sizeof(int32_t) : 0;
   w.n_bounds = (w.n_bounds + 255) & ~(size_t)255;
-  if (hkv > 0 && mfma_supports(dtype, d)) w.n_part = mfma_dkv_part_bytes(plan->host_items(2, mfma_dkv_tile(), hkv, xcd_segments(hkv)).n_pslots, hkv);
+  if (hkv > 0 && mfma_splits_dkv(dtype, d)) w.n_part = mfma_dkv_part_bytes(plan->host_items(2, mfma_dkv_tile(), hkv, xcd_segments(hkv)).n_pslots, hkv);
   return w;
 }
 
@@ -262,7 +262,7 @@ dcp_status_t dcp::bwd_launch(dcp_plan_t* plan, const dcp_tensors_t* t, void* wor
   DevGroup gq, gkv;
   const int n_seg = use_mfma ? xcd_segments(t->hkv) : 1;
   if ((st = plan->group_for(1, use_mfma ? mfma_dq_tile() : scalar_bwd_tile(), s, &gq, 0, may_alloc, n_seg)) != DCP_OK) return st;
-  if ((st = plan->group_for(2, use_mfma ? mfma_dkv_tile() : scalar_bwd_tile(), s, &gkv, use_mfma ? t->hkv : 0, may_alloc, n_seg)) != DCP_OK) return st;
+  if ((st = plan->group_for(2, use_mfma ? mfma_dkv_tile() : scalar_bwd_tile(), s, &gkv, use_mfma && mfma_splits_dkv(t->dtype, t->d) ? t->hkv : 0, may_alloc, n_seg)) != DCP_OK) return st;
   KTensors k = pack(plan, t);
   const size_t n_hT = wsz.n_hT;
   k.part = (float*)((char*)workspace + 2 * wsz.n_hT + wsz.n_bounds);

@@ -21,6 +21,7 @@ struct KTensors {
   int64_t q_st, q_sh, k_st, k_sh, v_st, v_sh, o_st, o_sh, do_st, do_sh, dq_st, dq_sh, dk_st, dk_sh, dv_st, dv_sh;
   int64_t q_rows;   // rows of the Q-type buffers (= packed tokens without block buffers): row pitch of lse / delta / lse2
   int32_t hq, hkv, d, block_size;
+  int32_t dtype;           // dcp_dtype_t
   float scale;
   int32_t use_slots;
 };
@@ -76,8 +77,10 @@ dcp_status_t scalar_fwd(const DevGroup& g, const KTensors& t, int32_t dtype, hip
 dcp_status_t scalar_bwd_dq(const DevGroup& g, const KTensors& t, int32_t dtype, hipStream_t s);
 dcp_status_t scalar_bwd_dkv(const DevGroup& g, const KTensors& t, int32_t dtype, hipStream_t s);
 
-// bf16 MFMA family (D = 128)
+// MFMA family: bf16 with D = 128 (kernels_mfma_fwd / dq / dkv), fp32 with D in {32, 64, 128} (kernels_mfma_f32)
 bool mfma_supports(int32_t dtype, int32_t d);
+// the dK/dV kernel takes cut work items (KTensors::part)
+inline bool mfma_splits_dkv(int32_t dtype, int32_t d) { return dtype == DCP_BF16 && d == 128; }
 int mfma_fwd_tile();
 int mfma_dq_tile();
 int mfma_dkv_tile();
@@ -85,6 +88,9 @@ size_t mfma_dkv_part_bytes(int32_t n_pslots, int32_t hkv);   // size of KTensors
 dcp_status_t mfma_fwd(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_bwd_dq(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_bwd_dkv(const DevGroup& g, const KTensors& t, hipStream_t s);
+dcp_status_t mfma_f32_fwd(const DevGroup& g, const KTensors& t, hipStream_t s);   // the fp32 part of the three above
+dcp_status_t mfma_f32_dq(const DevGroup& g, const KTensors& t, hipStream_t s);
+dcp_status_t mfma_f32_dkv(const DevGroup& g, const KTensors& t, hipStream_t s);
 void mfma_dkv_launch_ranges(const DevGroup& g, const KTensors& t, int grid, hipStream_t s);   // kernels_mfma_dkv_ranges.hip
 // per 32-row tile of every block: bounds of its rows' range arrays -> qbounds [n_t32 + 1][8]
 dcp_status_t mfma_range_bounds(const DevGroup& g, const KTensors& t, const int32_t* blk_t32, int32_t n_blocks, int32_t* qbounds,

@@ -1,0 +1,42 @@
+"""The fp32 MFMA kernels at the sizes where they can go wrong, against the fp64 oracle: rows and blocks around their
+32-row tiles and 128-row work items, units with fewer tiles than a workgroup has waves, every head dimension, mask kind
+and memory layout.  Bounds: those of fp32 I/O in helpers.TOL."""
+import pytest
+
+from paper_2510_10620_amd import workloads as W
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+LENS = [1, 31, 32, 33, 127, 129, 257, 300]
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("B,heads,spec", [
+    (64, (2, 1), W.MaskSpec("causal")), (96, (3, 3), W.MaskSpec("lambda", window=70, sink=9)), (512, (4, 2), W.MaskSpec("shared_question")),
+    (33, (2, 2), W.MaskSpec("window", window=40))], ids=lambda x: getattr(x, "kind", None))
+def test_f32_tiles(d, B, heads, spec):
+    w = W.custom_workload("f32", LENS, B, heads[0], heads[1], d, "f32", spec, seed=61, input_scale=0.5)
+    tensors, table = W.make_tensors(w), H.oracle_table(w)
+    ref = H.oracle_full(w, tensors, table)
+    window = (spec.window, spec.sink) if spec.kind == "window" else None
+    t = table.copy()
+    if window:
+        t[t[:, 2] == W.MASK_RANGES, 2] = W.MASK_WINDOW   # no range array: two numbers
+    g = H.GpuRun(w, tensors, t, window=window)
+    out, lse = g.forward()
+    dq, dk, dv = g.backward()
+    H.check(w, dict(out=out, lse=lse, dq=dq, dk=dk, dv=dv), ref, ("out", "lse", "dq", "dk", "dv"), f"f32 D{d} B{B} {spec.kind}")
+
+
+def test_f32_partial_slots_and_empty_rows():
+    """Divisions into partial slots with their merge, and a table that leaves query blocks and keys without partners."""
+    w = W.custom_workload("f32s", [150, 260], 64, 4, 2, 64, "f32", W.MaskSpec("causal"), seed=62, input_scale=0.5)
+    tensors, table = W.make_tensors(w), H.oracle_table(w)
+    table = table[::2]
+    slot, n_slots, _ = W.deal_divisions(table[:, 0], 2, 5)
+    ref = H.oracle_full(w, tensors, table)
+    g = H.GpuRun(w, tensors, table, slot, n_slots)
+    out, lse = g.forward()
+    dq, dk, dv = g.backward()
+    H.check(w, dict(out=out, lse=lse, dq=dq, dk=dk, dv=dv), ref, ("out", "lse", "dq", "dk", "dv"), "f32 slots")
