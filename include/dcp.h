@@ -243,7 +243,7 @@ dcp_status_t dcp_bwd_delta(const dcp_tensors_t* t, int64_t total_tokens, float* 
 /* Bytes of device workspace dcp_block_attn_bwd needs for this plan and shape: delta and the rescaled LSE, each
  * float [Hq, rows of the Q-type buffers], plus, for tables with RANGES or WINDOW rows, 32 bytes per 32-row tile of every block
  * (bounds of the rows' range arrays, which let the dK/dV kernel pass over query tiles that see none of its keys),
- * plus, for the bf16 MFMA kernels, 128 KiB per KV head for every part of a split dK/dV item (fp32 partial sums, see
+ * plus, for bf16 with D = 128, 128 KiB per KV head for every part of a split dK/dV item (fp32 partial sums, see
  * dcp_plan_export_dkv_items).  The first call for a given hkv builds and caches the work list in the plan. */
 size_t dcp_bwd_workspace_bytes(const dcp_plan_t* plan, int32_t hq, int32_t hkv, int32_t d, int32_t dtype);
 

@@ -74,7 +74,7 @@ static dcp_status_t check_tensor(const char* name, const void* p, int64_t st, in
 static dcp_status_t pick_impl(const dcp_tensors_t* t, bool* use_mfma) {
   const bool m_ok = mfma_supports(t->dtype, t->d), s_ok = scalar_supports(t->d);
   if (t->impl == DCP_IMPL_MFMA) {
-    if (!m_ok) return fail(DCP_ERR_UNSUPPORTED, "MFMA kernels cover bf16 with head_dim 128 and fp32 with head_dim 32, 64, 128");
+    if (!m_ok) return fail(DCP_ERR_UNSUPPORTED, "MFMA kernels cover head_dim 32, 64, 128");
     *use_mfma = true;
   } else if (t->impl == DCP_IMPL_SCALAR) {
     if (!s_ok) return fail(DCP_ERR_UNSUPPORTED, "scalar kernels cover head_dim 32, 64, 128");

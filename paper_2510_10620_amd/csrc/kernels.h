@@ -77,7 +77,8 @@ dcp_status_t scalar_fwd(const DevGroup& g, const KTensors& t, int32_t dtype, hip
 dcp_status_t scalar_bwd_dq(const DevGroup& g, const KTensors& t, int32_t dtype, hipStream_t s);
 dcp_status_t scalar_bwd_dkv(const DevGroup& g, const KTensors& t, int32_t dtype, hipStream_t s);
 
-// MFMA family: bf16 with D = 128 (kernels_mfma_fwd / dq / dkv), fp32 with D in {32, 64, 128} (kernels_mfma_f32)
+// MFMA family: bf16 with D = 128 (kernels_mfma_fwd / dq / dkv) and D in {32, 64} (kernels_mfma_narrow), fp32 with D in
+// {32, 64, 128} (kernels_mfma_f32)
 bool mfma_supports(int32_t dtype, int32_t d);
 // the dK/dV kernel takes cut work items (KTensors::part)
 inline bool mfma_splits_dkv(int32_t dtype, int32_t d) { return dtype == DCP_BF16 && d == 128; }
@@ -91,6 +92,9 @@ dcp_status_t mfma_bwd_dkv(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_f32_fwd(const DevGroup& g, const KTensors& t, hipStream_t s);   // the fp32 part of the three above
 dcp_status_t mfma_f32_dq(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_f32_dkv(const DevGroup& g, const KTensors& t, hipStream_t s);
+dcp_status_t mfma_narrow_fwd(const DevGroup& g, const KTensors& t, hipStream_t s);   // their part for bf16 with D < 128
+dcp_status_t mfma_narrow_dq(const DevGroup& g, const KTensors& t, hipStream_t s);
+dcp_status_t mfma_narrow_dkv(const DevGroup& g, const KTensors& t, hipStream_t s);
 void mfma_dkv_launch_ranges(const DevGroup& g, const KTensors& t, int grid, hipStream_t s);   // kernels_mfma_dkv_ranges.hip
 // per 32-row tile of every block: bounds of its rows' range arrays -> qbounds [n_t32 + 1][8]
 dcp_status_t mfma_range_bounds(const DevGroup& g, const KTensors& t, const int32_t* blk_t32, int32_t n_blocks, int32_t* qbounds,

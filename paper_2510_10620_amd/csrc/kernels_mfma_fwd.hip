@@ -463,7 +463,7 @@ __global__ __launch_bounds__(64 * kFwdWaves, (NQ == 1 ? 2 : 1)) void mfma_fwd_ke
   }
 }
 
-bool mfma_supports(int32_t dtype, int32_t d) { return dtype == DCP_BF16 ? d == kD : d == 32 || d == 64 || d == 128; }
+bool mfma_supports(int32_t dtype, int32_t d) { return (dtype == DCP_BF16 || dtype == DCP_F32) && (d == 32 || d == 64 || d == 128); }
 
 #ifndef DCP_FWD_NQ
 #define DCP_FWD_NQ 1
@@ -473,6 +473,7 @@ int mfma_fwd_tile() { return FwdCfg<DCP_FWD_NQ>::kTileM; }
 dcp_status_t mfma_fwd(const DevGroup& g, const KTensors& t, hipStream_t s) {
   if (g.n_items == 0) return DCP_OK;
   if (t.dtype == DCP_F32) return mfma_f32_fwd(g, t, s);
+  if (t.d != kD) return mfma_narrow_fwd(g, t, s);
   const int grid = xcd_grid(g, t.hkv, t.hq / t.hkv);
   if (t.masked) hipLaunchKernelGGL((mfma_fwd_kernel<DCP_FWD_NQ, true>), dim3(grid), dim3(64 * kFwdWaves), 0, s, g, t);
   else hipLaunchKernelGGL((mfma_fwd_kernel<DCP_FWD_NQ, false>), dim3(grid), dim3(64 * kFwdWaves), 0, s, g, t);

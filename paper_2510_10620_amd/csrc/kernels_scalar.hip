@@ -1,6 +1,6 @@
 // Scalar (fp32 vector-ALU) kernels for blockwise attention: one thread owns one query row (forward,
-// dQ) or one key row (dK/dV) of one head and walks the listed blocks key by key.  They cover the
-// fp32 I/O configuration and any (dtype, D) the MFMA family does not, and compute exactly the
+// dQ) or one key row (dK/dV) of one head and walks the listed blocks key by key.  They serve callers that ask for
+// DCP_IMPL_SCALAR, a second opinion on the MFMA kernels that shares none of their code, and compute exactly the
 // steps of the block-parallel attention listing (Listing 1, line 5) with the online-softmax
 // accumulation across the rows of one output unit.
 #include "device_utils.h"
