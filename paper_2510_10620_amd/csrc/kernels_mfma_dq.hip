@@ -57,25 +57,26 @@ __device__ __forceinline__ void dq_subtile(DqState& st, const char* k_lds, const
 template <bool RANGES>
 __global__ __launch_bounds__(256, 2) void mfma_dq_kernel(DevGroup g, KTensors t) {
   if (!RANGES) t.masked = 0;
-  constexpr int TM = 128;
   __shared__ __attribute__((aligned(1024))) char stage0[2 * kTileBytes];
   __shared__ __attribute__((aligned(1024))) char stage1[2 * kTileBytes];
   __shared__ int wg_bounds[4][8];
 
-  int item, head;
+  int item, head_x;
   const int G = t.hq / t.hkv;
-  if (!decode_wg(g, t.hkv, G, &item, &head)) return;
-  const int hk = head / G;
+  if (!decode_wg(g, t.hkv, G, &item, &head_x)) return;
+  const int hk = head_x / G;
   WorkItem w = g.items[item];
   w.unit = uni(w.unit); w.tile = uni(w.tile); w.e0 = uni(w.e0); w.e1 = uni(w.e1);
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
   const int li = lane & 31, lh = lane >> 5;
   const int blk_start = uni(w.blk_start), blk_len = uni(w.blk_len);
   const int qoff = uni(w.moff);                // rows of the Q-type buffers: packed index + qoff
-  const int row0 = w.tile * TM;
-  const int n_rows = min(TM, blk_len - row0);
+  const QSplit sp(w.tile, head_x, G, wave);
+  const int head = uni(sp.head), row0 = sp.row0;
+  const int n_rows = min(sp.rows, blk_len - row0);
+  if (n_rows <= 0) return;
   const int q_lo = blk_start + row0, q_hi = q_lo + n_rows - 1;
-  const int wrow0 = wave * 32;
+  const int wrow0 = uni(sp.wrow0);
   const int w_rows = max(0, min(32, n_rows - wrow0));
   const int wq_lo = q_lo + wrow0, wq_hi = wq_lo + w_rows - 1;
 

@@ -144,17 +144,20 @@ struct NQTile {
 
 template <bool RANGES>
 __device__ __forceinline__ bool nq_tile(const DevGroup& g, const KTensors& t, int lane, int wave, int (*wg_bounds)[8], NQTile* q) {
-  int item;
+  int item, head_x;
   const int G = t.hq / t.hkv;
-  if (!decode_wg(g, t.hkv, G, &item, &q->head)) return false;
-  q->hk = q->head / G;
+  if (!decode_wg(g, t.hkv, G, &item, &head_x)) return false;
   const WorkItem w = g.items[item];
+  const QSplit sp(uni(w.tile), head_x, G, wave);
+  q->head = uni(sp.head);
+  q->hk = head_x / G;
   q->unit = uni(w.unit); q->e0 = uni(w.e0); q->e1 = uni(w.e1);
   q->blk_start = uni(w.blk_start); q->qoff = uni(w.moff);
-  q->row0 = uni(w.tile) * 128;
-  q->n_rows = min(128, uni(w.blk_len) - q->row0);
+  q->row0 = sp.row0;
+  q->n_rows = min(sp.rows, uni(w.blk_len) - q->row0);
+  if (q->n_rows <= 0) return false;
   q->q_lo = q->blk_start + q->row0; q->q_hi = q->q_lo + q->n_rows - 1;
-  q->wrow0 = wave * 32;
+  q->wrow0 = uni(sp.wrow0);
   q->w_rows = max(0, min(32, q->n_rows - q->wrow0));
   q->wq_lo = q->q_lo + q->wrow0; q->wq_hi = q->wq_lo + q->w_rows - 1;
   const int r = q->wrow0 + (lane & 31);
