@@ -122,9 +122,9 @@ extern "C" dcp_status_t dcp_plan_prepare(dcp_plan_t* plan, int32_t hq, int32_t h
   if ((st = static_scratch(&scratch_addr)) != DCP_OK) return st;
   if (plan->total_tokens == 0) return DCP_OK;
   DevGroup g;
-  const int n_seg = use_mfma ? xcd_segments(hkv) : 1;
-  if ((st = plan->group_for(0, use_mfma ? mfma_fwd_tile() : scalar_fwd_tile(), s, &g, 0, true, n_seg)) != DCP_OK) return st;
-  if ((st = plan->group_for(1, use_mfma ? mfma_dq_tile() : scalar_bwd_tile(), s, &g, 0, true, n_seg)) != DCP_OK) return st;
+  const int n_seg = use_mfma ? xcd_segments(hkv) : 1, q_heads = use_mfma ? hq / hkv : 0;
+  if ((st = plan->group_for(0, use_mfma ? mfma_fwd_tile() : scalar_fwd_tile(), s, &g, q_heads, true, n_seg)) != DCP_OK) return st;
+  if ((st = plan->group_for(1, use_mfma ? mfma_dq_tile() : scalar_bwd_tile(), s, &g, q_heads, true, n_seg)) != DCP_OK) return st;
   return plan->group_for(2, use_mfma ? mfma_dkv_tile() : scalar_bwd_tile(), s, &g, use_mfma && mfma_splits_dkv(dtype, d) ? hkv : 0, true, n_seg);
 }
 
@@ -145,7 +145,8 @@ extern "C" dcp_status_t dcp_block_attn_fwd(dcp_plan_t* plan, const dcp_tensors_t
   if (plan->has_window && plan->window <= 0) return fail(DCP_ERR_INVALID_ARG, "table has WINDOW rows but dcp_plan_set_window was not called");
   hipStream_t s = (hipStream_t)stream;
   DevGroup g;
-  if ((st = plan->group_for(0, use_mfma ? mfma_fwd_tile() : scalar_fwd_tile(), s, &g, 0, true, use_mfma ? xcd_segments(t->hkv) : 1)) != DCP_OK) return st;
+  if ((st = plan->group_for(0, use_mfma ? mfma_fwd_tile() : scalar_fwd_tile(), s, &g,
+                            use_mfma ? t->hq / t->hkv : 0, true, use_mfma ? xcd_segments(t->hkv) : 1)) != DCP_OK) return st;
   KTensors k = pack(plan, t);
   ProfScope ps(DCP_K_FWD, s);
   return use_mfma ? mfma_fwd(g, k, s) : scalar_fwd(g, k, t->dtype, s);
@@ -260,8 +261,8 @@ dcp_status_t dcp::bwd_launch(dcp_plan_t* plan, const dcp_tensors_t* t, void* wor
   if (!workspace || workspace_bytes < need) return fail(DCP_ERR_WORKSPACE, "workspace is NULL or smaller than dcp_bwd_workspace_bytes");
   if (reinterpret_cast<uintptr_t>(workspace) & 255u) return fail(DCP_ERR_WORKSPACE, "workspace must be 256-byte aligned");
   DevGroup gq, gkv;
-  const int n_seg = use_mfma ? xcd_segments(t->hkv) : 1;
-  if ((st = plan->group_for(1, use_mfma ? mfma_dq_tile() : scalar_bwd_tile(), s, &gq, 0, may_alloc, n_seg)) != DCP_OK) return st;
+  const int n_seg = use_mfma ? xcd_segments(t->hkv) : 1, q_heads = use_mfma ? t->hq / t->hkv : 0;
+  if ((st = plan->group_for(1, use_mfma ? mfma_dq_tile() : scalar_bwd_tile(), s, &gq, q_heads, may_alloc, n_seg)) != DCP_OK) return st;
   if ((st = plan->group_for(2, use_mfma ? mfma_dkv_tile() : scalar_bwd_tile(), s, &gkv, use_mfma && mfma_splits_dkv(t->dtype, t->d) ? t->hkv : 0, may_alloc, n_seg)) != DCP_OK) return st;
   KTensors k = pack(plan, t);
   const size_t n_hT = wsz.n_hT;

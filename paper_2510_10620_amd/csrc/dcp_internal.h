@@ -121,9 +121,9 @@ struct dcp_plan {
   int32_t* dev_arena = nullptr;
   dcp::DevGroup d_fwd{}, d_bwdq{}, d_bwdkv{};
   const int32_t *d_merge_ptr = nullptr, *d_merge_idx = nullptr, *d_slot_qblk = nullptr, *d_q_mem0 = nullptr, *d_blk_t32 = nullptr;
-  // (group id, tile rows, split heads, segments) -> work list; split heads = 0: no splitting, else the number of
-  // workgroups launched per item (the long items are cut so that no workgroup outlasts the rest of the grid by much);
-  // segments: see DevGroup
+  // (group id, tile rows, heads, segments) -> work list; heads: the number of workgroups launched per item -- KV heads
+  // for the dK/dV group (the long items are then cut so that no workgroup outlasts the rest of the grid by much), query
+  // heads per KV head for the others -- or 0: strict longest-first, nothing cut; segments: see DevGroup
   typedef std::tuple<int, int, int, int> ItemKey;
   std::map<ItemKey, dcp::HostItems> h_items;
   std::map<ItemKey, dcp::DevItems> items;
@@ -131,8 +131,8 @@ struct dcp_plan {
   // may_alloc = false: fail (DCP_ERR_INVALID_ARG) instead of creating a device copy that does not exist yet
   dcp_status_t ensure_device(hipStream_t stream, bool may_alloc = true);
   // group id: 0 fwd, 1 bwdq, 2 bwdkv.  Host only; takes the plan's lock.
-  const dcp::HostItems& host_items(int group_id, int tile_rows, int split_heads, int n_seg = 1);
-  dcp_status_t group_for(int group_id, int tile_rows, hipStream_t stream, dcp::DevGroup* out, int split_heads = 0,
+  const dcp::HostItems& host_items(int group_id, int tile_rows, int heads, int n_seg = 1);
+  dcp_status_t group_for(int group_id, int tile_rows, hipStream_t stream, dcp::DevGroup* out, int heads = 0,
                          bool may_alloc = true, int n_seg = 1);
 };
 

@@ -592,9 +592,9 @@ static int64_t tile_cost(int32_t kind, int64_t r0, int64_t r1, int64_t c0, int64
 static constexpr int64_t kResidentWorkgroups = 512;
 static constexpr int32_t kMaxParts = 64;
 
-const HostItems& dcp_plan::host_items(int gid, int tile_rows, int split_heads, int n_seg) {
+const HostItems& dcp_plan::host_items(int gid, int tile_rows, int heads, int n_seg) {
   std::lock_guard<std::mutex> lock(mu);
-  const ItemKey key(gid, tile_rows, split_heads, n_seg);
+  const ItemKey key(gid, tile_rows, heads, n_seg);
   auto hit = h_items.find(key);
   if (hit != h_items.end()) return hit->second;
   HostGroup* hg = gid == 0 ? &fwd : (gid == 1 ? &bwdq : &bwdkv);
@@ -619,7 +619,7 @@ const HostItems& dcp_plan::host_items(int gid, int tile_rows, int split_heads, i
     }
   }
   HostItems hi;
-  if (split_heads > 0) {
+  if (gid == 2 && heads > 0) {
     // Long items are cut, along their table rows, into parts (each with a slot of fp32 partial sums that a reduce
     // kernel adds up): one key tile under a sink, or the first keys of the one long sequence of a small batch, can
     // otherwise outlast the rest of the grid.  Cutting costs partial-sum traffic and a second start-up per part
@@ -628,13 +628,13 @@ const HostItems& dcp_plan::host_items(int gid, int tile_rows, int split_heads, i
     // scheduling (items in the order they are issued, longest first, each on the workgroup slot that frees up
     // first) and items longer than 1/d of a slot's share are cut for d = 0 (none), 1, 2, 4 until the estimated
     // finish is within 5 % of the share, or d = 4 is reached.  Parts hold whole table rows, at most kMaxParts.
-    const double share = (double)total * split_heads / kResidentWorkgroups;
+    const double share = (double)total * heads / kResidentWorkgroups;
     auto finish_time = [&](std::vector<Scored> v) {
       std::stable_sort(v.begin(), v.end(), [](const Scored& a, const Scored& b) { return a.cost > b.cost; });
       std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> slots;
       for (int64_t i = 0; i < kResidentWorkgroups; i++) slots.push(0);
       int64_t end = 0;
-      for (int h = 0; h < split_heads; h++)          // the grid runs the list once per head, head-major
+      for (int h = 0; h < heads; h++)          // the grid runs the list once per head, head-major
         for (const Scored& it : v) {
           int64_t t0 = slots.top();
           slots.pop();
@@ -687,27 +687,39 @@ const HostItems& dcp_plan::host_items(int gid, int tile_rows, int split_heads, i
     }
   }
   std::stable_sort(sc.begin(), sc.end(), [](const Scored& a, const Scored& b) { return a.cost > b.cost; });
-  if (gid == 2 && split_heads > 0 && !sc.empty()) {
-    // dK/dV: sequence by sequence (the costliest sequence first, longest item first inside it) when that balances as
-    // well as strict longest-first does.  The key tiles of one sequence that run at the same time stream the same
-    // Q / dO rows (each walks its query tiles from the last one down), so their XCD's L2 serves those rows once:
-    // 13.9 -> 7.5 GB fetched per launch on the 65 536-token causal batch, and the step gains 1 % -- not in this kernel's
-    // own time but in the clock the chip grants its neighbours, its power being what is limited.  A batch of equal
-    // sequences balances badly in this order (every round of workgroups mixes long and short items), which the
-    // launch played through as list scheduling shows; it keeps strict longest-first.  (Longest-first by four or eight
-    // classes of length with sequences grouped inside a class was in between on traffic and 0.8 % slower; the same
-    // order for the forward and dQ lists changed nothing measurable.)
+  if (heads > 0 && !sc.empty() && (gid == 2 || !has_ranges)) {
+    // Sequence by sequence (the costliest sequence first, longest item first inside it) when that balances as well as
+    // strict longest-first does.  Items of one sequence that run at the same time read the same rows of the other
+    // side, so their XCD's L2 serves those rows once.  dK/dV: 13.9 -> 7.5 GB fetched per launch on the 65 536-token
+    // causal batch, and the step gains 1 % -- not in this kernel's own time but in the clock the chip grants its
+    // neighbours, its power being what is limited.  Forward and dQ: one KV head per
+    // four (65 536 causal tokens, 4/1 heads) 362 -> 333 and 486 -> 445 us, 16/4 heads 1 362 -> 1 331 and 1 784 -> 1 729,
+    // a 4 096-token window over 131 072 tokens 8.49 -> 8.23 and 10.69 -> 10.45 ms, 32/8 causal unchanged and 3 432 ->
+    // 3 398; where the table has RANGES rows their cost is a guess and the forward and dQ lists keep strict longest-first
+    // (causal blockwise dQ 3.20 -> 3.36 ms with the order that the guess allowed).  A dK/dV launch
+    // of equal sequences balances badly in this order (every round of workgroups mixes long and short items), which
+    // the launch played through as list scheduling shows; it keeps strict longest-first.  (Longest-first by four or
+    // eight classes of length with sequences grouped inside a class was in between on traffic and 0.8 % slower.)
+    // Who runs the list: in the dK/dV launch the whole chip, once per KV head; in the others the XCDs that share a KV
+    // head's list, each item once per query head.
+    const int64_t slots_n = gid == 2 ? kResidentWorkgroups : kResidentWorkgroups / 8 * n_seg;
     auto play = [&](const std::vector<Scored>& v) {
       std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> slots;
-      for (int64_t i = 0; i < kResidentWorkgroups; i++) slots.push(0);
+      for (int64_t i = 0; i < slots_n; i++) slots.push(0);
       int64_t end = 0;
-      for (int h = 0; h < split_heads; h++)          // the grid runs the list once per head, head-major
-        for (const Scored& it : v) {
-          const int64_t t0 = slots.top();
-          slots.pop();
-          slots.push(t0 + it.cost);
-          end = std::max(end, t0 + it.cost);
-        }
+      auto run = [&](const Scored& it) {
+        const int64_t t0 = slots.top();
+        slots.pop();
+        slots.push(t0 + it.cost);
+        end = std::max(end, t0 + it.cost);
+      };
+      if (gid == 2) {
+        for (int h = 0; h < heads; h++)          // the grid runs the list once per head, head-major
+          for (const Scored& it : v) run(it);
+      } else {
+        for (const Scored& it : v)
+          for (int h = 0; h < heads; h++) run(it);
+      }
       return end;
     };
     std::vector<int64_t> seq_cost(n_seq, 0);
@@ -780,14 +792,14 @@ static dcp_status_t upload(const std::vector<T>& v, T** dev, hipStream_t stream)
   return DCP_OK;
 }
 
-dcp_status_t dcp_plan::group_for(int gid, int tile_rows, hipStream_t stream, DevGroup* out, int split_heads, bool may_alloc,
+dcp_status_t dcp_plan::group_for(int gid, int tile_rows, hipStream_t stream, DevGroup* out, int heads, bool may_alloc,
                                  int n_seg) {
   dcp_status_t st = ensure_device(stream, may_alloc);
   if (st != DCP_OK) return st;
-  const HostItems& hi = host_items(gid, tile_rows, split_heads, n_seg);
+  const HostItems& hi = host_items(gid, tile_rows, heads, n_seg);
   std::lock_guard<std::mutex> lock(mu);
   DevGroup dg = gid == 0 ? d_fwd : (gid == 1 ? d_bwdq : d_bwdkv);
-  const ItemKey key(gid, tile_rows, split_heads, n_seg);
+  const ItemKey key(gid, tile_rows, heads, n_seg);
   auto it = items.find(key);
   if (it == items.end()) {
     if (!may_alloc) return fail(DCP_ERR_INVALID_ARG, "the plan has no work list for this shape yet: call dcp_plan_prepare first");
