@@ -95,7 +95,6 @@ dcp_status_t mfma_f32_dkv(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_narrow_fwd(const DevGroup& g, const KTensors& t, hipStream_t s);   // their part for bf16 with D < 128
 dcp_status_t mfma_narrow_dq(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_narrow_dkv(const DevGroup& g, const KTensors& t, hipStream_t s);
-void mfma_dkv_launch_ranges(const DevGroup& g, const KTensors& t, int grid, hipStream_t s);   // kernels_mfma_dkv_ranges.hip
 // per 32-row tile of every block: bounds of its rows' range arrays -> qbounds [n_t32 + 1][8]
 dcp_status_t mfma_range_bounds(const DevGroup& g, const KTensors& t, const int32_t* blk_t32, int32_t n_blocks, int32_t* qbounds,
                                hipStream_t s);

@@ -83,7 +83,7 @@ dcp_status_t mfma_bwd_dkv(const DevGroup& g, const KTensors& t, hipStream_t s) {
   if (t.dtype == DCP_F32) return mfma_f32_dkv(g, t, s);
   if (t.d != kD) return mfma_narrow_dkv(g, t, s);
   const int grid = xcd_grid(g, t.hkv, 1);
-  if (t.masked) mfma_dkv_launch_ranges(g, t, grid, s);   // the variant for per-token ranges lives in its own file
+  if (t.masked) hipLaunchKernelGGL(mfma_dkv_kernel<true>, dim3(grid), dim3(256), 0, s, g, t);
   else hipLaunchKernelGGL(mfma_dkv_kernel<false>, dim3(grid), dim3(256), 0, s, g, t);
   DCP_HIP_TRY(hipGetLastError());
   if (g.n_reduce > 0) {
