@@ -260,14 +260,6 @@ __device__ __forceinline__ void fwd_subtile(FwdState<NQ>& st, const char* k_lds,
     }
 }
 
-// A whole 64-key tile every pair of which is visible to the wave (kernel variant for tables with per-token ranges).
-template <int NQ>
-__device__ __forceinline__ void fwd_tile64(FwdState<NQ>& st, const char* k_lds, const char* v_lds, float c_log2) {
-  f32x16 s[2][NQ];
-  fwd_scores64<NQ, false>(st, k_lds, s);
-  fwd_softmax_pv<NQ>(st, s, v_lds, c_log2);
-}
-
 // RANGES = false: the table has no row with per-token ranges (RANGES or WINDOW) and every use of them folds away.
 template <int NQ, bool RANGES>
 __global__ __launch_bounds__(64 * kFwdWaves, (NQ == 1 ? 2 : 1)) void mfma_fwd_kernel(DevGroup g, KTensors t) {
@@ -369,22 +361,30 @@ __global__ __launch_bounds__(64 * kFwdWaves, (NQ == 1 ? 2 : 1)) void mfma_fwd_ke
       // the same short test as below spares the iterator and the classification: NONE and CAUSAL rows as there, rows
       // with per-token ranges when one of the two ranges of every row of the wave covers this tile and the next
       int cls0 = kFull, cls1 = kFull;
-      if (w_rows > 0 && (kind < 2 ? ks + 2 * kTN <= (kind ? min(c1, wq_lo + 1) : c1)
-                                  : ks + 2 * kTN <= c1 && wrb.all_see(ks, ks + 2 * kTN))) {
+      const bool common = w_rows > 0 && (kind < 2 ? ks + 2 * kTN <= (kind ? min(c1, wq_lo + 1) : c1)
+                                                  : ks + 2 * kTN <= c1 && wrb.all_see(ks, ks + 2 * kTN));
+      if (common) {
         it.jt++;
         it.ks += kTN;
       } else {
         have = it.next<RANGES>(q_hi, rb);
         if (w_rows > 0) { cls0 = classify32(kind, ks, c1, wq_lo, wq_hi, wrb); cls1 = classify32(kind, ks + 32, c1, wq_lo, wq_hi, wrb); }
-      }
-      if (have) {
-        st.dmak.load(nxt, kbase, it.ks + it.moff, it.c1 - 1 + it.moff, wave);
-        st.dmav.load(nxt + kTileBytes, vbase, it.ks + it.moff, it.c1 - 1 + it.moff, wave);
+        if (have) {
+          st.dmak.load(nxt, kbase, it.ks + it.moff, it.c1 - 1 + it.moff, wave);
+          st.dmav.load(nxt + kTileBytes, vbase, it.ks + it.moff, it.c1 - 1 + it.moff, wave);
+        }
       }
       if (w_rows > 0) {
-        // tables with per-token ranges: three self-contained paths (measured 4-5 % faster there than the joined form)
+        // tables with per-token ranges: self-contained paths (measured 4-5 % faster there than the joined form)
         if (cls0 == kFull && cls1 == kFull) {
-          fwd_tile64<NQ>(st, cur, cur + kTileBytes, c_log2);
+          f32x16 s[2][NQ];
+          if (common)
+            fwd_scores64<NQ, true>(st, cur, s, uni_ptr((const char*)kbase + (int64_t)(it.ks + it.moff) * st.dmak.sb),
+                                   uni_ptr((const char*)vbase + (int64_t)(it.ks + it.moff) * st.dmav.sb),
+                                   st.dmak.lds_of(nxt, wave), st.dmav.lds_of(nxt + kTileBytes, wave));
+          else
+            fwd_scores64<NQ, false>(st, cur, s);
+          fwd_softmax_pv<NQ>(st, s, cur + kTileBytes, c_log2);
         } else {
           if (cls0 != kSkip) fwd_subtile<NQ>(st, cur, cur + kTileBytes, 0, ks, kind, c0, c1, c_log2, lane, cls0 == kPartial);
           if (cls1 != kSkip) fwd_subtile<NQ>(st, cur, cur + kTileBytes, 1, ks + 32, kind, c0, c1, c_log2, lane, cls1 == kPartial);
