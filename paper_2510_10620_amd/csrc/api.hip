@@ -70,11 +70,22 @@ static dcp_status_t check_tensor(const char* name, const void* p, int64_t st, in
   return DCP_OK;
 }
 
-// Chooses the kernel family; MFMA iff requested or (AUTO and covered).
+// The fp32 and narrow-head MFMA kernels reach the rows of a tile through 32-bit byte offsets from its first row: 64 rows
+// of 2 bytes or 32 rows of 4 bytes, so token strides of up to 2^24 elements stay below 2^31.  A tensor the call does not
+// use has stride 0.
+static bool short_strides(const dcp_tensors_t* t) {
+  constexpr int64_t kMax = int64_t(1) << 24;
+  return t->q_stride_t <= kMax && t->k_stride_t <= kMax && t->v_stride_t <= kMax && t->o_stride_t <= kMax && t->do_stride_t <= kMax &&
+         t->dq_stride_t <= kMax && t->dk_stride_t <= kMax && t->dv_stride_t <= kMax;
+}
+
+// Chooses the kernel family.  AUTO: MFMA where it is covered and, outside bf16 with D = 128, the strides are short; else
+// the thread-per-row kernels.  A caller that asks for MFMA by name gets the bf16, D = 128 kernels or a refusal.
 static dcp_status_t pick_impl(const dcp_tensors_t* t, bool* use_mfma) {
-  const bool m_ok = mfma_supports(t->dtype, t->d), s_ok = scalar_supports(t->d);
+  const bool wide = t->dtype == DCP_BF16 && t->d == 128;
+  const bool m_ok = mfma_supports(t->dtype, t->d) && (wide || short_strides(t)), s_ok = scalar_supports(t->d);
   if (t->impl == DCP_IMPL_MFMA) {
-    if (!m_ok) return fail(DCP_ERR_UNSUPPORTED, "MFMA kernels cover head_dim 32, 64, 128");
+    if (!wide) return fail(DCP_ERR_UNSUPPORTED, "DCP_IMPL_MFMA covers bf16 with head_dim 128 only");
     *use_mfma = true;
   } else if (t->impl == DCP_IMPL_SCALAR) {
     if (!s_ok) return fail(DCP_ERR_UNSUPPORTED, "scalar kernels cover head_dim 32, 64, 128");

@@ -40,3 +40,23 @@ def test_f32_partial_slots_and_empty_rows():
     out, lse = g.forward()
     dq, dk, dv = g.backward()
     H.check(w, dict(out=out, lse=lse, dq=dq, dk=dk, dv=dv), ref, ("out", "lse", "dq", "dk", "dv"), "f32 slots")
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 32), ("bf16", 64), ("f32", 128)])
+def test_selector_and_token_strides(dtype, d):
+    """MFMA by name stays refused outside bf16 with D = 128, and token strides past the 32-bit offsets of the kernels for
+    these shapes (2^24 elements) run on the thread-per-row family: its results, bit for bit."""
+    import torch
+    import paper_2510_10620_amd as P
+    w = W.custom_workload("far", [3], 64, 1, 1, d, dtype, W.MaskSpec("causal"), seed=65, input_scale=0.5)
+    tensors, table = W.make_tensors(w), H.oracle_table(w)
+    with pytest.raises(P.DcpError) as ei:
+        H.GpuRun(w, tensors, table, impl=P.DCP_IMPL_MFMA).forward()
+    assert ei.value.status == P.DCP_ERR_UNSUPPORTED
+    ref = H.GpuRun(w, tensors, table, impl=P.DCP_IMPL_SCALAR)
+    far = H.GpuRun(w, tensors, table)
+    k = torch.empty(2 * ((1 << 24) + 8) + d, dtype=far.k.dtype, device="cuda").as_strided((3, 1, d), ((1 << 24) + 8, d, 1))
+    k.copy_(far.k)
+    far.k = k
+    for a, b in zip(ref.forward() + ref.backward(), far.forward() + far.backward()):
+        assert (a == b).all()
