@@ -2,9 +2,11 @@
 // of the D = 128 kernels (transposed scores, 64-row LDS tiles copied one ahead, transposing reads, one workgroup of four
 // waves x 32 rows per 128-row work item) with two differences.
 //
-//  * P and dS go into the products over keys (queries) as the sum of two bf16 numbers, the rounded value and what the
-//    rounding left over: 16 significant bits, so that the results are those of fp32 P and dS (which the thread-per-row
-//    kernels have, and which a narrow head can afford: at D = 64 the exponentials, not the MFMAs, are the larger part).
+//  * P and dS stay fp32 numbers: they go into the products over keys (queries) as three bf16 parts of 8 bits whose sum they
+//    are, each part a product of its own with the same bf16 operand on the other side (8 x 8 bits, exact in fp32).  Two
+//    rounded parts cost 17-19 % less time (16 384 causal tokens, 16/4 heads, D 64: forward 454 -> 545 us with the third, dQ
+//    500 -> 600, dK/dV 1 047 -> 1 291) but leave 2^-18 of every weight, which the fp32 weights of the thread-per-row kernels
+//    do not: their results were 1e-6 of the norm farther from a 64-bit reference, and far more where a sum cancels.
 //  * Nothing is scheduled by hand: with D = 64 a workgroup needs a third of the registers and half the LDS of the D = 128
 //    kernels, several are resident per CU, and their waves fill one another's waits.
 //
@@ -12,10 +14,9 @@
 // chunk c of a row sits at chunk ((row % (128 / D)) * (D / 8) + c) ^ swz(line) of its line; 16 consecutive rows at one
 // chunk (row-major reads) fall into 16 different chunks, 4 consecutive rows x 64 bytes (transposing reads) into 4
 // different 64-byte groups.
-// Measured against one thread per row (16 384 causal tokens, 16/4 heads, D 64): forward 21.8 -> 0.45 ms, dQ 36.0 -> 0.50,
-// dK/dV 76.8 -> 0.93 ms.  What bounds them on large batches is the MFMA rate that the chip holds on real data: counting
-// both halves of P and dS the three kernels execute 960, 1 040 and 950 TFLOP/s (65 536 tokens), a large bf16 matrix
-// product 1 270 on this card.
+// Measured against one thread per row (16 384 causal tokens, 16/4 heads, D 64): forward 21.8 -> 0.54 ms, dQ 36.0 -> 0.60,
+// dK/dV 76.8 -> 1.29 ms.  What bounds them on large batches is the MFMA rate that the chip holds on real data: counting
+// the three parts of P and dS the three kernels execute 1 090, 1 128 and 950 TFLOP/s (65 536 causal tokens, log-normal).
 #include "mfma_dkv_kernel.h"
 
 namespace dcp {
@@ -93,17 +94,23 @@ struct NDma {
   }
 };
 
-// Registers 8c .. 8c + 7 of a C tile as two bf16 operands whose sum is the value to 16 significant bits.
-__device__ __forceinline__ void pack_split(const f32x16& s, int c, bf16x8* hi, bf16x8* lo) {
-  uint32_t h[4], l[4];
+// Registers 8c .. 8c + 7 of a C tile as three bf16 operands that add up to the values exactly: 8 significant bits each, cut
+// off (not rounded: a finite value has finite parts), the remainders being exact in fp32.
+__device__ __forceinline__ void pack_split(const f32x16& s, int c, bf16x8 (&part)[3]) {
+  uint32_t w[3][4];
 #pragma unroll
   for (int e = 0; e < 4; e++) {
-    const float a = s[8 * c + 2 * e], b = s[8 * c + 2 * e + 1];
-    h[e] = pack_bf16x2(a, b);
-    l[e] = pack_bf16x2(a - __uint_as_float(h[e] << 16), b - __uint_as_float(h[e] & 0xffff0000u));
+    float a = s[8 * c + 2 * e], b = s[8 * c + 2 * e + 1];
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+      const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+      w[k][e] = __builtin_amdgcn_perm(ub, ua, 0x07060302);   // the upper halves of both
+      a -= __uint_as_float(ua & 0xffff0000u);
+      b -= __uint_as_float(ub & 0xffff0000u);
+    }
   }
-  *hi = as_frag(make_uint4(h[0], h[1], h[2], h[3]));
-  *lo = as_frag(make_uint4(l[0], l[1], l[2], l[3]));
+#pragma unroll
+  for (int k = 0; k < 3; k++) part[k] = as_frag(make_uint4(w[k][0], w[k][1], w[k][2], w[k][3]));
 }
 
 // store_tile32 for D columns
@@ -295,13 +302,13 @@ __global__ __launch_bounds__(256, 4) void narrow_fwd_kernel(DevGroup g, KTensors
         l += sum;
 #pragma unroll
         for (int c = 0; c < 2; c++) {
-          bf16x8 hi, lo;
-          pack_split(s[kt], c, &hi, &lo);
+          bf16x8 p[3];
+          pack_split(s[kt], c, p);
 #pragma unroll
           for (int dt = 0; dt < N::DT; dt++) {
             const bf16x8 v = fa.cols(v_lds, 32 * kt + 16 * c, dt);
-            o[dt] = mfma(v, hi, o[dt]);
-            o[dt] = mfma(v, lo, o[dt]);
+#pragma unroll
+            for (int k = 0; k < 3; k++) o[dt] = mfma(v, p[k], o[dt]);
           }
         }
       }
@@ -394,13 +401,13 @@ __global__ __launch_bounds__(256, 3) void narrow_dq_kernel(DevGroup g, KTensors 
       for (int r = 0; r < 16; r++) s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c_log2, -lse2)) * dp[r];
 #pragma unroll
       for (int c = 0; c < 2; c++) {
-        bf16x8 hi, lo;
-        pack_split(s, c, &hi, &lo);
+        bf16x8 ds[3];
+        pack_split(s, c, ds);
 #pragma unroll
         for (int dt = 0; dt < N::DT; dt++) {
-          const bf16x8 k = fa.cols(k_lds, 32 * kt + 16 * c, dt);
-          dq[dt] = mfma(k, hi, dq[dt]);
-          dq[dt] = mfma(k, lo, dq[dt]);
+          const bf16x8 kc = fa.cols(k_lds, 32 * kt + 16 * c, dt);
+#pragma unroll
+          for (int k = 0; k < 3; k++) dq[dt] = mfma(kc, ds[k], dq[dt]);
         }
       }
     }
@@ -414,8 +421,8 @@ __global__ __launch_bounds__(256, 3) void narrow_dq_kernel(DevGroup g, KTensors 
 // A workgroup's eight waves are NG = 8 / KW groups of KW waves: a wave has 32 keys, the groups own the same 32 KW keys
 // and take the query tiles in turn, each with LDS stages of its own, and add their sums at the end.  The dK/dV work items
 // are few and long (one per 128 keys and KV head in the D = 128 kernel) and a launch
-// waits for its longest (16 384 tokens, 16/4 heads, D 64: 1.44 ms with one group of four waves, 1.05 with two, 0.93 with
-// four groups of two waves; with many items the two-group form is the faster, see mfma_narrow_dkv).
+// waits for its longest (with P and dS in two parts, 16 384 tokens, 16/4 heads, D 64: 1.44 ms with one group of four waves,
+// 1.05 with two, 0.93 with four groups of two waves; with many items the two-group form is the faster, see mfma_narrow_dkv).
 template <int D, int KW, bool RANGES>
 __global__ __launch_bounds__(512, 2) void narrow_dkv_kernel(DevGroup g, KTensors t) {
   constexpr int NG = 8 / KW, SUB = 4 / KW;   // workgroups per 128-key work item
@@ -553,16 +560,17 @@ __global__ __launch_bounds__(512, 2) void narrow_dkv_kernel(DevGroup g, KTensors
         }
 #pragma unroll
         for (int c = 0; c < 2; c++) {
-          bf16x8 ph, pl, dh, dl;
-          pack_split(s, c, &ph, &pl);
-          pack_split(dp, c, &dh, &dl);
+          bf16x8 p[3], ds[3];
+          pack_split(s, c, p);
+          pack_split(dp, c, ds);
 #pragma unroll
           for (int dt = 0; dt < N::DT; dt++) {
             const bf16x8 a = fa.cols(do_lds, 32 * qt + 16 * c, dt), b = fa.cols(q_lds, 32 * qt + 16 * c, dt);
-            dv[dt] = mfma(a, ph, dv[dt]);
-            dk[dt] = mfma(b, dh, dk[dt]);
-            dv[dt] = mfma(a, pl, dv[dt]);
-            dk[dt] = mfma(b, dl, dk[dt]);
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+              dv[dt] = mfma(a, p[k], dv[dt]);
+              dk[dt] = mfma(b, ds[k], dk[dt]);
+            }
           }
         }
       }
@@ -627,8 +635,10 @@ static void narrow_dkv_launch(const DevGroup& g, const KTensors& t, hipStream_t 
 
 dcp_status_t mfma_narrow_dkv(const DevGroup& g, const KTensors& t, hipStream_t s) {
   // Four rounds of 128-key workgroups (one per CU) balance whatever the lengths are, and share each Q / dO tile among
-  // four waves (65 536 tokens, 16/4 heads, 2 048 items: 1.72 ms, 1.97 with 64 keys); with fewer the longest item decides
-  // (16 384 tokens, 16/4 heads, 512 items: 1.05 ms, 0.93 with 64 keys; 1 000 tokens: 104 and 64 us).
+  // four waves; with fewer the longest item decides, and half as many keys per workgroup shorten it.  128 against 64 keys,
+  // D 64, log-normal lengths: 2 048 items (65 536 tokens, 16/4 heads) 2.90 and 2.98 ms, (16 384 tokens, 16/16) 0.71 and 0.81;
+  // 1 024 items (32 768 tokens, 16/4) causal 1.90 and 2.04, sink and window 1.70 and 1.15; 512 items (16 384, 16/4) 1.06 and
+  // 0.86, (65 536, 4/1) 1.47 and 0.81; 128 items (4 096, 16/4) 0.26 and 0.15 ms.
   if ((int64_t)g.n_items * t.hkv > 1024) narrow_dkv_launch<4>(g, t, s);
   else narrow_dkv_launch<2>(g, t, s);
   DCP_HIP_TRY(hipGetLastError());

@@ -47,3 +47,64 @@ def test_narrow_slots_strides_and_empty_rows():
     out, lse = g.forward()
     dq, dk, dv = g.backward()
     H.check(w, dict(out=out, lse=lse, dq=dq, dk=dk, dv=dv), H.oracle_full(w, tensors, table), ALL, "narrow slots")
+
+
+@pytest.mark.parametrize("d", [32, 64])
+def test_narrow_weights_are_not_rounded(d):
+    """P and dS enter the products over keys and queries with all their 24 bits.  Sequences of four tokens whose last two
+    values (queries, keys, dO rows) are chosen so that the sums nearly cancel: what is left is 2^-18 of the terms, and
+    its bf16 rounding as fine as 2^-26, so that an error of the weights shows.  Against the same sums in 64 bits."""
+    import torch
+    import paper_2510_10620_amd as P
+    S, NH, n = 64, 2, 4
+    rng = np.random.default_rng(66)
+    bf = lambda x: W.bf16_bits_to_f64(W.f32_to_bf16_bits(np.asarray(x, np.float32)))
+    rnd = lambda *s: bf(rng.standard_normal(s))
+    scale = float(np.float32(1 / np.sqrt(d)))
+    q, k, v, do = (np.zeros((S, n, NH, d)) for _ in range(4))
+    A, B = slice(8, 8 + (d - 8) // 2), slice(8 + (d - 8) // 2, d)   # columns where q, where k is zero: free for the other
+    q[..., :8], k[..., :8] = rnd(S, n, NH, 8), rnd(S, n, NH, 8)
+    s = np.einsum("sihd,sjhd->shij", q, k) * scale
+    s[:, :, ~np.tril(np.ones((n, n), bool))] = -np.inf
+    lse = np.log(np.exp(s).sum(-1)).astype(np.float32)
+    p = np.exp(s - lse[..., None])
+
+    def cancel(x, w, cols):
+        """x[:, 2:] so that sum_j w[.., j] x[:, j] is nearly zero; w [S, heads, n]."""
+        x[:, :2, :, cols] = rnd(S, 2, NH, len(range(d)[cols]))
+        for j in (2, 3):
+            left = np.einsum("shj,sjhd->shd", w[..., :j], x[:, :j, :, cols])
+            x[:, j, :, cols] = bf(np.clip(-left / w[..., j, None], -64, 64))
+    cancel(v, p[:, :, 3], slice(0, d))
+    cancel(do, p[:, :, :, 0], slice(0, 2))                           # dO in two columns: dP and delta are short sums
+    o = np.einsum("shij,sjhd->sihd", p, v)
+    ob = bf(o)
+    dp, delta = np.einsum("sihd,sjhd->shij", do, v), np.einsum("sihd,sihd->shi", do, ob)
+    mag = p * (np.einsum("sihd,sjhd->shij", abs(do), abs(v)) + np.einsum("sihd,sihd->shi", abs(do), abs(ob))[..., None])
+    ds = p * (dp - delta[..., None])
+    cancel(k, ds[:, :, 3], A)
+    cancel(q, ds[:, :, :, 0], B)
+    ref = dict(out=o[:, 3], dv=np.einsum("shi,sihd->shd", p[..., 0], do), dq=scale * np.einsum("shj,sjhd->shd", ds[:, :, 3], k),
+               dk=scale * np.einsum("shi,sihd->shd", ds[..., 0], q))
+    # fp32 arithmetic: a weight is good to 2^-21 (score, exponential, LSE), dP - delta to 2^-22 of its terms; twice that
+    err = dict(out=2.0 ** -20 * np.einsum("shj,sjhd->shd", p[:, :, 3], abs(v)), dv=2.0 ** -20 * np.einsum("shi,sihd->shd", p[..., 0], abs(do)),
+               dq=scale * np.einsum("shj,sjhd->shd", 2.0 ** -20 * abs(ds)[:, :, 3] + 2.0 ** -21 * mag[:, :, 3], abs(k)),
+               dk=scale * np.einsum("shi,sihd->shd", 2.0 ** -20 * abs(ds)[..., 0] + 2.0 ** -21 * mag[..., 0], abs(q)))
+    cu = (n * np.arange(S + 1)).astype(np.int32)
+    table = np.array([[b, b, W.MASK_CAUSAL] for b in range(S)], np.int32)
+    dev = lambda x: torch.from_numpy(x.reshape(S * n, NH, d)).to(torch.bfloat16).cuda()
+    tq, tk, tv, tdo, to = (dev(x) for x in (q, k, v, do, ob))
+    plan = P.dcp_plan_create(cu, 64, table)
+    out, dq, dk, dv = (torch.empty_like(tq) for _ in range(4))
+    lse_t = torch.empty((NH, S * n), device="cuda")
+    P.dcp_block_attn_fwd(plan, tq, tk, tv, out, lse_t, scale, None)
+    lse_t.copy_(torch.from_numpy(lse.transpose(1, 0, 2).reshape(NH, S * n).copy()))
+    ws = torch.empty(max(256, P.dcp_bwd_workspace_bytes(plan, NH, NH, d, P.DCP_BF16)), dtype=torch.uint8, device="cuda")
+    P.dcp_block_attn_bwd(plan, tq, tk, tv, to, lse_t, tdo, dq, dk, dv, scale, ws, None)
+    torch.cuda.synchronize()
+    host = lambda x, row: H.from_torch(x).reshape(S, n, NH, d)[:, row]
+    got = dict(out=host(out, 3), dq=host(dq, 3), dk=host(dk, 0), dv=host(dv, 0))
+    for name in ref:   # half an ulp of bf16 is at most 2^-8 of the value
+        over = (np.abs(got[name] - ref[name]) - 2.0 ** -8 * (1 + 2.0 ** -8) * np.abs(ref[name])) / np.maximum(err[name], 1e-30)
+        print(name, "error beyond the rounding of the result, of its bound:", over.max(), flush=True)
+        assert over.max() <= 1, name
