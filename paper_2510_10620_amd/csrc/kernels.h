@@ -12,7 +12,7 @@ struct KTensors {
   float* delta_w;          // backward, MFMA family: where the dQ kernel leaves -delta and lse2 (the same arrays as below) for
   float* lse2_w;           //   the dK/dV kernel; null in the scalar family, where a preprocess kernel has filled them
   const float* delta;      // backward input [Hq,T]: delta (scalar family), -delta (MFMA family dK/dV, from the dQ kernel)
-  const float* lse2;       // backward input [Hq,T]: max(lse * log2(e), -FLT_MAX)
+  const float* lse2;       // backward input [Hq,T]: max(lse * log2(e), -FLT_MAX); fp32 and D < 128: +inf where lse is -inf or NaN
   const int32_t* ranges;   // [T,4] or null (tables without RANGES rows)
   int32_t window, sink;    // window > 0: the table has WINDOW rows; their per-token ranges are worked out, not read
   int32_t masked;          // the table has RANGES or WINDOW rows (rows with per-token ranges)

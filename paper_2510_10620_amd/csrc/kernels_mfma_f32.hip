@@ -386,7 +386,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dq_kernel(DevGroup g, KTensor
   }
   delta = xhalf_sum(delta);
   const int64_t at = (int64_t)q.head * t.q_rows + q.qi + q.qoff;
-  const float lse2 = fmaxf(t.lse[at] * kLog2eF, -3.402823466e38f);
+  const float lse2 = row_lse2(t.lse[at], &delta);
   if (wave == 0 && lh == 0 && li < q.n_rows) { t.delta_w[at] = -delta; t.lse2_w[at] = lse2; }
   const float* kb = (const float*)t.k + (int64_t)q.hk * t.k_sh;
   const float* vb = (const float*)t.v + (int64_t)q.hk * t.v_sh;

@@ -357,7 +357,7 @@ __global__ __launch_bounds__(256, 3) void narrow_dq_kernel(DevGroup g, KTensors 
     for (int e = 0; e < 8; e++) delta = fmaf((float)of[x][e], (float)dof[x][e], delta);
   delta = xhalf_sum(delta);
   const int64_t at = (int64_t)q.head * t.q_rows + q.qi + q.qoff;
-  const float lse2 = fmaxf(t.lse[at] * kLog2e, -3.402823466e38f);
+  const float lse2 = row_lse2(t.lse[at], &delta);
   if (q.qv && lh == 0) { t.delta_w[at] = -delta; t.lse2_w[at] = lse2; }
   f32x16 dq[N::DT];
 #pragma unroll

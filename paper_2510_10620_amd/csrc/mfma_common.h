@@ -333,6 +333,14 @@ __device__ __forceinline__ float xhalf_sum(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// The rescaled LSE a row's backward subtracts.  A row that saw no key anywhere (LSE -inf; NaN counts as that too) is off:
+// +inf gives every pair of it weight 0, whatever its score, and its delta is 0.
+__device__ __forceinline__ float row_lse2(float lse, float* delta) {
+  if (lse > -INFINITY) return fmaxf(lse * 1.44269504088896340736f, -3.402823466e38f);   // finite: scores under the mask are -inf
+  *delta = 0.f;
+  return INFINITY;
+}
+
 // Walks the (table row, key tile) pairs of a unit that the workgroup cannot skip.  All state is
 // wave-uniform.
 struct KvIter {
