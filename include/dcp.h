@@ -225,7 +225,10 @@ typedef struct {
  * computation block S = scale * Q_i K_j^T, mask, online softmax, acc += P V_j; rows of one output
  * unit accumulate in the kernel; O = acc / l, LSE = m + ln l (natural log of the sum of exp of
  * scaled scores).  A query row that sees no key gets O = 0, LSE = -inf.  Every row of every
- * q_blk (no slots) or of every used slot is written, also when no entry lists it. */
+ * q_blk (no slots) or of every used slot is written, also when no entry lists it.
+ * Inf and NaN in the inputs reach the rows that see them and no others, here and in the backward (which also leaves
+ * out query rows whose LSE is -inf or NaN); the MFMA kernels for bf16 with D = 128 are the exception: they may spread
+ * them to other rows of the 64-row tiles concerned. */
 dcp_status_t dcp_block_attn_fwd(dcp_plan_t* plan, const dcp_tensors_t* t, void* stream);
 
 /* Blockwise Reduction (Listing 1 line 6 "RescaleAndSum"; Sec. 5 "Blockwise Reduction"):

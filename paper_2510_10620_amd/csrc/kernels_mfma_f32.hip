@@ -19,6 +19,7 @@
 // rows in registers took 2.36 ms (the dK/dV kernel spilled, and its 512 workgroups of one round waited for the longest).
 #include "device_utils.h"
 #include "mfma_common.h"
+#include "nonfinite.h"
 
 namespace dcp {
 
@@ -231,22 +232,34 @@ __device__ __forceinline__ void stage_acc(float* slab, const f32x16 (&acc)[D / 3
     }
 }
 
-// Adds the waves' slabs up in wave order and stores rows r < n_rows.  wgt: factor of each (wave, row), or null (1).
+// Adds the waves' slabs up in wave order and stores rows r < n_rows.  wgt: factor of each (wave, row), or null (1).  Returns
+// which of the wave's four rows (4 wave + bit) hold a value that is not finite.
 template <int D>
-__device__ __forceinline__ void store_sum(const float* slabs, const float* wgt, float mul, int n_rows, float* dst, int64_t stride) {
+__device__ __forceinline__ uint32_t store_sum(const float* slabs, const float* wgt, float mul, int n_rows, float* dst, int64_t stride) {
   const int row = threadIdx.x / 16, seg = threadIdx.x % 16;
   static_assert(kThreads == 16 * kRows, "16 threads per row");
-  if (row >= n_rows) return;
-  for (int col = 4 * seg; col < D; col += 64) {
-    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+  float probe = 0.f;
+  if (row < n_rows)
+    for (int col = 4 * seg; col < D; col += 64) {
+      float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-    for (int w = 0; w < kWaves; w++) {
-      const float4 b = *(const float4*)(slabs + (w * kRows + row) * (D + 4) + col);
-      const float f = wgt ? wgt[w * kRows + row] : mul;
-      a.x = fmaf(b.x, f, a.x); a.y = fmaf(b.y, f, a.y); a.z = fmaf(b.z, f, a.z); a.w = fmaf(b.w, f, a.w);
+      for (int w = 0; w < kWaves; w++) {
+        const float4 b = *(const float4*)(slabs + (w * kRows + row) * (D + 4) + col);
+        const float f = wgt ? wgt[w * kRows + row] : mul;
+        a.x = fmaf(b.x, f, a.x); a.y = fmaf(b.y, f, a.y); a.z = fmaf(b.z, f, a.z); a.w = fmaf(b.w, f, a.w);
+      }
+      *(float4*)(dst + (int64_t)row * stride + col) = a;
+      probe = finite_probe(a.x, finite_probe(a.y, finite_probe(a.z, finite_probe(a.w, probe))));
     }
-    *(float4*)(dst + (int64_t)row * stride + col) = a;
-  }
+  const uint64_t bad = __ballot(probe != 0.f);
+  return ((bad & 0xffffull) != 0) | ((bad & 0xffff0000ull) != 0) << 1 | ((bad & 0xffff00000000ull) != 0) << 2 | ((bad >> 48) != 0) << 3;
+}
+
+// row r of the workgroup, for the functions of nonfinite.h
+__device__ __forceinline__ FixRow fix_row(const QTile& q, int r) {
+  return {q.q_lo + r, q.e0, q.e1,
+          make_int4(__builtin_amdgcn_readlane(q.qr.x, r), __builtin_amdgcn_readlane(q.qr.y, r), __builtin_amdgcn_readlane(q.qr.z, r),
+                    __builtin_amdgcn_readlane(q.qr.w, r))};
 }
 
 }  // namespace
@@ -355,7 +368,20 @@ __global__ __launch_bounds__(kThreads, 2) void f32_fwd_kernel(DevGroup g, KTenso
   }
   float* op = slot < 0 ? (float*)t.out + (int64_t)(q.q_lo + q.qoff) * t.o_st + (int64_t)q.head * t.o_sh
                        : (float*)t.out + (((int64_t)slot * t.block_size + q.row0) * t.hq + q.head) * D;
-  store_sum<D>(slabs, &sl[0][0], 1.f, q.n_rows, op, slot < 0 ? t.o_st : (int64_t)t.hq * D);
+  const int64_t op_st = slot < 0 ? t.o_st : (int64_t)t.hq * D;
+  uint32_t again = store_sum<D>(slabs, &sl[0][0], 1.f, q.n_rows, op, op_st);
+  if (again) {
+    DCP_WAIT_VMCNT(0);   // the stores above come first
+    const KernelArgs a = kernel_args();
+    for (; again; again &= again - 1) {
+      const int r = 4 * wave + __builtin_ctz(again);
+      if (lane_of(lt, r) != lane_of(lt, r)) continue;   // a NaN score: all of the row is NaN already
+      const FixRow f = fix_row(q, r);
+      const float mr = lane_of(mt, r);
+      fix_out<float, D>(a.g, a.t, f, q.hk, (const float*)a.t.q + (int64_t)(f.qi + q.qoff) * a.t.q_st + (int64_t)q.head * a.t.q_sh,
+                        mr == -INFINITY ? 0.f : mr * c_log2, lane_of(inv, r), op + r * op_st);
+    }
+  }
 }
 
 template <int D, bool RANGES>
@@ -442,7 +468,19 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dq_kernel(DevGroup g, KTensor
   __syncthreads();   // the own rows' slabs are free
   stage_acc<D>(slabs + wave * SLAB, dq, lane);
   __syncthreads();
-  store_sum<D>(slabs, nullptr, t.scale, q.n_rows, (float*)t.dq + (int64_t)(q.q_lo + q.qoff) * t.dq_st + (int64_t)q.head * t.dq_sh, t.dq_st);
+  float* dqp = (float*)t.dq + (int64_t)(q.q_lo + q.qoff) * t.dq_st + (int64_t)q.head * t.dq_sh;
+  uint32_t again = store_sum<D>(slabs, nullptr, t.scale, q.n_rows, dqp, t.dq_st);
+  if (again) {
+    DCP_WAIT_VMCNT(0);   // the stores above come first
+    const KernelArgs a = kernel_args();
+    for (; again; again &= again - 1) {
+      const int r = 4 * wave + __builtin_ctz(again);
+      const FixRow f = fix_row(q, r);
+      const int64_t mem = f.qi + q.qoff;
+      fix_dq<float, D>(a.g, a.t, f, q.hk, (const float*)a.t.q + mem * a.t.q_st + (int64_t)q.head * a.t.q_sh,
+                       (const float*)a.t.dout + mem * a.t.do_st + (int64_t)q.head * a.t.do_sh, lane_of(lse2, r), lane_of(delta, r), dqp + r * a.t.dq_st);
+    }
+  }
 }
 
 // dK / dV of 32 keys of one KV head: the waves take every eighth (query head, 32-query tile) of the listed q blocks.
@@ -581,11 +619,24 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dkv_kernel(DevGroup g, KTenso
   __syncthreads();   // the own rows' slabs are free
   stage_acc<D>(slab, dk, lane);
   __syncthreads();
-  store_sum<D>(slabs, nullptr, t.scale, n_rows, (float*)t.dk + (int64_t)(k_lo + koff) * t.dk_st + (int64_t)hk * t.dk_sh, t.dk_st);
+  float* dkp = (float*)t.dk + (int64_t)(k_lo + koff) * t.dk_st + (int64_t)hk * t.dk_sh;
+  float* dvp = (float*)t.dv + (int64_t)(k_lo + koff) * t.dv_st + (int64_t)hk * t.dv_sh;
+  uint32_t again = store_sum<D>(slabs, nullptr, t.scale, n_rows, dkp, t.dk_st);
   __syncthreads();
   stage_acc<D>(slab, dv, lane);
   __syncthreads();
-  store_sum<D>(slabs, nullptr, 1.f, n_rows, (float*)t.dv + (int64_t)(k_lo + koff) * t.dv_st + (int64_t)hk * t.dv_sh, t.dv_st);
+  again |= store_sum<D>(slabs, nullptr, 1.f, n_rows, dvp, t.dv_st);
+  if (again) {
+    DCP_WAIT_VMCNT(0);   // the stores above come first
+    const KernelArgs a = kernel_args();
+    const WorkItem w1 = a.g.items[item];
+    const int s0 = RANGES ? uni(a.g.blk_s0[uni(a.g.unit_blk[uni(w1.unit)])]) : 0;
+    for (; again; again &= again - 1) {
+      const int r = 4 * wave + __builtin_ctz(again), j = k_lo + r;
+      fix_dkv<float, D>(a.g, a.t, j, uni(w1.e0), uni(w1.e1), hk, s0, (const float*)a.t.k + (int64_t)(j + koff) * a.t.k_st + (int64_t)hk * a.t.k_sh,
+                        (const float*)a.t.v + (int64_t)(j + koff) * a.t.v_st + (int64_t)hk * a.t.v_sh, dkp + r * a.t.dk_st, dvp + r * a.t.dv_st);
+    }
+  }
 }
 
 #define DCP_F32_LAUNCH(KERNEL, INNER)                                                                                     \

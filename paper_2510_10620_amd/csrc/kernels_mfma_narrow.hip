@@ -18,6 +18,7 @@
 // dK/dV 76.8 -> 1.29 ms.  What bounds them on large batches is the MFMA rate that the chip holds on real data: counting
 // the three parts of P and dS the three kernels execute 1 090, 1 128 and 950 TFLOP/s (65 536 causal tokens, log-normal).
 #include "mfma_dkv_kernel.h"
+#include "nonfinite.h"
 
 namespace dcp {
 
@@ -141,6 +142,18 @@ __device__ __forceinline__ void store_rows32(char* ot, const f32x16 (&acc)[D / 3
   __builtin_amdgcn_wave_barrier();
 }
 
+// Rows r < n_valid of a wave's D x 32 tile (lane = row) that hold a value which is not finite, as a bit mask.
+template <int D>
+__device__ __forceinline__ uint32_t rows_not_finite(const f32x16 (&acc)[D / 32], int n_valid) {
+  float probe = 0.f;
+#pragma unroll
+  for (int dt = 0; dt < D / 32; dt++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) probe = finite_probe(acc[dt][r], probe);
+  const uint64_t bad = __ballot(probe != 0.f);
+  return ((uint32_t)bad | (uint32_t)(bad >> 32)) & (n_valid < 32 ? (1u << n_valid) - 1u : 0xffffffffu);
+}
+
 // What the query-side kernels know about their workgroup's and their wave's rows.
 struct NQTile {
   int head, hk, blk_start, row0, n_rows, q_lo, q_hi, qoff, wrow0, w_rows, wq_lo, wq_hi, qi, e0, e1, unit;
@@ -205,6 +218,13 @@ __device__ __forceinline__ void load_own(bf16x8 (&f)[D / 16], const void* base, 
   const bf16_t* p = (const bf16_t*)base + row * st + head_off + 8 * (lane >> 5);
 #pragma unroll
   for (int ks = 0; ks < D / 16; ks++) f[ks] = as_frag(*(const uint4*)(p + 16 * ks));
+}
+
+// row r of the wave, for the functions of nonfinite.h
+__device__ __forceinline__ FixRow fix_row(const NQTile& q, int r) {
+  return {q.wq_lo + r, q.e0, q.e1,
+          make_int4(__builtin_amdgcn_readlane(q.qr.x, r), __builtin_amdgcn_readlane(q.qr.y, r), __builtin_amdgcn_readlane(q.qr.z, r),
+                    __builtin_amdgcn_readlane(q.qr.w, r))};
 }
 
 __device__ __forceinline__ void n_mask(f32x16& s, const NQTile& q, int kind, int ks32, int c0, int c1, int lane) {
@@ -329,7 +349,21 @@ __global__ __launch_bounds__(256, 4) void narrow_fwd_kernel(DevGroup g, KTensors
   }
   bf16_t* op = slot < 0 ? (bf16_t*)t.out + (int64_t)(q.blk_start + brow0 + q.qoff) * t.o_st + (int64_t)q.head * t.o_sh
                         : (bf16_t*)t.out + (((int64_t)slot * t.block_size + brow0) * t.hq + q.head) * D;
-  store_rows32<D>(ot, o, inv, lane, q.w_rows, op, slot < 0 ? t.o_st : (int64_t)t.hq * D);
+  const int64_t op_st = slot < 0 ? t.o_st : (int64_t)t.hq * D;
+  uint32_t again = rows_not_finite<D>(o, q.w_rows);
+  store_rows32<D>(ot, o, inv, lane, q.w_rows, op, op_st);
+  if (again) {
+    DCP_WAIT_VMCNT(0);   // the stores above come first
+    const KernelArgs a = kernel_args();
+    for (; again; again &= again - 1) {
+      const int r = __builtin_ctz(again);
+      if (lane_of(lt, r) != lane_of(lt, r)) continue;   // a NaN score: all of the row is NaN already
+      const FixRow f = fix_row(q, r);
+      const float mr = lane_of(m, r);
+      fix_out<bf16_t, D>(a.g, a.t, f, q.hk, (const bf16_t*)a.t.q + (int64_t)(f.qi + q.qoff) * a.t.q_st + (int64_t)q.head * a.t.q_sh,
+                         mr == -INFINITY ? 0.f : mr * c_log2, lane_of(inv, r), op + r * op_st);
+    }
+  }
 }
 
 template <int D, bool RANGES>
@@ -414,8 +448,20 @@ __global__ __launch_bounds__(256, 3) void narrow_dq_kernel(DevGroup g, KTensors 
     DCP_WAIT_VMCNT(0);
     __syncthreads();
   }
-  store_rows32<D>(stages + wave * (32 * N::kORow), dq, t.scale, lane, q.w_rows,
-                  (bf16_t*)t.dq + (int64_t)(q.wq_lo + q.qoff) * t.dq_st + (int64_t)q.head * t.dq_sh, t.dq_st);
+  bf16_t* dqp = (bf16_t*)t.dq + (int64_t)(q.wq_lo + q.qoff) * t.dq_st + (int64_t)q.head * t.dq_sh;
+  uint32_t again = rows_not_finite<D>(dq, q.w_rows);
+  store_rows32<D>(stages + wave * (32 * N::kORow), dq, t.scale, lane, q.w_rows, dqp, t.dq_st);
+  if (again) {
+    DCP_WAIT_VMCNT(0);   // the stores above come first
+    const KernelArgs a = kernel_args();
+    for (; again; again &= again - 1) {
+      const int r = __builtin_ctz(again);
+      const FixRow f = fix_row(q, r);
+      const int64_t mem = f.qi + q.qoff;
+      fix_dq<bf16_t, D>(a.g, a.t, f, q.hk, (const bf16_t*)a.t.q + mem * a.t.q_st + (int64_t)q.head * a.t.q_sh,
+                        (const bf16_t*)a.t.dout + mem * a.t.do_st + (int64_t)q.head * a.t.do_sh, lane_of(lse2, r), lane_of(delta, r), dqp + r * a.t.dq_st);
+    }
+  }
 }
 
 // A workgroup's eight waves are NG = 8 / KW groups of KW waves: a wave has 32 keys, the groups own the same 32 KW keys
@@ -602,8 +648,22 @@ __global__ __launch_bounds__(512, 2) void narrow_dkv_kernel(DevGroup g, KTensors
   __syncthreads();
   if (group > 0) return;
   char* ot = all_stages + wave * (32 * N::kORow);
-  store_rows32<D>(ot, dk, t.scale, lane, w_rows, (bf16_t*)t.dk + (int64_t)(wk_lo + koff) * t.dk_st + (int64_t)hk * t.dk_sh, t.dk_st);
-  store_rows32<D>(ot, dv, 1.f, lane, w_rows, (bf16_t*)t.dv + (int64_t)(wk_lo + koff) * t.dv_st + (int64_t)hk * t.dv_sh, t.dv_st);
+  bf16_t* dkp = (bf16_t*)t.dk + (int64_t)(wk_lo + koff) * t.dk_st + (int64_t)hk * t.dk_sh;
+  bf16_t* dvp = (bf16_t*)t.dv + (int64_t)(wk_lo + koff) * t.dv_st + (int64_t)hk * t.dv_sh;
+  uint32_t again = rows_not_finite<D>(dk, w_rows) | rows_not_finite<D>(dv, w_rows);
+  store_rows32<D>(ot, dk, t.scale, lane, w_rows, dkp, t.dk_st);
+  store_rows32<D>(ot, dv, 1.f, lane, w_rows, dvp, t.dv_st);
+  if (again) {
+    DCP_WAIT_VMCNT(0);   // the stores above come first
+    const KernelArgs a = kernel_args();
+    const WorkItem w1 = a.g.items[item];
+    const int s0 = RANGES ? uni(a.g.blk_s0[uni(a.g.unit_blk[uni(w1.unit)])]) : 0;
+    for (; again; again &= again - 1) {
+      const int r = __builtin_ctz(again), j = wk_lo + r;
+      fix_dkv<bf16_t, D>(a.g, a.t, j, uni(w1.e0), uni(w1.e1), hk, s0, (const bf16_t*)a.t.k + (int64_t)(j + koff) * a.t.k_st + (int64_t)hk * a.t.k_sh,
+                         (const bf16_t*)a.t.v + (int64_t)(j + koff) * a.t.v_st + (int64_t)hk * a.t.v_sh, dkp + r * a.t.dk_st, dvp + r * a.t.dv_st);
+    }
+  }
 }
 
 #define DCP_NARROW_LAUNCH(KERNEL)                                                              \
