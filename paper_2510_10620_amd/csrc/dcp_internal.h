@@ -123,8 +123,10 @@ struct dcp_plan {
   const int32_t *d_merge_ptr = nullptr, *d_merge_idx = nullptr, *d_slot_qblk = nullptr, *d_q_mem0 = nullptr, *d_blk_t32 = nullptr;
   // (group id, tile rows, heads, segments) -> work list; heads: the number of workgroups launched per item -- KV heads
   // for the dK/dV group (the long items are then cut so that no workgroup outlasts the rest of the grid by much), query
-  // heads per KV head for the others -- or 0: strict longest-first, nothing cut; segments: see DevGroup
+  // heads per KV head for the others, whose lists hold the same items whatever it is (it only weighs their order, and is
+  // no part of the key) -- or 0: strict longest-first, nothing cut; segments: see DevGroup
   typedef std::tuple<int, int, int, int> ItemKey;
+  static ItemKey item_key(int group_id, int tile_rows, int heads, int n_seg) { return ItemKey(group_id, tile_rows, group_id == 2 ? heads : 0, n_seg); }
   std::map<ItemKey, dcp::HostItems> h_items;
   std::map<ItemKey, dcp::DevItems> items;
 

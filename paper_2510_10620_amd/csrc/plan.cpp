@@ -594,7 +594,7 @@ static constexpr int32_t kMaxParts = 64;
 
 const HostItems& dcp_plan::host_items(int gid, int tile_rows, int heads, int n_seg) {
   std::lock_guard<std::mutex> lock(mu);
-  const ItemKey key(gid, tile_rows, heads, n_seg);
+  const ItemKey key = item_key(gid, tile_rows, heads, n_seg);
   auto hit = h_items.find(key);
   if (hit != h_items.end()) return hit->second;
   HostGroup* hg = gid == 0 ? &fwd : (gid == 1 ? &bwdq : &bwdkv);
@@ -701,7 +701,8 @@ const HostItems& dcp_plan::host_items(int gid, int tile_rows, int heads, int n_s
     // the launch played through as list scheduling shows; it keeps strict longest-first.  (Longest-first by four or
     // eight classes of length with sequences grouped inside a class was in between on traffic and 0.8 % slower.)
     // Who runs the list: in the dK/dV launch the whole chip, once per KV head; in the others the XCDs that share a KV
-    // head's list, each item once per query head.
+    // head's list, each item once per query head (the number of the first caller: any order is right, and a plan made
+    // ready for one number of query heads serves every other).
     const int64_t slots_n = gid == 2 ? kResidentWorkgroups : kResidentWorkgroups / 8 * n_seg;
     auto play = [&](const std::vector<Scored>& v) {
       std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> slots;
@@ -799,7 +800,7 @@ dcp_status_t dcp_plan::group_for(int gid, int tile_rows, hipStream_t stream, Dev
   const HostItems& hi = host_items(gid, tile_rows, heads, n_seg);
   std::lock_guard<std::mutex> lock(mu);
   DevGroup dg = gid == 0 ? d_fwd : (gid == 1 ? d_bwdq : d_bwdkv);
-  const ItemKey key(gid, tile_rows, heads, n_seg);
+  const ItemKey key = item_key(gid, tile_rows, heads, n_seg);
   auto it = items.find(key);
   if (it == items.end()) {
     if (!may_alloc) return fail(DCP_ERR_INVALID_ARG, "the plan has no work list for this shape yet: call dcp_plan_prepare first");

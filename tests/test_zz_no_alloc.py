@@ -63,3 +63,20 @@ def test_static_workspace_backward_refuses_what_it_cannot_serve():
         P.dcp_block_attn_bwd_static(plan, q, k, k, q, lse, q, q, k, k, 0.1, None)
     assert ei.value.status == P.DCP_ERR_WORKSPACE and "static scratch" in str(ei.value)
     assert bool((q == 0).all()) and bool((k == 0).all())
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 64)])
+def test_static_workspace_backward_serves_other_query_heads(dtype, d):
+    """A plan prepared for 8/2 heads serves the static backward of 4/2: the work lists hold the same items."""
+    import torch
+    import paper_2510_10620_amd as P
+    w = W.custom_workload("static_heads", [300, 100], 128, 4, 2, d, dtype, W.MaskSpec("causal"), seed=65, input_scale=0.5)
+    g = H.GpuRun(w, W.make_tensors(w), H.oracle_table(w))
+    P.dcp_plan_prepare(g.plan, 8, 2, d, P.DCP_BF16 if dtype == "bf16" else P.DCP_F32)
+    g.forward_only()
+    outs = [torch.full_like(x, float("nan")) for x in (g.q, g.k, g.v)]
+    P.dcp_block_attn_bwd_static(g.plan, g.q, g.k, g.v, g.out, g.lse, g.dout, *outs, w.softmax_scale, g.ranges)
+    torch.cuda.synchronize()
+    got = [H.from_torch(x) for x in outs]
+    for a, b in zip(got, g.backward()):
+        assert (a == b).all()
