@@ -147,6 +147,8 @@ dcp_status_t dcp_plan_destroy(dcp_plan_t* plan);
  * and waits for `stream` (the upload of the arrays); after it, dcp_block_attn_fwd, dcp_block_attn_bwd and
  * dcp_merge_partials with this plan and shape only enqueue kernels.  Without it the first of those calls does the same
  * work itself, once.  Call it after dcp_plan_set_block_buffers, if that is used.  Errors as for the launching calls.
+ * The lists are the same for every kernel family, but for the cut dK/dV list of bf16 with D = 128: outside that shape a
+ * prepared plan serves calls that their strides or their `impl` send to another family, and other head counts.
  * A prepared plan's launches are kernel launches and nothing else (no memset or copy nodes, no events), so they may
  * be recorded into a HIP graph by stream capture and replayed. */
 dcp_status_t dcp_plan_prepare(dcp_plan_t* plan, int32_t hq, int32_t hkv, int32_t d, int32_t dtype, int32_t impl,

@@ -23,8 +23,11 @@ dcp_status_t fail(dcp_status_t code, const std::string& msg);
       return ::dcp::fail(DCP_ERR_HIP, std::string(#expr) + ": " + hipGetErrorString(e__));    \
   } while (0)
 
+// Rows of a work item, the same in every kernel family, so that they share the lists.
+static constexpr int kItemRows = 128;
+
 // One piece of work: `unit` indexes a Group's units, `tile` is the tile number inside the unit's own block
-// (tile * tile_rows is the first row), [e0, e1) the table rows of the unit this piece covers (all of them, unless
+// (tile * kItemRows is the first row), [e0, e1) the table rows of the unit this piece covers (all of them, unless
 // the work list was built with splitting).  `pslot` >= 0: the piece is one part of a split (unit, tile) and leaves
 // its fp32 result in that slot of the partial-sum workspace; -1: it writes the output itself.  32 bytes.
 struct WorkItem {
@@ -121,21 +124,22 @@ struct dcp_plan {
   int32_t* dev_arena = nullptr;
   dcp::DevGroup d_fwd{}, d_bwdq{}, d_bwdkv{};
   const int32_t *d_merge_ptr = nullptr, *d_merge_idx = nullptr, *d_slot_qblk = nullptr, *d_q_mem0 = nullptr, *d_blk_t32 = nullptr;
-  // (group id, tile rows, heads, segments) -> work list; heads: the number of workgroups launched per item -- KV heads
-  // for the dK/dV group (the long items are then cut so that no workgroup outlasts the rest of the grid by much), query
-  // heads per KV head for the others, whose lists hold the same items whatever it is (it only weighs their order, and is
-  // no part of the key) -- or 0: strict longest-first, nothing cut; segments: see DevGroup
-  typedef std::tuple<int, int, int, int> ItemKey;
-  static ItemKey item_key(int group_id, int tile_rows, int heads, int n_seg) { return ItemKey(group_id, tile_rows, group_id == 2 ? heads : 0, n_seg); }
+  // (group id, KV heads the dK/dV list is cut for, segments) -> work list.  The long items of a cut dK/dV list are split so
+  // that no workgroup outlasts the rest of the grid by much; 0: whole items, the only kind the other groups have.
+  // Segments: see DevGroup.
+  typedef std::tuple<int, int, int> ItemKey;
+  static ItemKey item_key(int group_id, int heads, int n_seg) { return ItemKey(group_id, group_id == 2 ? heads : 0, n_seg); }
   std::map<ItemKey, dcp::HostItems> h_items;
   std::map<ItemKey, dcp::DevItems> items;
 
   // may_alloc = false: fail (DCP_ERR_INVALID_ARG) instead of creating a device copy that does not exist yet
   dcp_status_t ensure_device(hipStream_t stream, bool may_alloc = true);
-  // group id: 0 fwd, 1 bwdq, 2 bwdkv.  Host only; takes the plan's lock.
-  const dcp::HostItems& host_items(int group_id, int tile_rows, int heads, int n_seg = 1);
-  dcp_status_t group_for(int group_id, int tile_rows, hipStream_t stream, dcp::DevGroup* out, int heads = 0,
-                         bool may_alloc = true, int n_seg = 1);
+  // group id: 0 fwd, 1 bwdq, 2 bwdkv.  heads: for dK/dV see ItemKey; for the others the query heads per KV head, which
+  // weigh the order of the list where the call creates it.  Host only; takes the plan's lock.
+  const dcp::HostItems& host_items(int group_id, int heads, int n_seg);
+  // Where the list is missing and must not be created (may_alloc false, or `stream` is being captured), a list of whole
+  // items with other segments takes its place: the same work, dealt to the XCDs less well.
+  dcp_status_t group_for(int group_id, hipStream_t stream, dcp::DevGroup* out, int heads, int n_seg, bool may_alloc = true);
 };
 
 // Blockwise Copy list: validated entries cut into chunks of at most kCopyChunkRows rows.

@@ -71,8 +71,6 @@ dcp_status_t static_scratch(void** ptr);
 
 // scalar fp32-ALU family (any dtype; D in {32, 64, 128})
 bool scalar_supports(int32_t d);
-int scalar_fwd_tile();
-int scalar_bwd_tile();
 dcp_status_t scalar_fwd(const DevGroup& g, const KTensors& t, int32_t dtype, hipStream_t s);
 dcp_status_t scalar_bwd_dq(const DevGroup& g, const KTensors& t, int32_t dtype, hipStream_t s);
 dcp_status_t scalar_bwd_dkv(const DevGroup& g, const KTensors& t, int32_t dtype, hipStream_t s);
@@ -82,9 +80,6 @@ dcp_status_t scalar_bwd_dkv(const DevGroup& g, const KTensors& t, int32_t dtype,
 bool mfma_supports(int32_t dtype, int32_t d);
 // the dK/dV kernel takes cut work items (KTensors::part)
 inline bool mfma_splits_dkv(int32_t dtype, int32_t d) { return dtype == DCP_BF16 && d == 128; }
-int mfma_fwd_tile();
-int mfma_dq_tile();
-int mfma_dkv_tile();
 size_t mfma_dkv_part_bytes(int32_t n_pslots, int32_t hkv);   // size of KTensors::part for that many slots
 dcp_status_t mfma_fwd(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_bwd_dq(const DevGroup& g, const KTensors& t, hipStream_t s);

@@ -76,7 +76,6 @@ dcp_status_t mfma_range_bounds(const DevGroup& g, const KTensors& t, const int32
   return DCP_OK;
 }
 
-int mfma_dkv_tile() { return 128; }
 
 dcp_status_t mfma_bwd_dkv(const DevGroup& g, const KTensors& t, hipStream_t s) {
   if (g.n_items == 0) return DCP_OK;

@@ -207,8 +207,6 @@ __global__ __launch_bounds__(256, 2) void mfma_dq_kernel(DevGroup g, KTensors t)
   store_tile32((wave < 2 ? stage0 : stage1) + (wave & 1) * (32 * kORow), st.dq, t.scale, lane, w_rows, op, t.dq_st);
 }
 
-int mfma_dq_tile() { return 128; }
-
 dcp_status_t mfma_bwd_dq(const DevGroup& g, const KTensors& t, hipStream_t s) {
   if (g.n_items == 0) return DCP_OK;
   if (t.dtype == DCP_F32) return mfma_f32_dq(g, t, s);

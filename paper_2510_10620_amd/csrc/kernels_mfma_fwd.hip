@@ -470,7 +470,6 @@ bool mfma_supports(int32_t dtype, int32_t d) { return (dtype == DCP_BF16 || dtyp
 #ifndef DCP_FWD_NQ
 #define DCP_FWD_NQ 1
 #endif
-int mfma_fwd_tile() { return FwdCfg<DCP_FWD_NQ>::kTileM; }
 
 dcp_status_t mfma_fwd(const DevGroup& g, const KTensors& t, hipStream_t s) {
   if (g.n_items == 0) return DCP_OK;

@@ -1,6 +1,7 @@
 // Scalar (fp32 vector-ALU) kernels for blockwise attention: one thread owns one query row (forward,
 // dQ) or one key row (dK/dV) of one head and walks the listed blocks key by key.  They serve callers that ask for
-// DCP_IMPL_SCALAR, a second opinion on the MFMA kernels that shares none of their code, and compute exactly the
+// DCP_IMPL_SCALAR, a second opinion on the MFMA kernels that shares none of their code, and fp32 or narrow tensors
+// with longer token strides than those kernels' 32-bit offsets reach.  They compute exactly the
 // steps of the block-parallel attention listing (Listing 1, line 5) with the online-softmax
 // accumulation across the rows of one output unit.
 #include "device_utils.h"
@@ -9,13 +10,15 @@
 namespace dcp {
 
 static constexpr int kTile = 64;  // rows per workgroup = one wavefront
+static constexpr int kSub = kItemRows / kTile;   // workgroups per work item
 
 template <typename T, int D>
 __global__ __launch_bounds__(kTile) void scalar_fwd_kernel(DevGroup g, KTensors t) {
-  const WorkItem w = g.items[blockIdx.x];
+  const WorkItem w = g.items[blockIdx.x / kSub];
   const int h = blockIdx.y, hk = h / (t.hq / t.hkv);
   const int qb = g.unit_blk[w.unit];
-  const int row = w.tile * kTile + threadIdx.x;
+  const int row = w.tile * kItemRows + (blockIdx.x % kSub) * kTile + threadIdx.x;
+  if (row - (int)threadIdx.x >= g.blk_len[qb]) return;
   const bool valid = row < g.blk_len[qb];
   const int i = g.blk_start[qb] + (valid ? row : 0);
   const int im = i + g.unit_moff[w.unit];   // the row's place in the Q-type buffers
@@ -69,10 +72,11 @@ __global__ __launch_bounds__(kTile) void scalar_fwd_kernel(DevGroup g, KTensors 
 
 template <typename T, int D>
 __global__ __launch_bounds__(kTile) void scalar_dq_kernel(DevGroup g, KTensors t) {
-  const WorkItem w = g.items[blockIdx.x];
+  const WorkItem w = g.items[blockIdx.x / kSub];
   const int h = blockIdx.y, hk = h / (t.hq / t.hkv);
   const int qb = g.unit_blk[w.unit];
-  const int row = w.tile * kTile + threadIdx.x;
+  const int row = w.tile * kItemRows + (blockIdx.x % kSub) * kTile + threadIdx.x;
+  if (row - (int)threadIdx.x >= g.blk_len[qb]) return;
   const bool valid = row < g.blk_len[qb];
   const int i = g.blk_start[qb] + (valid ? row : 0);
   const int im = i + g.unit_moff[w.unit];
@@ -115,10 +119,11 @@ __global__ __launch_bounds__(kTile) void scalar_dq_kernel(DevGroup g, KTensors t
 // One thread per key row of one KV head; sums over the query heads of the group.
 template <typename T, int D>
 __global__ __launch_bounds__(kTile) void scalar_dkv_kernel(DevGroup g, KTensors t) {
-  const WorkItem w = g.items[blockIdx.x];
+  const WorkItem w = g.items[blockIdx.x / kSub];
   const int hk = blockIdx.y, G = t.hq / t.hkv;
   const int kb = g.unit_blk[w.unit];
-  const int row = w.tile * kTile + threadIdx.x;
+  const int row = w.tile * kItemRows + (blockIdx.x % kSub) * kTile + threadIdx.x;
+  if (row - (int)threadIdx.x >= g.blk_len[kb]) return;
   const bool valid = row < g.blk_len[kb];
   const int j = g.blk_start[kb] + (valid ? row : 0);
   const int jm = j + g.unit_moff[w.unit];   // the row's place in the KV-type buffers
@@ -165,12 +170,10 @@ __global__ __launch_bounds__(kTile) void scalar_dkv_kernel(DevGroup g, KTensors 
 }
 
 bool scalar_supports(int32_t d) { return d == 32 || d == 64 || d == 128; }
-int scalar_fwd_tile() { return kTile; }
-int scalar_bwd_tile() { return kTile; }
 
 #define DCP_SCALAR_DISPATCH(KERNEL, HEADS)                                                              \
   if (g.n_items == 0) return DCP_OK;                                                                    \
-  dim3 grid(g.n_items, HEADS), block(kTile);                                                            \
+  dim3 grid(g.n_items * kSub, HEADS), block(kTile);                                                       \
   if (dtype == DCP_F32) {                                                                               \
     if (t.d == 32) hipLaunchKernelGGL((KERNEL<float, 32>), grid, block, 0, s, g, t);                    \
     else if (t.d == 64) hipLaunchKernelGGL((KERNEL<float, 64>), grid, block, 0, s, g, t);               \

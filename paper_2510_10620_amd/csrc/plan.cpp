@@ -592,9 +592,9 @@ static int64_t tile_cost(int32_t kind, int64_t r0, int64_t r1, int64_t c0, int64
 static constexpr int64_t kResidentWorkgroups = 512;
 static constexpr int32_t kMaxParts = 64;
 
-const HostItems& dcp_plan::host_items(int gid, int tile_rows, int heads, int n_seg) {
+const HostItems& dcp_plan::host_items(int gid, int heads, int n_seg) {
   std::lock_guard<std::mutex> lock(mu);
-  const ItemKey key = item_key(gid, tile_rows, heads, n_seg);
+  const ItemKey key = item_key(gid, heads, n_seg);
   auto hit = h_items.find(key);
   if (hit != h_items.end()) return hit->second;
   HostGroup* hg = gid == 0 ? &fwd : (gid == 1 ? &bwdq : &bwdkv);
@@ -607,10 +607,10 @@ const HostItems& dcp_plan::host_items(int gid, int tile_rows, int heads, int n_s
     int32_t b = hg->unit_blk[u];
     if (b < 0) continue;  // unused slot
     if (buffers && (gid == 2 ? kv_slot[b] : q_slot[b]) < 0) continue;  // block absent from its buffer: nothing to write
-    int32_t nt = (blk_len[b] + tile_rows - 1) / tile_rows;
+    int32_t nt = (blk_len[b] + kItemRows - 1) / kItemRows;
     for (int32_t t = 0; t < nt; t++) {
-      int64_t r0 = blk_start[b] + (int64_t)t * tile_rows;
-      int64_t r1 = std::min<int64_t>(r0 + tile_rows, blk_start[b] + blk_len[b]);
+      int64_t r0 = blk_start[b] + (int64_t)t * kItemRows;
+      int64_t r1 = std::min<int64_t>(r0 + kItemRows, blk_start[b] + blk_len[b]);
       int64_t cost = 0;
       for (int32_t e = hg->ptr[u]; e < hg->ptr[u + 1]; e++)
         cost += tile_cost(hg->ent_kind[e], r0, r1, hg->ent_start[e], hg->ent_start[e] + hg->ent_len[e], gid == 2);
@@ -653,8 +653,8 @@ const HostItems& dcp_plan::host_items(int gid, int tile_rows, int heads, int n_s
         const int32_t n_parts = (int32_t)std::min<int64_t>(std::min<int64_t>(want, n_ent), kMaxParts);
         if (n_parts <= 1) { cut.push_back(it); continue; }
         const WorkItem& w = it.w;
-        int64_t r0 = blk_start[hg->unit_blk[w.unit]] + (int64_t)w.tile * tile_rows;
-        int64_t r1 = std::min<int64_t>(r0 + tile_rows, blk_start[hg->unit_blk[w.unit]] + blk_len[hg->unit_blk[w.unit]]);
+        int64_t r0 = blk_start[hg->unit_blk[w.unit]] + (int64_t)w.tile * kItemRows;
+        int64_t r1 = std::min<int64_t>(r0 + kItemRows, blk_start[hg->unit_blk[w.unit]] + blk_len[hg->unit_blk[w.unit]]);
         ecost.assign(n_ent, 0);
         for (int32_t e = w.e0; e < w.e1; e++)
           ecost[e - w.e0] = tile_cost(hg->ent_kind[e], r0, r1, hg->ent_start[e], hg->ent_start[e] + hg->ent_len[e], gid == 2);
@@ -793,15 +793,26 @@ static dcp_status_t upload(const std::vector<T>& v, T** dev, hipStream_t stream)
   return DCP_OK;
 }
 
-dcp_status_t dcp_plan::group_for(int gid, int tile_rows, hipStream_t stream, DevGroup* out, int heads, bool may_alloc,
-                                 int n_seg) {
+static bool is_capturing(hipStream_t stream) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(stream, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
+}
+
+dcp_status_t dcp_plan::group_for(int gid, hipStream_t stream, DevGroup* out, int heads, int n_seg, bool may_alloc) {
   dcp_status_t st = ensure_device(stream, may_alloc);
   if (st != DCP_OK) return st;
-  const HostItems& hi = host_items(gid, tile_rows, heads, n_seg);
+  const HostItems& hi = host_items(gid, heads, n_seg);
   std::lock_guard<std::mutex> lock(mu);
   DevGroup dg = gid == 0 ? d_fwd : (gid == 1 ? d_bwdq : d_bwdkv);
-  const ItemKey key = item_key(gid, tile_rows, heads, n_seg);
+  dg.n_seg = hi.n_seg;
+  for (int k = 0; k <= 8; k++) dg.seg[k] = hi.seg[k];
+  const ItemKey key = item_key(gid, heads, n_seg);
   auto it = items.find(key);
+  if (it == items.end() && (!may_alloc || is_capturing(stream)) && std::get<1>(key) == 0) {
+    for (it = items.begin(); it != items.end() && (std::get<0>(it->first) != gid || std::get<1>(it->first) != 0); ++it) {}
+    if (it != items.end())   // any cut of a list into n_seg runs covers it
+      for (int k = 0; k <= 8; k++) dg.seg[k] = (int32_t)((int64_t)it->second.n_items * std::min(k, n_seg) / n_seg);
+  }
   if (it == items.end()) {
     if (!may_alloc) return fail(DCP_ERR_INVALID_ARG, "the plan has no work list for this shape yet: call dcp_plan_prepare first");
     DevItems di;
@@ -818,8 +829,6 @@ dcp_status_t dcp_plan::group_for(int gid, int tile_rows, hipStream_t stream, Dev
   dg.n_items = it->second.n_items;
   dg.reduce = it->second.reduce;
   dg.n_reduce = it->second.n_reduce;
-  dg.n_seg = hi.n_seg;
-  for (int k = 0; k <= 8; k++) dg.seg[k] = hi.seg[k];
   *out = dg;
   return DCP_OK;
 }

@@ -16,6 +16,7 @@
 namespace dcp {
 extern int64_t g_fake_kv_rows;
 extern int32_t g_fake_n_slots;
+extern bool g_fake_capturing;
 long fake_rows_walked();
 }
 
@@ -154,7 +155,9 @@ static void one_case(Rng& r, int iter) {
   t.attn_ranges = ranges.data();
   t.out = slots ? (void*)o_part.data() : (void*)q.data();
   t.lse = slots ? lse_part.data() : lse.data();
-  if (rnd(r, 0, 1)) EXPECT(dcp_plan_prepare(plan, hq, hkv, d, dtype, DCP_IMPL_AUTO, nullptr) == DCP_OK);
+  const bool prepared = rnd(r, 0, 1) == 1;
+  if (prepared) EXPECT(dcp_plan_prepare(plan, hq, hkv, d, dtype, DCP_IMPL_AUTO, nullptr) == DCP_OK);
+  dcp::g_fake_capturing = prepared;
   EXPECT(dcp_block_attn_fwd(plan, &t, nullptr) == DCP_OK);
   if (slots) EXPECT(dcp_merge_partials(plan, o_part.data(), lse_part.data(), q.data(), (int64_t)hq * d, d, lse.data(), hq, d, dtype, nullptr) == DCP_OK);
   t.out = q.data(); t.lse = lse.data();
@@ -163,6 +166,19 @@ static void one_case(Rng& r, int iter) {
   EXPECT(posix_memalign(&ws, 256, wsb ? wsb : 256) == 0);
   EXPECT(dcp_block_attn_bwd(plan, &t, ws, wsb, nullptr) == DCP_OK);
   if (wsb > 256) EXPECT(dcp_block_attn_bwd(plan, &t, ws, wsb - 1, nullptr) == DCP_ERR_WORKSPACE);
+  if (prepared && !mfma) {   // lists of whole items serve other head counts, either family and every stride, also under capture
+    dcp_tensors_t t2 = t;
+    t2.hq = rnd(r, 1, hq);
+    t2.hkv = t2.hq % hkv == 0 ? hkv : 1;
+    t2.impl = rnd(r, 0, 1) ? DCP_IMPL_SCALAR : DCP_IMPL_AUTO;
+    if (rnd(r, 0, 1)) t2.k_stride_t = (int64_t(1) << 24) + 8;   // (the stand-in kernels look at rows, not at strides)
+    t2.out = slots ? (void*)o_part.data() : (void*)q.data();
+    t2.lse = slots ? lse_part.data() : lse.data();
+    EXPECT(dcp_block_attn_fwd(plan, &t2, nullptr) == DCP_OK);
+    t2.out = q.data(); t2.lse = lse.data();
+    EXPECT(dcp_block_attn_bwd(plan, &t2, ws, wsb, nullptr) == DCP_OK);
+  }
+  dcp::g_fake_capturing = false;
   EXPECT(dcp_bwd_delta(&t, q_rows, (float*)ws, nullptr) == DCP_OK || wsb < (size_t)hq * q_rows * 4);
 
   // Blockwise Copy: block-wise moves into the Q-type buffer; lists that leave their buffers or collide are refused

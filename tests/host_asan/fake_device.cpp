@@ -17,10 +17,15 @@
 #include "kernels.h"
 
 // ---------------------------------------------------------------- HIP runtime, host memory only
+namespace dcp { bool g_fake_capturing = false; }   // a stream under capture: no hipMalloc, nothing that is waited for
 extern "C" {
-hipError_t hipMalloc(void** p, size_t n) { *p = std::malloc(n ? n : 1); return *p ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipMalloc(void** p, size_t n) {
+  if (dcp::g_fake_capturing) return hipErrorStreamCaptureUnsupported;
+  *p = std::malloc(n ? n : 1); return *p ? hipSuccess : hipErrorOutOfMemory;
+}
 hipError_t hipFree(void* p) { std::free(p); return hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) { *s = dcp::g_fake_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone; return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
@@ -44,7 +49,7 @@ long fake_rows_walked() { return g_rows_walked; }
 
 // What every attention kernel reads before its tile loop, and per table row inside it.
 // own_rows / other_rows: extents of the tensors on the unit's side and on the other side.
-static dcp_status_t walk_group(const DevGroup& g, int tile_rows, int64_t own_rows, int64_t other_rows, int32_t n_slots,
+static dcp_status_t walk_group(const DevGroup& g, int64_t own_rows, int64_t other_rows, int32_t n_slots,
                                int32_t block_size, bool reduce_list) {
   // the segments of the work list cover it in order
   WALK_CHECK(g.n_seg >= 1 && g.n_seg <= 8 && g.seg[0] == 0 && g.seg[g.n_seg] == g.n_items, "work-list segments do not cover the list");
@@ -57,10 +62,10 @@ static dcp_status_t walk_group(const DevGroup& g, int tile_rows, int64_t own_row
     WALK_CHECK(g.blk_start[b] == w.blk_start && g.blk_len[b] == w.blk_len, "work item's block record disagrees with the block arrays");
     WALK_CHECK(g.unit_moff[w.unit] == w.moff, "work item's memory offset disagrees with the unit's");
     WALK_CHECK(g.blk_s0[b] <= w.blk_start, "sequence start after the block");
-    WALK_CHECK(w.tile >= 0 && (int64_t)w.tile * tile_rows < w.blk_len, "tile past the block");
+    WALK_CHECK(w.tile >= 0 && (int64_t)w.tile * kItemRows < w.blk_len, "tile past the block");
     WALK_CHECK(g.ptr[w.unit] <= w.e0 && w.e0 <= w.e1 && w.e1 <= g.ptr[w.unit + 1], "table rows outside the unit's CSR range");
-    const int64_t r0 = (int64_t)w.blk_start + (int64_t)w.tile * tile_rows + w.moff;
-    const int64_t r1 = (int64_t)w.blk_start + std::min<int64_t>(w.blk_len, (int64_t)(w.tile + 1) * tile_rows) + w.moff;
+    const int64_t r0 = (int64_t)w.blk_start + (int64_t)w.tile * kItemRows + w.moff;
+    const int64_t r1 = (int64_t)w.blk_start + std::min<int64_t>(w.blk_len, (int64_t)(w.tile + 1) * kItemRows) + w.moff;
     const int32_t slot = g.unit_out[w.unit];
     if (slot >= 0) WALK_CHECK(slot < n_slots && w.blk_len <= block_size, "output slot out of range");
     else WALK_CHECK(r0 >= 0 && r1 <= own_rows, "own rows outside the tensor");
@@ -86,29 +91,24 @@ static dcp_status_t walk_group(const DevGroup& g, int tile_rows, int64_t own_row
 dcp_status_t static_scratch(void** ptr) { static char buf[256]; *ptr = buf; return DCP_OK; }
 
 bool scalar_supports(int32_t d) { return d == 32 || d == 64 || d == 128; }
-int scalar_fwd_tile() { return 64; }
-int scalar_bwd_tile() { return 64; }
 bool mfma_supports(int32_t dtype, int32_t d) { return dtype == DCP_BF16 && d == 128; }
-int mfma_fwd_tile() { return 128; }
-int mfma_dq_tile() { return 128; }
-int mfma_dkv_tile() { return 128; }
 size_t mfma_dkv_part_bytes(int32_t n_pslots, int32_t hkv) { return (size_t)n_pslots * (size_t)hkv * 2 * 128 * 128 * sizeof(float); }
 
 // the fake tensors' extents travel in KTensors::q_rows (Q side) and, for the KV side, in a global the driver sets
 int64_t g_fake_kv_rows = 0;
 int32_t g_fake_n_slots = 0;
 
-dcp_status_t scalar_fwd(const DevGroup& g, const KTensors& t, int32_t, hipStream_t) { return walk_group(g, 64, t.q_rows, g_fake_kv_rows, g_fake_n_slots, t.block_size, false); }
-dcp_status_t scalar_bwd_dq(const DevGroup& g, const KTensors& t, int32_t, hipStream_t) { return walk_group(g, 64, t.q_rows, g_fake_kv_rows, 0, t.block_size, false); }
-dcp_status_t scalar_bwd_dkv(const DevGroup& g, const KTensors& t, int32_t, hipStream_t) { return walk_group(g, 64, g_fake_kv_rows, t.q_rows, 0, t.block_size, false); }
-dcp_status_t mfma_fwd(const DevGroup& g, const KTensors& t, hipStream_t) { return walk_group(g, 128, t.q_rows, g_fake_kv_rows, g_fake_n_slots, t.block_size, false); }
+dcp_status_t scalar_fwd(const DevGroup& g, const KTensors& t, int32_t, hipStream_t) { return walk_group(g, t.q_rows, g_fake_kv_rows, g_fake_n_slots, t.block_size, false); }
+dcp_status_t scalar_bwd_dq(const DevGroup& g, const KTensors& t, int32_t, hipStream_t) { return walk_group(g, t.q_rows, g_fake_kv_rows, 0, t.block_size, false); }
+dcp_status_t scalar_bwd_dkv(const DevGroup& g, const KTensors& t, int32_t, hipStream_t) { return walk_group(g, g_fake_kv_rows, t.q_rows, 0, t.block_size, false); }
+dcp_status_t mfma_fwd(const DevGroup& g, const KTensors& t, hipStream_t) { return walk_group(g, t.q_rows, g_fake_kv_rows, g_fake_n_slots, t.block_size, false); }
 dcp_status_t mfma_bwd_dq(const DevGroup& g, const KTensors& t, hipStream_t) {
   // the preprocess fused into this kernel writes one float per (head, row) into each of the two workspace arrays
   if (g.n_items > 0) { t.delta_w[(int64_t)t.hq * t.q_rows - 1] = 0.f; t.lse2_w[(int64_t)t.hq * t.q_rows - 1] = 0.f; }
-  return walk_group(g, 128, t.q_rows, g_fake_kv_rows, 0, t.block_size, false);
+  return walk_group(g, t.q_rows, g_fake_kv_rows, 0, t.block_size, false);
 }
 dcp_status_t mfma_bwd_dkv(const DevGroup& g, const KTensors& t, hipStream_t) {
-  dcp_status_t st = walk_group(g, 128, g_fake_kv_rows, t.q_rows, 0, t.block_size, true);
+  dcp_status_t st = walk_group(g, g_fake_kv_rows, t.q_rows, 0, t.block_size, true);
   if (st != DCP_OK) return st;
   // every part slot of a cut item lies inside the partial-sum area of the workspace: touch its last float
   for (int32_t i = 0; i < g.n_items; i++)

@@ -80,3 +80,44 @@ def test_static_workspace_backward_serves_other_query_heads(dtype, d):
     got = [H.from_torch(x) for x in outs]
     for a, b in zip(got, g.backward()):
         assert (a == b).all()
+
+
+@pytest.mark.parametrize("how", ["stride", "scalar", "heads", "stride_captured"])
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 32)])
+def test_a_prepared_plan_serves_every_route(dtype, d, how):
+    """After dcp_plan_prepare the static backward runs whatever kernel family the call leads to (a token stride beyond
+    the MFMA kernels' 2^24 elements, the thread-per-row kernels by name) and whatever its head counts; and the ordinary
+    calls only enqueue kernels, so that they can be captured."""
+    import torch
+    import paper_2510_10620_amd as P
+    heads = (4, 4) if how == "heads" else (1, 1)
+    w = W.custom_workload("static_routes", [3] if how.startswith("stride") else [3, 90], 64, *heads, d, dtype, W.MaskSpec("causal"),
+                          seed=66, input_scale=0.5)
+    tensors, table = W.make_tensors(w), H.oracle_table(w)
+    impl = P.DCP_IMPL_SCALAR if how == "scalar" else P.DCP_IMPL_AUTO
+    g = H.GpuRun(w, tensors, table, impl=impl)
+    P.dcp_plan_prepare(g.plan, 8 if how == "heads" else heads[0], 2 if how == "heads" else heads[1], d,
+                       P.DCP_BF16 if dtype == "bf16" else P.DCP_F32)
+    if how.startswith("stride"):
+        k = torch.empty(2 * ((1 << 24) + 8) + d, dtype=g.k.dtype, device="cuda").as_strided((3, 1, d), ((1 << 24) + 8, d, 1))
+        k.copy_(g.k)
+        g.k = k
+    ws = torch.empty(max(256, P.dcp_bwd_workspace_bytes(g.plan, *heads, d, P.DCP_BF16 if dtype == "bf16" else P.DCP_F32)),
+                     dtype=torch.uint8, device="cuda")
+    outs = [torch.full(x.shape, float("nan"), dtype=x.dtype, device="cuda") for x in (g.q, g.k, g.v)]
+    if how == "stride_captured":
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            P.dcp_block_attn_fwd(g.plan, g.q, g.k, g.v, g.out, g.lse, w.softmax_scale, None, impl)
+            P.dcp_block_attn_bwd(g.plan, g.q, g.k, g.v, g.out, g.lse, g.dout, *outs, w.softmax_scale, ws, None, impl)
+        graph.replay()
+    else:
+        P.dcp_block_attn_bwd_static(g.plan, g.q, g.k, g.v, g.out.zero_(), g.lse.zero_(), g.dout, *outs, w.softmax_scale, None, impl)
+    torch.cuda.synchronize()
+    got = [H.from_torch(x) for x in outs]
+    if how == "stride_captured":
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all((H.from_torch(x) == a).all() for x, a in zip(outs, got))
+    for a, b in zip(got, g.backward()):
+        assert (a == b).all()
