@@ -509,12 +509,13 @@ __global__ __launch_bounds__(512, 2) void narrow_dkv_kernel(DevGroup g, KTensors
     const int head = hk * G + it.hh, last = it.q1 - 1;
     dmaq.load(stage, (const bf16_t*)t.q + (int64_t)head * t.q_sh, it.qs + it.moff, last + it.moff, wave);
     dmao.load(stage + N::kBytes, (const bf16_t*)t.dout + (int64_t)head * t.do_sh, it.qs + it.moff, last + it.moff, wave);
-    const int qrow = min(it.qs + lane, last), qmem = qrow + it.moff;
-    if (wave == 0) dma4((unsigned)qmem * 4u, uni_ptr(t.lse2 + (int64_t)head * t.q_rows), lds_addr(stage + LSE));
-    if (wave == 1) dma4((unsigned)qmem * 4u, uni_ptr(t.delta + (int64_t)head * t.q_rows), lds_addr(stage + DEL));
+    const int ql = min(lane, last - it.qs);   // row of the tile: the lane's 32-bit offset runs from the tile's first row
+    const int64_t at = (int64_t)head * t.q_rows + it.qs + it.moff;
+    if (wave == 0) dma4((unsigned)ql * 4u, uni_ptr(t.lse2 + at), lds_addr(stage + LSE));
+    if (wave == 1) dma4((unsigned)ql * 4u, uni_ptr(t.delta + at), lds_addr(stage + DEL));
     if (RANGES && wave == KW - 2 && it.kind == 2) {
-      if (t.window > 0) *((int4*)(stage + RNG) + lane) = range_row(t, qrow, seq0);
-      else dma16((unsigned)qrow * 16u, uni_ptr(t.ranges), lds_addr(stage + RNG));
+      if (t.window > 0) *((int4*)(stage + RNG) + lane) = range_row(t, it.qs + ql, seq0);
+      else dma16((unsigned)ql * 16u, uni_ptr(t.ranges + 4 * (int64_t)it.qs), lds_addr(stage + RNG));
     }
     if (RANGES && wave == KW - 1 && it.kind == 2)
       dma16((unsigned)(lane & 3) * 16u, uni_ptr(t.qbounds + (int64_t)(it.t32 + 2 * it.jt) * 8), lds_addr(stage + BND));

@@ -282,7 +282,7 @@ __global__ __launch_bounds__(256, 2) void mfma_dkv_kernel(DevGroup g, KTensors t
       // the rows' ranges: copied from the array, or (WINDOW rows) worked out and stored; the barrier that ends the
       // step orders the store before the reads
       if (t.window > 0) *((int4*)(stage + kStageRanges) + ln) = range_row(t, qrow, seq0);
-      else dma16((unsigned)qrow * 16u, uni_ptr(t.ranges), lds_addr(stage + kStageRanges));
+      else dma16((unsigned)(qrow - it.qs) * 16u, uni_ptr(t.ranges + 4 * (int64_t)it.qs), lds_addr(stage + kStageRanges));
     }
     // the bounds of the tile's two halves (4 x 16 B; the other lanes repeat them into the reserved space)
     if (RANGES && wave == 3 && it.kind == 2 && t.qbounds)
