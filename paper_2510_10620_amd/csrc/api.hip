@@ -288,7 +288,7 @@ dcp_status_t dcp::bwd_launch(dcp_plan_t* plan, const dcp_tensors_t* t, void* wor
   if (k.masked && use_mfma) {
     int32_t* qb = (int32_t*)((char*)workspace + 2 * n_hT);
     k.qbounds = qb;
-    if ((st = mfma_range_bounds(gkv, k, plan->d_blk_t32, plan->n_blocks, qb, s)) != DCP_OK) return st;
+    if ((st = mfma_range_bounds(gkv, k, plan->d_blk_t32, plan->n_blocks, plan->longest_block, qb, s)) != DCP_OK) return st;
   }
   if (use_mfma) {
     // the MFMA dQ kernel computes delta and the rescaled LSE of its own rows and leaves them for the dK/dV kernel

@@ -104,7 +104,7 @@ struct DevItems {
 }  // namespace dcp
 
 struct dcp_plan {
-  int32_t n_seq = 0, block_size = 0, n_blocks = 0, n_slots = 0;
+  int32_t n_seq = 0, block_size = 0, n_blocks = 0, n_slots = 0, longest_block = 0;
   int64_t total_tokens = 0, n_kept = 0;
   bool use_slots = false, has_ranges = false, has_window = false;
   int32_t window = 0, sink = 0;   // parameters of the WINDOW rows (window 0: not set)

@@ -91,8 +91,8 @@ dcp_status_t mfma_narrow_fwd(const DevGroup& g, const KTensors& t, hipStream_t s
 dcp_status_t mfma_narrow_dq(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_narrow_dkv(const DevGroup& g, const KTensors& t, hipStream_t s);
 // per 32-row tile of every block: bounds of its rows' range arrays -> qbounds [n_t32 + 1][8]
-dcp_status_t mfma_range_bounds(const DevGroup& g, const KTensors& t, const int32_t* blk_t32, int32_t n_blocks, int32_t* qbounds,
-                               hipStream_t s);
+dcp_status_t mfma_range_bounds(const DevGroup& g, const KTensors& t, const int32_t* blk_t32, int32_t n_blocks, int32_t longest_block,
+                               int32_t* qbounds, hipStream_t s);
 
 // streaming (HBM-bound) kernels
 dcp_status_t stream_merge(const int32_t* merge_ptr, const int32_t* merge_idx, const int32_t* blk_mem0,

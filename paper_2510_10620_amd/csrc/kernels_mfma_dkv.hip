@@ -68,14 +68,13 @@ __global__ __launch_bounds__(256) void dkv_reduce_kernel(DevGroup g, KTensors t)
   *(uint4*)(dst + (mem0 + row) * st_t + (int64_t)hk * st_h + col) = o;
 }
 
-dcp_status_t mfma_range_bounds(const DevGroup& g, const KTensors& t, const int32_t* blk_t32, int32_t n_blocks, int32_t* qbounds,
-                               hipStream_t s) {
+dcp_status_t mfma_range_bounds(const DevGroup& g, const KTensors& t, const int32_t* blk_t32, int32_t n_blocks, int32_t longest_block,
+                               int32_t* qbounds, hipStream_t s) {
   if (n_blocks == 0) return DCP_OK;
-  hipLaunchKernelGGL(range_bounds_kernel, dim3((t.block_size + 127) / 128, n_blocks), dim3(256), 0, s, g, t, blk_t32, qbounds);
+  hipLaunchKernelGGL(range_bounds_kernel, dim3((longest_block - 1) / 128 + 1, n_blocks), dim3(256), 0, s, g, t, blk_t32, qbounds);
   DCP_HIP_TRY(hipGetLastError());
   return DCP_OK;
 }
-
 
 dcp_status_t mfma_bwd_dkv(const DevGroup& g, const KTensors& t, hipStream_t s) {
   if (g.n_items == 0) return DCP_OK;

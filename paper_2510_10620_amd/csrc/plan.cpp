@@ -308,7 +308,10 @@ extern "C" dcp_status_t dcp_plan_create(dcp_plan_t** out, const int32_t* cu, int
   pl->q_rows = pl->kv_rows = pl->total_tokens;
   pl->q_moff.assign(pl->n_blocks, 0);
   pl->blk_t32.assign(pl->n_blocks + 1, 0);
-  for (int32_t b = 0; b < pl->n_blocks; b++) pl->blk_t32[b + 1] = pl->blk_t32[b] + (p.len[b] + 31) / 32;
+  for (int32_t b = 0; b < pl->n_blocks; b++) {
+    pl->blk_t32[b + 1] = pl->blk_t32[b] + (p.len[b] + 31) / 32;
+    pl->longest_block = std::max(pl->longest_block, p.len[b]);
+  }
   pl->kv_moff.assign(pl->n_blocks, 0);
   pl->cu.assign(cu, cu + (n_seq > 0 ? n_seq + 1 : 0));
   pl->blk_start = p.start;

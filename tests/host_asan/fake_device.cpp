@@ -115,10 +115,11 @@ dcp_status_t mfma_bwd_dkv(const DevGroup& g, const KTensors& t, hipStream_t) {
     if (g.items[i].pslot >= 0) t.part[((int64_t)(g.items[i].pslot + 1) * t.hkv) * 2 * 128 * 128 - 1] = 0.f;
   return DCP_OK;
 }
-dcp_status_t mfma_range_bounds(const DevGroup& g, const KTensors& t, const int32_t* blk_t32, int32_t n_blocks, int32_t* qbounds,
-                               hipStream_t) {
+dcp_status_t mfma_range_bounds(const DevGroup& g, const KTensors& t, const int32_t* blk_t32, int32_t n_blocks, int32_t longest_block,
+                               int32_t* qbounds, hipStream_t) {
   for (int32_t b = 0; b < n_blocks; b++) {
     const int32_t n32 = (g.blk_len[b] + 31) / 32;
+    WALK_CHECK(g.blk_len[b] <= longest_block, "a block longer than the longest");
     WALK_CHECK(blk_t32[b + 1] - blk_t32[b] == n32, "32-row tile prefix sums disagree with the block lengths");
     for (int32_t x = 0; x < n32; x++)
       for (int k = 0; k < 8; k++) qbounds[(int64_t)(blk_t32[b] + x) * 8 + k] = 0;   // inside the workspace area

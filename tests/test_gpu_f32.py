@@ -60,3 +60,26 @@ def test_selector_and_token_strides(dtype, d):
     far.k = k
     for a, b in zip(ref.forward() + ref.backward(), far.forward() + far.backward()):
         assert (a == b).all()
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 32), ("bf16", 64)])
+def test_largest_block_size_under_a_mask(dtype, d):
+    """Blocks as long as an int allows (one per sequence) in a table with per-token ranges, whose bounds the backward
+    works out block by block."""
+    import torch
+    import paper_2510_10620_amd as P
+    B = 2 ** 31 - 1
+    w = W.custom_workload("blocks", [150, 33], B, 2, 1, d, dtype, W.MaskSpec("window", window=3), seed=71, input_scale=0.5)
+    tensors, table = W.make_tensors(w), P.dcp_build_block_table(w.cu_seqlens, B, w.ranges)
+    assert (table[:, 2] == W.MASK_RANGES).all()
+    fast, slow = H.GpuRun(w, tensors, table), H.GpuRun(w, tensors, table, impl=P.DCP_IMPL_SCALAR)
+    ref = slow.forward() + slow.backward()
+    got = fast.forward()
+    outs = [torch.full_like(x, float("nan")) for x in (fast.q, fast.k, fast.v)]
+    code = P.DCP_BF16 if dtype == "bf16" else P.DCP_F32
+    ws = torch.full((P.dcp_bwd_workspace_bytes(fast.plan, 2, 1, d, code),), 0x7f, dtype=torch.uint8, device="cuda")   # bounds left as they are hide every tile
+    P.dcp_block_attn_bwd(fast.plan, fast.q, fast.k, fast.v, fast.out, fast.lse, fast.dout, *outs, w.softmax_scale, ws, fast.ranges)
+    torch.cuda.synchronize()
+    got += tuple(H.from_torch(x) for x in outs)
+    names = ("out", "lse", "dq", "dk", "dv")
+    H.check(w, dict(zip(names, got)), dict(zip(names, ref)), names, f"block size {B}")
