@@ -79,8 +79,8 @@ static bool short_strides(const dcp_tensors_t* t) {
          t->dq_stride_t <= kMax && t->dk_stride_t <= kMax && t->dv_stride_t <= kMax;
 }
 
-// Chooses the kernel family.  AUTO: MFMA where it is covered and, outside bf16 with D = 128, the strides are short; else
-// the thread-per-row kernels.  A caller that asks for MFMA by name gets the bf16, D = 128 kernels or a refusal.
+// Chooses the kernel family.  AUTO: MFMA where it is covered and, outside bf16 with D = 128, the strides are short (and, as
+// the callers check, the launch fits); else the thread-per-row kernels.  A caller that asks for MFMA by name gets the bf16, D = 128 kernels or a refusal.
 static dcp_status_t pick_impl(const dcp_tensors_t* t, bool* use_mfma) {
   const bool wide = t->dtype == DCP_BF16 && t->d == 128;
   const bool m_ok = mfma_supports(t->dtype, t->d) && (wide || short_strides(t)), s_ok = scalar_supports(t->d);
@@ -161,6 +161,7 @@ extern "C" dcp_status_t dcp_block_attn_fwd(dcp_plan_t* plan, const dcp_tensors_t
   hipStream_t s = (hipStream_t)stream;
   DevGroup g;
   if ((st = plan->group_for(0, s, &g, t->hq / t->hkv, xcd_segments(t->hkv))) != DCP_OK) return st;
+  use_mfma = use_mfma && mfma_launch_fits(g, false, t->dtype, t->d, t->hq, t->hkv);
   KTensors k = pack(plan, t);
   ProfScope ps(DCP_K_FWD, s);
   return use_mfma ? mfma_fwd(g, k, s) : scalar_fwd(g, k, t->dtype, s);
@@ -278,6 +279,7 @@ dcp_status_t dcp::bwd_launch(dcp_plan_t* plan, const dcp_tensors_t* t, void* wor
   const int n_seg = xcd_segments(t->hkv);
   if ((st = plan->group_for(1, s, &gq, t->hq / t->hkv, n_seg, may_alloc)) != DCP_OK) return st;
   if ((st = plan->group_for(2, s, &gkv, cut_heads(use_mfma, t->dtype, t->d, t->hkv), n_seg, may_alloc)) != DCP_OK) return st;
+  use_mfma = use_mfma && mfma_launch_fits(gq, false, t->dtype, t->d, t->hq, t->hkv) && mfma_launch_fits(gkv, true, t->dtype, t->d, t->hq, t->hkv);
   KTensors k = pack(plan, t);
   const size_t n_hT = wsz.n_hT;
   k.part = (float*)((char*)workspace + 2 * wsz.n_hT + wsz.n_bounds);

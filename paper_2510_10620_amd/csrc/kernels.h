@@ -41,15 +41,29 @@ __device__ __forceinline__ int4 range_row(const KTensors& t, int i, int s0) {
 
 // Grid of a launch whose workgroups find their work with decode_wg: 8 times the largest number of workgroups any XCD
 // needs for its (KV head, segment) units.
-inline int xcd_grid(const DevGroup& g, int heads_outer, int heads_inner) {
+inline int64_t xcd_grid(const DevGroup& g, int heads_outer, int heads_inner) {
   const int upx = (heads_outer * g.n_seg) / 8;
-  int most = 0;
+  int64_t most = 0;
   for (int x = 0; x < 8; x++) {
-    int n = 0;
-    for (int u = x * upx; u < (x + 1) * upx; u++) n += (g.seg[u % g.n_seg + 1] - g.seg[u % g.n_seg]) * heads_inner;
+    int64_t n = 0;
+    for (int u = x * upx; u < (x + 1) * upx; u++) n += (int64_t)(g.seg[u % g.n_seg + 1] - g.seg[u % g.n_seg]) * heads_inner;
     most = n > most ? n : most;
   }
   return 8 * most;
+}
+
+// Workgroups that the fp32 and the narrow-head kernels launch per work item and KV head, and their threads.
+// kF32Sub: 32 rows each; the narrow dK/dV kernel takes two per item where there are few (kernels_mfma_narrow.hip).
+constexpr int kF32Sub = kItemRows / 32, kF32Threads = 512, kNarrowThreads = 256, kNarrowDkvThreads = 512;
+constexpr int64_t kNarrowDkvFew = 1024;
+
+// A launch counts its threads in 32 bits.  Whether that of a query-side group (or the dK/dV group) of these kernels fits;
+// the D = 128 kernels' tensors would outgrow the memory first.
+inline bool mfma_launch_fits(const DevGroup& g, bool dkv, int32_t dtype, int32_t d, int hq, int hkv) {
+  if (dtype == DCP_BF16 && d == 128) return true;
+  const bool f32 = dtype == DCP_F32;
+  const int per_item = (dkv ? 1 : hq / hkv) * (f32 ? kF32Sub : dkv && g.n_items * (int64_t)hkv <= kNarrowDkvFew ? 2 : 1);
+  return xcd_grid(g, hkv, per_item) * (f32 ? kF32Threads : dkv ? kNarrowDkvThreads : kNarrowThreads) <= (int64_t)UINT32_MAX;
 }
 
 // Optional per-kernel event timing (see dcp_profile_enable).

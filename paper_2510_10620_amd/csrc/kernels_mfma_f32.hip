@@ -27,10 +27,10 @@ namespace {
 
 constexpr float kLog2eF = 1.44269504088896340736f;
 constexpr float kLn2F = 0.69314718055994530942f;
-constexpr int kWaves = 8;       // waves of a workgroup: they share the 32 rows and split the other side
-constexpr int kThreads = 64 * kWaves;
+constexpr int kThreads = kF32Threads;
+constexpr int kWaves = kThreads / 64;   // waves of a workgroup: they share the 32 rows and split the other side
 constexpr int kRows = 32;       // rows of a workgroup, and of a tile of the other side
-constexpr int kSub = 4;         // workgroups per 128-row work item
+constexpr int kSub = kF32Sub;   // workgroups per work item
 constexpr float kRaise = 8.f;   // the running maximum is raised when a tile exceeds it by more than 2^8
 
 __device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }

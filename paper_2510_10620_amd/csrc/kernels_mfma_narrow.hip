@@ -238,7 +238,7 @@ __device__ __forceinline__ void n_mask(f32x16& s, const NQTile& q, int kind, int
 }  // namespace
 
 template <int D, bool RANGES>
-__global__ __launch_bounds__(256, 4) void narrow_fwd_kernel(DevGroup g, KTensors t) {
+__global__ __launch_bounds__(kNarrowThreads, 4) void narrow_fwd_kernel(DevGroup g, KTensors t) {
   typedef Narrow<D> N;
   __shared__ __attribute__((aligned(1024))) char stages[4 * N::kBytes];   // two stages, each [K tile | V tile]
   __shared__ int wg_bounds[4][8];
@@ -367,7 +367,7 @@ __global__ __launch_bounds__(256, 4) void narrow_fwd_kernel(DevGroup g, KTensors
 }
 
 template <int D, bool RANGES>
-__global__ __launch_bounds__(256, 3) void narrow_dq_kernel(DevGroup g, KTensors t) {
+__global__ __launch_bounds__(kNarrowThreads, 3) void narrow_dq_kernel(DevGroup g, KTensors t) {
   typedef Narrow<D> N;
   __shared__ __attribute__((aligned(1024))) char stages[4 * N::kBytes];
   __shared__ int wg_bounds[4][8];
@@ -470,7 +470,7 @@ __global__ __launch_bounds__(256, 3) void narrow_dq_kernel(DevGroup g, KTensors 
 // waits for its longest (with P and dS in two parts, 16 384 tokens, 16/4 heads, D 64: 1.44 ms with one group of four waves,
 // 1.05 with two, 0.93 with four groups of two waves; with many items the two-group form is the faster, see mfma_narrow_dkv).
 template <int D, int KW, bool RANGES>
-__global__ __launch_bounds__(512, 2) void narrow_dkv_kernel(DevGroup g, KTensors t) {
+__global__ __launch_bounds__(kNarrowDkvThreads, 2) void narrow_dkv_kernel(DevGroup g, KTensors t) {
   constexpr int NG = 8 / KW, SUB = 4 / KW;   // workgroups per 128-key work item
   typedef Narrow<D> N;
   // stage: Q tile, dO tile, then per query row lse2, -delta and ranges, and the range bounds of the tile's two halves
@@ -684,7 +684,7 @@ dcp_status_t mfma_narrow_dq(const DevGroup& g, const KTensors& t, hipStream_t s)
 
 template <int KW>
 static void narrow_dkv_launch(const DevGroup& g, const KTensors& t, hipStream_t s) {
-  const dim3 grid(xcd_grid(g, t.hkv, 4 / KW)), block(512);
+  const dim3 grid(xcd_grid(g, t.hkv, 4 / KW)), block(kNarrowDkvThreads);
   if (t.masked) {
     if (t.d == 32) hipLaunchKernelGGL((narrow_dkv_kernel<32, KW, true>), grid, block, 0, s, g, t);
     else hipLaunchKernelGGL((narrow_dkv_kernel<64, KW, true>), grid, block, 0, s, g, t);
@@ -700,7 +700,7 @@ dcp_status_t mfma_narrow_dkv(const DevGroup& g, const KTensors& t, hipStream_t s
   // D 64, log-normal lengths: 2 048 items (65 536 tokens, 16/4 heads) 2.90 and 2.98 ms, (16 384 tokens, 16/16) 0.71 and 0.81;
   // 1 024 items (32 768 tokens, 16/4) causal 1.90 and 2.04, sink and window 1.70 and 1.15; 512 items (16 384, 16/4) 1.06 and
   // 0.86, (65 536, 4/1) 1.47 and 0.81; 128 items (4 096, 16/4) 0.26 and 0.15 ms.
-  if ((int64_t)g.n_items * t.hkv > 1024) narrow_dkv_launch<4>(g, t, s);
+  if ((int64_t)g.n_items * t.hkv > kNarrowDkvFew) narrow_dkv_launch<4>(g, t, s);
   else narrow_dkv_launch<2>(g, t, s);
   DCP_HIP_TRY(hipGetLastError());
   return DCP_OK;

@@ -135,8 +135,9 @@ static void one_case(Rng& r, int iter) {
     std::vector<int32_t> buf((size_t)len + 1);
     EXPECT(dcp_plan_export(plan, (dcp_export_t)which, buf.data(), len, &len) == DCP_OK);
   }
-  const bool mfma = rnd(r, 0, 1) == 1;
-  const int hkv = rnd(r, 1, 3), hq = hkv * rnd(r, 1, 4), d = mfma ? 128 : 64, dtype = mfma ? DCP_BF16 : DCP_F32;
+  const bool wide = rnd(r, 0, 1) == 1;   // the shape whose dK/dV items are cut
+  const int hkv = rnd(r, 1, 3), hq = hkv * rnd(r, 1, 4), dtype = wide || rnd(r, 0, 1) ? DCP_BF16 : DCP_F32;
+  const int d = wide ? 128 : 32 << rnd(r, 0, dtype == DCP_BF16 ? 1 : 2);
   { int64_t ni = 0; EXPECT(dcp_plan_export_dkv_items(plan, hkv, nullptr, 0, &ni) == DCP_OK);
     std::vector<int32_t> it((size_t)ni * 5 + 1); EXPECT(dcp_plan_export_dkv_items(plan, hkv, it.data(), ni, &ni) == DCP_OK); }
 
@@ -166,7 +167,7 @@ static void one_case(Rng& r, int iter) {
   EXPECT(posix_memalign(&ws, 256, wsb ? wsb : 256) == 0);
   EXPECT(dcp_block_attn_bwd(plan, &t, ws, wsb, nullptr) == DCP_OK);
   if (wsb > 256) EXPECT(dcp_block_attn_bwd(plan, &t, ws, wsb - 1, nullptr) == DCP_ERR_WORKSPACE);
-  if (prepared && !mfma) {   // lists of whole items serve other head counts, either family and every stride, also under capture
+  if (prepared && !wide) {   // lists of whole items serve other head counts, either family and every stride, also under capture
     dcp_tensors_t t2 = t;
     t2.hq = rnd(r, 1, hq);
     t2.hkv = t2.hq % hkv == 0 ? hkv : 1;
@@ -238,10 +239,35 @@ static void one_case(Rng& r, int iter) {
   EXPECT(dcp_plan_destroy(plan) == DCP_OK);
 }
 
+// 2^26 tokens of four fp32 heads: 2^32 threads in the fp32 kernels' launches, so the thread-per-row family takes the call
+static void largest_batch() {
+  const int T = 1 << 26, B = 1 << 20, nb = T / B, h = 4, d = 32;
+  const int32_t cu[2] = {0, T};
+  std::vector<int32_t> table;
+  for (int b = 0; b < nb; b++) table.insert(table.end(), {b, b, DCP_MASK_CAUSAL});
+  dcp_plan_t* plan = nullptr;
+  EXPECT(dcp_plan_create(&plan, cu, 1, B, table.data(), nb, nullptr, 0) == DCP_OK);
+  dcp::g_fake_kv_rows = T; dcp::g_fake_n_slots = 0;
+  alignas(16) static char some[16];   // the stand-in kernels touch no tensor
+  dcp_tensors_t t{};
+  t.hq = t.hkv = h; t.d = d; t.dtype = DCP_F32; t.softmax_scale = 0.1f;
+  t.q = t.k = t.v = t.dout = t.out = t.dq = t.dk = t.dv = some; t.lse = (float*)some;
+  t.q_stride_t = t.k_stride_t = t.v_stride_t = t.o_stride_t = t.do_stride_t = t.dq_stride_t = t.dk_stride_t = t.dv_stride_t = h * d;
+  t.q_stride_h = t.k_stride_h = t.v_stride_h = t.o_stride_h = t.do_stride_h = t.dq_stride_h = t.dk_stride_h = t.dv_stride_h = d;
+  EXPECT(dcp_block_attn_fwd(plan, &t, nullptr) == DCP_OK);
+  const size_t wsb = dcp_bwd_workspace_bytes(plan, h, h, d, DCP_F32);
+  void* ws = nullptr;
+  EXPECT(posix_memalign(&ws, 256, wsb) == 0);
+  EXPECT(dcp_block_attn_bwd(plan, &t, ws, wsb, nullptr) == DCP_OK);
+  std::free(ws);
+  EXPECT(dcp_plan_destroy(plan) == DCP_OK);
+}
+
 int main(int argc, char** argv) {
   const int iters = argc > 1 ? std::atoi(argv[1]) : 150;
   Rng r(20251028);
   for (int i = 0; i < iters && g_fail == 0; i++) one_case(r, i);
+  if (g_fail == 0) largest_batch();
   // the empty plan and NULL arguments
   dcp_plan_t* plan = nullptr;
   int32_t cu0 = 0;

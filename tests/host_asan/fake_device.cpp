@@ -91,7 +91,7 @@ static dcp_status_t walk_group(const DevGroup& g, int64_t own_rows, int64_t othe
 dcp_status_t static_scratch(void** ptr) { static char buf[256]; *ptr = buf; return DCP_OK; }
 
 bool scalar_supports(int32_t d) { return d == 32 || d == 64 || d == 128; }
-bool mfma_supports(int32_t dtype, int32_t d) { return dtype == DCP_BF16 && d == 128; }
+bool mfma_supports(int32_t dtype, int32_t d) { return (dtype == DCP_BF16 || dtype == DCP_F32) && (d == 32 || d == 64 || d == 128); }
 size_t mfma_dkv_part_bytes(int32_t n_pslots, int32_t hkv) { return (size_t)n_pslots * (size_t)hkv * 2 * 128 * 128 * sizeof(float); }
 
 // the fake tensors' extents travel in KTensors::q_rows (Q side) and, for the KV side, in a global the driver sets
@@ -101,13 +101,17 @@ int32_t g_fake_n_slots = 0;
 dcp_status_t scalar_fwd(const DevGroup& g, const KTensors& t, int32_t, hipStream_t) { return walk_group(g, t.q_rows, g_fake_kv_rows, g_fake_n_slots, t.block_size, false); }
 dcp_status_t scalar_bwd_dq(const DevGroup& g, const KTensors& t, int32_t, hipStream_t) { return walk_group(g, t.q_rows, g_fake_kv_rows, 0, t.block_size, false); }
 dcp_status_t scalar_bwd_dkv(const DevGroup& g, const KTensors& t, int32_t, hipStream_t) { return walk_group(g, g_fake_kv_rows, t.q_rows, 0, t.block_size, false); }
-dcp_status_t mfma_fwd(const DevGroup& g, const KTensors& t, hipStream_t) { return walk_group(g, t.q_rows, g_fake_kv_rows, g_fake_n_slots, t.block_size, false); }
+// a launch of more threads than 32 bits count must not come this way
+#define FITS(dkv) WALK_CHECK(mfma_launch_fits(g, dkv, t.dtype, t.d, t.hq, t.hkv), "more threads than a launch can count")
+dcp_status_t mfma_fwd(const DevGroup& g, const KTensors& t, hipStream_t) { FITS(false); return walk_group(g, t.q_rows, g_fake_kv_rows, g_fake_n_slots, t.block_size, false); }
 dcp_status_t mfma_bwd_dq(const DevGroup& g, const KTensors& t, hipStream_t) {
+  FITS(false);
   // the preprocess fused into this kernel writes one float per (head, row) into each of the two workspace arrays
   if (g.n_items > 0) { t.delta_w[(int64_t)t.hq * t.q_rows - 1] = 0.f; t.lse2_w[(int64_t)t.hq * t.q_rows - 1] = 0.f; }
   return walk_group(g, t.q_rows, g_fake_kv_rows, 0, t.block_size, false);
 }
 dcp_status_t mfma_bwd_dkv(const DevGroup& g, const KTensors& t, hipStream_t) {
+  FITS(true);
   dcp_status_t st = walk_group(g, g_fake_kv_rows, t.q_rows, 0, t.block_size, true);
   if (st != DCP_OK) return st;
   // every part slot of a cut item lies inside the partial-sum area of the workspace: touch its last float
