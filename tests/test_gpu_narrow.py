@@ -1,6 +1,6 @@
 """The bf16 kernels for heads of 32 and 64 at the sizes where they can go wrong, against the fp64 oracle: rows and blocks
 around their 32-row sub-tiles, 64-row tiles and 128-row work items, every mask kind, slots and strided inputs.  Bounds:
-those of bf16 I/O in helpers.TOL; and, for O, what 16 significant bits of P and one bf16 rounding allow."""
+those of bf16 I/O in helpers.TOL; and, for O, one bf16 rounding beside fp32 sums."""
 import numpy as np
 import pytest
 
@@ -29,8 +29,8 @@ def test_narrow_tiles(d, B, heads, spec):
     out, lse = g.forward()
     dq, dk, dv = g.backward()
     H.check(w, dict(out=out, lse=lse, dq=dq, dk=dk, dv=dv), ref, ALL, f"narrow D{d} B{B} {spec.kind}")
-    # O = sum_j P_j v_j with P to 2^-17 (and sum_j P_j = 1), rounded to bf16 once: half an ulp is at most 2^-8 |O|; the
-    # fp32 sums add less than 2^-17 max |v| again
+    # O = sum_j P_j v_j (and sum_j P_j = 1), rounded to bf16 once: half an ulp is at most 2^-8 |O|; the scores, weights and
+    # fp32 sums add less than 2^-16 max |v|
     vmax = np.abs(W.to_f64(w, tensors["v"])).max()
     assert (np.abs(out - ref["out"]) <= 2.0 ** -8 * np.abs(ref["out"]) + 2.0 ** -16 * vmax).all()
 
@@ -47,6 +47,27 @@ def test_narrow_slots_strides_and_empty_rows():
     out, lse = g.forward()
     dq, dk, dv = g.backward()
     H.check(w, dict(out=out, lse=lse, dq=dq, dk=dk, dv=dv), H.oracle_full(w, tensors, table), ALL, "narrow slots")
+
+
+@pytest.mark.parametrize("d", [32, 64])
+@pytest.mark.parametrize("n_items", [64, 65])
+@pytest.mark.parametrize("spec,window_rows", [(W.MaskSpec("causal"), False), (W.MaskSpec("lambda", window=50, sink=9), False),
+                                              (W.MaskSpec("lambda", window=50, sink=9), True)], ids=["causal", "ranges", "window"])
+def test_narrow_dkv_on_both_sides_of_its_rule(d, n_items, spec, window_rows):
+    """Up to 1 024 (work item, KV head) pairs the dK/dV kernel takes 64 keys per workgroup in four groups of waves, above
+    that 128 keys in two: 64 and 65 items with 16 KV heads.  Sequences of 1 to 128 tokens beside one of 700."""
+    lens = [700, 129, 128, 127, 65, 64, 33, 1] + [1 + 7 * i % 128 for i in range(n_items - 14)]
+    w = W.custom_workload("narrow_rule", lens, 128, 32, 16, d, "bf16", spec, seed=72, input_scale=0.5)
+    assert sum(-(-n // 128) for n in lens) == n_items
+    tensors, table = W.make_tensors(w), H.oracle_table(w)
+    ref = H.oracle_full(w, tensors, table)
+    t = table.copy()
+    if window_rows:
+        t[t[:, 2] == W.MASK_RANGES, 2] = W.MASK_WINDOW
+    g = H.GpuRun(w, tensors, t, window=(spec.window, spec.sink) if window_rows else None)
+    out, lse = g.forward()
+    dq, dk, dv = g.backward()
+    H.check(w, dict(out=out, lse=lse, dq=dq, dk=dk, dv=dv), ref, ALL, f"narrow D{d} {n_items} items {spec.kind}")
 
 
 @pytest.mark.parametrize("d", [32, 64])

@@ -78,6 +78,24 @@ def test_inf_and_nan_reach_visible_pairs_only(dtype, d, spec):
             _same(a, b, w, f"{name} planted, {n}")
 
 
+@pytest.mark.parametrize("d", [32, 64])
+def test_inf_and_nan_in_a_large_narrow_batch(d):
+    """More than 1 024 (work item, KV head) pairs: the other form of the narrow dK/dV kernel."""
+    import torch
+    import paper_2510_10620_amd as P
+    w = W.custom_workload("nonfinite_l", [700, 129] + [40] * 57, 128, 16, 16, d, "bf16", W.MaskSpec("causal"), seed=73, input_scale=0.5)
+    tensors, table = W.make_tensors(w), H.oracle_table(w)
+    fast, slow = H.GpuRun(w, tensors, table), H.GpuRun(w, tensors, table, impl=P.DCP_IMPL_SCALAR)
+    for g in (fast, slow):
+        g.v[40, 3, 1], g.v[650, 5], g.q[300, 7, 2], g.dout[820, 15, 9] = float("inf"), float("nan"), float("inf"), float("nan")
+    ref = slow.forward()
+    for a, b, n in zip(fast.forward(), ref, ("out", "lse")):
+        _same(a, b, w, n)
+    lse = torch.where(torch.isfinite(slow.lse), slow.lse, 1.0)
+    for a, b, n in zip(fast.backward(slow.out, lse), slow.backward(slow.out, lse), ("dq", "dk", "dv")):
+        _same(a, b, w, n)
+
+
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 64)])
 def test_inf_in_partial_slots_and_block_buffers(dtype, d):
     """The same through partial slots and permuted block buffers (rows live elsewhere than their packed index says)."""

@@ -101,12 +101,14 @@ def test_random_small_cases(seed):
             f"random {seed}: lens {lens} B {B} {hq}/{hkv} {spec.kind}")
 
 
-@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 32), ("f32", 128), ("f32", 32)])
-def test_shapes_only_the_scalar_family_covers(dtype, d):
-    """dtype / head-dim pairs outside the MFMA family (bf16, D 128): AUTO must pick the scalar kernels and be right."""
+@pytest.mark.parametrize("impl", list(IMPLS), ids=list(IMPLS))
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 32), ("f32", 128), ("f32", 64), ("f32", 32)])
+def test_shapes_outside_bf16_d128(dtype, d, impl):
+    """dtype / head-dim pairs other than bf16 with D 128: AUTO takes the MFMA kernels for fp32 and narrow heads, SCALAR
+    by name the thread-per-row kernels, which long token strides lead to as well."""
     w = W.custom_workload("scalar_shapes", [210, 75], 64, 4, 2, d, dtype, W.MaskSpec("lambda", window=60, sink=5), seed=37,
                           input_scale=0.5)
-    run_case(w, H.oracle_table(w), IMPLS["auto"], label=f"{dtype}/D{d}")
+    run_case(w, H.oracle_table(w), IMPLS[impl], label=f"{dtype}/D{d}/{impl}")
 
 
 @pytest.mark.parametrize("hq,hkv", [(2, 2), (8, 1), (6, 2), (6, 3), (12, 12), (16, 16)])
