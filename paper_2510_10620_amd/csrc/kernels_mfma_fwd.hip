@@ -1,7 +1,7 @@
 // Blockwise attention forward on bf16 MFMA (Listing 1 line 5 + the in-kernel part of line 6).
 //
-// One workgroup (4 waves) owns a query tile of 4 * 32 * NQ rows of one head and walks the KV tiles
-// (64 keys) of every table row of its output unit.  Scores are computed transposed,
+// One workgroup (4 waves of 32 rows) owns 128 / HP query rows of HP = gcd(query heads per KV head, 4) heads of one KV head
+// (QSplit) and walks the KV tiles (64 keys) of every table row of its output unit.  Scores are computed transposed,
 // S^T = K Q^T, so that a lane owns one query column: the running max / sum are per-lane scalars,
 // the only cross-lane step is one exchange between the two wave halves per 32 keys, and P^T in the
 // MFMA accumulator layout is directly the B operand of O^T += V^T P^T.  K and V tiles are copied
@@ -14,18 +14,11 @@ namespace dcp {
 
 static constexpr float kLazy = 8.f;  // rescale threshold, log2 units
 
-#ifndef DCP_FWD_NW
-#define DCP_FWD_NW 4
-#endif
-static constexpr int kFwdWaves = DCP_FWD_NW;   // waves per workgroup
-static_assert(kFwdWaves == 4, "the step's inline tile copies are written for four waves (four copy instructions per wave and tile)");
+static constexpr int kFwdWaves = 4;   // waves per workgroup; the step's inline tile copies and QSplit are written for four
 
-template <int NQ>
-struct FwdCfg {
-  static constexpr int kWaveRows = 32 * NQ;
-  static constexpr int kTileM = kFwdWaves * kWaveRows;
-};
-
+// NQ: 32-query tiles per wave, which is 1 (QSplit).  It stays a parameter for the instruction schedule alone: with plain
+// members in place of arrays of one, the variant for per-token ranges spilled scalars and took 8.59 instead of 7.94 ms
+// (a 4 096-token window over 131 072 tokens; causal blockwise 2.66 and 2.75, the other variant the same).
 template <int NQ>
 struct FwdState {
   bf16x8 qf[NQ][8];
@@ -262,9 +255,9 @@ __device__ __forceinline__ void fwd_subtile(FwdState<NQ>& st, const char* k_lds,
 
 // RANGES = false: the table has no row with per-token ranges (RANGES or WINDOW) and every use of them folds away.
 template <int NQ, bool RANGES>
-__global__ __launch_bounds__(64 * kFwdWaves, (NQ == 1 ? 2 : 1)) void mfma_fwd_kernel(DevGroup g, KTensors t) {
+__global__ __launch_bounds__(64 * kFwdWaves, 2) void mfma_fwd_kernel(DevGroup g, KTensors t) {
+  static_assert(NQ == 1, "a wave has 32 rows");
   if (!RANGES) t.masked = 0;
-  constexpr int WR = FwdCfg<NQ>::kWaveRows, TM = FwdCfg<NQ>::kTileM;
   // two stages, each [K tile | V tile]
   __shared__ __attribute__((aligned(1024))) char stage0[2 * kTileBytes];
   __shared__ __attribute__((aligned(1024))) char stage1[2 * kTileBytes];
@@ -286,7 +279,7 @@ __global__ __launch_bounds__(64 * kFwdWaves, (NQ == 1 ? 2 : 1)) void mfma_fwd_ke
   if (n_rows <= 0) return;
   const int q_lo = blk_start + row0, q_hi = q_lo + n_rows - 1;
   const int wrow0 = uni(sp.wrow0);                    // wave's first row inside the tile
-  const int w_rows = max(0, min(WR, n_rows - wrow0)); // wave's valid rows
+  const int w_rows = max(0, min(32, n_rows - wrow0)); // wave's valid rows
   const int wq_lo = q_lo + wrow0, wq_hi = wq_lo + w_rows - 1;
 
   FwdState<NQ> st;
@@ -467,17 +460,13 @@ __global__ __launch_bounds__(64 * kFwdWaves, (NQ == 1 ? 2 : 1)) void mfma_fwd_ke
 
 bool mfma_supports(int32_t dtype, int32_t d) { return (dtype == DCP_BF16 || dtype == DCP_F32) && (d == 32 || d == 64 || d == 128); }
 
-#ifndef DCP_FWD_NQ
-#define DCP_FWD_NQ 1
-#endif
-
 dcp_status_t mfma_fwd(const DevGroup& g, const KTensors& t, hipStream_t s) {
   if (g.n_items == 0) return DCP_OK;
   if (t.dtype == DCP_F32) return mfma_f32_fwd(g, t, s);
   if (t.d != kD) return mfma_narrow_fwd(g, t, s);
   const int grid = xcd_grid(g, t.hkv, t.hq / t.hkv);
-  if (t.masked) hipLaunchKernelGGL((mfma_fwd_kernel<DCP_FWD_NQ, true>), dim3(grid), dim3(64 * kFwdWaves), 0, s, g, t);
-  else hipLaunchKernelGGL((mfma_fwd_kernel<DCP_FWD_NQ, false>), dim3(grid), dim3(64 * kFwdWaves), 0, s, g, t);
+  if (t.masked) hipLaunchKernelGGL((mfma_fwd_kernel<1, true>), dim3(grid), dim3(64 * kFwdWaves), 0, s, g, t);
+  else hipLaunchKernelGGL((mfma_fwd_kernel<1, false>), dim3(grid), dim3(64 * kFwdWaves), 0, s, g, t);
   DCP_HIP_TRY(hipGetLastError());
   return DCP_OK;
 }
