@@ -142,7 +142,7 @@ __device__ __forceinline__ f32x16 splat(float x) {
 }
 
 // The wave's tiles of a unit's table rows: 32-row tiles of the other side's blocks, numbered through the whole batch
-// (t32), so that tile number mod 4 deals them evenly to the waves whatever the block size.
+// (t32), so that tile number mod kWaves deals them evenly to the waves whatever the block size.
 struct Walk {
   const int4* rec;
   int e, e_end, wave;

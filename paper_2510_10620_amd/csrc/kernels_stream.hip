@@ -259,7 +259,7 @@ __global__ __launch_bounds__(256) void delta_kernel(const T* __restrict__ o, int
   const int ntok = (int)min((int64_t)kDeltaTok, total_tokens - t0);
   // HBM-bound.  Thread x keeps chunk x % chunks; the (token, head) pairs of the workgroup go round in steps of
   // 256 / chunks without a division, and four steps' loads are requested before the first is reduced (in DPP steps, not
-  // LDS ones): 65 536 tokens, 32 heads of 128 in bf16 207 -> 168 us, 6.4 TB/s.
+  // LDS ones): 65 536 tokens, 32 heads of 128 in bf16 207 -> 168-175 us, 6.0-6.4 TB/s.
   const int chunks = d / 8;  // power of two <= 32
   const int step = 256 / chunks, n_pairs = ntok * hq;
   const int c = threadIdx.x & (chunks - 1);
@@ -324,7 +324,7 @@ struct PartPtrs {
 };
 
 // HBM-bound.  One 16- or 32-byte piece per part and thread, all parts requested before the first is added, every byte
-// past the caches: two bf16 parts of 512 MiB 293 -> 248 us (6.5 TB/s) against 4 096 workgroups that walked the arrays
+// past the caches: two bf16 parts of 512 MiB 293 -> 248-258 us (6.2-6.5 TB/s) against 4 096 workgroups that walked the arrays
 // with one load at a time.
 template <typename TI, typename TO>
 __global__ __launch_bounds__(256) void sum_kernel(PartPtrs parts, int32_t n_parts, TO* __restrict__ dst, int64_t n8) {

@@ -698,14 +698,16 @@ const HostItems& dcp_plan::host_items(int gid, int heads, int n_seg) {
     // neighbours, its power being what is limited.  Forward and dQ: one KV head per
     // four (65 536 causal tokens, 4/1 heads) 362 -> 333 and 486 -> 445 us, 16/4 heads 1 362 -> 1 331 and 1 784 -> 1 729,
     // a 4 096-token window over 131 072 tokens 8.49 -> 8.23 and 10.69 -> 10.45 ms, 32/8 causal unchanged and 3 432 ->
-    // 3 398; where the table has RANGES rows their cost is a guess and the forward and dQ lists keep strict longest-first
-    // (causal blockwise dQ 3.20 -> 3.36 ms with the order that the guess allowed).  A dK/dV launch
+    // 3 398; where the table has RANGES rows the forward and dQ lists keep strict longest-first (causal blockwise dQ 3.20 ->
+    // 3.36 ms in the other order).  The cost of a row with per-token ranges is the same guess, half its area, for RANGES and
+    // for WINDOW rows: that they go different ways rests on these two measurements alone.  A dK/dV launch
     // of equal sequences balances badly in this order (every round of workgroups mixes long and short items), which
     // the launch played through as list scheduling shows; it keeps strict longest-first.  (Longest-first by four or
     // eight classes of length with sequences grouped inside a class was in between on traffic and 0.8 % slower.)
     // Who runs the list: in the dK/dV launch the whole chip, once per KV head; in the others the XCDs that share a KV
     // head's list, each item once per query head (the number of the first caller: any order is right, and a plan made
-    // ready for one number of query heads serves every other).
+    // ready for one number of query heads serves every other).  The residency assumed is that of the D = 128 kernels; the
+    // fp32 kernels (one workgroup of 512 threads a CU, four an item) take the order that comes of it, not weighed for them.
     const int64_t slots_n = gid == 2 ? kResidentWorkgroups : kResidentWorkgroups / 8 * n_seg;
     auto play = [&](const std::vector<Scored>& v) {
       std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> slots;
