@@ -109,7 +109,9 @@ struct FixRow {
   int4 qr;
 };
 
-// O of the row: exponents are taken against max2 (the row's maximum times c_log2), inv is 1 / the row's sum
+// O of the row: exponents are taken against max2 (the row's reference maximum times c_log2), inv is 1 / the row's sum, and
+// the weights are normalised before they meet V: the reference is raised lazily, so that exponentials reach 2^8, and with
+// V beyond 2^120 a sum that is finite when normalised would overflow (as it may have in the kernel's own pass).
 template <typename T, int D>
 __device__ void fix_out(const DevGroup& g, const KTensors& t, const FixRow& f, int hk, const T* q, float max2, float inv, T* dst) {
   const int lane = threadIdx.x & 63;
@@ -125,12 +127,12 @@ __device__ void fix_out(const DevGroup& g, const KTensors& t, const FixRow& f, i
       const uint64_t on = __ballot(vis);
       if (!on) continue;
       float p = 0.f;
-      if (vis) p = __builtin_amdgcn_exp2f(fmaf(dot_row<T, D>(q, kb + (int64_t)(j + moff) * t.k_st), c_log2, -max2));
+      if (vis) p = __builtin_amdgcn_exp2f(fmaf(dot_row<T, D>(q, kb + (int64_t)(j + moff) * t.k_st), c_log2, -max2)) * inv;
       add_rows<T, D>(acc, p, on, vb + (int64_t)(j0 + moff) * t.v_st, t.v_st, lane);
       if (all_nan(acc, lane < D)) { e = f.e1; break; }
     }
   }
-  put_row<T, D>(dst, acc, inv, lane);
+  put_row<T, D>(dst, acc, 1.f, lane);
 }
 
 // dQ of the row, which is 0 for a row that is off (lse2 = +inf)

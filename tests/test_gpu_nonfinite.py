@@ -78,6 +78,20 @@ def test_inf_and_nan_reach_visible_pairs_only(dtype, d, spec):
             _same(a, b, w, f"{name} planted, {n}")
 
 
+@pytest.mark.parametrize("dtype,d", SHAPES)
+def test_values_near_the_largest(dtype, d):
+    """V of 1e38: the running maximum is raised lazily, so weights of 2^7 meet V before the division by their sum; O is
+    finite all the same.  One key beyond the first tiles outweighs the others."""
+    w = W.custom_workload("large", [300], 512, 1, 1, d, dtype, W.MaskSpec("causal"), seed=74)
+    g = H.GpuRun(w, W.make_tensors(w), H.oracle_table(w))
+    g.q.fill_(1.0)
+    g.k.zero_()
+    g.k[261] = 7 * np.log(2) / np.sqrt(d)
+    g.v.fill_(1e38)
+    out, _ = g.forward()
+    assert (np.abs(out / 1e38 - 1) <= (1e-5 if dtype == "f32" else 2.0 ** -7)).all()
+
+
 @pytest.mark.parametrize("d", [32, 64])
 def test_inf_and_nan_in_a_large_narrow_batch(d):
     """More than 1 024 (work item, KV head) pairs: the other form of the narrow dK/dV kernel."""
