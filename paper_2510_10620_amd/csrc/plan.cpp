@@ -800,7 +800,11 @@ static dcp_status_t upload(const std::vector<T>& v, T** dev, hipStream_t stream)
 
 static bool is_capturing(hipStream_t stream) {
   hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(stream, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &status) != hipSuccess) {   // the legacy stream beside a capture elsewhere
+    (void)hipGetLastError();                                   // is not for the next launch to report
+    return false;
+  }
+  return status != hipStreamCaptureStatusNone;
 }
 
 dcp_status_t dcp_plan::group_for(int gid, hipStream_t stream, DevGroup* out, int heads, int n_seg, bool may_alloc) {
