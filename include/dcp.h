@@ -69,7 +69,8 @@ typedef enum {
 typedef enum { DCP_BF16 = 0, DCP_F32 = 1 } dcp_dtype_t;
 
 /* Which kernel family runs.  AUTO picks MFMA when (dtype, D) is covered, else SCALAR; outside bf16 with D = 128 it also
- * picks SCALAR where a token stride exceeds 2^24 elements.  MFMA by name is bf16 with D = 128 only. */
+ * picks SCALAR where a token stride exceeds 2^24 elements, a launch would have 2^32 threads or more, or the plan's blocks
+ * are so short and many that SCALAR is estimated to be the faster.  MFMA by name is bf16 with D = 128 only. */
 typedef enum { DCP_IMPL_AUTO = 0, DCP_IMPL_SCALAR = 1, DCP_IMPL_MFMA = 2 } dcp_impl_t;
 
 typedef struct dcp_plan dcp_plan_t; /* opaque; created and destroyed by the library */

@@ -97,6 +97,36 @@ static dcp_status_t pick_impl(const dcp_tensors_t* t, bool* use_mfma) {
   return DCP_OK;
 }
 
+// Whether the thread-per-row kernels are the faster ones: a walk over many short blocks costs the MFMA kernels a round trip to
+// memory per table row and a mostly empty tile, the others a few instructions a key.  Times of a launch are estimated as
+// walk x the rounds that its workgroups (waves) take on the chip, with constants fitted to both families' times for
+// sequences of 1 to 64 tokens and blocks of 1 to 32.  Where the two are 2.5 times apart it is on the right side: fp32, D 64,
+// 4/2 heads, forward + backward, thread per row against MFMA: 4 000 sequences of 8 tokens 1 148 and 4 060 us, 1 000 of 32
+// 1 041 and 1 162, 500 of 64 1 079 and 677; one of 2 048 under a 64-token window in blocks of 4 996 and 2 258, of 16 458 and
+// 273.  bf16 with D 64 has no such range (at most a tenth), and D 128 never had the choice.
+static bool rows_are_faster(const dcp_plan_t* plan, const dcp_tensors_t* t, bool backward) {
+  struct Fit { int32_t dtype, d; double row_us, start_rows, wgs, key_us, waves; };   // wgs, waves: as many run at once
+  static const Fit fits[] = {{DCP_F32, 32, 2.4, 6.5, 512, 1.0, 1470}, {DCP_F32, 64, 4.0, 5, 256, 1.9, 700},
+                             {DCP_F32, 128, 6.7, 5, 256, 5.3, 530}, {DCP_BF16, 32, 4.0, 3, 1024, 1.5, 1500}};
+  for (const Fit& f : fits) {
+    if (f.dtype != t->dtype || f.d != t->d) continue;
+    const int group = t->hq / t->hkv;
+    double mfma = 0, rows = 0;
+    auto add = [&](const GroupSize& z, int heads, int walked_heads) {
+      if (z.tiles == 0) return;
+      // heads that share a workgroup in the narrow kernels' query side (QSplit)
+      const int shared = f.dtype == DCP_BF16 && walked_heads == 0 ? (group % 4 == 0 ? 4 : group % 2 == 0 ? 2 : 1) : 1;
+      const double g = std::max(1, walked_heads), n_wgs = (double)z.tiles * heads / shared, n_waves = (double)z.waves * heads;
+      mfma += f.row_us * (f.start_rows + (z.tile_ents + z.tile_tiles * g / 8) / z.tiles) * std::max(1.0, n_wgs / f.wgs);
+      rows += 12 + f.key_us * (2 + z.wave_keys * g / z.waves) * std::max(1.0, n_waves / f.waves);
+    };
+    if (!backward) add(plan->size[0], t->hq, 0);
+    else { add(plan->size[1], t->hq, 0); add(plan->size[2], t->hkv, group); }
+    return rows < mfma;
+  }
+  return false;
+}
+
 // KV heads the dK/dV list is cut for (0: whole items).  All other lists are the same for every kernel family, so a plan
 // made ready for a shape serves it whichever family a call's strides or its `impl` choose.
 static int cut_heads(bool use_mfma, int32_t dtype, int32_t d, int32_t hkv) { return use_mfma && mfma_splits_dkv(dtype, d) ? hkv : 0; }
@@ -161,7 +191,7 @@ extern "C" dcp_status_t dcp_block_attn_fwd(dcp_plan_t* plan, const dcp_tensors_t
   hipStream_t s = (hipStream_t)stream;
   DevGroup g;
   if ((st = plan->group_for(0, s, &g, t->hq / t->hkv, xcd_segments(t->hkv))) != DCP_OK) return st;
-  use_mfma = use_mfma && mfma_launch_fits(g, false, t->dtype, t->d, t->hq, t->hkv);
+  use_mfma = use_mfma && mfma_launch_fits(g, false, t->dtype, t->d, t->hq, t->hkv) && !rows_are_faster(plan, t, false);
   KTensors k = pack(plan, t);
   ProfScope ps(DCP_K_FWD, s);
   return use_mfma ? mfma_fwd(g, k, s) : scalar_fwd(g, k, t->dtype, s);
@@ -279,7 +309,8 @@ dcp_status_t dcp::bwd_launch(dcp_plan_t* plan, const dcp_tensors_t* t, void* wor
   const int n_seg = xcd_segments(t->hkv);
   if ((st = plan->group_for(1, s, &gq, t->hq / t->hkv, n_seg, may_alloc)) != DCP_OK) return st;
   if ((st = plan->group_for(2, s, &gkv, cut_heads(use_mfma, t->dtype, t->d, t->hkv), n_seg, may_alloc)) != DCP_OK) return st;
-  use_mfma = use_mfma && mfma_launch_fits(gq, false, t->dtype, t->d, t->hq, t->hkv) && mfma_launch_fits(gkv, true, t->dtype, t->d, t->hq, t->hkv);
+  use_mfma = use_mfma && mfma_launch_fits(gq, false, t->dtype, t->d, t->hq, t->hkv) && mfma_launch_fits(gkv, true, t->dtype, t->d, t->hq, t->hkv) &&
+             !rows_are_faster(plan, t, true);
   KTensors k = pack(plan, t);
   const size_t n_hT = wsz.n_hT;
   k.part = (float*)((char*)workspace + 2 * wsz.n_hT + wsz.n_bounds);

@@ -87,6 +87,12 @@ struct HostGroup {
   std::vector<int32_t> unit_blk, unit_out, ptr, idx, ent_blk, ent_start, ent_len, ent_kind;
 };
 
+// How much a group's launch walks, for the choice between the kernel families.
+struct GroupSize {
+  int64_t tiles = 0, tile_ents = 0, tile_tiles = 0;   // 32-row tiles of the units; over them, table rows and 32-row tiles walked
+  int64_t waves = 0, wave_keys = 0;                   // 64-row tiles; over them, rows of the other side walked one by one
+};
+
 struct HostItems {
   std::vector<WorkItem> items;
   std::vector<ReduceItem> reduce;
@@ -117,6 +123,7 @@ struct dcp_plan {
   std::vector<int32_t> table;  // original rows [n,3]
   std::vector<int32_t> slot_qblk, merge_ptr, merge_idx;
   dcp::HostGroup fwd, bwdq, bwdkv;
+  dcp::GroupSize size[3];   // of fwd, bwdq, bwdkv
 
   // device mirrors (created lazily on the device that is current at first launch)
   std::mutex mu;

@@ -61,6 +61,7 @@ constexpr int64_t kNarrowDkvFew = 1024;
 // the D = 128 kernels' tensors would outgrow the memory first.
 inline bool mfma_launch_fits(const DevGroup& g, bool dkv, int32_t dtype, int32_t d, int hq, int hkv) {
   if (dtype == DCP_BF16 && d == 128) return true;
+  if ((int64_t)g.n_items * hq < (UINT32_MAX >> 3) / (kF32Sub * kF32Threads)) return true;   // whatever the XCDs' shares are
   const bool f32 = dtype == DCP_F32;
   const int per_item = (dkv ? 1 : hq / hkv) * (f32 ? kF32Sub : dkv && g.n_items * (int64_t)hkv <= kNarrowDkvFew ? 2 : 1);
   return xcd_grid(g, hkv, per_item) * (f32 ? kF32Threads : dkv ? kNarrowDkvThreads : kNarrowThreads) <= (int64_t)UINT32_MAX;

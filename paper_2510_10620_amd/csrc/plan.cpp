@@ -288,6 +288,23 @@ static void build_group(const dcp_plan& pl, const std::vector<int64_t>& kept, in
   }
 }
 
+static void measure_groups(dcp_plan* plan) {
+  const HostGroup* gs[3] = {&plan->fwd, &plan->bwdq, &plan->bwdkv};
+  for (int i = 0; i < 3; i++) {
+    GroupSize z;
+    for (size_t u = 0; u < gs[i]->unit_blk.size(); u++) {
+      const int32_t b = gs[i]->unit_blk[u];
+      if (b < 0 || (plan->buffers && (i == 2 ? plan->kv_slot[b] : plan->q_slot[b]) < 0)) continue;
+      const int64_t tiles = (plan->blk_len[b] + 31) / 32, waves = (plan->blk_len[b] + 63) / 64;
+      int64_t other = 0, other_tiles = 0;
+      for (int32_t e = gs[i]->ptr[u]; e < gs[i]->ptr[u + 1]; e++) { other += gs[i]->ent_len[e]; other_tiles += (gs[i]->ent_len[e] + 31) / 32; }
+      z.tiles += tiles; z.tile_ents += tiles * (gs[i]->ptr[u + 1] - gs[i]->ptr[u]); z.tile_tiles += tiles * other_tiles;
+      z.waves += waves; z.wave_keys += waves * other;
+    }
+    plan->size[i] = z;
+  }
+}
+
 extern "C" dcp_status_t dcp_plan_create(dcp_plan_t** out, const int32_t* cu, int32_t n_seq, int32_t B,
                                         const int32_t* table, int64_t n_entries, const int32_t* out_slot,
                                         int32_t n_slots) {
@@ -380,6 +397,7 @@ extern "C" dcp_status_t dcp_plan_create(dcp_plan_t** out, const int32_t* cu, int
     for (int32_t s = 0; s < pl->n_slots; s++)
       if (pl->slot_qblk[s] >= 0) pl->merge_idx[fill[pl->slot_qblk[s]]++] = s;
   }
+  measure_groups(pl.get());
   *out = pl.release();
   return DCP_OK;
 }
@@ -427,6 +445,7 @@ extern "C" dcp_status_t dcp_plan_set_block_buffers(dcp_plan_t* plan, const int32
   }
   plan->q_rows = (int64_t)n_q_slots * B;
   plan->kv_rows = (int64_t)n_kv_slots * B;
+  measure_groups(plan);
   return DCP_OK;
 }
 

@@ -83,3 +83,23 @@ def test_largest_block_size_under_a_mask(dtype, d):
     got += tuple(H.from_torch(x) for x in outs)
     names = ("out", "lse", "dq", "dk", "dv")
     H.check(w, dict(zip(names, got)), dict(zip(names, ref)), names, f"block size {B}")
+
+
+@pytest.mark.parametrize("dtype,d,hq,hkv", [("f32", 32, 4, 2), ("f32", 64, 4, 2), ("f32", 128, 4, 1), ("bf16", 32, 4, 2)])
+@pytest.mark.parametrize("slots", [False, True])
+def test_many_short_sequences_take_the_thread_per_row_kernels(dtype, d, hq, hkv, slots):
+    """3 000 sequences of 1 to 3 tokens, where the MFMA kernels took up to 20 times as long: AUTO gives the bits of the
+    thread-per-row kernels, and the right results."""
+    import numpy as np
+    import paper_2510_10620_amd as P
+    lens = [1 + i % 3 for i in range(3000)]
+    w = W.custom_workload("short", lens, 64, hq, hkv, d, dtype, W.MaskSpec("causal"), seed=75, input_scale=0.5)
+    tensors, table = W.make_tensors(w), H.oracle_table(w)
+    slot, n_slots, _ = W.deal_divisions(table[:, 0], 2, 5) if slots else (None, 0, None)
+    auto, rows = (H.GpuRun(w, tensors, table, slot, n_slots, impl) for impl in (P.DCP_IMPL_AUTO, P.DCP_IMPL_SCALAR))
+    ref = rows.forward() + rows.backward()
+    got = auto.forward() + auto.backward()
+    for a, b in zip(got, ref):
+        assert np.array_equal(a, b)
+    names = ("out", "lse", "dq", "dk", "dv")
+    H.check(w, dict(zip(names, got)), H.oracle_full(w, tensors, table), names, f"short {dtype} D{d}")
