@@ -13,7 +13,11 @@ template <> struct Vec8<bf16_t> {
   typedef float f8 __attribute__((ext_vector_type(8)));
   typedef uint32_t u4 __attribute__((ext_vector_type(4)));
   typedef u4 Raw;   // 8 elements as memory holds them
-  static __device__ __forceinline__ Raw raw_nt(const bf16_t* p) { return __builtin_nontemporal_load((const u4*)p); }
+  // NT: past the caches
+  template <bool NT> static __device__ __forceinline__ Raw raw(const bf16_t* p) {
+    if constexpr (NT) return __builtin_nontemporal_load((const u4*)p);
+    else return *(const u4*)p;
+  }
   static __device__ __forceinline__ void expand(const Raw& w, float* f) {
 #pragma unroll
     for (int i = 0; i < 4; i++) { f[2 * i] = __uint_as_float(w[i] << 16); f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u); }
@@ -31,8 +35,10 @@ template <> struct Vec8<bf16_t> {
 template <> struct Vec8<float> {
   typedef float f32x4 __attribute__((ext_vector_type(4)));
   struct Raw { f32x4 a, b; };
-  static __device__ __forceinline__ Raw raw_nt(const float* p) {
-    return {__builtin_nontemporal_load((const f32x4*)p), __builtin_nontemporal_load((const f32x4*)(p + 4))};
+  // a lane's 32 bytes are two loads, each of them half of every line that the wave touches
+  template <bool NT> static __device__ __forceinline__ Raw raw(const float* p) {
+    if constexpr (NT) return {__builtin_nontemporal_load((const f32x4*)p), __builtin_nontemporal_load((const f32x4*)(p + 4))};
+    else return {*(const f32x4*)p, *(const f32x4*)(p + 4)};
   }
   static __device__ __forceinline__ void expand(const Raw& r, float* f) {
 #pragma unroll
@@ -265,6 +271,8 @@ __global__ __launch_bounds__(256) void delta_kernel(const T* __restrict__ o, int
   const int c = threadIdx.x & (chunks - 1);
   const int step_t = step / hq, step_h = step % hq;
   int pair = threadIdx.x / chunks, tl = pair / hq, h = pair % hq;
+  // bf16 past the caches; fp32, two loads a line, through them (16 MB of it 47 -> 40 us)
+  constexpr bool NT = sizeof(T) == 2;
   constexpr int U = 4;
   for (int k = 0; k < n_pairs; k += U * step) {   // the same trip count for every thread: the reduction uses all lanes
     typename Vec8<T>::Raw a[U], b[U];
@@ -273,8 +281,8 @@ __global__ __launch_bounds__(256) void delta_kernel(const T* __restrict__ o, int
     for (int u = 0; u < U; u++) {
       at[u] = pair < n_pairs ? h * (kDeltaTok + 1) + tl : -1;
       if (at[u] >= 0) {
-        a[u] = Vec8<T>::raw_nt(o + (t0 + tl) * o_st + (int64_t)h * o_sh + c * 8);
-        b[u] = Vec8<T>::raw_nt(dout + (t0 + tl) * do_st + (int64_t)h * do_sh + c * 8);
+        a[u] = Vec8<T>::template raw<NT>(o + (t0 + tl) * o_st + (int64_t)h * o_sh + c * 8);
+        b[u] = Vec8<T>::template raw<NT>(dout + (t0 + tl) * do_st + (int64_t)h * do_sh + c * 8);
       }
       pair += step; tl += step_t; h += step_h;
       if (h >= hq) { h -= hq; tl++; }
@@ -323,16 +331,17 @@ struct PartPtrs {
   const void* p[8];
 };
 
-// HBM-bound.  One 16- or 32-byte piece per part and thread, all parts requested before the first is added, every byte
-// past the caches: two bf16 parts of 512 MiB 293 -> 248-258 us (6.2-6.5 TB/s) against 4 096 workgroups that walked the arrays
-// with one load at a time.
-template <typename TI, typename TO>
+// HBM-bound.  One 16- or 32-byte piece per part and thread, all parts requested before the first is added: two bf16 parts of
+// 512 MiB 293 -> 248-258 us (6.2-6.5 TB/s) against 4 096 workgroups that walked the arrays with one load at a time.
+// What goes past the caches: bf16 results (16 bytes a lane, whole lines); fp32 results do not, their two stores a lane are
+// half lines (one bf16 part of 2^28 elements to fp32: 403 us past, 272 through).  NT: the parts too, see stream_sum.
+template <typename TI, typename TO, bool NT>
 __global__ __launch_bounds__(256) void sum_kernel(PartPtrs parts, int32_t n_parts, TO* __restrict__ dst, int64_t n8) {
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n8; i += (int64_t)gridDim.x * 256) {
     typename Vec8<TI>::Raw raw[8];
 #pragma unroll
     for (int p = 0; p < 8; p++)
-      if (p < n_parts) raw[p] = Vec8<TI>::raw_nt((const TI*)parts.p[p] + i * 8);
+      if (p < n_parts) raw[p] = Vec8<TI>::template raw<NT>((const TI*)parts.p[p] + i * 8);
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int p = 0; p < 8; p++)
@@ -342,7 +351,8 @@ __global__ __launch_bounds__(256) void sum_kernel(PartPtrs parts, int32_t n_part
 #pragma unroll
         for (int k = 0; k < 8; k++) acc[k] += f[k];
       }
-    Vec8<TO>::store_nt(dst + i * 8, acc);
+    if constexpr (sizeof(TO) == 2) Vec8<TO>::store_nt(dst + i * 8, acc);
+    else Vec8<TO>::store(dst + i * 8, acc);
   }
 }
 
@@ -353,14 +363,21 @@ dcp_status_t stream_sum(const void* const* parts, int32_t n_parts, int32_t parts
   for (int i = 0; i < n_parts; i++) pp.p[i] = parts[i];
   const int64_t n8 = n / 8;
   dim3 grid((unsigned)std::min<int64_t>((n8 + 255) / 256, 1 << 22)), block(256);   // one pass up to 2^33 elements
-  if (parts_dtype == DCP_F32 && dst_dtype == DCP_BF16)
-    hipLaunchKernelGGL((sum_kernel<float, bf16_t>), grid, block, 0, s, pp, n_parts, (bf16_t*)dst, n8);
-  else if (parts_dtype == DCP_F32 && dst_dtype == DCP_F32)
-    hipLaunchKernelGGL((sum_kernel<float, float>), grid, block, 0, s, pp, n_parts, (float*)dst, n8);
-  else if (parts_dtype == DCP_BF16 && dst_dtype == DCP_BF16)
-    hipLaunchKernelGGL((sum_kernel<bf16_t, bf16_t>), grid, block, 0, s, pp, n_parts, (bf16_t*)dst, n8);
-  else
-    hipLaunchKernelGGL((sum_kernel<bf16_t, float>), grid, block, 0, s, pp, n_parts, (float*)dst, n8);
+  // Parts that the 256 MB behind the L2s can hold are read through it (a kernel before may have left them there), larger
+  // ones past it.  To bf16, past and through: four bf16 parts of 2^25 elements (268 MB) 56 and 47 us, two of 2^27 (537 MB) 124
+  // and 133; two fp32 parts of 2^25 (268 MB) 53 and 46, of 2^26 (537 MB) 107 and 114.
+  const bool nt = n * n_parts * (parts_dtype == DCP_F32 ? 4 : 2) > 300000000;
+  if (parts_dtype == DCP_F32 && dst_dtype == DCP_BF16) {
+    if (nt) hipLaunchKernelGGL((sum_kernel<float, bf16_t, true>), grid, block, 0, s, pp, n_parts, (bf16_t*)dst, n8);
+    else hipLaunchKernelGGL((sum_kernel<float, bf16_t, false>), grid, block, 0, s, pp, n_parts, (bf16_t*)dst, n8);
+  } else if (parts_dtype == DCP_F32 && dst_dtype == DCP_F32) {
+    hipLaunchKernelGGL((sum_kernel<float, float, false>), grid, block, 0, s, pp, n_parts, (float*)dst, n8);
+  } else if (parts_dtype == DCP_BF16 && dst_dtype == DCP_BF16) {
+    if (nt) hipLaunchKernelGGL((sum_kernel<bf16_t, bf16_t, true>), grid, block, 0, s, pp, n_parts, (bf16_t*)dst, n8);
+    else hipLaunchKernelGGL((sum_kernel<bf16_t, bf16_t, false>), grid, block, 0, s, pp, n_parts, (bf16_t*)dst, n8);
+  } else {
+    hipLaunchKernelGGL((sum_kernel<bf16_t, float, false>), grid, block, 0, s, pp, n_parts, (float*)dst, n8);
+  }
   DCP_HIP_TRY(hipGetLastError());
   return DCP_OK;
 }

@@ -37,3 +37,15 @@ def test_sum_edges(n, n_parts, src, dst):
     for p in parts:   # the documented order: first part to last, in fp32
         ref = ref + p.float()
     assert torch.equal(out, ref.to(dst))
+
+
+@pytest.mark.parametrize("src,n,n_parts", [(torch.bfloat16, 1 << 26, 2), (torch.bfloat16, 1 << 26, 3), (torch.float32, (1 << 25) + 8, 3)])
+def test_sum_on_both_sides_of_the_cache(src, n, n_parts):
+    """268 MB of parts are read through the caches, 403 MB past them: the same sums."""
+    parts = [_randn((n,), src, 10 + i) for i in range(n_parts)]
+    out = torch.full((n,), float("nan"), device="cuda", dtype=torch.bfloat16)
+    P.dcp_sum_partials(parts, out)
+    ref = parts[0].float()
+    for p in parts[1:]:
+        ref = ref + p.float()
+    assert torch.equal(out, ref.to(torch.bfloat16))
