@@ -106,22 +106,20 @@ static dcp_status_t pick_impl(const dcp_tensors_t* t, bool* use_mfma) {
 // 273.  bf16 with D 64 has no such range (at most a tenth), and D 128 never had the choice.
 static bool rows_are_faster(const dcp_plan_t* plan, const dcp_tensors_t* t, bool backward) {
   struct Fit { int32_t dtype, d; double row_us, start_rows, wgs, key_us, waves; };   // wgs, waves: as many run at once
-  static const Fit fits[] = {{DCP_F32, 32, 2.4, 6.5, 512, 1.0, 1470}, {DCP_F32, 64, 4.0, 5, 256, 1.9, 700},
-                             {DCP_F32, 128, 6.7, 5, 256, 5.3, 530}, {DCP_BF16, 32, 4.0, 3, 1024, 1.5, 1500}};
+  static const Fit fits[] = {{DCP_F32, 32, 2.4, 6.5, 280, 1.0, 1470}, {DCP_F32, 64, 4.0, 5, 256, 1.9, 700},
+                             {DCP_F32, 128, 6.7, 5, 256, 5.3, 530}, {DCP_BF16, 32, 4.0, 3, 2048, 1.5, 1500}};
   for (const Fit& f : fits) {
     if (f.dtype != t->dtype || f.d != t->d) continue;
     const int group = t->hq / t->hkv;
     double mfma = 0, rows = 0;
-    auto add = [&](const GroupSize& z, int heads, int walked_heads) {
+    auto add = [&](const GroupSize& z, int heads, int g) {   // g: query heads walked by a workgroup or a thread
       if (z.tiles == 0) return;
-      // heads that share a workgroup in the narrow kernels' query side (QSplit)
-      const int shared = f.dtype == DCP_BF16 && walked_heads == 0 ? (group % 4 == 0 ? 4 : group % 2 == 0 ? 2 : 1) : 1;
-      const double g = std::max(1, walked_heads), n_wgs = (double)z.tiles * heads / shared, n_waves = (double)z.waves * heads;
-      mfma += f.row_us * (f.start_rows + (z.tile_ents + z.tile_tiles * g / 8) / z.tiles) * std::max(1.0, n_wgs / f.wgs);
-      rows += 12 + f.key_us * (2 + z.wave_keys * g / z.waves) * std::max(1.0, n_waves / f.waves);
+      const double n_wgs = (double)z.tiles * heads, n_waves = (double)z.waves * heads;
+      mfma += f.row_us * (f.start_rows + (z.tile_ents + z.tile_tiles * g / 8.0) / z.tiles) * std::max(1.0, n_wgs / f.wgs);
+      rows += 12 + f.key_us * (2 + z.wave_keys * (double)g / z.waves) * std::max(1.0, n_waves / f.waves);
     };
-    if (!backward) add(plan->size[0], t->hq, 0);
-    else { add(plan->size[1], t->hq, 0); add(plan->size[2], t->hkv, group); }
+    if (!backward) add(plan->size[0], t->hq, 1);
+    else { add(plan->size[1], t->hq, 1); add(plan->size[2], t->hkv, group); }
     return rows < mfma;
   }
   return false;

@@ -71,7 +71,7 @@ __global__ __launch_bounds__(256, 2) void mfma_dq_kernel(DevGroup g, KTensors t)
   const int li = lane & 31, lh = lane >> 5;
   const int blk_start = uni(w.blk_start), blk_len = uni(w.blk_len);
   const int qoff = uni(w.moff);                // rows of the Q-type buffers: packed index + qoff
-  const QSplit sp(w.tile, head_x, G, wave);
+  const QSplit sp(w.tile, blk_len, head_x, G, wave);
   const int head = uni(sp.head), row0 = sp.row0;
   const int n_rows = min(sp.rows, blk_len - row0);
   if (n_rows <= 0) return;

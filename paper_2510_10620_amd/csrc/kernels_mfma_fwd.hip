@@ -1,7 +1,7 @@
 // Blockwise attention forward on bf16 MFMA (Listing 1 line 5 + the in-kernel part of line 6).
 //
-// One workgroup (4 waves of 32 rows) owns 128 / HP query rows of HP = gcd(query heads per KV head, 4) heads of one KV head
-// (QSplit) and walks the KV tiles (64 keys) of every table row of its output unit.  Scores are computed transposed,
+// One workgroup (4 waves of 32 rows) owns 128 / HP query rows of HP = 1, 2 or 4 query heads of one KV head (QSplit)
+// and walks the KV tiles (64 keys) of every table row of its output unit.  Scores are computed transposed,
 // S^T = K Q^T, so that a lane owns one query column: the running max / sum are per-lane scalars,
 // the only cross-lane step is one exchange between the two wave halves per 32 keys, and P^T in the
 // MFMA accumulator layout is directly the B operand of O^T += V^T P^T.  K and V tiles are copied
@@ -273,7 +273,7 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void mfma_fwd_kernel(DevGroup g,
   const int li = lane & 31, lh = lane >> 5;
   const int blk_start = uni(w.blk_start), blk_len = uni(w.blk_len);
   const int qoff = uni(w.moff);                       // rows of the Q-type buffers: packed index + qoff
-  const QSplit sp(w.tile, head_x, G, wave);
+  const QSplit sp(w.tile, blk_len, head_x, G, wave);
   const int head = uni(sp.head), row0 = sp.row0;      // first row of the workgroup inside the block
   const int n_rows = min(sp.rows, blk_len - row0);    // its valid rows
   if (n_rows <= 0) return;

@@ -168,7 +168,7 @@ __device__ __forceinline__ bool nq_tile(const DevGroup& g, const KTensors& t, in
   const int G = t.hq / t.hkv;
   if (!decode_wg(g, t.hkv, G, &item, &head_x)) return false;
   const WorkItem w = g.items[item];
-  const QSplit sp(uni(w.tile), head_x, G, wave);
+  const QSplit sp(uni(w.tile), uni(w.blk_len), head_x, G, wave);
   q->head = uni(sp.head);
   q->hk = head_x / G;
   q->unit = uni(w.unit); q->e0 = uni(w.e0); q->e1 = uni(w.e1);

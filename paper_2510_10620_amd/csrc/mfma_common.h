@@ -412,21 +412,23 @@ __device__ __forceinline__ bool decode_wg(const DevGroup& g, int heads_outer, in
 }
 
 // How the four waves of a query-side workgroup divide a 128-row work item and the G query heads of its KV head: a
-// workgroup takes HP = gcd(G, 4) heads x 128 / HP rows (a wave 32 rows of one head), and the G workgroups of an item are
+// workgroup takes HP heads (gcd(G, 4); 1 for an item of at most 64 rows) x 128 / HP rows (a wave 32 rows of one head), and the G workgroups of an item are
 // G / HP head groups x HP row parts.  With HP = 4 all waves have the SAME rows: under a mask they need the same key
 // tiles (of 128 rows of one head the first 32 have nothing to do in the last tile under a causal mask and wait at its
 // barrier), and the key range of 32 rows fits its tiles more tightly.  65 536 causal tokens, 32/8 heads, 128 rows of one
 // head -> this: sequences of 1 024, forward 774 -> 743 us, dQ 1 083 -> 1 054; of 512, 514 -> 489, 757 -> 717; log-normal
-// lengths (median 2 048) 2 605 -> 2 583, 3 537 -> 3 503.
+// lengths (median 2 048) 2 605 -> 2 583, 3 537 -> 3 503.  Items of at most 64 rows keep 128 rows of one head: with HP = 4 half
+// or three quarters of their workgroups would have no row and cost their launch all the same (32/8 heads, HP = 4 -> 1: 1 000
+// sequences of 20 tokens, forward 390 -> 340 us; 4 096 tokens in blocks of 32, 919 -> 816).
 struct QSplit {
   int head, row0, rows, wrow0;   // the wave's head; the workgroup's first row and row count inside the block; the wave's first of them
-  __device__ __forceinline__ QSplit(int item_tile, int head_x, int G, int wave) {
-    const int hp = (G & 3) == 0 ? 4 : ((G & 1) == 0 ? 2 : 1);
-    const int hk = head_x / G, x = head_x % G;
-    rows = 128 / hp;
-    row0 = item_tile * 128 + (x % hp) * rows;
-    head = hk * G + (x / hp) * hp + wave % hp;
-    wrow0 = (wave / hp) * 32;
+  __device__ __forceinline__ QSplit(int item_tile, int blk_len, int head_x, int G, int wave) {
+    const int sh = blk_len - item_tile * 128 <= 64 || (G & 1) ? 0 : (G & 3) ? 1 : 2, hp = 1 << sh;
+    const int hk = head_x / G, x = head_x - hk * G;
+    rows = 128 >> sh;
+    row0 = item_tile * 128 + (x & (hp - 1)) * rows;
+    head = hk * G + (x & ~(hp - 1)) + (wave & (hp - 1));
+    wrow0 = (wave >> sh) * 32;
   }
 };
 

@@ -121,6 +121,17 @@ def test_head_group_sizes(hq, hkv):
     run_case(w, H.oracle_table(w), IMPLS["auto"], label=f"hq{hq}/hkv{hkv}")
 
 
+@pytest.mark.parametrize("d", [128, 64, 32])
+@pytest.mark.parametrize("hq,hkv", [(1, 1), (2, 1), (3, 1), (4, 1), (6, 1), (8, 2)])
+def test_items_around_64_rows_for_every_head_split(hq, hkv, d):
+    """An item of at most 64 rows gives a workgroup's waves 128 rows of one head, a longer one (for an even number of
+    heads per KV head) 32 or 64 rows of several: lengths and blocks whose last item is on either side, and exactly there."""
+    for B in (64, 200):
+        w = W.custom_workload("items", [1, 63, 64, 65, 96, 97, 128, 129, 192, 193, 400], B, hq, hkv, d, "bf16", W.MaskSpec("causal"), seed=39,
+                              input_scale=0.5)
+        run_case(w, H.oracle_table(w), IMPLS["auto"], label=f"{hq}/{hkv} D{d} B{B}")
+
+
 def test_library_loaded_before_torch_touches_the_gpu():
     """A fresh process that calls a host function of the binding (which loads the library) before anything has
     imported torch must still find the GPU afterwards: the loader imports torch first so that the process holds one
