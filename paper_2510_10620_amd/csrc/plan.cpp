@@ -709,7 +709,7 @@ const HostItems& dcp_plan::host_items(int gid, int heads, int n_seg) {
     }
   }
   std::stable_sort(sc.begin(), sc.end(), [](const Scored& a, const Scored& b) { return a.cost > b.cost; });
-  if (heads > 0 && !sc.empty() && (gid == 2 || !has_ranges)) {
+  if (heads > 0 && !sc.empty() && (gid == 2 || (!has_ranges && (int64_t)sc.size() * heads > kResidentWorkgroups / 8 * n_seg))) {
     // Sequence by sequence (the costliest sequence first, longest item first inside it) when that balances as well as
     // strict longest-first does.  Items of one sequence that run at the same time read the same rows of the other
     // side, so their XCD's L2 serves those rows once.  dK/dV: 13.9 -> 7.5 GB fetched per launch on the 65 536-token
@@ -723,6 +723,8 @@ const HostItems& dcp_plan::host_items(int gid, int heads, int n_seg) {
     // of equal sequences balances badly in this order (every round of workgroups mixes long and short items), which
     // the launch played through as list scheduling shows; it keeps strict longest-first.  (Longest-first by four or
     // eight classes of length with sequences grouped inside a class was in between on traffic and 0.8 % slower.)
+    // A forward or dQ list that the chip holds at once has no order to gain from, and its long items would start behind
+    // short ones of earlier sequences: 64 causal sequences of 256 tokens, 4/1 heads, forward 16.7 us in this order, 15.0 in strict one.
     // Who runs the list: in the dK/dV launch the whole chip, once per KV head; in the others the XCDs that share a KV
     // head's list, each item once per query head (the number of the first caller: any order is right, and a plan made
     // ready for one number of query heads serves every other).  The residency assumed is that of the D = 128 kernels; the
