@@ -65,7 +65,7 @@ __global__ __launch_bounds__(256, 2) void mfma_dq_kernel(DevGroup g, KTensors t)
   const int G = t.hq / t.hkv;
   if (!decode_wg(g, t.hkv, G, &item, &head_x)) return;
   const int hk = head_x / G;
-  WorkItem w = g.items[item];
+  WorkItem w = plan_load(g.items, item);
   w.unit = uni(w.unit); w.tile = uni(w.tile); w.e0 = uni(w.e0); w.e1 = uni(w.e1);
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
   const int li = lane & 31, lh = lane >> 5;
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(256, 2) void mfma_dq_kernel(DevGroup g, KTensors t)
   RangeBounds wrb;
   wrb.init();
   if (t.masked) {
-    st.qr = range_row(t, st.qi, uni(g.blk_s0[uni(g.unit_blk[w.unit])]));
+    st.qr = range_row(t, st.qi, uni(plan_load(g.blk_s0, plan_load(g.unit_blk, w.unit))));
     if (qv) wrb.add(st.qr);
   }
   RangeBounds rb = wrb;

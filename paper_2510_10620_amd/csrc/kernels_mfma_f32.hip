@@ -157,9 +157,9 @@ struct Walk {
       jt += kWaves;
       while (c0 + kRows * jt >= lim) {
         if (++e >= e_end) return false;
-        const int4 r = rec[2 * e];
+        const int4 r = plan_load(rec, 2 * e);
         c0 = uni(r.x); c1 = c0 + uni(r.y); kind = uni(r.z); moff = uni(r.w);
-        t32 = uni(rec[2 * e + 1].x);
+        t32 = uni(plan_load(rec, 2 * e + 1).x);
         lim = kind == 1 ? min(c1, q_hi + 1) : c1;
         jt = (wave - t32) & (kWaves - 1);
       }
@@ -182,7 +182,7 @@ __device__ __forceinline__ bool q_tile(const DevGroup& g, const KTensors& t, int
   if (!decode_wg(g, t.hkv, G * kSub, &item, &x)) return false;
   q->hk = x / (G * kSub);
   q->head = q->hk * G + (x % (G * kSub)) / kSub;
-  WorkItem w = g.items[item];
+  WorkItem w = plan_load(g.items, item);
   q->unit = uni(w.unit); q->e0 = uni(w.e0); q->e1 = uni(w.e1);
   q->blk_start = uni(w.blk_start); q->qoff = uni(w.moff);
   q->row0 = uni(w.tile) * (kSub * kRows) + (x % kSub) * kRows;
@@ -194,7 +194,7 @@ __device__ __forceinline__ bool q_tile(const DevGroup& g, const KTensors& t, int
   q->qr = make_int4(0, 0, 0, 0);
   q->rb.init();
   if (RANGES) {
-    q->qr = range_row(t, q->qi, uni(g.blk_s0[uni(g.unit_blk[q->unit])]));
+    q->qr = range_row(t, q->qi, uni(plan_load(g.blk_s0, plan_load(g.unit_blk, q->unit))));
     q->rb.add(q->qr);
     q->rb.wave_reduce();
 #pragma unroll
@@ -360,7 +360,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_fwd_kernel(DevGroup g, KTenso
     for (int w = 0; w < kWaves; w++) sl[w][li] = f[w] * inv;
   }
   __syncthreads();
-  const int slot = g.unit_out[q.unit];
+  const int slot = plan_load(g.unit_out, q.unit);
   if (wave == 0 && lh == 0 && li < q.n_rows) {
     const float lse = lt > 0.f ? (mt * c_log2 + __builtin_amdgcn_logf(lt)) * kLn2F : -INFINITY;
     if (slot < 0) t.lse[(int64_t)q.head * t.q_rows + q.q_lo + q.qoff + li] = lse;
@@ -493,13 +493,13 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dkv_kernel(DevGroup g, KTenso
   const int G = t.hq / t.hkv;
   if (!decode_wg(g, t.hkv, kSub, &item, &x)) return;
   const int hk = x / kSub;
-  const WorkItem w = g.items[item];
+  const WorkItem w = plan_load(g.items, item);
   const int e1 = uni(w.e1), koff = uni(w.moff);
   const int row0 = uni(w.tile) * (kSub * kRows) + (x % kSub) * kRows;
   const int n_rows = min(kRows, uni(w.blk_len) - row0);
   if (n_rows <= 0) return;
   const int k_lo = uni(w.blk_start) + row0, k_hi = k_lo + n_rows - 1;
-  const int seq0 = RANGES ? uni(g.blk_s0[uni(g.unit_blk[uni(w.unit)])]) : 0;
+  const int seq0 = RANGES ? uni(plan_load(g.blk_s0, plan_load(g.unit_blk, uni(w.unit)))) : 0;
   const float* k_lds = slabs;
   const float* v_lds = slabs + SLAB;
   own_rows<D>(slabs, (const float*)t.k + (int64_t)hk * t.k_sh, t.k_st, k_lo + koff, k_hi + koff);
@@ -520,8 +520,8 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dkv_kernel(DevGroup g, KTenso
         if (++hh >= G) {
           if (++e >= e1) return false;
           hh = 0;
-          const int4 r = rec[2 * e];
-          q0 = uni(r.x); q1 = q0 + uni(r.y); kind = uni(r.z); moff = uni(r.w); t32 = uni(rec[2 * e + 1].x);
+          const int4 r = plan_load(rec, 2 * e);
+          q0 = uni(r.x); q1 = q0 + uni(r.y); kind = uni(r.z); moff = uni(r.w); t32 = uni(plan_load(rec, 2 * e + 1).x);
           n_t = (q1 - q0 + kRows - 1) / kRows;
           jt0 = kind == 1 ? max(0, (k_lo - q0) / kRows) : 0;
         }
@@ -629,8 +629,8 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dkv_kernel(DevGroup g, KTenso
   if (again) {
     DCP_WAIT_VMCNT(0);   // the stores above come first
     const KernelArgs a = kernel_args();
-    const WorkItem w1 = a.g.items[item];
-    const int s0 = RANGES ? uni(a.g.blk_s0[uni(a.g.unit_blk[uni(w1.unit)])]) : 0;
+    const WorkItem w1 = plan_load(a.g.items, item);
+    const int s0 = RANGES ? uni(plan_load(a.g.blk_s0, plan_load(a.g.unit_blk, uni(w1.unit)))) : 0;
     for (; again; again &= again - 1) {
       const int r = 4 * wave + __builtin_ctz(again), j = k_lo + r;
       fix_dkv<float, D>(a.g, a.t, j, uni(w1.e0), uni(w1.e1), hk, s0, (const float*)a.t.k + (int64_t)(j + koff) * a.t.k_st + (int64_t)hk * a.t.k_sh,

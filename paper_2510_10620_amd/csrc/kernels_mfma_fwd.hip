@@ -267,7 +267,7 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void mfma_fwd_kernel(DevGroup g,
   const int G = t.hq / t.hkv;
   if (!decode_wg(g, t.hkv, G, &item, &head_x)) return;
   const int hk = head_x / G;
-  WorkItem w = g.items[item];
+  WorkItem w = plan_load(g.items, item);
   w.unit = uni(w.unit); w.tile = uni(w.tile); w.e0 = uni(w.e0); w.e1 = uni(w.e1);
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
   const int li = lane & 31, lh = lane >> 5;
@@ -296,7 +296,7 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void mfma_fwd_kernel(DevGroup g,
     st.qi[nq] = q_lo + min(r, n_rows - 1);
     st.qr[nq] = make_int4(0, 0, 0, 0);
     if (t.masked) {
-      st.qr[nq] = range_row(t, st.qi[nq], uni(g.blk_s0[uni(g.unit_blk[w.unit])]));
+      st.qr[nq] = range_row(t, st.qi[nq], uni(plan_load(g.blk_s0, plan_load(g.unit_blk, w.unit))));
       if (qv[nq]) wrb.add(st.qr[nq]);
     }
   }
@@ -441,7 +441,7 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void mfma_fwd_kernel(DevGroup g,
   // are free after the last step's barrier, two waves stage in each)
   static_assert(2 * 32 * kORow <= 2 * kTileBytes, "two waves stage their output tiles in one tile stage");
   char* ot = (wave < 2 ? stage0 : stage1) + (wave & 1) * (32 * kORow);
-  const int slot = g.unit_out[w.unit];
+  const int slot = plan_load(g.unit_out, w.unit);
 #pragma unroll
   for (int nq = 0; nq < NQ; nq++) {
     const float lt = xhalf_sum(st.l[nq]);

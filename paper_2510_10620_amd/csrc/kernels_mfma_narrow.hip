@@ -167,7 +167,7 @@ __device__ __forceinline__ bool nq_tile(const DevGroup& g, const KTensors& t, in
   int item, head_x;
   const int G = t.hq / t.hkv;
   if (!decode_wg(g, t.hkv, G, &item, &head_x)) return false;
-  const WorkItem w = g.items[item];
+  const WorkItem w = plan_load(g.items, item);
   const QSplit sp(uni(w.tile), uni(w.blk_len), head_x, G, wave);
   q->head = uni(sp.head);
   q->hk = head_x / G;
@@ -187,7 +187,7 @@ __device__ __forceinline__ bool nq_tile(const DevGroup& g, const KTensors& t, in
   q->wrb.init();
   q->rb.init();
   if (RANGES) {
-    q->qr = range_row(t, q->qi, uni(g.blk_s0[uni(g.unit_blk[q->unit])]));
+    q->qr = range_row(t, q->qi, uni(plan_load(g.blk_s0, plan_load(g.unit_blk, q->unit))));
     if (q->qv) q->wrb.add(q->qr);
     q->wrb.wave_reduce();
 #pragma unroll
@@ -338,7 +338,7 @@ __global__ __launch_bounds__(kNarrowThreads, 4) void narrow_fwd_kernel(DevGroup 
   }
   char* ot = stages + wave * (32 * N::kORow);
   static_assert(4 * 32 * N::kORow <= 4 * N::kBytes, "the waves' output tiles fit in the stages");
-  const int slot = g.unit_out[q.unit];
+  const int slot = plan_load(g.unit_out, q.unit);
   const float lt = xhalf_sum(l);
   const float inv = lt > 0.f ? 1.f / lt : 0.f;
   const float lse = lt > 0.f ? (m * c_log2 + __builtin_amdgcn_logf(lt)) * 0.69314718055994530942f : -INFINITY;
@@ -480,12 +480,12 @@ __global__ __launch_bounds__(kNarrowDkvThreads, 2) void narrow_dkv_kernel(DevGro
   int item, x;
   if (!decode_wg(g, t.hkv, SUB, &item, &x)) return;
   const int hk = x / SUB, G = t.hq / t.hkv;
-  const WorkItem w = g.items[item];
+  const WorkItem w = plan_load(g.items, item);
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6) % KW, group = uni(tid >> 6) / KW, li = lane & 31, lh = lane >> 5;
   char* stages = all_stages + group * (2 * kStage);
   const int koff = uni(w.moff), row0 = uni(w.tile) * 128 + (x % SUB) * (32 * KW), n_rows = min(32 * KW, uni(w.blk_len) - row0);
   if (n_rows <= 0) return;
-  const int seq0 = RANGES ? uni(g.blk_s0[uni(g.unit_blk[uni(w.unit)])]) : 0;
+  const int seq0 = RANGES ? uni(plan_load(g.blk_s0, plan_load(g.unit_blk, uni(w.unit)))) : 0;
   const int k_lo = uni(w.blk_start) + row0, k_end = k_lo + n_rows, wrow0 = wave * 32;
   const int w_rows = max(0, min(32, n_rows - wrow0));
   const int wk_lo = k_lo + wrow0, wk_hi = wk_lo + w_rows - 1;
@@ -657,8 +657,8 @@ __global__ __launch_bounds__(kNarrowDkvThreads, 2) void narrow_dkv_kernel(DevGro
   if (again) {
     DCP_WAIT_VMCNT(0);   // the stores above come first
     const KernelArgs a = kernel_args();
-    const WorkItem w1 = a.g.items[item];
-    const int s0 = RANGES ? uni(a.g.blk_s0[uni(a.g.unit_blk[uni(w1.unit)])]) : 0;
+    const WorkItem w1 = plan_load(a.g.items, item);
+    const int s0 = RANGES ? uni(plan_load(a.g.blk_s0, plan_load(a.g.unit_blk, uni(w1.unit)))) : 0;
     for (; again; again &= again - 1) {
       const int r = __builtin_ctz(again), j = wk_lo + r;
       fix_dkv<bf16_t, D>(a.g, a.t, j, uni(w1.e0), uni(w1.e1), hk, s0, (const bf16_t*)a.t.k + (int64_t)(j + koff) * a.t.k_st + (int64_t)hk * a.t.k_sh,

@@ -62,8 +62,8 @@ struct QIter {
           e--;
           if (e < e_end) return false;
           hh = 0;
-          const int4 r = rec[2 * e];
-          q0 = uni(r.x); q1 = q0 + uni(r.y); kind = uni(r.z); moff = uni(r.w); t32 = uni(rec[2 * e + 1].x);
+          const int4 r = plan_load(rec, 2 * e);
+          q0 = uni(r.x); q1 = q0 + uni(r.y); kind = uni(r.z); moff = uni(r.w); t32 = uni(plan_load(rec, 2 * e + 1).x);
           n_t = (q1 - q0 + kTN - 1) / kTN;
           jt0 = kind == 1 ? max(0, (k_lo - q0) / kTN) : 0;
           if (RANGES && kind == 2 && qbounds && n_t <= 64) {
@@ -234,13 +234,13 @@ __global__ __launch_bounds__(256, 2) void mfma_dkv_kernel(DevGroup g, KTensors t
   int item, hk;
   if (!decode_wg(g, t.hkv, 1, &item, &hk)) return;
   const int G = t.hq / t.hkv;
-  WorkItem w = g.items[item];
+  WorkItem w = plan_load(g.items, item);
   w.unit = uni(w.unit); w.tile = uni(w.tile); w.e0 = uni(w.e0); w.e1 = uni(w.e1); w.pslot = uni(w.pslot);
 
   const int wave = uni(threadIdx.x >> 6);
   const int blk_start = uni(w.blk_start), blk_len = uni(w.blk_len);
   const int koff = uni(w.moff);   // rows of the KV-type buffers: packed index + koff
-  const int seq0 = RANGES ? uni(g.blk_s0[uni(g.unit_blk[w.unit])]) : 0;   // first token of the sequence (keys and queries share it)
+  const int seq0 = RANGES ? uni(plan_load(g.blk_s0, plan_load(g.unit_blk, w.unit))) : 0;   // first token of the sequence (keys and queries share it)
   const int row0 = w.tile * TK;
   const int n_rows = min(TK, blk_len - row0);
   const int k_lo = blk_start + row0, k_end = k_lo + n_rows;
