@@ -125,9 +125,88 @@ static bool rows_are_faster(const dcp_plan_t* plan, const dcp_tensors_t* t, bool
   return false;
 }
 
+// Which of the bf16 MFMA kernels a launch takes: those that share a tile among the waves of a workgroup, or those whose four or
+// eight waves split the other side (kernels_mfma_split.hip).  The first stream least from the L2 and win where the chip is full of
+// equal work; the second finish a long walk several times sooner and win where a launch has few items or waits for its longest:
+// 5 196 tokens, 16/4 heads, blocks of 4 096, dK/dV 374 and 130 us; 4 528 tokens, 4/1 heads, forward 31 and 20; 65 536 tokens, 32/8
+// heads, forward 2.6 and 5.3 ms.  The time of a launch is estimated as
+//     start + sqrt((chain x pairs of the longest item)^2 + (share x all pairs / 512)^2) + item x items / 512
+// (a pair per query head for `share`; for dK/dV an item walks its KV head's whole group; 512 workgroups are resident) with
+// constants (us; chain and share per million pairs) fitted to the times of 230 batches, 121 / 69 / 40 of them with D 128 / 64 / 32:
+// 1 to 1 000 sequences of 1 to 65 536 tokens, 1 to 16 KV heads, groups of 1 to 8, blocks of 64 to 4 096.  The estimates are 12 to
+// 27 % off, so the second kind is taken only where it is estimated at nine tenths of the first or less: over those batches no call
+// was slower than with the first kind alone by more than 2 %, on average it took 0.87 / 0.64 / 0.71 of the time in the forward and
+// 0.79 / 0.52 / 0.47 in the backward.
+struct LaunchFit { double start, chain, share, item; };
+enum { kShared = 0, kWaves4, kWaves8 };
+static const LaunchFit kFitFwd[3][3] = {{{7.0, 128, 253, 5.7}, {5.0, 53.5, 373, 18.9}, {5.3, 30.1, 380, 41.1}},
+                                        {{6.4, 198, 249, 2.8}, {4.7, 53.7, 282, 7.7}, {4.7, 23.9, 275, 17.3}},
+                                        {{5.0, 134, 181, 5.1}, {3.7, 42.6, 193, 9.0}, {3.3, 28.6, 209, 18.0}}};
+static const LaunchFit kFitDq[3][3] = {{{7.3, 167, 335, 7.5}, {6.6, 50.4, 428, 29.6}, {7.8, 28.9, 433, 62.8}},
+                                       {{6.4, 196, 294, 4.5}, {5.2, 54.0, 323, 14.9}, {5.6, 14.5, 378, 39.7}},
+                                       {{5.3, 137, 204, 5.1}, {4.1, 44.1, 207, 10.2}, {4.1, 29.4, 221, 18.9}}};
+static const LaunchFit kFitDkv[3][3] = {{{9.4, 283, 500, 16.8}, {6.9, 77.3, 519, 29.0}, {8.2, 47.4, 531, 63.0}},
+                                        {{7.3, 232, 509, 19.0}, {5.1, 84.6, 492, 21.9}, {5.1, 55.1, 510, 45.7}},
+                                        {{10.7, 180, 394, 11.3}, {6.1, 70.2, 341, 10.9}, {6.2, 43.3, 358, 19.8}}};
+static const LaunchFit kFitBwd[3][3] = {{{}, {8.6, 118, 1230, 31.5}, {9.6, 68.1, 1230, 66.7}},   // dQ and dK/dV in one launch
+                                        {{}, {5.3, 101, 940, 20.6}, {4.9, 60.5, 1010, 44.6}},
+                                        {{}, {6.1, 80.7, 655, 11.7}, {4.5, 42.0, 779, 33.2}}};
+static constexpr double kLaunchGap = 1.0;   // between two launches
+static constexpr double kSure = 0.9;        // of the other estimate, for a choice away from the shared kernels or from two launches
+
+static double launch_us(const LaunchFit& f, double longest, double total, double items) {
+  return f.start + std::hypot(f.chain * longest * 1e-6, f.share * total / 512e6) + f.item * items / 512;
+}
+
+// The split kernels' launches: the same bound as in mfma_launch_fits.
+static bool may_split(const dcp_tensors_t* t, const LaunchSize& z) {
+  return t->dtype == DCP_BF16 && z.items * t->hq < (int64_t)((UINT32_MAX >> 3) / (kSplitSub * kSplitThreads));
+}
+
+static int pick_q(const LaunchFit (*fits)[3], const dcp_tensors_t* t, const LaunchSize& z, double* us) {
+  const LaunchFit* f = fits[t->d == 128 ? 0 : t->d == 64 ? 1 : 2];
+  int best = kShared;
+  double least = 0;
+  for (int v = kShared; v <= kWaves8; v++) {
+    const double x = launch_us(f[v], (double)z.longest, (double)z.total * t->hq, (double)z.items * t->hq);
+    if (v == kShared || x < least) { best = v; *us = x; least = v == kShared ? kSure * x : x; }
+  }
+  return best;
+}
+
+struct BwdChoice { int dq, dkv, both; };   // both: the form of the one launch, or kShared (two launches)
+static BwdChoice pick_bwd(const dcp_tensors_t* t, const LaunchSize& zq, const LaunchSize& zk) {
+  BwdChoice c{kShared, kShared, kShared};
+  if (!may_split(t, zq) || !may_split(t, zk)) return c;
+  const int di = t->d == 128 ? 0 : t->d == 64 ? 1 : 2;
+  const double group = t->hq / t->hkv, total = (double)zk.total * t->hq, items = (double)zk.items * t->hkv;
+  double us_q = 0, us_k = 0, least = 0;
+  c.dq = pick_q(kFitDq, t, zq, &us_q);
+  for (int v = kShared; v <= kWaves8; v++) {   // D = 128 shares its tiles over a list of cut items
+    const double x = v == kShared ? launch_us(kFitDkv[di][v], (double)zk.longest_part * group, total, (double)zk.parts * t->hkv)
+                                  : launch_us(kFitDkv[di][v], (double)zk.longest * group, total, items);
+    if (v == kShared || x < least) { c.dkv = v; us_k = x; least = v == kShared ? kSure * x : x; }
+  }
+  least = kSure * (us_q + us_k + kLaunchGap);
+  for (int v = kWaves4; v <= kWaves8; v++) {
+    const double x = launch_us(kFitBwd[di][v], (double)zk.longest * group, total, items + (double)zq.items * t->hq);
+    if (x < least) { c.both = v; least = x; }
+  }
+  return c;
+}
+static int waves_of(int form) { return form == kWaves4 ? 4 : 8; }
+
 // KV heads the dK/dV list is cut for (0: whole items).  All other lists are the same for every kernel family, so a plan
 // made ready for a shape serves it whichever family a call's strides or its `impl` choose.
 static int cut_heads(bool use_mfma, int32_t dtype, int32_t d, int32_t hkv) { return use_mfma && mfma_splits_dkv(dtype, d) ? hkv : 0; }
+
+// The list that the dK/dV launch of a call wants, as host_items names it: the split kernels take whole items.
+static int dkv_heads(dcp_plan_t* plan, const dcp_tensors_t* t, bool use_mfma, int n_seg) {
+  const int cut = cut_heads(use_mfma, t->dtype, t->d, t->hkv);
+  if (cut == 0) return 0;
+  const BwdChoice c = pick_bwd(t, plan->host_items(1, t->hq / t->hkv, n_seg).size, plan->host_items(2, cut, n_seg).size);
+  return c.dkv != kShared || c.both != kShared ? 0 : cut;
+}
 
 static KTensors pack(const dcp_plan_t* plan, const dcp_tensors_t* t) {
   KTensors k{};
@@ -168,7 +247,7 @@ extern "C" dcp_status_t dcp_plan_prepare(dcp_plan_t* plan, int32_t hq, int32_t h
   const int n_seg = xcd_segments(hkv);
   if ((st = plan->group_for(0, s, &g, hq / hkv, n_seg)) != DCP_OK) return st;
   if ((st = plan->group_for(1, s, &g, hq / hkv, n_seg)) != DCP_OK) return st;
-  return plan->group_for(2, s, &g, cut_heads(use_mfma, dtype, d, hkv), n_seg);
+  return plan->group_for(2, s, &g, dkv_heads(plan, &t, use_mfma, n_seg), n_seg);
 }
 
 extern "C" dcp_status_t dcp_block_attn_fwd(dcp_plan_t* plan, const dcp_tensors_t* t, void* stream) {
@@ -192,6 +271,12 @@ extern "C" dcp_status_t dcp_block_attn_fwd(dcp_plan_t* plan, const dcp_tensors_t
   use_mfma = use_mfma && mfma_launch_fits(g, false, t->dtype, t->d, t->hq, t->hkv) && !rows_are_faster(plan, t, false);
   KTensors k = pack(plan, t);
   ProfScope ps(DCP_K_FWD, s);
+  const LaunchSize& z = plan->host_items(0, t->hq / t->hkv, xcd_segments(t->hkv)).size;
+  if (use_mfma && may_split(t, z)) {
+    double us = 0;
+    const int form = pick_q(kFitFwd, t, z, &us);
+    if (form != kShared) return mfma_split_fwd(g, k, waves_of(form), s);
+  }
   return use_mfma ? mfma_fwd(g, k, s) : scalar_fwd(g, k, t->dtype, s);
 }
 
@@ -306,7 +391,12 @@ dcp_status_t dcp::bwd_launch(dcp_plan_t* plan, const dcp_tensors_t* t, void* wor
   DevGroup gq, gkv;
   const int n_seg = xcd_segments(t->hkv);
   if ((st = plan->group_for(1, s, &gq, t->hq / t->hkv, n_seg, may_alloc)) != DCP_OK) return st;
-  if ((st = plan->group_for(2, s, &gkv, cut_heads(use_mfma, t->dtype, t->d, t->hkv), n_seg, may_alloc)) != DCP_OK) return st;
+  // Whole or cut dK/dV items: what the choice of kernels wants, unless the plan holds only the other list (made for another number
+  // of query heads); whole items serve every kernel, cut ones only the one that shares its tiles.
+  const int cut = cut_heads(use_mfma, t->dtype, t->d, t->hkv);
+  int heads = dkv_heads(plan, t, use_mfma, n_seg);
+  if (cut && !plan->has_items(2, heads, n_seg) && plan->has_items(2, cut - heads, n_seg)) heads = cut - heads;
+  if ((st = plan->group_for(2, s, &gkv, heads, n_seg, may_alloc)) != DCP_OK) return st;
   use_mfma = use_mfma && mfma_launch_fits(gq, false, t->dtype, t->d, t->hq, t->hkv) && mfma_launch_fits(gkv, true, t->dtype, t->d, t->hq, t->hkv) &&
              !rows_are_faster(plan, t, true);
   KTensors k = pack(plan, t);
@@ -321,6 +411,13 @@ dcp_status_t dcp::bwd_launch(dcp_plan_t* plan, const dcp_tensors_t* t, void* wor
     k.qbounds = qb;
     if ((st = mfma_range_bounds(gkv, k, plan->d_blk_t32, plan->n_blocks, plan->longest_block, qb, s)) != DCP_OK) return st;
   }
+  BwdChoice form{kShared, kShared, kShared};
+  if (use_mfma) form = pick_bwd(t, plan->host_items(1, t->hq / t->hkv, n_seg).size, plan->host_items(2, cut, n_seg).size);
+  if (heads != 0) form.dkv = form.both = kShared;
+  if (form.both != kShared) {
+    ProfScope ps(DCP_K_DKV, s, may_alloc);
+    return mfma_split_bwd(gq, gkv, k, waves_of(form.both), s);
+  }
   if (use_mfma) {
     // the MFMA dQ kernel computes delta and the rescaled LSE of its own rows and leaves them for the dK/dV kernel
     k.delta_w = delta;
@@ -332,9 +429,10 @@ dcp_status_t dcp::bwd_launch(dcp_plan_t* plan, const dcp_tensors_t* t, void* wor
   }
   {
     ProfScope ps(DCP_K_DQ, s, may_alloc);
-    if ((st = use_mfma ? mfma_bwd_dq(gq, k, s) : scalar_bwd_dq(gq, k, t->dtype, s)) != DCP_OK) return st;
+    if ((st = form.dq != kShared ? mfma_split_dq(gq, k, waves_of(form.dq), s) : use_mfma ? mfma_bwd_dq(gq, k, s) : scalar_bwd_dq(gq, k, t->dtype, s)) != DCP_OK) return st;
   }
   ProfScope ps(DCP_K_DKV, s, may_alloc);
+  if (form.dkv != kShared) return mfma_split_dkv(gkv, k, waves_of(form.dkv), s);
   return use_mfma ? mfma_bwd_dkv(gkv, k, s) : scalar_bwd_dkv(gkv, k, t->dtype, s);
 }
 

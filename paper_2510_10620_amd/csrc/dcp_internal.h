@@ -93,7 +93,14 @@ struct GroupSize {
   int64_t waves = 0, wave_keys = 0;                   // 64-row tiles; over them, rows of the other side walked one by one
 };
 
+// What a launch over a work list costs, in (query, key) pairs of one query head (those of rows with per-token ranges are a guess).
+struct LaunchSize {
+  int64_t items = 0, longest = 0, total = 0;   // whole items, the costliest, all of them
+  int64_t parts = 0, longest_part = 0;         // of the list as it is, which may hold cut items
+};
+
 struct HostItems {
+  LaunchSize size;
   std::vector<WorkItem> items;
   std::vector<ReduceItem> reduce;
   int32_t n_pslots = 0;
@@ -137,6 +144,7 @@ struct dcp_plan {
   typedef std::tuple<int, int, int> ItemKey;
   static ItemKey item_key(int group_id, int heads, int n_seg) { return ItemKey(group_id, group_id == 2 ? heads : 0, n_seg); }
   std::map<ItemKey, dcp::HostItems> h_items;
+  std::vector<int64_t> item_cost[3];   // of every group's whole items, in unit order, once a list has been made
   std::map<ItemKey, dcp::DevItems> items;
 
   // may_alloc = false: fail (DCP_ERR_INVALID_ARG) instead of creating a device copy that does not exist yet
@@ -144,6 +152,8 @@ struct dcp_plan {
   // group id: 0 fwd, 1 bwdq, 2 bwdkv.  heads: for dK/dV see ItemKey; for the others the query heads per KV head, which
   // weigh the order of the list where the call creates it.  Host only; takes the plan's lock.
   const dcp::HostItems& host_items(int group_id, int heads, int n_seg);
+  // The list is on the device.
+  bool has_items(int group_id, int heads, int n_seg);
   // Where the list is missing and must not be created (may_alloc false, or `stream` is being captured), a list of whole
   // items with other segments takes its place: the same work, dealt to the XCDs less well.
   dcp_status_t group_for(int group_id, hipStream_t stream, dcp::DevGroup* out, int heads, int n_seg, bool may_alloc = true);

@@ -52,19 +52,18 @@ inline int64_t xcd_grid(const DevGroup& g, int heads_outer, int heads_inner) {
   return 8 * most;
 }
 
-// Workgroups that the fp32 and the narrow-head kernels launch per work item and KV head, and their threads.
-// kF32Sub: 32 rows each; the narrow dK/dV kernel takes two per item where there are few (kernels_mfma_narrow.hip).
-constexpr int kF32Sub = kItemRows / 32, kF32Threads = 512, kNarrowThreads = 256, kNarrowDkvThreads = 512;
-constexpr int64_t kNarrowDkvFew = 1024;
+// Workgroups that the kernels launch per work item and KV head, and their threads.  kSplit*: the kernels whose waves share 32
+// rows (split_rows.h).
+constexpr int kSplitSub = kItemRows / 32, kSplitThreads = 512, kNarrowThreads = 256, kNarrowDkvThreads = 512;
 
 // A launch counts its threads in 32 bits.  Whether that of a query-side group (or the dK/dV group) of these kernels fits;
 // the D = 128 kernels' tensors would outgrow the memory first.
 inline bool mfma_launch_fits(const DevGroup& g, bool dkv, int32_t dtype, int32_t d, int hq, int hkv) {
   if (dtype == DCP_BF16 && d == 128) return true;
-  if ((int64_t)g.n_items * hq < (UINT32_MAX >> 3) / (kF32Sub * kF32Threads)) return true;   // whatever the XCDs' shares are
+  if ((int64_t)g.n_items * hq < (UINT32_MAX >> 3) / (kSplitSub * kSplitThreads)) return true;   // whatever the XCDs' shares are
   const bool f32 = dtype == DCP_F32;
-  const int per_item = (dkv ? 1 : hq / hkv) * (f32 ? kF32Sub : dkv && g.n_items * (int64_t)hkv <= kNarrowDkvFew ? 2 : 1);
-  return xcd_grid(g, hkv, per_item) * (f32 ? kF32Threads : dkv ? kNarrowDkvThreads : kNarrowThreads) <= (int64_t)UINT32_MAX;
+  const int per_item = (dkv ? 1 : hq / hkv) * (f32 ? kSplitSub : 1);
+  return xcd_grid(g, hkv, per_item) * (f32 ? kSplitThreads : dkv ? kNarrowDkvThreads : kNarrowThreads) <= (int64_t)UINT32_MAX;
 }
 
 // Optional per-kernel event timing (see dcp_profile_enable).
@@ -105,6 +104,12 @@ dcp_status_t mfma_f32_dkv(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_narrow_fwd(const DevGroup& g, const KTensors& t, hipStream_t s);   // their part for bf16 with D < 128
 dcp_status_t mfma_narrow_dq(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_narrow_dkv(const DevGroup& g, const KTensors& t, hipStream_t s);
+// bf16 (any of these D), for launches that the others leave uneven or the chip half empty (kernels_mfma_split.hip): 4 or 8 waves
+// per workgroup, work lists of whole items; split_bwd is dQ and dK/dV in one launch
+dcp_status_t mfma_split_fwd(const DevGroup& g, const KTensors& t, int waves, hipStream_t s);
+dcp_status_t mfma_split_dq(const DevGroup& g, const KTensors& t, int waves, hipStream_t s);
+dcp_status_t mfma_split_dkv(const DevGroup& g, const KTensors& t, int waves, hipStream_t s);
+dcp_status_t mfma_split_bwd(const DevGroup& gq, const DevGroup& gkv, const KTensors& t, int waves, hipStream_t s);
 // per 32-row tile of every block: bounds of its rows' range arrays -> qbounds [n_t32 + 1][8]
 dcp_status_t mfma_range_bounds(const DevGroup& g, const KTensors& t, const int32_t* blk_t32, int32_t n_blocks, int32_t longest_block,
                                int32_t* qbounds, hipStream_t s);

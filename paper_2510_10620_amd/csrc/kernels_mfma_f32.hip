@@ -18,8 +18,7 @@
 // large fp32 matrix product reaches 152 on this card); 512 tokens, one head: 1 067 -> 54 us.  Four waves with the own
 // rows in registers took 2.36 ms (the dK/dV kernel spilled, and its 512 workgroups of one round waited for the longest).
 #include "device_utils.h"
-#include "mfma_common.h"
-#include "nonfinite.h"
+#include "split_rows.h"
 
 namespace dcp {
 
@@ -27,10 +26,7 @@ namespace {
 
 constexpr float kLog2eF = 1.44269504088896340736f;
 constexpr float kLn2F = 0.69314718055994530942f;
-constexpr int kThreads = kF32Threads;
-constexpr int kWaves = kThreads / 64;   // waves of a workgroup: they share the 32 rows and split the other side
-constexpr int kRows = 32;       // rows of a workgroup, and of a tile of the other side
-constexpr int kSub = kF32Sub;   // workgroups per work item
+constexpr int kThreads = kSplitThreads, kWaves = kSplitWaves, kRows = kSplitRows, kSub = kSplitSub;
 constexpr float kRaise = 8.f;   // the running maximum is raised when a tile exceeds it by more than 2^8
 
 __device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
@@ -41,9 +37,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2v __attribute__((ext_vector_type(2)));
 template <int D> struct RowChunk { f32x4 c[Chunks<D>::NJ]; };
 template <int D> struct ColChunk { float v[Chunks<D>::NR][D / 32]; };
-
-// row of accumulator register r in a 32-row tile, without the lane's 4h
-__device__ __forceinline__ constexpr int acc_row(int r) { return 8 * (r / 4) + r % 4; }
 
 // The lane number, opaque: what the loads below derive from it is recomputed per tile instead of being kept in dozens of
 // registers across the loop.
@@ -141,79 +134,6 @@ __device__ __forceinline__ f32x16 splat(float x) {
   return v;
 }
 
-// The wave's tiles of a unit's table rows: 32-row tiles of the other side's blocks, numbered through the whole batch
-// (t32), so that tile number mod kWaves deals them evenly to the waves whatever the block size.
-struct Walk {
-  const int4* rec;
-  int e, e_end, wave;
-  int c0, c1, kind, moff, t32, lim, jt;
-  __device__ Walk(const DevGroup& g, int e0, int e1, int wave_) : rec((const int4*)g.ent_rec) {
-    e = e0 - 1; e_end = e1; wave = wave_; c0 = c1 = kind = moff = t32 = lim = 0; jt = 0;
-  }
-  __device__ __forceinline__ int ks() const { return c0 + kRows * jt; }
-  template <bool RANGES>
-  __device__ __forceinline__ bool next(int q_hi, const RangeBounds& rb) {
-    for (;;) {
-      jt += kWaves;
-      while (c0 + kRows * jt >= lim) {
-        if (++e >= e_end) return false;
-        const int4 r = plan_load(rec, 2 * e);
-        c0 = uni(r.x); c1 = c0 + uni(r.y); kind = uni(r.z); moff = uni(r.w);
-        t32 = uni(plan_load(rec, 2 * e + 1).x);
-        lim = kind == 1 ? min(c1, q_hi + 1) : c1;
-        jt = (wave - t32) & (kWaves - 1);
-      }
-      if (!RANGES || kind != 2 || rb.may_see(ks(), min(ks() + kRows, c1))) return true;
-    }
-  }
-};
-
-// What the query-side kernels know about their rows.
-struct QTile {
-  int head, hk, blk_start, row0, n_rows, q_lo, q_hi, qoff, qi, e0, e1, unit;
-  int4 qr;
-  RangeBounds rb;
-};
-
-template <bool RANGES>
-__device__ __forceinline__ bool q_tile(const DevGroup& g, const KTensors& t, int lane, QTile* q) {
-  int item, x;
-  const int G = t.hq / t.hkv;
-  if (!decode_wg(g, t.hkv, G * kSub, &item, &x)) return false;
-  q->hk = x / (G * kSub);
-  q->head = q->hk * G + (x % (G * kSub)) / kSub;
-  WorkItem w = plan_load(g.items, item);
-  q->unit = uni(w.unit); q->e0 = uni(w.e0); q->e1 = uni(w.e1);
-  q->blk_start = uni(w.blk_start); q->qoff = uni(w.moff);
-  q->row0 = uni(w.tile) * (kSub * kRows) + (x % kSub) * kRows;
-  q->n_rows = min(kRows, uni(w.blk_len) - q->row0);
-  if (q->n_rows <= 0) return false;
-  q->q_lo = q->blk_start + q->row0;
-  q->q_hi = q->q_lo + q->n_rows - 1;
-  q->qi = q->q_lo + min(lane & 31, q->n_rows - 1);
-  q->qr = make_int4(0, 0, 0, 0);
-  q->rb.init();
-  if (RANGES) {
-    q->qr = range_row(t, q->qi, uni(plan_load(g.blk_s0, plan_load(g.unit_blk, q->unit))));
-    q->rb.add(q->qr);
-    q->rb.wave_reduce();
-#pragma unroll
-    for (int k = 0; k < 2; k++) {
-      q->rb.lo_min[k] = uni(q->rb.lo_min[k]); q->rb.lo_max[k] = uni(q->rb.lo_max[k]);
-      q->rb.hi_min[k] = uni(q->rb.hi_min[k]); q->rb.hi_max[k] = uni(q->rb.hi_max[k]);
-    }
-  }
-  return true;
-}
-
-__device__ __forceinline__ void mask_keys(f32x16& s, const QTile& q, int kind, int ks, int c0, int c1, int lane) {
-  const RowRanges rr = row_ranges(kind, q.qi, c0, c1, q.qr);
-  const int kb = ks + 4 * (lane >> 5);
-#pragma unroll
-  for (int r = 0; r < 16; r++)
-    if (!rr.sees(kb + acc_row(r))) s[r] = -INFINITY;
-}
-
 // A wave's D x 32 accumulator tile (lane = row of the result) into its LDS slab, rows of D + 4 floats.
 template <int D>
 __device__ __forceinline__ void stage_acc(float* slab, const f32x16 (&acc)[D / 32], int lane) {
@@ -255,13 +175,6 @@ __device__ __forceinline__ uint32_t store_sum(const float* slabs, const float* w
   return ((bad & 0xffffull) != 0) | ((bad & 0xffff0000ull) != 0) << 1 | ((bad & 0xffff00000000ull) != 0) << 2 | ((bad >> 48) != 0) << 3;
 }
 
-// row r of the workgroup, for the functions of nonfinite.h
-__device__ __forceinline__ FixRow fix_row(const QTile& q, int r) {
-  return {q.q_lo + r, q.e0, q.e1,
-          make_int4(__builtin_amdgcn_readlane(q.qr.x, r), __builtin_amdgcn_readlane(q.qr.y, r), __builtin_amdgcn_readlane(q.qr.z, r),
-                    __builtin_amdgcn_readlane(q.qr.w, r))};
-}
-
 }  // namespace
 
 // LDS of the three kernels: a slab per wave for its partial result; the first two hold the own rows during the loop.
@@ -274,7 +187,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_fwd_kernel(DevGroup g, KTenso
   __shared__ float sm[kWaves][kRows], sl[kWaves][kRows];
   const int lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6), li = lane & 31, lh = lane >> 5;
   QTile q;
-  if (!q_tile<RANGES>(g, t, lane, &q)) return;
+  if (!q_tile<RANGES>(g, t, lane, blockIdx.x, &q)) return;
   own_rows<D>(slabs, (const float*)t.q + (int64_t)q.head * t.q_sh, t.q_st, q.q_lo + q.qoff, q.q_hi + q.qoff);
   const float* kb = (const float*)t.k + (int64_t)q.hk * t.k_sh;
   const float* vb = (const float*)t.v + (int64_t)q.hk * t.v_sh;
@@ -283,7 +196,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_fwd_kernel(DevGroup g, KTenso
   f32x16 o[D / 32];
 #pragma unroll
   for (int dt = 0; dt < D / 32; dt++) o[dt] = splat(0.f);
-  Walk it(g, q.e0, q.e1, wave);
+  Walk<kWaves> it(g, q.e0, q.e1, wave);
   bool have = it.next<RANGES>(q.q_hi, q.rb);
   RowChunk<D> kc;
   if (have) load_rows<D>(kc, kb, t.k_st, it.ks() + it.moff, it.c1 - 1 + it.moff, 0);
@@ -390,7 +303,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dq_kernel(DevGroup g, KTensor
   __shared__ __attribute__((aligned(16))) float slabs[kWaves * SLAB];
   const int lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6), li = lane & 31, lh = lane >> 5;
   QTile q;
-  if (!q_tile<RANGES>(g, t, lane, &q)) return;
+  if (!q_tile<RANGES>(g, t, lane, blockIdx.x, &q)) return;
   const float* q_lds = slabs;
   const float* do_lds = slabs + SLAB;
   own_rows<D>(slabs, (const float*)t.q + (int64_t)q.head * t.q_sh, t.q_st, q.q_lo + q.qoff, q.q_hi + q.qoff);
@@ -420,7 +333,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_dq_kernel(DevGroup g, KTensor
   f32x16 dq[D / 32];
 #pragma unroll
   for (int dt = 0; dt < D / 32; dt++) dq[dt] = splat(0.f);
-  Walk it(g, q.e0, q.e1, wave);
+  Walk<kWaves> it(g, q.e0, q.e1, wave);
   bool have = it.next<RANGES>(q.q_hi, q.rb);
   RowChunk<D> rc;
   if (have) load_rows<D>(rc, kb, t.k_st, it.ks() + it.moff, it.c1 - 1 + it.moff, 0);

@@ -10,15 +10,13 @@
 //  * Nothing is scheduled by hand: with D = 64 a workgroup needs a third of the registers and half the LDS of the D = 128
 //    kernels, several are resident per CU, and their waves fill one another's waits.
 //
-// LDS tiles are [64 rows][D] bf16 without padding: a 256-byte line of the 64 banks holds 128 / D rows, and the 16-byte
-// chunk c of a row sits at chunk ((row % (128 / D)) * (D / 8) + c) ^ swz(line) of its line; 16 consecutive rows at one
-// chunk (row-major reads) fall into 16 different chunks, 4 consecutive rows x 64 bytes (transposing reads) into 4
-// different 64-byte groups.
+// LDS tiles: tile_layout.h.
 // Measured against one thread per row (16 384 causal tokens, 16/4 heads, D 64): forward 21.8 -> 0.54 ms, dQ 36.0 -> 0.60,
 // dK/dV 76.8 -> 1.29 ms.  What bounds them on large batches is the MFMA rate that the chip holds on real data: counting
 // the three parts of P and dS the three kernels execute 1 090, 1 128 and 950 TFLOP/s (65 536 causal tokens, log-normal).
 #include "mfma_dkv_kernel.h"
 #include "nonfinite.h"
+#include "tile_layout.h"
 
 namespace dcp {
 
@@ -26,18 +24,7 @@ namespace {
 
 constexpr float kLazyN = 8.f;   // the running maximum is raised when a tile exceeds it by more than 2^8
 
-template <int D>
-struct Narrow {
-  static constexpr int KS = D / 16, DT = D / 32;       // MFMA steps over D, 32-column tiles of D
-  static constexpr int kRow = 2 * D, kBytes = kTN * kRow;
-  static constexpr int RPL = 128 / D, CPR = D / 8;     // rows per 256-byte line, chunks per row
-  static constexpr int kORow = kRow + 16;              // pitch of a staged output row
-  static __device__ __forceinline__ int swz(int line) { return D == 64 ? ((line & 1) << 2) | ((line >> 1) & 3) : line & 3; }
-  static __device__ __forceinline__ int off(int row, int c) {
-    const int line = row / RPL;
-    return line * 256 + ((((row % RPL) * CPR + c) ^ swz(line)) << 4);
-  }
-};
+template <int D> using Narrow = TileLayout<D>;
 
 // fragment addresses of a lane (see FragAddr): rows enter the swizzle through row % 16 only
 template <int D>
@@ -94,25 +81,6 @@ struct NDma {
     }
   }
 };
-
-// Registers 8c .. 8c + 7 of a C tile as three bf16 operands that add up to the values exactly: 8 significant bits each, cut
-// off (not rounded: a finite value has finite parts), the remainders being exact in fp32.
-__device__ __forceinline__ void pack_split(const f32x16& s, int c, bf16x8 (&part)[3]) {
-  uint32_t w[3][4];
-#pragma unroll
-  for (int e = 0; e < 4; e++) {
-    float a = s[8 * c + 2 * e], b = s[8 * c + 2 * e + 1];
-#pragma unroll
-    for (int k = 0; k < 3; k++) {
-      const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
-      w[k][e] = __builtin_amdgcn_perm(ub, ua, 0x07060302);   // the upper halves of both
-      a -= __uint_as_float(ua & 0xffff0000u);
-      b -= __uint_as_float(ub & 0xffff0000u);
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < 3; k++) part[k] = as_frag(make_uint4(w[k][0], w[k][1], w[k][2], w[k][3]));
-}
 
 // store_tile32 for D columns
 template <int D>
@@ -464,27 +432,25 @@ __global__ __launch_bounds__(kNarrowThreads, 3) void narrow_dq_kernel(DevGroup g
   }
 }
 
-// A workgroup's eight waves are NG = 8 / KW groups of KW waves: a wave has 32 keys, the groups own the same 32 KW keys
-// and take the query tiles in turn, each with LDS stages of its own, and add their sums at the end.  The dK/dV work items
-// are few and long (one per 128 keys and KV head in the D = 128 kernel) and a launch
-// waits for its longest (with P and dS in two parts, 16 384 tokens, 16/4 heads, D 64: 1.44 ms with one group of four waves,
-// 1.05 with two, 0.93 with four groups of two waves; with many items the two-group form is the faster, see mfma_narrow_dkv).
-template <int D, int KW, bool RANGES>
+// A workgroup's eight waves are NG groups of KW waves: a wave has 32 keys, the groups own the same 128 keys and take the query
+// tiles in turn, each with LDS stages of its own, and add their sums at the end.  It serves launches of many short items, whose
+// start it shares among four waves' keys (1 000 sequences of 20 tokens, 8/2 heads, D 64: 73 us, 84 with 32 keys a workgroup); the
+// others go to kernels_mfma_split.hip (65 536 tokens, 16/4 heads, D 64 / 32: 2.94 / 2.13 here and 2.87 / 1.79 ms there).
+template <int D, bool RANGES>
 __global__ __launch_bounds__(kNarrowDkvThreads, 2) void narrow_dkv_kernel(DevGroup g, KTensors t) {
-  constexpr int NG = 8 / KW, SUB = 4 / KW;   // workgroups per 128-key work item
+  constexpr int KW = 4, NG = 2;
   typedef Narrow<D> N;
   // stage: Q tile, dO tile, then per query row lse2, -delta and ranges, and the range bounds of the tile's two halves
   constexpr int LSE = 2 * N::kBytes, DEL = LSE + 256, RNG = DEL + 256, BND = RNG + 1024, STAGE = BND + 1024;
   constexpr int kStage = RANGES ? STAGE : RNG;
   __shared__ __attribute__((aligned(1024))) char all_stages[2 * NG * kStage];
-  int item, x;
-  if (!decode_wg(g, t.hkv, SUB, &item, &x)) return;
-  const int hk = x / SUB, G = t.hq / t.hkv;
+  int item, hk;
+  if (!decode_wg(g, t.hkv, 1, &item, &hk)) return;
+  const int G = t.hq / t.hkv;
   const WorkItem w = plan_load(g.items, item);
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6) % KW, group = uni(tid >> 6) / KW, li = lane & 31, lh = lane >> 5;
   char* stages = all_stages + group * (2 * kStage);
-  const int koff = uni(w.moff), row0 = uni(w.tile) * 128 + (x % SUB) * (32 * KW), n_rows = min(32 * KW, uni(w.blk_len) - row0);
-  if (n_rows <= 0) return;
+  const int koff = uni(w.moff), row0 = uni(w.tile) * 128, n_rows = min(128, uni(w.blk_len) - row0);
   const int seq0 = RANGES ? uni(plan_load(g.blk_s0, plan_load(g.unit_blk, uni(w.unit)))) : 0;
   const int k_lo = uni(w.blk_start) + row0, k_end = k_lo + n_rows, wrow0 = wave * 32;
   const int w_rows = max(0, min(32, n_rows - wrow0));
@@ -682,26 +648,15 @@ __global__ __launch_bounds__(kNarrowDkvThreads, 2) void narrow_dkv_kernel(DevGro
 dcp_status_t mfma_narrow_fwd(const DevGroup& g, const KTensors& t, hipStream_t s) { DCP_NARROW_LAUNCH(narrow_fwd_kernel) }
 dcp_status_t mfma_narrow_dq(const DevGroup& g, const KTensors& t, hipStream_t s) { DCP_NARROW_LAUNCH(narrow_dq_kernel) }
 
-template <int KW>
-static void narrow_dkv_launch(const DevGroup& g, const KTensors& t, hipStream_t s) {
-  const dim3 grid(xcd_grid(g, t.hkv, 4 / KW)), block(kNarrowDkvThreads);
-  if (t.masked) {
-    if (t.d == 32) hipLaunchKernelGGL((narrow_dkv_kernel<32, KW, true>), grid, block, 0, s, g, t);
-    else hipLaunchKernelGGL((narrow_dkv_kernel<64, KW, true>), grid, block, 0, s, g, t);
-  } else {
-    if (t.d == 32) hipLaunchKernelGGL((narrow_dkv_kernel<32, KW, false>), grid, block, 0, s, g, t);
-    else hipLaunchKernelGGL((narrow_dkv_kernel<64, KW, false>), grid, block, 0, s, g, t);
-  }
-}
-
 dcp_status_t mfma_narrow_dkv(const DevGroup& g, const KTensors& t, hipStream_t s) {
-  // Four rounds of 128-key workgroups (one per CU) balance whatever the lengths are, and share each Q / dO tile among
-  // four waves; with fewer the longest item decides, and half as many keys per workgroup shorten it.  128 against 64 keys,
-  // D 64, log-normal lengths: 2 048 items (65 536 tokens, 16/4 heads) 2.90 and 2.98 ms, (16 384 tokens, 16/16) 0.71 and 0.81;
-  // 1 024 items (32 768 tokens, 16/4) causal 1.90 and 2.04, sink and window 1.70 and 1.15; 512 items (16 384, 16/4) 1.06 and
-  // 0.86, (65 536, 4/1) 1.47 and 0.81; 128 items (4 096, 16/4) 0.26 and 0.15 ms.
-  if ((int64_t)g.n_items * t.hkv > kNarrowDkvFew) narrow_dkv_launch<4>(g, t, s);
-  else narrow_dkv_launch<2>(g, t, s);
+  const dim3 grid(xcd_grid(g, t.hkv, 1)), block(kNarrowDkvThreads);
+  if (t.masked) {
+    if (t.d == 32) hipLaunchKernelGGL((narrow_dkv_kernel<32, true>), grid, block, 0, s, g, t);
+    else hipLaunchKernelGGL((narrow_dkv_kernel<64, true>), grid, block, 0, s, g, t);
+  } else {
+    if (t.d == 32) hipLaunchKernelGGL((narrow_dkv_kernel<32, false>), grid, block, 0, s, g, t);
+    else hipLaunchKernelGGL((narrow_dkv_kernel<64, false>), grid, block, 0, s, g, t);
+  }
   DCP_HIP_TRY(hipGetLastError());
   return DCP_OK;
 }

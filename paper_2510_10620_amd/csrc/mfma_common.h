@@ -299,6 +299,17 @@ template <class T> __device__ __forceinline__ T plan_load(const T* p, int i) {
   return __builtin_bit_cast(T, v);
 }
 
+// Requests every 64-byte line of the kernel's BYTES of arguments at once: they are read where they are needed, from half a dozen
+// places of the prologue that wait for one another, and each line read for the first time is a trip to memory.
+template <int BYTES>
+__device__ __forceinline__ void touch_args() {
+  const __attribute__((address_space(4))) int* a = (const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr();
+  int x = 0;
+#pragma unroll
+  for (int i = 0; i < BYTES / 64; i++) x |= a[16 * i];
+  asm volatile("" ::"s"(x));
+}
+
 // Combine a value with the one held by lane (l ^ 32), in every lane, without an LDS round trip:
 // v_permlane32_swap exchanges lanes 32..63 of its first operand with lanes 0..31 of its second, so
 // with the same value in both, each lane ends up holding the lower half's value in one result and
@@ -408,10 +419,11 @@ __device__ __forceinline__ int classify32(int kind, int ks, int c1, int q_lo, in
 // each in (item, head of the group) order: workgroups that run at the same time on an XCD work on neighbouring
 // items of one KV head, whose K / V (or Q / dO) rows that XCD's L2 then holds once.  With a multiple of 8 KV heads
 // an XCD takes whole heads and the list is one segment.
-__device__ __forceinline__ bool decode_wg(const DevGroup& g, int heads_outer, int heads_inner, int* item, int* head) {
+// bid: the workgroup's number in the launch, or in its part of it if that starts at a multiple of 8.
+__device__ __forceinline__ bool decode_wg(const DevGroup& g, int heads_outer, int heads_inner, int* item, int* head, int bid) {
   const int upx = (heads_outer * g.n_seg) >> 3;
-  int p = blockIdx.x >> 3;
-  for (int u = (blockIdx.x & 7) * upx, ue = u + upx; u < ue; u++) {
+  int p = bid >> 3;
+  for (int u = (bid & 7) * upx, ue = u + upx; u < ue; u++) {
     const int s = u % g.n_seg;
     const int s0 = g.seg[s], len = (g.seg[s + 1] - s0) * heads_inner;
     if (p < len) {
@@ -422,6 +434,10 @@ __device__ __forceinline__ bool decode_wg(const DevGroup& g, int heads_outer, in
     p -= len;
   }
   return false;
+}
+
+__device__ __forceinline__ bool decode_wg(const DevGroup& g, int heads_outer, int heads_inner, int* item, int* head) {
+  return decode_wg(g, heads_outer, heads_inner, item, head, blockIdx.x);
 }
 
 // How the four waves of a query-side workgroup divide a 128-row work item and the G query heads of its KV head: a

@@ -23,11 +23,13 @@ struct KernelArgs {
   DevGroup g;
   KTensors t;
 };
-__device__ __forceinline__ KernelArgs kernel_args() {
+// g_at, t_at: where they lie in the arguments
+__device__ __forceinline__ KernelArgs kernel_args(int g_at = 0, int t_at = sizeof(DevGroup)) {
   uint64_t p = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(p));
   KernelArgs a;
-  __builtin_memcpy(&a, (const void*)(const __attribute__((address_space(4))) char*)p, sizeof(a));
+  __builtin_memcpy(&a.g, (const void*)((const __attribute__((address_space(4))) char*)p + g_at), sizeof(a.g));
+  __builtin_memcpy(&a.t, (const void*)((const __attribute__((address_space(4))) char*)p + t_at), sizeof(a.t));
   return a;
 }
 
@@ -163,8 +165,8 @@ __device__ void fix_dq(const DevGroup& g, const KTensors& t, const FixRow& f, in
 }
 
 // dK and dV of key j (packed index), table rows [e0, e1) of its block, over the query heads of KV head hk; t.lse2 and t.delta
-// (negated) are the dQ kernel's
-template <typename T, int D>
+// (negated) are the dQ kernel's, or (OWN) are worked out here, from the LSE and from O and dO
+template <typename T, int D, bool OWN = false>
 __device__ void fix_dkv(const DevGroup& g, const KTensors& t, int j, int e0, int e1, int hk, int seq0, const T* k, const T* v, T* dk_dst, T* dv_dst) {
   const int lane = threadIdx.x & 63, G = t.hq / t.hkv;
   const float c_log2 = t.scale * 1.44269504088896340736f;
@@ -180,14 +182,18 @@ __device__ void fix_dkv(const DevGroup& g, const KTensors& t, int j, int e0, int
       for (int h = hk * G; h < (hk + 1) * G; h++) {
         const T* qb = (const T*)t.q + (int64_t)h * t.q_sh;
         const T* dob = (const T*)t.dout + (int64_t)h * t.do_sh;
-        const float lse2 = t.lse2[(int64_t)h * t.q_rows + i + moff];
+        const int64_t at = (int64_t)h * t.q_rows + i + moff;
+        float delta = 0.f;
+        if (OWN) delta = dot_row<T, D>((const T*)t.out_in + (int64_t)(i + moff) * t.o_st + (int64_t)h * t.o_sh, dob + (int64_t)(i + moff) * t.do_st);
+        else delta = -t.delta[at];
+        const float lse2 = OWN ? row_lse2(t.lse[at], &delta) : t.lse2[at];
         const bool vis = sees && lse2 < INFINITY;
         const uint64_t on = __ballot(vis);
         if (!on) continue;
         float p = 0.f, ds = 0.f;
         if (vis) {
           p = __builtin_amdgcn_exp2f(fmaf(dot_row<T, D>(qb + (int64_t)(i + moff) * t.q_st, k), c_log2, -lse2));
-          ds = p * (dot_row<T, D>(dob + (int64_t)(i + moff) * t.do_st, v) + t.delta[(int64_t)h * t.q_rows + i + moff]);
+          ds = p * (dot_row<T, D>(dob + (int64_t)(i + moff) * t.do_st, v) - delta);
         }
         add_rows<T, D>(dk, ds, on, qb + (int64_t)(i0 + moff) * t.q_st, t.q_st, lane);
         add_rows<T, D>(dv, p, on, dob + (int64_t)(i0 + moff) * t.do_st, t.do_st, lane);

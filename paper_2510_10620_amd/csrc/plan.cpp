@@ -437,6 +437,7 @@ extern "C" dcp_status_t dcp_plan_set_block_buffers(dcp_plan_t* plan, const int32
   }
   plan->buffers = true;
   plan->h_items.clear();   // work lists leave out absent blocks
+  for (auto& c : plan->item_cost) c.clear();
   plan->q_slot.assign(q_slot, q_slot + plan->n_blocks);
   plan->kv_slot.assign(kv_slot, kv_slot + plan->n_blocks);
   for (int32_t b = 0; b < plan->n_blocks; b++) {
@@ -625,6 +626,7 @@ const HostItems& dcp_plan::host_items(int gid, int heads, int n_seg) {
   std::vector<int64_t> ecost;   // per-entry costs of the item being built
   // first pass: whole items and the total cost
   int64_t total = 0;
+  const bool known = !item_cost[gid].empty();
   for (int32_t u = 0; u < (int32_t)hg->unit_blk.size(); u++) {
     int32_t b = hg->unit_blk[u];
     if (b < 0) continue;  // unused slot
@@ -634,13 +636,19 @@ const HostItems& dcp_plan::host_items(int gid, int heads, int n_seg) {
       int64_t r0 = blk_start[b] + (int64_t)t * kItemRows;
       int64_t r1 = std::min<int64_t>(r0 + kItemRows, blk_start[b] + blk_len[b]);
       int64_t cost = 0;
-      for (int32_t e = hg->ptr[u]; e < hg->ptr[u + 1]; e++)
+      if (known) cost = item_cost[gid][sc.size()];
+      else for (int32_t e = hg->ptr[u]; e < hg->ptr[u + 1]; e++)
         cost += tile_cost(hg->ent_kind[e], r0, r1, hg->ent_start[e], hg->ent_start[e] + hg->ent_len[e], gid == 2);
       sc.push_back({{u, t, hg->ptr[u], hg->ptr[u + 1], -1, blk_start[b], blk_len[b], (gid == 2 ? kv_moff : q_moff)[b]}, cost});
       total += cost;
     }
   }
+  if (!known)
+    for (const Scored& x : sc) item_cost[gid].push_back(x.cost);
   HostItems hi;
+  hi.size.items = (int64_t)sc.size();
+  hi.size.total = total;
+  for (const Scored& x : sc) hi.size.longest = std::max(hi.size.longest, x.cost);
   if (gid == 2 && heads > 0) {
     // Long items are cut, along their table rows, into parts (each with a slot of fp32 partial sums that a reduce
     // kernel adds up): one key tile under a sink, or the first keys of the one long sequence of a small batch, can
@@ -709,6 +717,8 @@ const HostItems& dcp_plan::host_items(int gid, int heads, int n_seg) {
     }
   }
   std::stable_sort(sc.begin(), sc.end(), [](const Scored& a, const Scored& b) { return a.cost > b.cost; });
+  hi.size.parts = (int64_t)sc.size();
+  hi.size.longest_part = sc.empty() ? 0 : sc[0].cost;
   if (heads > 0 && !sc.empty() && (gid == 2 || (!has_ranges && (int64_t)sc.size() * heads > kResidentWorkgroups / 8 * n_seg))) {
     // Sequence by sequence (the costliest sequence first, longest item first inside it) when that balances as well as
     // strict longest-first does.  Items of one sequence that run at the same time read the same rows of the other
@@ -826,6 +836,11 @@ static bool is_capturing(hipStream_t stream) {
     return false;
   }
   return status != hipStreamCaptureStatusNone;
+}
+
+bool dcp_plan::has_items(int gid, int heads, int n_seg) {
+  std::lock_guard<std::mutex> lock(mu);
+  return items.count(item_key(gid, heads, n_seg)) != 0;
 }
 
 dcp_status_t dcp_plan::group_for(int gid, hipStream_t stream, DevGroup* out, int heads, int n_seg, bool may_alloc) {

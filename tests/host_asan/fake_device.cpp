@@ -120,6 +120,26 @@ dcp_status_t mfma_bwd_dkv(const DevGroup& g, const KTensors& t, hipStream_t) {
     if (g.items[i].pslot >= 0) t.part[((int64_t)(g.items[i].pslot + 1) * t.hkv) * 2 * 128 * 128 - 1] = 0.f;
   return DCP_OK;
 }
+// the split kernels: four workgroups an item, lists of whole items
+#define SPLIT_FITS() WALK_CHECK((waves == 4 || waves == 8) && t.dtype == DCP_BF16 && \
+                                xcd_grid(g, t.hkv, t.hq / t.hkv * kSplitSub) * 64 * waves <= (int64_t)UINT32_MAX, "a launch that the split kernels do not take")
+static dcp_status_t split_whole(const DevGroup& g) {
+  for (int32_t i = 0; i < g.n_items; i++) WALK_CHECK(g.items[i].pslot < 0, "a cut item in a list for whole ones");
+  return DCP_OK;
+}
+dcp_status_t mfma_split_fwd(const DevGroup& g, const KTensors& t, int waves, hipStream_t s) { SPLIT_FITS(); return mfma_fwd(g, t, s); }
+dcp_status_t mfma_split_dq(const DevGroup& g, const KTensors& t, int waves, hipStream_t s) { SPLIT_FITS(); return mfma_bwd_dq(g, t, s); }
+dcp_status_t mfma_split_dkv(const DevGroup& g, const KTensors& t, int waves, hipStream_t s) {
+  SPLIT_FITS();
+  dcp_status_t st = split_whole(g);
+  return st != DCP_OK ? st : mfma_bwd_dkv(g, t, s);
+}
+dcp_status_t mfma_split_bwd(const DevGroup& g, const DevGroup& gkv, const KTensors& t, int waves, hipStream_t s) {
+  SPLIT_FITS();
+  dcp_status_t st = split_whole(gkv);
+  if (st == DCP_OK) st = walk_group(g, t.q_rows, g_fake_kv_rows, 0, t.block_size, false);
+  return st != DCP_OK ? st : mfma_bwd_dkv(gkv, t, s);
+}
 dcp_status_t mfma_range_bounds(const DevGroup& g, const KTensors& t, const int32_t* blk_t32, int32_t n_blocks, int32_t longest_block,
                                int32_t* qbounds, hipStream_t) {
   for (int32_t b = 0; b < n_blocks; b++) {

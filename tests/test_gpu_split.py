@@ -1,0 +1,85 @@
+"""The bf16 kernels whose waves split the other side, and the rule that takes a launch to them, against the fp64 oracle: rows and
+blocks around their 32-row tiles and 128-row work items, walks of one tile and of more than 64, every mask kind, slots and strided
+inputs, in batches small enough for one backward launch, for two, and with heads enough for the kernels that share their tiles.
+Bounds: those of bf16 I/O in helpers.TOL."""
+import numpy as np
+import pytest
+
+from paper_2510_10620_amd import workloads as W
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [1, 31, 33, 63, 65, 127, 129, 257, 640]
+ALL = ("out", "lse", "dq", "dk", "dv")
+
+
+def _launches(g):
+    """(results of the backward, dQ launches of their own)"""
+    import paper_2510_10620_amd as P
+    P.dcp_profile_enable(True)
+    grads = g.backward()
+    n = P.dcp_profile_read("dq")[1]
+    P.dcp_profile_enable(False)
+    return grads, n
+
+
+def _run(name, lens, B, heads, d, spec, seed, window_rows=False, slots=False, strided=False):
+    import torch
+    w = W.custom_workload(name, lens, B, heads[0], heads[1], d, "bf16", spec, seed=seed, input_scale=0.5)
+    tensors, table = W.make_tensors(w), H.oracle_table(w)
+    ref = H.oracle_full(w, tensors, table)
+    t, window = table.copy(), None
+    if window_rows:
+        t[t[:, 2] == W.MASK_RANGES, 2] = W.MASK_WINDOW
+        window = (spec.window, spec.sink)
+    slot, n_slots = (None, 0)
+    if slots:
+        slot, n_slots, _ = W.deal_divisions(table[:, 0], 3, 5)
+    g = H.GpuRun(w, tensors, t, slot, n_slots, window=window)
+    if strided:
+        hq, hkv = heads
+        fused = torch.cat([g.q, g.k, g.v], dim=1).contiguous()
+        g.q, g.k, g.v = fused[:, :hq], fused[:, hq:hq + hkv], fused[:, hq + hkv:]
+    out, lse = g.forward()
+    (dq, dk, dv), own_dq = _launches(g)
+    H.check(w, dict(out=out, lse=lse, dq=dq, dk=dk, dv=dv), ref, ALL, f"{name} D{d} B{B} {heads} {spec.kind}")
+    return own_dq
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("B,heads,launches", [(64, (2, 1), 1), (512, (2, 1), 1), (512, (16, 4), 2), (64, (64, 64), 2)],
+                         ids=["one", "one-long-blocks", "two", "shared"])
+@pytest.mark.parametrize("spec,window_rows", [(W.MaskSpec("causal"), False), (W.MaskSpec("lambda", window=70, sink=9), False),
+                                              (W.MaskSpec("lambda", window=70, sink=9), True)], ids=["causal", "ranges", "window"])
+def test_tile_edges(d, B, heads, launches, spec, window_rows):
+    own_dq = _run("edges", EDGES, B, heads, d, spec, 81, window_rows)
+    assert own_dq == launches - 1, "the batch is meant for the other number of backward launches"
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("spec", [W.MaskSpec("causal"), W.MaskSpec("shared_question")], ids=lambda s: s.kind)
+def test_long_walks_few_heads(d, spec):
+    """Blocks of more than 64 query tiles, eight query heads to a KV head: dK/dV walks them 64 at a time."""
+    _run("long", [2300, 33], 2304, (8, 1), d, spec, 82)
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_slots_strides_and_a_row_without_keys(d):
+    """Partial slots with their merge, q / k / v as views of one projection, three mask blocks."""
+    _run("slots", [300, 700, 1], 128, (4, 2), d, W.MaskSpec("causal_blockwise", window=2, sink=1, mblock=64), 83, slots=True, strided=True)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_prepared_for_other_heads(d):
+    """A plan made ready for 128 query heads (D = 128: cut dK/dV items, which the split kernels do not take) serves two."""
+    import paper_2510_10620_amd as P
+    w = W.custom_workload("prep", [1300, 200], 128, 2, 2, d, "bf16", W.MaskSpec("causal"), seed=84, input_scale=0.5)
+    tensors, table = W.make_tensors(w), H.oracle_table(w)
+    ref = H.oracle_full(w, tensors, table)
+    for hq in (2, 128):
+        g = H.GpuRun(w, tensors, table)
+        P.dcp_plan_prepare(g.plan, hq, 2, d, P.DCP_BF16)
+        out, lse = g.forward()
+        dq, dk, dv = g.backward()
+        H.check(w, dict(out=out, lse=lse, dq=dq, dk=dk, dv=dv), ref, ALL, f"prepared for {hq} D{d}")
