@@ -296,7 +296,7 @@ extern "C" dcp_status_t dcp_merge_partials(dcp_plan_t* plan, const void* o_part,
   if ((st = plan->ensure_device(s)) != DCP_OK) return st;
   ProfScope ps(DCP_K_MERGE, s);
   return stream_merge(plan->d_merge_ptr, plan->d_merge_idx, plan->d_q_mem0, plan->d_fwd.blk_len, plan->n_blocks,
-                      plan->block_size, o_part, lse_part, out, o_stride_t, o_stride_h, lse, plan->q_rows, hq, d,
+                      plan->longest_block, plan->block_size, o_part, lse_part, out, o_stride_t, o_stride_h, lse, plan->q_rows, hq, d,
                       dtype, s);
 }
 

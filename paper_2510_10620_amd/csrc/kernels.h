@@ -116,7 +116,7 @@ dcp_status_t mfma_range_bounds(const DevGroup& g, const KTensors& t, const int32
 
 // streaming (HBM-bound) kernels
 dcp_status_t stream_merge(const int32_t* merge_ptr, const int32_t* merge_idx, const int32_t* blk_mem0,
-                          const int32_t* blk_len, int32_t n_blocks, int32_t block_size, const void* o_part,
+                          const int32_t* blk_len, int32_t n_blocks, int32_t longest_block, int32_t block_size, const void* o_part,
                           const float* lse_part, void* out, int64_t o_st, int64_t o_sh, float* lse,
                           int64_t total_tokens, int32_t hq, int32_t d, int32_t dtype, hipStream_t s);
 dcp_status_t stream_delta(const void* o, int64_t o_st, int64_t o_sh, const void* dout, int64_t do_st, int64_t do_sh,

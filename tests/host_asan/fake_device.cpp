@@ -154,10 +154,11 @@ dcp_status_t mfma_range_bounds(const DevGroup& g, const KTensors& t, const int32
 }
 
 dcp_status_t stream_merge(const int32_t* merge_ptr, const int32_t* merge_idx, const int32_t* blk_mem0, const int32_t* blk_len,
-                          int32_t n_blocks, int32_t block_size, const void*, const float*, void*, int64_t, int64_t, float*,
+                          int32_t n_blocks, int32_t longest_block, int32_t block_size, const void*, const float*, void*, int64_t, int64_t, float*,
                           int64_t q_rows, int32_t, int32_t, int32_t, hipStream_t) {
   for (int32_t b = 0; b < n_blocks; b++) {
     WALK_CHECK(merge_ptr[b] <= merge_ptr[b + 1], "merge CSR not monotone");
+    WALK_CHECK(blk_len[b] <= longest_block, "a block longer than the longest");
     for (int32_t p = merge_ptr[b]; p < merge_ptr[b + 1]; p++) WALK_CHECK(merge_idx[p] >= 0 && merge_idx[p] < g_fake_n_slots, "merge slot out of range");
     if (blk_mem0[b] >= 0) WALK_CHECK((int64_t)blk_mem0[b] + blk_len[b] <= q_rows && blk_len[b] <= block_size, "merged block outside the output");
   }

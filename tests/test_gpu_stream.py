@@ -1,9 +1,11 @@
 """The streaming kernels where their splits end: heads and chunks that do not divide a workgroup's steps, a ragged last
 workgroup, one to eight parts."""
+import numpy as np
 import pytest
 import torch
 
 import paper_2510_10620_amd as P
+from paper_2510_10620_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
@@ -49,3 +51,52 @@ def test_sum_on_both_sides_of_the_cache(src, n, n_parts):
     for p in parts[1:]:
         ref = ref + p.float()
     assert torch.equal(out, ref.to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("d,hq", [(128, 1), (128, 3), (128, 8), (128, 16), (128, 24), (128, 40), (64, 5), (64, 32), (32, 7), (32, 64), (32, 100)])
+def test_merge_of_none_to_six_partials(d, hq):
+    """bf16 merge for head counts below, at and above the pairs of one step; blocks with 0 to 6 partials, short last blocks, a
+    sequence shorter than its block.  Against fp64: half an ulp of the bf16 result is 2^-8 of it at most, the fp32 weights and
+    sums of six terms add less than 2^-16 of the largest term."""
+    B, lens = 16, [6 * 16 - 5, 3, 16]
+    cu = W.cu_from_lengths(lens)
+    table = [[i, j, 1 if i == j else 0] for i in range(6) for j in range(i + 1)] + [[6, 6, 1]]   # block 7 has no row: no partial
+    table = np.array(table, dtype=np.int32)
+    n_slots = len(table)
+    plan = P.dcp_plan_create(cu, B, table, np.arange(n_slots, dtype=np.int32), n_slots)
+    T = int(cu[-1])
+    gen = torch.Generator(device="cuda").manual_seed(hq * 7 + d)
+    o = torch.randn((n_slots, B, hq, d), device="cuda", generator=gen).to(torch.bfloat16)
+    lse = torch.randn((n_slots, hq, B), device="cuda", generator=gen) * 3
+    lse[torch.rand(lse.shape, device="cuda", generator=gen) < 0.2] = -float("inf")
+    value = o.double()
+    o = o.masked_fill((lse == -float("inf")).transpose(1, 2)[..., None], float("nan"))   # a dead partial's rows reach nothing
+    out, l = torch.full((T, hq, d), float("nan"), device="cuda", dtype=torch.bfloat16), torch.full((hq, T), float("nan"), device="cuda")
+    P.dcp_merge_partials(plan, o, lse, out, l)
+    start, length = plan.export("BLK_START"), plan.export("BLK_LEN")
+    for b in range(len(start)):
+        s = np.nonzero(table[:, 0] == b)[0]
+        n, a = int(length[b]), int(start[b])
+        x = lse[s][:, :, :n].double()                                    # [parts, hq, n]
+        ref_l = torch.logsumexp(x, 0) if len(s) else torch.full((hq, n), -float("inf"), device="cuda", dtype=torch.float64)
+        wgt = torch.where(x > -float("inf"), torch.exp(x - ref_l), torch.zeros_like(x))
+        terms = wgt.transpose(1, 2)[..., None] * value[s][:, :n]    # [parts, n, hq, d]
+        ref = terms.sum(0) if len(s) else torch.zeros((n, hq, d), device="cuda", dtype=torch.float64)
+        slack = 2.0 ** -16 * (terms.abs().amax() if len(s) else 0)
+        assert ((out[a:a + n].double() - ref).abs() <= 2.0 ** -8 * ref.abs() + slack).all(), (b, len(s))
+        dead = ref_l == -float("inf")
+        assert (l[:, a:a + n][dead] == -float("inf")).all()
+        assert ((l[:, a:a + n].double() - ref_l)[~dead].abs() <= 1e-5).all(), (b, len(s))
+
+
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 128), (torch.bfloat16, 8), (torch.float32, 64)])
+@pytest.mark.parametrize("T", [1, 7, 8, 9, 32 * 1024 - 1, 32 * 1024])
+def test_delta_tokens_per_workgroup(T, dtype, d):
+    """Both sides of the rule for 8 or 32 tokens a workgroup, odd head counts.  fp32 sums of d terms in any order: d 2^-24 of
+    the terms' magnitudes."""
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    o, do = (torch.randn((T, 3, d), device="cuda", generator=gen).to(dtype) for _ in range(2))
+    delta = torch.full((3, T), float("nan"), device="cuda")
+    P.dcp_bwd_delta(o, do, delta)
+    t = o.double() * do.double()
+    assert ((delta.double() - t.sum(-1).T).abs() <= d * 2.0 ** -24 * t.abs().sum(-1).T).all()
