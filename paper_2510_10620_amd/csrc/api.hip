@@ -125,76 +125,86 @@ static bool rows_are_faster(const dcp_plan_t* plan, const dcp_tensors_t* t, bool
   return false;
 }
 
-// Which of the bf16 MFMA kernels a launch takes: those that share a tile among the waves of a workgroup, or those whose four or
-// eight waves split the other side (kernels_mfma_split.hip).  The first stream least from the L2 and win where the chip is full of
-// equal work; the second finish a long walk several times sooner and win where a launch has few items or waits for its longest:
-// 5 196 tokens, 16/4 heads, blocks of 4 096, dK/dV 374 and 130 us; 4 528 tokens, 4/1 heads, forward 31 and 20; 65 536 tokens, 32/8
-// heads, forward 2.6 and 5.3 ms.  The time of a launch is estimated as
+// Which of the MFMA kernels a launch takes.  bf16: those that share a tile among the waves of a workgroup, or those whose four or
+// eight waves split the other side (kernels_mfma_split.hip); fp32: 32 or 16 rows a workgroup.  The first kind streams least from the
+// L2 and wins where the chip is full of equal work; the second finishes a long walk several times sooner and wins where a launch
+// has few items or waits for its longest: bf16, 5 196 tokens, 16/4 heads, blocks of 4 096, dK/dV 374 and 130 us; 4 528 tokens, 4/1
+// heads, forward 31 and 20; 65 536 tokens, 32/8 heads, forward 2.6 and 5.3 ms; fp32, 1 723 tokens, one head of 64, dK/dV 70 and 44 us,
+// 8 192 tokens, 8/2 heads, dQ 504 and 608.  The time of a launch is estimated as
 //     start + sqrt((chain x pairs of the longest item)^2 + (share x all pairs / 512)^2) + item x items / 512
 // (a pair per query head for `share`; for dK/dV an item walks its KV head's whole group; 512 workgroups are resident) with
-// constants (us; chain and share per million pairs) fitted to the times of 230 batches, 121 / 69 / 40 of them with D 128 / 64 / 32:
-// 1 to 1 000 sequences of 1 to 65 536 tokens, 1 to 16 KV heads, groups of 1 to 8, blocks of 64 to 4 096.  The estimates are 12 to
-// 27 % off, so the second kind is taken only where it is estimated at nine tenths of the first or less: over those batches no call
-// was slower than with the first kind alone by more than 2 %, on average it took 0.87 / 0.64 / 0.71 of the time in the forward and
-// 0.79 / 0.52 / 0.47 in the backward.
+// constants (us; chain and share per million pairs) fitted to the times of 230 batches in bf16, 121 / 69 / 40 of them with D 128 /
+// 64 / 32, and 105 in fp32, 32 / 47 / 26: 1 to 1 000 sequences of 1 to 65 536 tokens, 1 to 16 KV heads, groups of 1 to 8, blocks of 64
+// to 4 096.  The estimates are 12 to 27 % off, so the second kind is taken only where it is estimated at 0.9 (fp32: 0.85 to 0.87) of
+// the first or less: over those batches no call was slower than with the first kind alone by more than 2 %, on average it took 0.87 /
+// 0.64 / 0.71 of the time in the forward and 0.79 / 0.52 / 0.47 in the backward (fp32 0.78 / 0.88 / 0.92 and 0.66 / 0.71 / 0.66).
 struct LaunchFit { double start, chain, share, item; };
-enum { kShared = 0, kWaves4, kWaves8 };
-static const LaunchFit kFitFwd[3][3] = {{{7.0, 128, 253, 5.7}, {5.0, 53.5, 373, 18.9}, {5.3, 30.1, 380, 41.1}},
-                                        {{6.4, 198, 249, 2.8}, {4.7, 53.7, 282, 7.7}, {4.7, 23.9, 275, 17.3}},
-                                        {{5.0, 134, 181, 5.1}, {3.7, 42.6, 193, 9.0}, {3.3, 28.6, 209, 18.0}}};
-static const LaunchFit kFitDq[3][3] = {{{7.3, 167, 335, 7.5}, {6.6, 50.4, 428, 29.6}, {7.8, 28.9, 433, 62.8}},
-                                       {{6.4, 196, 294, 4.5}, {5.2, 54.0, 323, 14.9}, {5.6, 14.5, 378, 39.7}},
-                                       {{5.3, 137, 204, 5.1}, {4.1, 44.1, 207, 10.2}, {4.1, 29.4, 221, 18.9}}};
-static const LaunchFit kFitDkv[3][3] = {{{9.4, 283, 500, 16.8}, {6.9, 77.3, 519, 29.0}, {8.2, 47.4, 531, 63.0}},
-                                        {{7.3, 232, 509, 19.0}, {5.1, 84.6, 492, 21.9}, {5.1, 55.1, 510, 45.7}},
-                                        {{10.7, 180, 394, 11.3}, {6.1, 70.2, 341, 10.9}, {6.2, 43.3, 358, 19.8}}};
-static const LaunchFit kFitBwd[3][3] = {{{}, {8.6, 118, 1230, 31.5}, {9.6, 68.1, 1230, 66.7}},   // dQ and dK/dV in one launch
-                                        {{}, {5.3, 101, 940, 20.6}, {4.9, 60.5, 1010, 44.6}},
-                                        {{}, {6.1, 80.7, 655, 11.7}, {4.5, 42.0, 779, 33.2}}};
+enum { kShared = 0, kSplit, kSplit8, kForms };   // bf16: shared tiles, four waves, eight waves; fp32: 32 rows, 16 rows
+struct LaunchFits { int32_t dtype, d; double sure; LaunchFit fwd[kForms], dq[kForms], dkv[kForms], bwd[kForms]; };   // bwd: dQ and dK/dV in one launch
+static const LaunchFits kFits[] = {
+    {DCP_BF16, 128, 0.9, {{7.0, 128, 253, 5.7}, {5.0, 53.5, 373, 18.9}, {5.3, 30.1, 380, 41.1}}, {{7.3, 167, 335, 7.5}, {6.6, 50.4, 428, 29.6}, {7.8, 28.9, 433, 62.8}},
+     {{9.4, 283, 500, 16.8}, {6.9, 77.3, 519, 29.0}, {8.2, 47.4, 531, 63.0}}, {{}, {8.6, 118, 1230, 31.5}, {9.6, 68.1, 1230, 66.7}}},
+    {DCP_BF16, 64, 0.9, {{6.4, 198, 249, 2.8}, {4.7, 53.7, 282, 7.7}, {4.7, 23.9, 275, 17.3}}, {{6.4, 196, 294, 4.5}, {5.2, 54.0, 323, 14.9}, {5.6, 14.5, 378, 39.7}},
+     {{7.3, 232, 509, 19.0}, {5.1, 84.6, 492, 21.9}, {5.1, 55.1, 510, 45.7}}, {{}, {5.3, 101, 940, 20.6}, {4.9, 60.5, 1010, 44.6}}},
+    {DCP_BF16, 32, 0.9, {{5.0, 134, 181, 5.1}, {3.7, 42.6, 193, 9.0}, {3.3, 28.6, 209, 18.0}}, {{5.3, 137, 204, 5.1}, {4.1, 44.1, 207, 10.2}, {4.1, 29.4, 221, 18.9}},
+     {{10.7, 180, 394, 11.3}, {6.1, 70.2, 341, 10.9}, {6.2, 43.3, 358, 19.8}}, {{}, {6.1, 80.7, 655, 11.7}, {4.5, 42.0, 779, 33.2}}},
+    {DCP_F32, 128, 0.85, {{9.6, 223, 2220, 82.9}, {7.6, 151, 2810, 32.9}}, {{13.9, 314, 3240, 120}, {9.9, 248, 4860, 40.2}},
+     {{15.9, 448, 3710, 183}, {10.8, 274, 4960, 89.9}}, {{}, {11.4, 364, 11050, 76.4}}},
+    {DCP_F32, 64, 0.87, {{6.9, 125, 1180, 41.4}, {5.4, 88.9, 1300, 31.5}}, {{8.7, 174, 1640, 54.4}, {6.3, 144, 2160, 38.8}},
+     {{12.5, 252, 1990, 61.7}, {8.1, 164, 2310, 31.5}}, {{}, {8.6, 170, 5574, 51.4}}},
+    {DCP_F32, 32, 0.86, {{5.1, 70.8, 573, 21.1}, {4.8, 42.8, 748, 23.3}}, {{5.8, 97.3, 789, 24.6}, {4.8, 71.1, 1130, 27.4}},
+     {{6.6, 152, 1120, 52.6}, {5.9, 94.8, 1390, 26.6}}, {{}, {4.5, 109, 2975, 41.0}}}};
 static constexpr double kLaunchGap = 1.0;   // between two launches
-static constexpr double kSure = 0.9;        // of the other estimate, for a choice away from the shared kernels or from two launches
 
 static double launch_us(const LaunchFit& f, double longest, double total, double items) {
   return f.start + std::hypot(f.chain * longest * 1e-6, f.share * total / 512e6) + f.item * items / 512;
 }
 
-// The split kernels' launches: the same bound as in mfma_launch_fits.
-static bool may_split(const dcp_tensors_t* t, const LaunchSize& z) {
-  return t->dtype == DCP_BF16 && z.items * t->hq < (int64_t)((UINT32_MAX >> 3) / (kSplitSub * kSplitThreads));
+// The row of the table, or null where there is no choice: launches that may have more threads than 32 bits count.
+static const LaunchFits* fits_of(const dcp_tensors_t* t, const LaunchSize& z) {
+  if (z.items * t->hq >= (int64_t)((UINT32_MAX >> 3) / (kItemRows / 16 * kSplitThreads))) return nullptr;
+  for (const LaunchFits& f : kFits)
+    if (f.dtype == t->dtype && f.d == t->d) return &f;
+  return nullptr;
+}
+static int last_form(const dcp_tensors_t* t) { return t->dtype == DCP_BF16 ? kSplit8 : kSplit; }
+
+// The form of a launch whose estimates are us[kShared ..], and its estimate.
+static int least_form(const LaunchFits& f, const dcp_tensors_t* t, const double* us, double* out) {
+  int best = kShared;
+  double least = f.sure * us[kShared];
+  for (int v = kSplit; v <= last_form(t); v++)
+    if (us[v] < least) { best = v; least = us[v]; }
+  *out = us[best];
+  return best;
 }
 
-static int pick_q(const LaunchFit (*fits)[3], const dcp_tensors_t* t, const LaunchSize& z, double* us) {
-  const LaunchFit* f = fits[t->d == 128 ? 0 : t->d == 64 ? 1 : 2];
-  int best = kShared;
-  double least = 0;
-  for (int v = kShared; v <= kWaves8; v++) {
-    const double x = launch_us(f[v], (double)z.longest, (double)z.total * t->hq, (double)z.items * t->hq);
-    if (v == kShared || x < least) { best = v; *us = x; least = v == kShared ? kSure * x : x; }
-  }
-  return best;
+static int pick_q(const LaunchFits& fits, const LaunchFit* f, const dcp_tensors_t* t, const LaunchSize& z, double* us) {
+  double x[kForms];
+  for (int v = kShared; v <= last_form(t); v++) x[v] = launch_us(f[v], (double)z.longest, (double)z.total * t->hq, (double)z.items * t->hq);
+  return least_form(fits, t, x, us);
 }
 
 struct BwdChoice { int dq, dkv, both; };   // both: the form of the one launch, or kShared (two launches)
 static BwdChoice pick_bwd(const dcp_tensors_t* t, const LaunchSize& zq, const LaunchSize& zk) {
   BwdChoice c{kShared, kShared, kShared};
-  if (!may_split(t, zq) || !may_split(t, zk)) return c;
-  const int di = t->d == 128 ? 0 : t->d == 64 ? 1 : 2;
-  const double group = t->hq / t->hkv, total = (double)zk.total * t->hq, items = (double)zk.items * t->hkv;
-  double us_q = 0, us_k = 0, least = 0;
-  c.dq = pick_q(kFitDq, t, zq, &us_q);
-  for (int v = kShared; v <= kWaves8; v++) {   // D = 128 shares its tiles over a list of cut items
-    const double x = v == kShared ? launch_us(kFitDkv[di][v], (double)zk.longest_part * group, total, (double)zk.parts * t->hkv)
-                                  : launch_us(kFitDkv[di][v], (double)zk.longest * group, total, items);
-    if (v == kShared || x < least) { c.dkv = v; us_k = x; least = v == kShared ? kSure * x : x; }
-  }
-  least = kSure * (us_q + us_k + kLaunchGap);
-  for (int v = kWaves4; v <= kWaves8; v++) {
-    const double x = launch_us(kFitBwd[di][v], (double)zk.longest * group, total, items + (double)zq.items * t->hq);
-    if (x < least) { c.both = v; least = x; }
+  const LaunchFits* f = fits_of(t, zq);
+  if (!f || !fits_of(t, zk)) return c;
+  const double longest = (double)zk.longest * (t->hq / t->hkv), total = (double)zk.total * t->hq, items = (double)zk.items * t->hkv;
+  double us_q = 0, us_k = 0, x[kForms];
+  c.dq = pick_q(*f, f->dq, t, zq, &us_q);
+  for (int v = kShared; v <= last_form(t); v++) x[v] = launch_us(f->dkv[v], longest, total, items);
+  if (mfma_splits_dkv(t->dtype, t->d))   // shared tiles go over a list of cut items
+    x[kShared] = launch_us(f->dkv[kShared], (double)zk.longest_part * (t->hq / t->hkv), total, (double)zk.parts * t->hkv);
+  c.dkv = least_form(*f, t, x, &us_k);
+  double least = f->sure * (us_q + us_k + kLaunchGap);
+  for (int v = kSplit; v <= last_form(t); v++) {
+    const double us = launch_us(f->bwd[v], longest, total, items + (double)zq.items * t->hq);
+    if (us < least) { c.both = v; least = us; }
   }
   return c;
 }
-static int waves_of(int form) { return form == kWaves4 ? 4 : 8; }
+static int waves_of(int form) { return form == kSplit ? 4 : 8; }
 
 // KV heads the dK/dV list is cut for (0: whole items).  All other lists are the same for every kernel family, so a plan
 // made ready for a shape serves it whichever family a call's strides or its `impl` choose.
@@ -272,10 +282,10 @@ extern "C" dcp_status_t dcp_block_attn_fwd(dcp_plan_t* plan, const dcp_tensors_t
   KTensors k = pack(plan, t);
   ProfScope ps(DCP_K_FWD, s);
   const LaunchSize& z = plan->host_items(0, t->hq / t->hkv, xcd_segments(t->hkv)).size;
-  if (use_mfma && may_split(t, z)) {
+  if (const LaunchFits* f = use_mfma ? fits_of(t, z) : nullptr) {
     double us = 0;
-    const int form = pick_q(kFitFwd, t, z, &us);
-    if (form != kShared) return mfma_split_fwd(g, k, waves_of(form), s);
+    const int form = pick_q(*f, f->fwd, t, z, &us);
+    if (form != kShared) return t->dtype == DCP_F32 ? mfma_f32_fwd(g, k, 16, s) : mfma_split_fwd(g, k, waves_of(form), s);
   }
   return use_mfma ? mfma_fwd(g, k, s) : scalar_fwd(g, k, t->dtype, s);
 }
@@ -416,7 +426,7 @@ dcp_status_t dcp::bwd_launch(dcp_plan_t* plan, const dcp_tensors_t* t, void* wor
   if (heads != 0) form.dkv = form.both = kShared;
   if (form.both != kShared) {
     ProfScope ps(DCP_K_DKV, s, may_alloc);
-    return mfma_split_bwd(gq, gkv, k, waves_of(form.both), s);
+    return t->dtype == DCP_F32 ? mfma_f32_bwd(gq, gkv, k, s) : mfma_split_bwd(gq, gkv, k, waves_of(form.both), s);
   }
   if (use_mfma) {
     // the MFMA dQ kernel computes delta and the rescaled LSE of its own rows and leaves them for the dK/dV kernel
@@ -429,10 +439,12 @@ dcp_status_t dcp::bwd_launch(dcp_plan_t* plan, const dcp_tensors_t* t, void* wor
   }
   {
     ProfScope ps(DCP_K_DQ, s, may_alloc);
-    if ((st = form.dq != kShared ? mfma_split_dq(gq, k, waves_of(form.dq), s) : use_mfma ? mfma_bwd_dq(gq, k, s) : scalar_bwd_dq(gq, k, t->dtype, s)) != DCP_OK) return st;
+    if (form.dq != kShared) st = t->dtype == DCP_F32 ? mfma_f32_dq(gq, k, 16, s) : mfma_split_dq(gq, k, waves_of(form.dq), s);
+    else st = use_mfma ? mfma_bwd_dq(gq, k, s) : scalar_bwd_dq(gq, k, t->dtype, s);
+    if (st != DCP_OK) return st;
   }
   ProfScope ps(DCP_K_DKV, s, may_alloc);
-  if (form.dkv != kShared) return mfma_split_dkv(gkv, k, waves_of(form.dkv), s);
+  if (form.dkv != kShared) return t->dtype == DCP_F32 ? mfma_f32_dkv(gkv, k, 16, s) : mfma_split_dkv(gkv, k, waves_of(form.dkv), s);
   return use_mfma ? mfma_bwd_dkv(gkv, k, s) : scalar_bwd_dkv(gkv, k, t->dtype, s);
 }
 

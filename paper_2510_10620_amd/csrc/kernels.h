@@ -98,10 +98,12 @@ size_t mfma_dkv_part_bytes(int32_t n_pslots, int32_t hkv);   // size of KTensors
 dcp_status_t mfma_fwd(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_bwd_dq(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_bwd_dkv(const DevGroup& g, const KTensors& t, hipStream_t s);
-dcp_status_t mfma_f32_fwd(const DevGroup& g, const KTensors& t, hipStream_t s);   // the fp32 part of the three above
-dcp_status_t mfma_f32_dq(const DevGroup& g, const KTensors& t, hipStream_t s);
-dcp_status_t mfma_f32_dkv(const DevGroup& g, const KTensors& t, hipStream_t s);
-dcp_status_t mfma_narrow_fwd(const DevGroup& g, const KTensors& t, hipStream_t s);   // their part for bf16 with D < 128
+// fp32, 32 or 16 rows per workgroup; f32_bwd is dQ and dK/dV in one launch (16 rows)
+dcp_status_t mfma_f32_fwd(const DevGroup& g, const KTensors& t, int rows, hipStream_t s);
+dcp_status_t mfma_f32_dq(const DevGroup& g, const KTensors& t, int rows, hipStream_t s);
+dcp_status_t mfma_f32_dkv(const DevGroup& g, const KTensors& t, int rows, hipStream_t s);
+dcp_status_t mfma_f32_bwd(const DevGroup& gq, const DevGroup& gkv, const KTensors& t, hipStream_t s);
+dcp_status_t mfma_narrow_fwd(const DevGroup& g, const KTensors& t, hipStream_t s);   // the part of the three above for D < 128
 dcp_status_t mfma_narrow_dq(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_narrow_dkv(const DevGroup& g, const KTensors& t, hipStream_t s);
 // bf16 (any of these D), for launches that the others leave uneven or the chip half empty (kernels_mfma_split.hip): 4 or 8 waves

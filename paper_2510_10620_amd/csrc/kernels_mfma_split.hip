@@ -45,12 +45,6 @@ template <int D> constexpr int kRegion = kSlab<D> > 2 * kTile<D> ? kSlab<D> : 2 
 template <int D> constexpr int kStages = D < 128 ? 2 : 1;
 template <int D> constexpr int kRegionKv = D < 128 ? 4 * kTile<D> : kRegion<D>;
 
-__device__ __forceinline__ int fresh_lane() {
-  int lane = threadIdx.x & 63;
-  asm volatile("" : "+v"(lane));
-  return lane;
-}
-
 // Fragment addresses from two registers: every other one is an XOR of these with a constant.
 template <int D>
 struct Frags {
@@ -235,7 +229,7 @@ __global__ __launch_bounds__(64 * NW, 2) void split_fwd_kernel(DevGroup g, KTens
   const int lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6), li = lane & 31, lh = lane >> 5;
   QTile q;
   touch_args<sizeof(DevGroup) + sizeof(KTensors)>();
-  if (!q_tile<RANGES>(g, t, lane, blockIdx.x, &q)) return;
+  if (!q_tile<kRows, RANGES>(g, t, lane, blockIdx.x, &q)) return;
   const int slot = plan_load(g.unit_out, q.unit);
   char* k_lds = lds + wave * kRegion<D>;
   char* v_lds = k_lds + kTile<D>;
@@ -357,7 +351,7 @@ __device__ __forceinline__ void split_dq(const DevGroup& g, const KTensors& t, c
   typedef TileLayout<D> L;
   const int lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6), lh = lane >> 5;
   QTile q;
-  if (!q_tile<RANGES>(g, t, lane, bid, &q)) return;
+  if (!q_tile<kRows, RANGES>(g, t, lane, bid, &q)) return;
   char* k_lds = lds + wave * kRegion<D>;
   char* v_lds = k_lds + kTile<D>;
   const bf16_t* kb = (const bf16_t*)t.k + (int64_t)q.hk * t.k_sh;
@@ -434,65 +428,6 @@ __device__ __forceinline__ void split_dq(const DevGroup& g, const KTensors& t, c
       }
     }
 }
-
-namespace {
-
-// The wave's (query head, 32-query tile) pairs of a KV unit's table rows, dealt by tile number and head; 64 tiles of a block at a
-// time, those that see none of the keys [k_lo, k_end) left out.  All state is wave-uniform.
-template <int NW, bool RANGES>
-struct QWalk {
-  const int4* rec;
-  const int4* qbounds;
-  int e, e_end, wave, G, hh, base, n_t, q0, q1, kind, moff, t32, jt;
-  uint64_t sees, all, todo;   // of the 64 tiles from `base` on: may see a key, every row sees every key; left of the current head
-  __device__ QWalk(const DevGroup& g, int e0, int e1, int G_, int wave_, const int32_t* qb)
-      : rec((const int4*)g.ent_rec), qbounds((const int4*)qb) {
-    e = e0 - 1; e_end = e1; wave = wave_; G = G_; hh = G_ - 1; base = n_t = q0 = q1 = kind = moff = t32 = jt = 0; sees = all = todo = 0;
-  }
-  __device__ __forceinline__ int qs() const { return q0 + kRows * jt; }
-  __device__ __forceinline__ bool next(int k_lo, int k_end) {
-    while (!todo) {
-      if (++hh >= G) {
-        hh = 0;
-        base += 64;
-        if (base >= n_t) {
-          if (++e >= e_end) return false;
-          const int4 r = plan_load(rec, 2 * e);
-          q0 = uni(r.x); q1 = q0 + uni(r.y); kind = uni(r.z); moff = uni(r.w); t32 = uni(plan_load(rec, 2 * e + 1).x);
-          n_t = (q1 - q0 + kRows - 1) / kRows;
-          base = 0;
-        }
-        const int n = min(64, n_t - base);
-        const uint64_t there = n >= 64 ? ~0ull : (1ull << n) - 1ull;
-        if (RANGES && kind == 2) {
-          const int lane = fresh_lane();
-          bool see = false, every = false;
-          if (lane < n) {
-            const int4 a = qbounds[2 * (int64_t)(t32 + base + lane)], b = qbounds[2 * (int64_t)(t32 + base + lane) + 1];
-            see = (k_lo < a.w && k_end > a.x) || (k_lo < b.w && k_end > b.x);           // RangeBounds::may_see
-            every = (k_lo >= a.y && k_end <= a.z) || (k_lo >= b.y && k_end <= b.z);     // RangeBounds::all_see
-          }
-          sees = __ballot(see);
-          all = __ballot(every);
-        } else {
-          const int first = kind == 1 ? max(0, (k_lo - q0) / kRows - base) : 0;   // earlier tiles end before the first key
-          sees = first >= 64 ? 0ull : there & (~0ull << first);
-        }
-      }
-      todo = sees & ((NW == 8 ? 0x0101010101010101ull : 0x1111111111111111ull) << ((wave - t32 - hh) & (NW - 1)));
-    }
-    const int b = __builtin_ctzll(todo);
-    todo &= todo - 1;
-    jt = base + b;
-    return true;
-  }
-  // every pair of the current tile and the keys [.., k_hi] (all kRows of them there) is visible
-  __device__ __forceinline__ bool full(int k_hi) const {
-    return qs() + kRows <= q1 && (kind == 0 || (kind == 1 && qs() >= k_hi) || (RANGES && kind == 2 && (all >> (jt & 63) & 1)));
-  }
-};
-
-}  // namespace
 
 // per wave, for the query rows of a tile: lse2 [64], -delta [64], ranges [64] (32 rows, and what the other lanes of a copy repeat)
 template <bool RANGES> constexpr int kRowBytesLds = RANGES ? 1536 : 512;

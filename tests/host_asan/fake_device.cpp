@@ -140,6 +140,17 @@ dcp_status_t mfma_split_bwd(const DevGroup& g, const DevGroup& gkv, const KTenso
   if (st == DCP_OK) st = walk_group(g, t.q_rows, g_fake_kv_rows, 0, t.block_size, false);
   return st != DCP_OK ? st : mfma_bwd_dkv(gkv, t, s);
 }
+// fp32 with 16 rows a workgroup: eight workgroups an item
+#define F32_FITS() WALK_CHECK(t.dtype == DCP_F32 && xcd_grid(g, t.hkv, t.hq / t.hkv * (kItemRows / 16)) * kSplitThreads <= (int64_t)UINT32_MAX, \
+                              "a launch that the fp32 kernels do not take")
+dcp_status_t mfma_f32_fwd(const DevGroup& g, const KTensors& t, int, hipStream_t s) { F32_FITS(); return mfma_fwd(g, t, s); }
+dcp_status_t mfma_f32_dq(const DevGroup& g, const KTensors& t, int, hipStream_t s) { F32_FITS(); return mfma_bwd_dq(g, t, s); }
+dcp_status_t mfma_f32_dkv(const DevGroup& g, const KTensors& t, int, hipStream_t s) { F32_FITS(); return mfma_bwd_dkv(g, t, s); }
+dcp_status_t mfma_f32_bwd(const DevGroup& g, const DevGroup& gkv, const KTensors& t, hipStream_t s) {
+  F32_FITS();
+  dcp_status_t st = walk_group(g, t.q_rows, g_fake_kv_rows, 0, t.block_size, false);
+  return st != DCP_OK ? st : mfma_bwd_dkv(gkv, t, s);
+}
 dcp_status_t mfma_range_bounds(const DevGroup& g, const KTensors& t, const int32_t* blk_t32, int32_t n_blocks, int32_t longest_block,
                                int32_t* qbounds, hipStream_t) {
   for (int32_t b = 0; b < n_blocks; b++) {

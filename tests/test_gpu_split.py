@@ -1,7 +1,7 @@
-"""The bf16 kernels whose waves split the other side, and the rule that takes a launch to them, against the fp64 oracle: rows and
-blocks around their 32-row tiles and 128-row work items, walks of one tile and of more than 64, every mask kind, slots and strided
+"""The bf16 kernels whose waves split the other side, the fp32 kernels of 16 rows a workgroup, and the rule that takes a launch to
+them, against the fp64 oracle: rows and blocks around their 32-row tiles and 128-row work items, walks of one tile and of more than 64, every mask kind, slots and strided
 inputs, in batches small enough for one backward launch, for two, and with heads enough for the kernels that share their tiles.
-Bounds: those of bf16 I/O in helpers.TOL."""
+Bounds: those of the I/O type in helpers.TOL."""
 import numpy as np
 import pytest
 
@@ -24,9 +24,9 @@ def _launches(g):
     return grads, n
 
 
-def _run(name, lens, B, heads, d, spec, seed, window_rows=False, slots=False, strided=False):
+def _run(name, lens, B, heads, d, spec, seed, window_rows=False, slots=False, strided=False, dtype="bf16"):
     import torch
-    w = W.custom_workload(name, lens, B, heads[0], heads[1], d, "bf16", spec, seed=seed, input_scale=0.5)
+    w = W.custom_workload(name, lens, B, heads[0], heads[1], d, dtype, spec, seed=seed, input_scale=0.5)
     tensors, table = W.make_tensors(w), H.oracle_table(w)
     ref = H.oracle_full(w, tensors, table)
     t, window = table.copy(), None
@@ -55,6 +55,21 @@ def _run(name, lens, B, heads, d, spec, seed, window_rows=False, slots=False, st
 def test_tile_edges(d, B, heads, launches, spec, window_rows):
     own_dq = _run("edges", EDGES, B, heads, d, spec, 81, window_rows)
     assert own_dq == launches - 1, "the batch is meant for the other number of backward launches"
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("B,heads,launches", [(64, (1, 1), 1), (512, (8, 8), 2), (64, (32, 32), 2)], ids=["one", "two", "many"])
+@pytest.mark.parametrize("spec,window_rows", [(W.MaskSpec("causal"), False), (W.MaskSpec("lambda", window=70, sink=9), False),
+                                              (W.MaskSpec("lambda", window=70, sink=9), True)], ids=["causal", "ranges", "window"])
+def test_tile_edges_f32(d, B, heads, launches, spec, window_rows):
+    own_dq = _run("edges", EDGES, B, heads, d, spec, 85, window_rows, dtype="f32")
+    assert own_dq == launches - 1, "the batch is meant for the other number of backward launches"
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_f32_long_walks_slots_and_strides(d):
+    _run("long", [2300, 33], 2304, (4, 1), d, W.MaskSpec("causal"), 86, dtype="f32")
+    _run("slots", [300, 700, 1], 128, (4, 2), d, W.MaskSpec("causal_blockwise", window=2, sink=1, mblock=64), 87, slots=True, strided=True, dtype="f32")
 
 
 @pytest.mark.parametrize("d", [32, 64, 128])
