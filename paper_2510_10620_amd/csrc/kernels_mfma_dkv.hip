@@ -19,7 +19,7 @@ __global__ __launch_bounds__(256) void range_bounds_kernel(DevGroup g, KTensors 
   RangeBounds rb;
   rb.init();
   if (row < len) rb.add(range_row(t, g.blk_start[b] + row, g.blk_s0[b]));
-  rb.wave_reduce();
+  rb.wave_reduce<32>();
   if (lane == 0) {
     int32_t* o = qbounds + (int64_t)(blk_t32[b] + tile) * 8;
     o[0] = rb.lo_min[0]; o[1] = rb.lo_max[0]; o[2] = rb.hi_min[0]; o[3] = rb.hi_max[0];

@@ -90,71 +90,68 @@ __global__ __launch_bounds__(256, 2) void mfma_dq_kernel(DevGroup g, KTensors t)
   st.qr = make_int4(0, 0, 0, 0);
   RangeBounds wrb;
   wrb.init();
-  if (t.masked) {
-    st.qr = range_row(t, st.qi, uni(plan_load(g.blk_s0, plan_load(g.unit_blk, w.unit))));
-    if (qv) wrb.add(st.qr);
-  }
-  RangeBounds rb = wrb;
-  if (t.masked) {
-    wrb.wave_reduce();
-    if (lane == 0) {
-      wg_bounds[wave][0] = wrb.lo_min[0]; wg_bounds[wave][1] = wrb.lo_max[0]; wg_bounds[wave][2] = wrb.hi_min[0]; wg_bounds[wave][3] = wrb.hi_max[0];
-      wg_bounds[wave][4] = wrb.lo_min[1]; wg_bounds[wave][5] = wrb.lo_max[1]; wg_bounds[wave][6] = wrb.hi_min[1]; wg_bounds[wave][7] = wrb.hi_max[1];
-    }
-    __syncthreads();
-    rb.init();
-    for (int x = 0; x < 4; x++) {
-      rb.lo_min[0] = min(rb.lo_min[0], wg_bounds[x][0]); rb.lo_max[0] = max(rb.lo_max[0], wg_bounds[x][1]);
-      rb.hi_min[0] = min(rb.hi_min[0], wg_bounds[x][2]); rb.hi_max[0] = max(rb.hi_max[0], wg_bounds[x][3]);
-      rb.lo_min[1] = min(rb.lo_min[1], wg_bounds[x][4]); rb.lo_max[1] = max(rb.lo_max[1], wg_bounds[x][5]);
-      rb.hi_min[1] = min(rb.hi_min[1], wg_bounds[x][6]); rb.hi_max[1] = max(rb.hi_max[1], wg_bounds[x][7]);
-    }
+  if (RANGES) st.qr = unit_range_row(t, g, w.unit, st.qi);
+  // everything the rows need of memory is requested before the ranges are waited for
+  const bf16_t* qp = (const bf16_t*)t.q + (int64_t)(st.qi + qoff) * t.q_st + (int64_t)head * t.q_sh + 8 * lh;
+  const bf16_t* dop = (const bf16_t*)t.dout + (int64_t)(st.qi + qoff) * t.do_st + (int64_t)head * t.do_sh + 8 * lh;
+  const bf16_t* outp = (const bf16_t*)t.out_in + (int64_t)(st.qi + qoff) * t.o_st + (int64_t)head * t.o_sh + 8 * lh;
+  uint4 of[8];
 #pragma unroll
-    for (int k = 0; k < 2; k++) {
-      rb.lo_min[k] = uni(rb.lo_min[k]); rb.lo_max[k] = uni(rb.lo_max[k]); rb.hi_min[k] = uni(rb.hi_min[k]); rb.hi_max[k] = uni(rb.hi_max[k]);
-      wrb.lo_min[k] = uni(wrb.lo_min[k]); wrb.lo_max[k] = uni(wrb.lo_max[k]); wrb.hi_min[k] = uni(wrb.hi_min[k]); wrb.hi_max[k] = uni(wrb.hi_max[k]);
+  for (int ks = 0; ks < 8; ks++) {
+    st.qf[ks] = as_frag(*(const uint4*)(qp + 16 * ks));
+    st.dof[ks] = as_frag(*(const uint4*)(dop + 16 * ks));
+    of[ks] = *(const uint4*)(outp + 16 * ks);
+  }
+  st.lse2 = t.lse[(int64_t)head * t.q_rows + st.qi + qoff];
+  if (RANGES && qv) wrb.add(st.qr);
+  RangeBounds rb = wrb;
+  if (RANGES) {
+    wrb.wave_reduce<32>();
+    rb = wrb;
+    if (sp.rows > 32) {   // the waves have different rows
+      if (lane == 0) {
+        wg_bounds[wave][0] = wrb.lo_min[0]; wg_bounds[wave][1] = wrb.lo_max[0]; wg_bounds[wave][2] = wrb.hi_min[0]; wg_bounds[wave][3] = wrb.hi_max[0];
+        wg_bounds[wave][4] = wrb.lo_min[1]; wg_bounds[wave][5] = wrb.lo_max[1]; wg_bounds[wave][6] = wrb.hi_min[1]; wg_bounds[wave][7] = wrb.hi_max[1];
+      }
+      __syncthreads();
+      rb.init();
+      for (int x = 0; x < 4; x++) {
+        rb.lo_min[0] = min(rb.lo_min[0], wg_bounds[x][0]); rb.lo_max[0] = max(rb.lo_max[0], wg_bounds[x][1]);
+        rb.hi_min[0] = min(rb.hi_min[0], wg_bounds[x][2]); rb.hi_max[0] = max(rb.hi_max[0], wg_bounds[x][3]);
+        rb.lo_min[1] = min(rb.lo_min[1], wg_bounds[x][4]); rb.lo_max[1] = max(rb.lo_max[1], wg_bounds[x][5]);
+        rb.hi_min[1] = min(rb.hi_min[1], wg_bounds[x][6]); rb.hi_max[1] = max(rb.hi_max[1], wg_bounds[x][7]);
+      }
+#pragma unroll
+      for (int k = 0; k < 2; k++) {
+        rb.lo_min[k] = uni(rb.lo_min[k]); rb.lo_max[k] = uni(rb.lo_max[k]); rb.hi_min[k] = uni(rb.hi_min[k]); rb.hi_max[k] = uni(rb.hi_max[k]);
+      }
     }
   }
   {
-    const bf16_t* qp = (const bf16_t*)t.q + (int64_t)(st.qi + qoff) * t.q_st + (int64_t)head * t.q_sh + 8 * lh;
-    const bf16_t* dop = (const bf16_t*)t.dout + (int64_t)(st.qi + qoff) * t.do_st + (int64_t)head * t.do_sh + 8 * lh;
+    // the backward preprocess, fused: delta = sum_d dO * O of the lane's row from the final O, and the saved LSE in
+    // the exp2 domain (clamped to a finite value: a row that saw nothing has every score masked); -delta and the
+    // LSE are left in the workspace for the dK/dV kernel, which runs after this one and starts its dP accumulators
+    // from -delta
+    float dl = 0.f;
 #pragma unroll
     for (int ks = 0; ks < 8; ks++) {
-      st.qf[ks] = as_frag(*(const uint4*)(qp + 16 * ks));
-      st.dof[ks] = as_frag(*(const uint4*)(dop + 16 * ks));
-    }
-    {
-      // the backward preprocess, fused: delta = sum_d dO * O of the lane's row from the final O, and the saved LSE in
-      // the exp2 domain (clamped to a finite value: a row that saw nothing has every score masked); -delta and the
-      // LSE are left in the workspace for the dK/dV kernel, which runs after this one and starts its dP accumulators
-      // from -delta
-      const bf16_t* outp = (const bf16_t*)t.out_in + (int64_t)(st.qi + qoff) * t.o_st + (int64_t)head * t.o_sh + 8 * lh;
-      float dl = 0.f;
+      const uint32_t ow[4] = {of[ks].x, of[ks].y, of[ks].z, of[ks].w};
+      const uint4 dd = __builtin_bit_cast(uint4, st.dof[ks]);
+      const uint32_t dw[4] = {dd.x, dd.y, dd.z, dd.w};
 #pragma unroll
-      for (int ks = 0; ks < 8; ks++) {
-        const uint4 u = *(const uint4*)(outp + 16 * ks);
-        const uint32_t ow[4] = {u.x, u.y, u.z, u.w};
-        const uint4 dd = __builtin_bit_cast(uint4, st.dof[ks]);
-        const uint32_t dw[4] = {dd.x, dd.y, dd.z, dd.w};
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-          dl = fmaf(__uint_as_float(ow[i] << 16), __uint_as_float(dw[i] << 16), dl);
-          dl = fmaf(__uint_as_float(ow[i] & 0xffff0000u), __uint_as_float(dw[i] & 0xffff0000u), dl);
-        }
-      }
-      st.delta = xhalf_sum(dl);
-#pragma unroll
-      for (int r = 0; r < 16; r++) st.neg_delta[r] = -st.delta;
-      st.lse2 = fmaxf(t.lse[(int64_t)head * t.q_rows + st.qi + qoff] * kLog2e, -3.402823466e38f);
-      if (qv && lh == 0) {
-        t.delta_w[(int64_t)head * t.q_rows + st.qi + qoff] = -st.delta;
-        t.lse2_w[(int64_t)head * t.q_rows + st.qi + qoff] = st.lse2;
+      for (int i = 0; i < 4; i++) {
+        dl = fmaf(__uint_as_float(ow[i] << 16), __uint_as_float(dw[i] << 16), dl);
+        dl = fmaf(__uint_as_float(ow[i] & 0xffff0000u), __uint_as_float(dw[i] & 0xffff0000u), dl);
       }
     }
+    st.delta = xhalf_sum(dl);
 #pragma unroll
-    for (int dt = 0; dt < 4; dt++)
-#pragma unroll
-      for (int x = 0; x < 16; x++) st.dq[dt][x] = 0.f;
+    for (int r = 0; r < 16; r++) st.neg_delta[r] = -st.delta;
+    st.lse2 = fmaxf(st.lse2 * kLog2e, -3.402823466e38f);
+  }
+  if (qv && lh == 0) {
+    t.delta_w[(int64_t)head * t.q_rows + st.qi + qoff] = -st.delta;
+    t.lse2_w[(int64_t)head * t.q_rows + st.qi + qoff] = st.lse2;
   }
   const float c_log2 = t.scale * kLog2e;
   const bf16_t* kbase = (const bf16_t*)t.k + (int64_t)hk * t.k_sh;
@@ -166,15 +163,18 @@ __global__ __launch_bounds__(256, 2) void mfma_dq_kernel(DevGroup g, KTensors t)
     st.dmak.load(stage0, kbase, it.ks + it.moff, it.c1 - 1 + it.moff, wave);
     st.dmav.load(stage0 + kTileBytes, vbase, it.ks + it.moff, it.c1 - 1 + it.moff, wave);
   }
+#pragma unroll
+  for (int dt = 0; dt < 4; dt++)
+#pragma unroll
+    for (int x = 0; x < 16; x++) st.dq[dt][x] = 0.f;
   DCP_WAIT_VMCNT(0);
   __syncthreads();
   auto step = [&](const char* cur, char* nxt) {
     const int ks = it.ks, c0 = it.c0, c1 = it.c1, kind = RANGES ? it.kind : (it.kind & 1);
     int cls0 = kFull, cls1 = kFull;
     bool fast;
-    // (rows with per-token ranges take the general path: the test on the range bounds that would spare it costs as
-    // much as it saves here)
-    fast = (!RANGES || kind < 2) && w_rows > 0 && ks + 2 * kTN <= (kind ? min(c1, wq_lo + 1) : c1);
+    fast = w_rows > 0 && (!RANGES || kind < 2 ? ks + 2 * kTN <= (kind ? min(c1, wq_lo + 1) : c1)
+                                              : ks + 2 * kTN <= c1 && wrb.all_see(ks, ks + 2 * kTN));
     if (fast) {
       // the common step, found with a handful of scalar instructions: this tile and the next one of the same table
       // row are whole and visible to every row of the wave; the iterator moves by one tile and nothing is classified

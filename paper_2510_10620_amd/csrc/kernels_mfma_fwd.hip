@@ -102,15 +102,16 @@ __device__ __forceinline__ void fwd_scores64(const FwdState<NQ>& st, const char*
 // accumulators: every kind of tile (fully visible, mask edge, half skipped) computes its scores on its own path and
 // joins here, so the accumulators never meet at a control-flow merge with different register assignments (which
 // costs a copy of all 64 of them, there and back, per tile).  There is no branch on which sub-tiles are active
-// either (a skipped one has scores -inf, so P = 0 and its MFMAs add nothing): one straight block, in which the P.V
+// either (a skipped one has scores -inf, so P = 0 and its MFMAs add nothing; for tables with per-token ranges this form
+// replaced one with a section per kind of tile, 9 984 -> 9 814 us forward and backward in the case named at KvIter::next): one straight block, in which the P.V
 // MFMAs of the first 32 keys are issued between the exponentials of the second 32 (the scheduling groups below say
-// so; exponentials are their own instruction class there).  NQ = 1.
+// so; exponentials are their own instruction class there).  NQ = 1.  v0_lds, v1_lds: the V tile for its first and second 32 keys.
 template <int NQ>
-__device__ __forceinline__ void fwd_softmax_pv(FwdState<NQ>& st, f32x16 (&s)[2][NQ], const char* v_lds, float c_log2) {
+__device__ __forceinline__ void fwd_softmax_pv(FwdState<NQ>& st, f32x16 (&s)[2][NQ], const char* v0_lds, const char* v1_lds, float c_log2) {
   static_assert(NQ == 1, "one query per lane");
   bf16x8 va[4];
 #pragma unroll
-  for (int dt = 0; dt < 4; dt++) va[dt] = frag_tr(v_lds, st.fa, 0, dt);
+  for (int dt = 0; dt < 4; dt++) va[dt] = frag_tr(v0_lds, st.fa, 0, dt);
   __builtin_amdgcn_sched_barrier(0);
   float mx = fmaxf(fmaxf(s[0][0][0], s[0][0][1]), s[1][0][0]);
   mx = fmaxf(mx, s[1][0][1]);
@@ -120,7 +121,10 @@ __device__ __forceinline__ void fwd_softmax_pv(FwdState<NQ>& st, f32x16 (&s)[2][
     mx = fmaxf(fmaxf(mx, s[1][0][r]), s[1][0][r + 1]);
   }
   mx = xhalf_max(mx);
-  // the reference max is raised lazily (see fwd_subtile); a row that has seen no key yet keeps m = -inf and uses 0
+  // The reference max m is raised only when the tile's max exceeds it by more than 2^kLazy (in the exp2 domain): until then
+  // P = exp2(c (s - m)) stays below 2^kLazy, exact in fp32 and bf16 range, and the accumulators need no rescaling.  O and l are
+  // divided by the same sum at the end, so the result does not depend on which m was used.  A row that has seen no key yet keeps
+  // m = -inf and uses 0.
   const bool raise = (mx - st.m[0]) * c_log2 > kLazy;
   const float m_new = raise ? mx : st.m[0];
   const float m_use = m_new == -INFINITY ? 0.f : m_new;
@@ -147,11 +151,11 @@ __device__ __forceinline__ void fwd_softmax_pv(FwdState<NQ>& st, f32x16 (&s)[2][
   // region: 8 MFMAs of the first 32 keys + the exponentials of the second 32, interleaved by the group barriers below
   bf16x8 vb[4], vc[4];
 #pragma unroll
-  for (int dt = 0; dt < 4; dt++) vb[dt] = frag_tr(v_lds, st.fa, 16, dt);
+  for (int dt = 0; dt < 4; dt++) vb[dt] = frag_tr(v0_lds, st.fa, 16, dt);
 #pragma unroll
   for (int dt = 0; dt < 4; dt++) st.o[0][dt] = mfma(va[dt], p00, st.o[0][dt]);
 #pragma unroll
-  for (int dt = 0; dt < 4; dt++) vc[dt] = frag_tr(v_lds, st.fa, 32, dt);
+  for (int dt = 0; dt < 4; dt++) vc[dt] = frag_tr(v1_lds, st.fa, 32, dt);
 #pragma unroll
   for (int dt = 0; dt < 4; dt++) st.o[0][dt] = mfma(vb[dt], p01, st.o[0][dt]);
   float sum1 = 0.f;
@@ -172,85 +176,11 @@ __device__ __forceinline__ void fwd_softmax_pv(FwdState<NQ>& st, f32x16 (&s)[2][
   st.l[0] += sum0 + sum1;
   const bf16x8 p10 = pack_frag(s[1][0], 0), p11 = pack_frag(s[1][0], 1);
 #pragma unroll
-  for (int dt = 0; dt < 4; dt++) vb[dt] = frag_tr(v_lds, st.fa, 48, dt);
+  for (int dt = 0; dt < 4; dt++) vb[dt] = frag_tr(v1_lds, st.fa, 48, dt);
 #pragma unroll
   for (int dt = 0; dt < 4; dt++) st.o[0][dt] = mfma(vc[dt], p10, st.o[0][dt]);
 #pragma unroll
   for (int dt = 0; dt < 4; dt++) st.o[0][dt] = mfma(vb[dt], p11, st.o[0][dt]);
-}
-
-// One 32-key sub-tile: S^T = K Q^T, mask, online softmax, O^T += V^T P^T.
-template <int NQ>
-__device__ __forceinline__ void fwd_subtile(FwdState<NQ>& st, const char* k_lds, const char* v_lds, int kt, int ks32,
-                                            int kind, int c0, int c1, float c_log2, int lane, bool MASK) {
-  const int lh = lane >> 5;
-  f32x16 s[NQ];
-#pragma unroll
-  for (int nq = 0; nq < NQ; nq++)
-#pragma unroll
-    for (int r = 0; r < 16; r++) s[nq][r] = 0.f;
-#pragma unroll
-  for (int ksd = 0; ksd < 8; ksd++) {
-    const bf16x8 a = frag_rm(k_lds, st.fa, 32 * kt, ksd);
-#pragma unroll
-    for (int nq = 0; nq < NQ; nq++) s[nq] = mfma(a, st.qf[nq][ksd], s[nq]);
-  }
-  if (MASK) {
-#pragma unroll
-    for (int nq = 0; nq < NQ; nq++) {
-      const RowRanges rr = row_ranges(kind, st.qi[nq], c0, c1, st.qr[nq]);
-      const int kb = ks32 + 4 * lh;
-#pragma unroll
-      for (int r = 0; r < 16; r++) {
-        const int key = kb + 8 * (r / 4) + (r % 4);
-        if (!rr.sees(key)) s[nq][r] = -INFINITY;
-      }
-    }
-  }
-  bf16x8 p[NQ][2];
-#pragma unroll
-  for (int nq = 0; nq < NQ; nq++) {
-    float mx = fmaxf(fmaxf(s[nq][0], s[nq][1]), s[nq][2]);
-#pragma unroll
-    for (int r = 3; r < 15; r += 2) mx = fmaxf(fmaxf(mx, s[nq][r]), s[nq][r + 1]);
-    mx = fmaxf(mx, s[nq][15]);
-    mx = xhalf_max(mx);
-    // The reference max m is raised only when the tile's max exceeds it by more than 2^kLazy
-    // (in the exp2 domain): until then P = exp2(c (s - m)) stays below 2^kLazy, exact in fp32 and
-    // bf16 range, and the accumulators need no rescaling.  O and l are divided by the same sum at
-    // the end, so the result does not depend on which m was used.
-    const bool raise = (mx - st.m[nq]) * c_log2 > kLazy;   // also true for the first visible key (m = -inf)
-    const float m_new = raise ? mx : st.m[nq];
-    const float m_use = m_new == -INFINITY ? 0.f : m_new;
-    const float mc = m_use * c_log2;
-    if (__any(raise)) {
-      const float alpha = raise ? __builtin_amdgcn_exp2f((st.m[nq] - m_use) * c_log2) : 1.f;
-      st.l[nq] *= alpha;
-#pragma unroll
-      for (int dt = 0; dt < 4; dt++)
-#pragma unroll
-        for (int r = 0; r < 16; r++) st.o[nq][dt][r] *= alpha;
-    }
-    st.m[nq] = m_new;
-    float sum = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; r++) {
-      const float e = __builtin_amdgcn_exp2f(fmaf(s[nq][r], c_log2, -mc));
-      s[nq][r] = e;
-      sum += e;
-    }
-    st.l[nq] += sum;
-#pragma unroll
-    for (int c = 0; c < 2; c++) p[nq][c] = pack_frag(s[nq], c);
-  }
-#pragma unroll
-  for (int c = 0; c < 2; c++)
-#pragma unroll
-    for (int dt = 0; dt < 4; dt++) {
-      const bf16x8 a = frag_tr(v_lds, st.fa, 32 * kt + 16 * c, dt);
-#pragma unroll
-      for (int nq = 0; nq < NQ; nq++) st.o[nq][dt] = mfma(a, p[nq][c], st.o[nq][dt]);
-    }
 }
 
 // RANGES = false: the table has no row with per-token ranges (RANGES or WINDOW) and every use of them folds away.
@@ -295,39 +225,39 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void mfma_fwd_kernel(DevGroup g,
     qv[nq] = r < n_rows;
     st.qi[nq] = q_lo + min(r, n_rows - 1);
     st.qr[nq] = make_int4(0, 0, 0, 0);
-    if (t.masked) {
-      st.qr[nq] = range_row(t, st.qi[nq], uni(plan_load(g.blk_s0, plan_load(g.unit_blk, w.unit))));
-      if (qv[nq]) wrb.add(st.qr[nq]);
-    }
-  }
-  RangeBounds rb = wrb;  // workgroup bounds
-  if (t.masked) {
-    wrb.wave_reduce();
-    if (lane == 0) {
-      wg_bounds[wave][0] = wrb.lo_min[0]; wg_bounds[wave][1] = wrb.lo_max[0]; wg_bounds[wave][2] = wrb.hi_min[0]; wg_bounds[wave][3] = wrb.hi_max[0];
-      wg_bounds[wave][4] = wrb.lo_min[1]; wg_bounds[wave][5] = wrb.lo_max[1]; wg_bounds[wave][6] = wrb.hi_min[1]; wg_bounds[wave][7] = wrb.hi_max[1];
-    }
-    __syncthreads();
-    rb.init();
-    for (int x = 0; x < kFwdWaves; x++) {
-      rb.lo_min[0] = min(rb.lo_min[0], wg_bounds[x][0]); rb.lo_max[0] = max(rb.lo_max[0], wg_bounds[x][1]);
-      rb.hi_min[0] = min(rb.hi_min[0], wg_bounds[x][2]); rb.hi_max[0] = max(rb.hi_max[0], wg_bounds[x][3]);
-      rb.lo_min[1] = min(rb.lo_min[1], wg_bounds[x][4]); rb.lo_max[1] = max(rb.lo_max[1], wg_bounds[x][5]);
-      rb.hi_min[1] = min(rb.hi_min[1], wg_bounds[x][6]); rb.hi_max[1] = max(rb.hi_max[1], wg_bounds[x][7]);
-    }
-#pragma unroll
-    for (int k = 0; k < 2; k++) {
-      rb.lo_min[k] = uni(rb.lo_min[k]); rb.lo_max[k] = uni(rb.lo_max[k]); rb.hi_min[k] = uni(rb.hi_min[k]); rb.hi_max[k] = uni(rb.hi_max[k]);
-      wrb.lo_min[k] = uni(wrb.lo_min[k]); wrb.lo_max[k] = uni(wrb.lo_max[k]); wrb.hi_min[k] = uni(wrb.hi_min[k]); wrb.hi_max[k] = uni(wrb.hi_max[k]);
-    }
-  }
-
-  // Q fragments (B operand: lane = query column li, d = 16 ks + 8 lh ..)
-#pragma unroll
-  for (int nq = 0; nq < NQ; nq++) {
+    if (RANGES) st.qr[nq] = unit_range_row(t, g, w.unit, st.qi[nq]);
+    // Q fragments (B operand: lane = query column li, d = 16 ks + 8 lh ..)
     const bf16_t* qp = (const bf16_t*)t.q + (int64_t)(st.qi[nq] + qoff) * t.q_st + (int64_t)head * t.q_sh + 8 * lh;
 #pragma unroll
     for (int ks = 0; ks < 8; ks++) st.qf[nq][ks] = as_frag(*(const uint4*)(qp + 16 * ks));
+    if (RANGES && qv[nq]) wrb.add(st.qr[nq]);
+  }
+  RangeBounds rb = wrb;  // workgroup bounds
+  if (RANGES) {
+    wrb.wave_reduce<32>();
+    rb = wrb;
+    if (sp.rows > 32) {   // the waves have different rows
+      if (lane == 0) {
+        wg_bounds[wave][0] = wrb.lo_min[0]; wg_bounds[wave][1] = wrb.lo_max[0]; wg_bounds[wave][2] = wrb.hi_min[0]; wg_bounds[wave][3] = wrb.hi_max[0];
+        wg_bounds[wave][4] = wrb.lo_min[1]; wg_bounds[wave][5] = wrb.lo_max[1]; wg_bounds[wave][6] = wrb.hi_min[1]; wg_bounds[wave][7] = wrb.hi_max[1];
+      }
+      __syncthreads();
+      rb.init();
+      for (int x = 0; x < kFwdWaves; x++) {
+        rb.lo_min[0] = min(rb.lo_min[0], wg_bounds[x][0]); rb.lo_max[0] = max(rb.lo_max[0], wg_bounds[x][1]);
+        rb.hi_min[0] = min(rb.hi_min[0], wg_bounds[x][2]); rb.hi_max[0] = max(rb.hi_max[0], wg_bounds[x][3]);
+        rb.lo_min[1] = min(rb.lo_min[1], wg_bounds[x][4]); rb.lo_max[1] = max(rb.lo_max[1], wg_bounds[x][5]);
+        rb.hi_min[1] = min(rb.hi_min[1], wg_bounds[x][6]); rb.hi_max[1] = max(rb.hi_max[1], wg_bounds[x][7]);
+      }
+#pragma unroll
+      for (int k = 0; k < 2; k++) {
+        rb.lo_min[k] = uni(rb.lo_min[k]); rb.lo_max[k] = uni(rb.lo_max[k]); rb.hi_min[k] = uni(rb.hi_min[k]); rb.hi_max[k] = uni(rb.hi_max[k]);
+      }
+    }
+  }
+
+#pragma unroll
+  for (int nq = 0; nq < NQ; nq++) {
     st.m[nq] = -INFINITY; st.l[nq] = 0.f;
 #pragma unroll
     for (int dt = 0; dt < 4; dt++)
@@ -350,84 +280,55 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void mfma_fwd_kernel(DevGroup g,
   // one pipeline step: prefetch the next tile into `nxt`, compute the current one from `cur`
   auto step = [&](const char* cur, char* nxt) {
     const int ks = it.ks, c0 = it.c0, c1 = it.c1, kind = RANGES ? it.kind : (it.kind & 1);
-    if constexpr (RANGES) {
-      // the same short test as below spares the iterator and the classification: NONE and CAUSAL rows as there, rows
-      // with per-token ranges when one of the two ranges of every row of the wave covers this tile and the next
-      int cls0 = kFull, cls1 = kFull;
-      const bool common = w_rows > 0 && (kind < 2 ? ks + 2 * kTN <= (kind ? min(c1, wq_lo + 1) : c1)
-                                                  : ks + 2 * kTN <= c1 && wrb.all_see(ks, ks + 2 * kTN));
-      if (common) {
-        it.jt++;
-        it.ks += kTN;
-      } else {
-        have = it.next<RANGES>(q_hi, rb);
-        if (w_rows > 0) { cls0 = classify32(kind, ks, c1, wq_lo, wq_hi, wrb); cls1 = classify32(kind, ks + 32, c1, wq_lo, wq_hi, wrb); }
-        if (have) {
-          st.dmak.load(nxt, kbase, it.ks + it.moff, it.c1 - 1 + it.moff, wave);
-          st.dmav.load(nxt + kTileBytes, vbase, it.ks + it.moff, it.c1 - 1 + it.moff, wave);
-        }
-      }
-      if (w_rows > 0) {
-        // tables with per-token ranges: self-contained paths (measured 4-5 % faster there than the joined form)
-        if (cls0 == kFull && cls1 == kFull) {
-          f32x16 s[2][NQ];
-          if (common)
-            fwd_scores64<NQ, true>(st, cur, s, uni_ptr((const char*)kbase + (int64_t)(it.ks + it.moff) * st.dmak.sb),
-                                   uni_ptr((const char*)vbase + (int64_t)(it.ks + it.moff) * st.dmav.sb),
-                                   st.dmak.lds_of(nxt, wave), st.dmav.lds_of(nxt + kTileBytes, wave));
-          else
-            fwd_scores64<NQ, false>(st, cur, s);
-          fwd_softmax_pv<NQ>(st, s, cur + kTileBytes, c_log2);
-        } else {
-          if (cls0 != kSkip) fwd_subtile<NQ>(st, cur, cur + kTileBytes, 0, ks, kind, c0, c1, c_log2, lane, cls0 == kPartial);
-          if (cls1 != kSkip) fwd_subtile<NQ>(st, cur, cur + kTileBytes, 1, ks + 32, kind, c0, c1, c_log2, lane, cls1 == kPartial);
-        }
-      }
+    // the score paths join in one softmax + PV section (4 % faster: no copies of the accumulators at the merge)
+    f32x16 s[2][NQ];
+    bool pv;
+    int v0 = 0, v1 = 0;   // where the V rows of the two halves lie, from their own place
+    const bool common = !RANGES || kind < 2 ? ks + 2 * kTN <= (kind ? min(c1, wq_lo + 1) : c1)
+                                            : ks + 2 * kTN <= c1 && wrb.all_see(ks, ks + 2 * kTN);
+    if (w_rows > 0 && common) {
+      // The common step, found with a handful of scalar instructions: this tile and the next one of the same table
+      // row are whole and visible to every row of the wave.  The iterator moves by one tile, nothing is classified,
+      // and the copies of the next tile are issued between the score MFMAs: issued back to back at the top of the
+      // step, the copy instructions of the four waves queue behind one another at the address unit and the waves
+      // issue nothing else meanwhile; the general path's scalar bookkeeping costs some hundred issue slots more.
+      it.jt++;
+      it.ks += kTN;
+      fwd_scores64<NQ, true>(st, cur, s, uni_ptr((const char*)kbase + (int64_t)(it.ks + it.moff) * st.dmak.sb),
+                             uni_ptr((const char*)vbase + (int64_t)(it.ks + it.moff) * st.dmav.sb),
+                             st.dmak.lds_of(nxt, wave), st.dmav.lds_of(nxt + kTileBytes, wave));
+      pv = true;
     } else {
-      // NONE / CAUSAL tables: the score paths join in one softmax + PV section (4 % faster there: no copies of the
-      // accumulators at the merge)
-      f32x16 s[2][NQ];
-      bool pv;
-      if (w_rows > 0 && ks + 2 * kTN <= (kind ? min(c1, wq_lo + 1) : c1)) {
-        // The common step, found with a handful of scalar instructions: this tile and the next one of the same table
-        // row are whole and visible to every row of the wave.  The iterator moves by one tile, nothing is classified,
-        // and the copies of the next tile are issued between the score MFMAs: issued back to back at the top of the
-        // step, the copy instructions of the four waves queue behind one another at the address unit and the waves
-        // issue nothing else meanwhile; the general path's scalar bookkeeping costs some hundred issue slots more.
-        it.jt++;
-        it.ks += kTN;
-        fwd_scores64<NQ, true>(st, cur, s, uni_ptr((const char*)kbase + (int64_t)(it.ks + it.moff) * st.dmak.sb),
-                               uni_ptr((const char*)vbase + (int64_t)(it.ks + it.moff) * st.dmav.sb),
-                               st.dmak.lds_of(nxt, wave), st.dmav.lds_of(nxt + kTileBytes, wave));
-        pv = true;
-      } else {
-        have = it.next<RANGES>(q_hi, rb);
-        if (have) {
-          st.dmak.load(nxt, kbase, it.ks + it.moff, it.c1 - 1 + it.moff, wave);
-          st.dmav.load(nxt + kTileBytes, vbase, it.ks + it.moff, it.c1 - 1 + it.moff, wave);
-        }
-        const int cls0 = w_rows > 0 ? classify32(kind, ks, c1, wq_lo, wq_hi, wrb) : kSkip;
-        const int cls1 = w_rows > 0 ? classify32(kind, ks + 32, c1, wq_lo, wq_hi, wrb) : kSkip;
-        pv = cls0 != kSkip || cls1 != kSkip;
-        if (cls0 == kFull && cls1 == kFull) {
-          fwd_scores64<NQ, false>(st, cur, s);
-        } else if (pv) {
+      have = it.next<RANGES>(q_hi, rb);
+      if (have) {
+        st.dmak.load(nxt, kbase, it.ks + it.moff, it.c1 - 1 + it.moff, wave);
+        st.dmav.load(nxt + kTileBytes, vbase, it.ks + it.moff, it.c1 - 1 + it.moff, wave);
+      }
+      const int cls0 = w_rows > 0 ? classify32(kind, ks, c1, wq_lo, wq_hi, wrb) : kSkip;
+      const int cls1 = w_rows > 0 ? classify32(kind, ks + 32, c1, wq_lo, wq_hi, wrb) : kSkip;
+      pv = cls0 != kSkip || cls1 != kSkip;
+      if (RANGES) {   // weight 0 meets the rows of the half that is seen: those of an unseen half need not be finite
+        v0 = cls0 == kSkip ? 32 * kRowBytes : 0;
+        v1 = cls1 == kSkip ? -32 * kRowBytes : 0;
+      }
+      if (cls0 == kFull && cls1 == kFull) {
+        fwd_scores64<NQ, false>(st, cur, s);
+      } else if (pv) {
 #pragma unroll
-          for (int kt = 0; kt < 2; kt++) {
-            const int cls = kt ? cls1 : cls0;
-            if (cls != kSkip) {
-              fwd_scores32<NQ>(st, cur, kt, ks + 32 * kt, kind, c0, c1, lane, cls == kPartial, s[kt]);
-            } else {
+        for (int kt = 0; kt < 2; kt++) {
+          const int cls = kt ? cls1 : cls0;
+          if (cls != kSkip) {
+            fwd_scores32<NQ>(st, cur, kt, ks + 32 * kt, kind, c0, c1, lane, cls == kPartial, s[kt]);
+          } else {
 #pragma unroll
-              for (int nq = 0; nq < NQ; nq++)
+            for (int nq = 0; nq < NQ; nq++)
 #pragma unroll
-                for (int r = 0; r < 16; r++) s[kt][nq][r] = -INFINITY;
-            }
+              for (int r = 0; r < 16; r++) s[kt][nq][r] = -INFINITY;
           }
         }
       }
-      if (pv) fwd_softmax_pv<NQ>(st, s, cur + kTileBytes, c_log2);
     }
+    if (pv) fwd_softmax_pv<NQ>(st, s, cur + kTileBytes + v0, cur + kTileBytes + v1, c_log2);
     DCP_WAIT_VMCNT(0);
     __syncthreads();  // the copy into `nxt` has landed and `cur` may be overwritten
   };

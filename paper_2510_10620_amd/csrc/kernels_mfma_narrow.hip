@@ -155,27 +155,28 @@ __device__ __forceinline__ bool nq_tile(const DevGroup& g, const KTensors& t, in
   q->wrb.init();
   q->rb.init();
   if (RANGES) {
-    q->qr = range_row(t, q->qi, uni(plan_load(g.blk_s0, plan_load(g.unit_blk, q->unit))));
+    q->qr = unit_range_row(t, g, q->unit, q->qi);
     if (q->qv) q->wrb.add(q->qr);
-    q->wrb.wave_reduce();
-#pragma unroll
-    for (int k = 0; k < 2; k++) {
-      q->wrb.lo_min[k] = uni(q->wrb.lo_min[k]); q->wrb.lo_max[k] = uni(q->wrb.lo_max[k]);
-      q->wrb.hi_min[k] = uni(q->wrb.hi_min[k]); q->wrb.hi_max[k] = uni(q->wrb.hi_max[k]);
+    q->wrb.wave_reduce<32>();
+    q->rb = q->wrb;
+    if (sp.rows > 32) {   // the waves have different rows
       if (lane == 0) {
-        wg_bounds[wave][4 * k] = q->wrb.lo_min[k]; wg_bounds[wave][4 * k + 1] = q->wrb.lo_max[k];
-        wg_bounds[wave][4 * k + 2] = q->wrb.hi_min[k]; wg_bounds[wave][4 * k + 3] = q->wrb.hi_max[k];
-      }
-    }
-    __syncthreads();
 #pragma unroll
-    for (int k = 0; k < 2; k++) {
-      for (int x = 0; x < 4; x++) {
-        q->rb.lo_min[k] = min(q->rb.lo_min[k], wg_bounds[x][4 * k]); q->rb.lo_max[k] = max(q->rb.lo_max[k], wg_bounds[x][4 * k + 1]);
-        q->rb.hi_min[k] = min(q->rb.hi_min[k], wg_bounds[x][4 * k + 2]); q->rb.hi_max[k] = max(q->rb.hi_max[k], wg_bounds[x][4 * k + 3]);
+        for (int k = 0; k < 2; k++) {
+          wg_bounds[wave][4 * k] = q->wrb.lo_min[k]; wg_bounds[wave][4 * k + 1] = q->wrb.lo_max[k];
+          wg_bounds[wave][4 * k + 2] = q->wrb.hi_min[k]; wg_bounds[wave][4 * k + 3] = q->wrb.hi_max[k];
+        }
       }
-      q->rb.lo_min[k] = uni(q->rb.lo_min[k]); q->rb.lo_max[k] = uni(q->rb.lo_max[k]);
-      q->rb.hi_min[k] = uni(q->rb.hi_min[k]); q->rb.hi_max[k] = uni(q->rb.hi_max[k]);
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < 2; k++) {
+        for (int x = 0; x < 4; x++) {
+          q->rb.lo_min[k] = min(q->rb.lo_min[k], wg_bounds[x][4 * k]); q->rb.lo_max[k] = max(q->rb.lo_max[k], wg_bounds[x][4 * k + 1]);
+          q->rb.hi_min[k] = min(q->rb.hi_min[k], wg_bounds[x][4 * k + 2]); q->rb.hi_max[k] = max(q->rb.hi_max[k], wg_bounds[x][4 * k + 3]);
+        }
+        q->rb.lo_min[k] = uni(q->rb.lo_min[k]); q->rb.lo_max[k] = uni(q->rb.lo_max[k]);
+        q->rb.hi_min[k] = uni(q->rb.hi_min[k]); q->rb.hi_max[k] = uni(q->rb.hi_max[k]);
+      }
     }
   }
   return true;

@@ -19,7 +19,7 @@ static constexpr int kStageBytes = kStageBounds + 1024;
 template <bool RANGES>
 struct QIter {
   const int4* rec;       // per table row: {first query, length, mask kind, memory offset of the Q block}, {first 32-row tile, ..}
-  const int4* qbounds;   // range-bound summaries per 32-row tile, or null
+  const int4* qbounds;   // RANGES: range-bound summaries per 32-row tile
   int e, e_end, hh, G, jt, n_t, jt0;
   int q0, q1, kind;
   int moff;  // the Q block's rows sit at (packed index + moff) in the Q-type buffers
@@ -66,7 +66,7 @@ struct QIter {
           q0 = uni(r.x); q1 = q0 + uni(r.y); kind = uni(r.z); moff = uni(r.w); t32 = uni(plan_load(rec, 2 * e + 1).x);
           n_t = (q1 - q0 + kTN - 1) / kTN;
           jt0 = kind == 1 ? max(0, (k_lo - q0) / kTN) : 0;
-          if (RANGES && kind == 2 && qbounds && n_t <= 64) {
+          if (RANGES && kind == 2 && n_t <= 64) {
             const unsigned long long m = tiles_that_see(k_lo, k_end);
             if (m == 0) { n_t = 0; }
             else { jt0 = __builtin_ctzll(m); n_t = 64 - __builtin_clzll(m); }
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(256, 2) void mfma_dkv_kernel(DevGroup g, KTensors t
   const int wave = uni(threadIdx.x >> 6);
   const int blk_start = uni(w.blk_start), blk_len = uni(w.blk_len);
   const int koff = uni(w.moff);   // rows of the KV-type buffers: packed index + koff
-  const int seq0 = RANGES ? uni(plan_load(g.blk_s0, plan_load(g.unit_blk, w.unit))) : 0;   // first token of the sequence (keys and queries share it)
+  const int seq0 = RANGES && t.window > 0 ? uni(plan_load(g.blk_s0, plan_load(g.unit_blk, w.unit))) : 0;   // first token of the sequence (keys and queries share it)
   const int row0 = w.tile * TK;
   const int n_rows = min(TK, blk_len - row0);
   const int k_lo = blk_start + row0, k_end = k_lo + n_rows;
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(256, 2) void mfma_dkv_kernel(DevGroup g, KTensors t
       else dma16((unsigned)(qrow - it.qs) * 16u, uni_ptr(t.ranges + 4 * (int64_t)it.qs), lds_addr(stage + kStageRanges));
     }
     // the bounds of the tile's two halves (4 x 16 B; the other lanes repeat them into the reserved space)
-    if (RANGES && wave == 3 && it.kind == 2 && t.qbounds)
+    if (RANGES && wave == 3 && it.kind == 2)
       dma16((unsigned)(ln & 3) * 16u, uni_ptr(t.qbounds + (int64_t)(it.t32 + 2 * it.jt) * 8), lds_addr(stage + kStageBounds));
   };
   bool have = it.next(k_lo, k_end);
@@ -308,7 +308,7 @@ __global__ __launch_bounds__(256, 2) void mfma_dkv_kernel(DevGroup g, KTensors t
         int cls = kPartial;
         if (kind == 0) cls = whole ? kFull : kPartial;
         if (kind == 1) cls = min(qs32 + 31, q1 - 1) < wk_lo ? kSkip : ((whole && qs32 >= wk_hi) ? kFull : kPartial);
-        if (RANGES && kind == 2 && t.qbounds) {
+        if (RANGES && kind == 2) {
           // the 32 queries' range bounds against the wave's keys (the empty asm keeps the compiler from hoisting
           // these LDS reads, and their wait, out of the branch into every step)
           asm volatile("" ::: "memory");

@@ -132,14 +132,9 @@ __device__ __forceinline__ bool q_tile(const DevGroup& g, const KTensors& t, int
   q->qr = make_int4(0, 0, 0, 0);
   q->rb.init();
   if (RANGES) {
-    q->qr = range_row(t, q->qi, uni(plan_load(g.blk_s0, plan_load(g.unit_blk, q->unit))));
+    q->qr = unit_range_row(t, g, q->unit, q->qi);
     q->rb.add(q->qr);
-    q->rb.wave_reduce();
-#pragma unroll
-    for (int k = 0; k < 2; k++) {
-      q->rb.lo_min[k] = uni(q->rb.lo_min[k]); q->rb.lo_max[k] = uni(q->rb.lo_max[k]);
-      q->rb.hi_min[k] = uni(q->rb.hi_min[k]); q->rb.hi_max[k] = uni(q->rb.hi_max[k]);
-    }
+    q->rb.wave_reduce<R>();
   }
   return true;
 }

@@ -1,0 +1,43 @@
+"""Walks over rows with per-token ranges that leave tiles out, in launches large enough for the kernels whose waves share their
+tiles, against the fp64 oracle: both ranges in one block with unseen tiles between, before and behind them, ragged blocks, rows that
+see nothing of a block, and workgroups of 128, 64 and 32 rows (1, 2, 3 and 4 query heads to a KV head), whose waves' bounds are
+exchanged or the same.  Bounds: those of the I/O type in helpers.TOL."""
+import numpy as np
+import pytest
+
+from paper_2510_10620_amd import workloads as W
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads", [(64, 64), (128, 64), (96, 32), (128, 32)], ids=lambda h: f"group{h[0] // h[1]}")
+@pytest.mark.parametrize("spec,window_rows", [(W.MaskSpec("lambda", window=70, sink=9), False), (W.MaskSpec("lambda", window=70, sink=9), True),
+                                              (W.MaskSpec("causal_blockwise", window=1, sink=1, mblock=64), False), (W.MaskSpec("shared_question"), False)],
+                         ids=["ranges", "window", "blockwise", "shared_question"])
+def test_unseen_tiles(d, heads, spec, window_rows):
+    w = W.custom_workload("walk", [601, 129, 33, 1], 512, heads[0], heads[1], d, "bf16", spec, seed=91, input_scale=0.5)
+    tensors, table = W.make_tensors(w), H.oracle_table(w)
+    ref = H.oracle_full(w, tensors, table)
+    t, window = table.copy(), None
+    if window_rows:
+        t[t[:, 2] == W.MASK_RANGES, 2] = W.MASK_WINDOW
+        window = (spec.window, spec.sink)
+    g = H.GpuRun(w, tensors, t, window=window)
+    out, lse = g.forward()
+    dq, dk, dv = g.backward()
+    # dV by row: a key that all four heads' queries of a question weigh highly sums coefficients P near 1, and their rounding to bf16
+    # and the output's, in otherwise exact arithmetic on the CPU, come to 2.046e-2 on an element below 4 (shared_question, D 128)
+    H.check(w, dict(out=out, lse=lse, dq=dq, dk=dk, dv=dv), ref, ("out", "lse", "dq", "dk", "dv"), f"walk D{d} {heads} {spec.kind}", by_row=("dv",))
+
+
+def test_values_in_an_unseen_half_of_a_tile():
+    """D = 128: V rows that are not finite in 32 keys of a 64-key tile which a workgroup's 32 rows see nothing of, beside 32 that they see in part:
+    the rows come out as without them, bit for bit (64 query rows and their keys at most 33 back: the first 32 keys are unseen)."""
+    w = W.custom_workload("half", [601, 129], 512, 128, 32, 128, "bf16", W.MaskSpec("window", window=33), seed=92, input_scale=0.5)
+    g = H.GpuRun(w, W.make_tensors(w), H.oracle_table(w))
+    clean, _ = g.forward()
+    g.v[:32] = float("inf")
+    poisoned, _ = g.forward()
+    assert np.isfinite(clean).all() and np.array_equal(clean[64:], poisoned[64:])
