@@ -186,7 +186,7 @@ static int pick_q(const LaunchFits& fits, const LaunchFit* f, const dcp_tensors_
 }
 
 struct BwdChoice { int dq, dkv, both; };   // both: the form of the one launch, or kShared (two launches)
-static BwdChoice pick_bwd(const dcp_tensors_t* t, const LaunchSize& zq, const LaunchSize& zk) {
+static BwdChoice pick_bwd(const dcp_tensors_t* t, const LaunchSize& zq, const LaunchSize& zk, bool one_launch) {
   BwdChoice c{kShared, kShared, kShared};
   const LaunchFits* f = fits_of(t, zq);
   if (!f || !fits_of(t, zk)) return c;
@@ -198,11 +198,34 @@ static BwdChoice pick_bwd(const dcp_tensors_t* t, const LaunchSize& zq, const La
     x[kShared] = launch_us(f->dkv[kShared], (double)zk.longest_part * (t->hq / t->hkv), total, (double)zk.parts * t->hkv);
   c.dkv = least_form(*f, t, x, &us_k);
   double least = f->sure * (us_q + us_k + kLaunchGap);
-  for (int v = kSplit; v <= last_form(t); v++) {
+  for (int v = kSplit; one_launch && v <= last_form(t); v++) {
     const double us = launch_us(f->bwd[v], longest, total, items + (double)zq.items * t->hq);
     if (us < least) { c.both = v; least = us; }
   }
   return c;
+}
+
+// Whether dQ and dK/dV may run side by side: each reads Q, K, V, O, dO and the LSE to its end, so no gradient may share memory with
+// them.  Two launches allow dQ over O, dK over K and dV over V: a workgroup loads its own rows of these before it stores them,
+// and dK/dV, which starts when dQ has ended, does not read O.  Tensors that only interleave count as sharing.
+static bool one_launch_is_safe(const dcp_plan_t* plan, const dcp_tensors_t* t) {
+  struct Span { uintptr_t lo, hi; };
+  const int64_t es = t->dtype == DCP_BF16 ? 2 : 4;
+  auto span = [&](const void* p, int64_t rows, int heads, int64_t st, int64_t sh) {
+    const uintptr_t lo = (uintptr_t)p;
+    return Span{lo, rows > 0 ? lo + (uintptr_t)(((rows - 1) * st + (heads - 1) * sh + t->d) * es) : lo};
+  };
+  const int64_t nq = plan->q_rows, nk = plan->kv_rows;
+  const Span in[] = {span(t->q, nq, t->hq, t->q_stride_t, t->q_stride_h), span(t->k, nk, t->hkv, t->k_stride_t, t->k_stride_h),
+                     span(t->v, nk, t->hkv, t->v_stride_t, t->v_stride_h), span(t->out, nq, t->hq, t->o_stride_t, t->o_stride_h),
+                     span(t->dout, nq, t->hq, t->do_stride_t, t->do_stride_h),
+                     {(uintptr_t)t->lse, (uintptr_t)t->lse + (uintptr_t)(t->hq * nq) * sizeof(float)}};
+  const Span out[] = {span(t->dq, nq, t->hq, t->dq_stride_t, t->dq_stride_h), span(t->dk, nk, t->hkv, t->dk_stride_t, t->dk_stride_h),
+                      span(t->dv, nk, t->hkv, t->dv_stride_t, t->dv_stride_h)};
+  for (const Span& o : out)
+    for (const Span& i : in)
+      if (o.lo < i.hi && i.lo < o.hi) return false;
+  return true;
 }
 static int waves_of(int form) { return form == kSplit ? 4 : 8; }
 
@@ -211,10 +234,10 @@ static int waves_of(int form) { return form == kSplit ? 4 : 8; }
 static int cut_heads(bool use_mfma, int32_t dtype, int32_t d, int32_t hkv) { return use_mfma && mfma_splits_dkv(dtype, d) ? hkv : 0; }
 
 // The list that the dK/dV launch of a call wants, as host_items names it: the split kernels take whole items.
-static int dkv_heads(dcp_plan_t* plan, const dcp_tensors_t* t, bool use_mfma, int n_seg) {
+static int dkv_heads(dcp_plan_t* plan, const dcp_tensors_t* t, bool use_mfma, int n_seg, bool one_launch) {
   const int cut = cut_heads(use_mfma, t->dtype, t->d, t->hkv);
   if (cut == 0) return 0;
-  const BwdChoice c = pick_bwd(t, plan->host_items(1, t->hq / t->hkv, n_seg).size, plan->host_items(2, cut, n_seg).size);
+  const BwdChoice c = pick_bwd(t, plan->host_items(1, t->hq / t->hkv, n_seg).size, plan->host_items(2, cut, n_seg).size, one_launch);
   return c.dkv != kShared || c.both != kShared ? 0 : cut;
 }
 
@@ -257,7 +280,7 @@ extern "C" dcp_status_t dcp_plan_prepare(dcp_plan_t* plan, int32_t hq, int32_t h
   const int n_seg = xcd_segments(hkv);
   if ((st = plan->group_for(0, s, &g, hq / hkv, n_seg)) != DCP_OK) return st;
   if ((st = plan->group_for(1, s, &g, hq / hkv, n_seg)) != DCP_OK) return st;
-  return plan->group_for(2, s, &g, dkv_heads(plan, &t, use_mfma, n_seg), n_seg);
+  return plan->group_for(2, s, &g, dkv_heads(plan, &t, use_mfma, n_seg, true), n_seg);
 }
 
 extern "C" dcp_status_t dcp_block_attn_fwd(dcp_plan_t* plan, const dcp_tensors_t* t, void* stream) {
@@ -404,7 +427,8 @@ dcp_status_t dcp::bwd_launch(dcp_plan_t* plan, const dcp_tensors_t* t, void* wor
   // Whole or cut dK/dV items: what the choice of kernels wants, unless the plan holds only the other list (made for another number
   // of query heads); whole items serve every kernel, cut ones only the one that shares its tiles.
   const int cut = cut_heads(use_mfma, t->dtype, t->d, t->hkv);
-  int heads = dkv_heads(plan, t, use_mfma, n_seg);
+  const bool one_launch = one_launch_is_safe(plan, t);
+  int heads = dkv_heads(plan, t, use_mfma, n_seg, one_launch);
   if (cut && !plan->has_items(2, heads, n_seg) && plan->has_items(2, cut - heads, n_seg)) heads = cut - heads;
   if ((st = plan->group_for(2, s, &gkv, heads, n_seg, may_alloc)) != DCP_OK) return st;
   use_mfma = use_mfma && mfma_launch_fits(gq, false, t->dtype, t->d, t->hq, t->hkv) && mfma_launch_fits(gkv, true, t->dtype, t->d, t->hq, t->hkv) &&
@@ -422,7 +446,7 @@ dcp_status_t dcp::bwd_launch(dcp_plan_t* plan, const dcp_tensors_t* t, void* wor
     if ((st = mfma_range_bounds(gkv, k, plan->d_blk_t32, plan->n_blocks, plan->longest_block, qb, s)) != DCP_OK) return st;
   }
   BwdChoice form{kShared, kShared, kShared};
-  if (use_mfma) form = pick_bwd(t, plan->host_items(1, t->hq / t->hkv, n_seg).size, plan->host_items(2, cut, n_seg).size);
+  if (use_mfma) form = pick_bwd(t, plan->host_items(1, t->hq / t->hkv, n_seg).size, plan->host_items(2, cut, n_seg).size, one_launch);
   if (heads != 0) form.dkv = form.both = kShared;
   if (form.both != kShared) {
     ProfScope ps(DCP_K_DKV, s, may_alloc);

@@ -17,6 +17,7 @@ namespace dcp {
 extern int64_t g_fake_kv_rows;
 extern int32_t g_fake_n_slots;
 extern bool g_fake_capturing;
+extern long g_fake_one_launch;
 long fake_rows_walked();
 }
 
@@ -144,13 +145,15 @@ static void one_case(Rng& r, int iter) {
   // launches against the stand-in device: buffers of exactly the documented sizes
   dcp::g_fake_kv_rows = kv_rows; dcp::g_fake_n_slots = n_slots;
   const size_t es = dtype == DCP_BF16 ? 2 : 4;
-  std::vector<char> q((size_t)q_rows * hq * d * es + 16), kv((size_t)kv_rows * hkv * d * es + 16);
+  std::vector<char> q((size_t)q_rows * hq * d * es + 16), kv((size_t)kv_rows * hkv * d * es + 16), gq(q.size()), gkv(kv.size());
+  const bool in_place = rnd(r, 0, 1) == 1;   // the gradients over the inputs (the stand-in kernels write none)
   std::vector<float> lse((size_t)hq * q_rows + 1);
   std::vector<char> o_part((size_t)n_slots * B * hq * d * es + 16);
   std::vector<float> lse_part((size_t)n_slots * hq * B + 1);
   dcp_tensors_t t{};
   t.hq = hq; t.hkv = hkv; t.d = d; t.dtype = dtype; t.impl = DCP_IMPL_AUTO; t.softmax_scale = 0.1f;
-  t.q = q.data(); t.k = kv.data(); t.v = kv.data(); t.dout = q.data(); t.dq = q.data(); t.dk = kv.data(); t.dv = kv.data();
+  t.q = q.data(); t.k = kv.data(); t.v = kv.data(); t.dout = q.data();
+  t.dq = in_place ? q.data() : gq.data(); t.dk = t.dv = in_place ? kv.data() : gkv.data();
   t.q_stride_t = t.do_stride_t = t.dq_stride_t = t.o_stride_t = (int64_t)hq * d; t.q_stride_h = t.do_stride_h = t.dq_stride_h = t.o_stride_h = d;
   t.k_stride_t = t.v_stride_t = t.dk_stride_t = t.dv_stride_t = (int64_t)hkv * d; t.k_stride_h = t.v_stride_h = t.dk_stride_h = t.dv_stride_h = d;
   t.attn_ranges = ranges.data();
@@ -263,11 +266,54 @@ static void largest_batch() {
   EXPECT(dcp_plan_destroy(plan) == DCP_OK);
 }
 
+// A backward whose gradients lie over its inputs (dQ over O, dK over K, dV over V, or any other overlap) must not have dQ and
+// dK/dV side by side in one launch: each half reads what the other writes.
+static void in_place_backward(int32_t dtype, int32_t d) {
+  const int T = 300, B = 128, nb = 3, hq = 4, hkv = 2;
+  const int32_t cu[2] = {0, T};
+  std::vector<int32_t> table;
+  for (int i = 0; i < nb; i++)
+    for (int j = 0; j <= i; j++) table.insert(table.end(), {i, j, i == j ? DCP_MASK_CAUSAL : DCP_MASK_NONE});
+  dcp_plan_t* plan = nullptr;
+  EXPECT(dcp_plan_create(&plan, cu, 1, B, table.data(), (int64_t)table.size() / 3, nullptr, 0) == DCP_OK);
+  dcp::g_fake_kv_rows = T; dcp::g_fake_n_slots = 0;
+  const size_t nq = (size_t)T * hq * d, nkv = (size_t)T * hkv * d;
+  enum { Q, K, V, O, DO, DQ, DK, DV, N };
+  std::vector<float> buf[N];   // large enough for either type
+  for (int i = 0; i < N; i++) buf[i].resize((i == K || i == V || i == DK || i == DV ? nkv : nq) + 4);
+  std::vector<float> lse((size_t)hq * T);
+  const size_t wsb = dcp_bwd_workspace_bytes(plan, hq, hkv, d, dtype);
+  void* ws = nullptr;
+  EXPECT(posix_memalign(&ws, 256, wsb) == 0);
+  auto at = [&](int i) { return (void*)(((uintptr_t)buf[i].data() + 15) & ~(uintptr_t)15); };
+  auto one_launch = [&](void* dq, void* dk, void* dv) {
+    dcp_tensors_t t{};
+    t.hq = hq; t.hkv = hkv; t.d = d; t.dtype = dtype; t.softmax_scale = 0.1f;
+    t.q = at(Q); t.k = at(K); t.v = at(V); t.out = at(O); t.dout = at(DO); t.dq = dq; t.dk = dk; t.dv = dv; t.lse = lse.data();
+    t.q_stride_t = t.o_stride_t = t.do_stride_t = t.dq_stride_t = hq * d;
+    t.k_stride_t = t.v_stride_t = t.dk_stride_t = t.dv_stride_t = hkv * d;
+    t.q_stride_h = t.k_stride_h = t.v_stride_h = t.o_stride_h = t.do_stride_h = t.dq_stride_h = t.dk_stride_h = t.dv_stride_h = d;
+    const long before = dcp::g_fake_one_launch;
+    EXPECT(dcp_block_attn_bwd(plan, &t, ws, wsb, nullptr) == DCP_OK);
+    return dcp::g_fake_one_launch - before;
+  };
+  const size_t es = dtype == DCP_BF16 ? 2 : 4;
+  EXPECT(one_launch(at(DQ), at(DK), at(DV)) == 1);
+  EXPECT(one_launch(at(O), at(DK), at(DV)) == 0);
+  EXPECT(one_launch(at(DQ), at(K), at(DV)) == 0);
+  EXPECT(one_launch(at(DQ), at(DK), at(V)) == 0);
+  EXPECT(one_launch(at(O), at(K), at(V)) == 0);
+  EXPECT(one_launch(at(DQ), (char*)at(O) + (nq - 8) * es, at(DV)) == 0);   // eight elements in common
+  std::free(ws);
+  EXPECT(dcp_plan_destroy(plan) == DCP_OK);
+}
+
 int main(int argc, char** argv) {
   const int iters = argc > 1 ? std::atoi(argv[1]) : 150;
   Rng r(20251028);
   for (int i = 0; i < iters && g_fail == 0; i++) one_case(r, i);
   if (g_fail == 0) largest_batch();
+  for (int d = 32; d <= 128; d *= 2) { in_place_backward(DCP_BF16, d); in_place_backward(DCP_F32, d); }
   // the empty plan and NULL arguments
   dcp_plan_t* plan = nullptr;
   int32_t cu0 = 0;

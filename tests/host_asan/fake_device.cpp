@@ -120,6 +120,7 @@ dcp_status_t mfma_bwd_dkv(const DevGroup& g, const KTensors& t, hipStream_t) {
     if (g.items[i].pslot >= 0) t.part[((int64_t)(g.items[i].pslot + 1) * t.hkv) * 2 * 128 * 128 - 1] = 0.f;
   return DCP_OK;
 }
+long g_fake_one_launch = 0;   // backward calls that were dQ and dK/dV side by side in one launch
 // the split kernels: four workgroups an item, lists of whole items
 #define SPLIT_FITS() WALK_CHECK((waves == 4 || waves == 8) && t.dtype == DCP_BF16 && \
                                 xcd_grid(g, t.hkv, t.hq / t.hkv * kSplitSub) * 64 * waves <= (int64_t)UINT32_MAX, "a launch that the split kernels do not take")
@@ -136,6 +137,7 @@ dcp_status_t mfma_split_dkv(const DevGroup& g, const KTensors& t, int waves, hip
 }
 dcp_status_t mfma_split_bwd(const DevGroup& g, const DevGroup& gkv, const KTensors& t, int waves, hipStream_t s) {
   SPLIT_FITS();
+  g_fake_one_launch++;
   dcp_status_t st = split_whole(gkv);
   if (st == DCP_OK) st = walk_group(g, t.q_rows, g_fake_kv_rows, 0, t.block_size, false);
   return st != DCP_OK ? st : mfma_bwd_dkv(gkv, t, s);
@@ -148,6 +150,7 @@ dcp_status_t mfma_f32_dq(const DevGroup& g, const KTensors& t, int, hipStream_t 
 dcp_status_t mfma_f32_dkv(const DevGroup& g, const KTensors& t, int, hipStream_t s) { F32_FITS(); return mfma_bwd_dkv(g, t, s); }
 dcp_status_t mfma_f32_bwd(const DevGroup& g, const DevGroup& gkv, const KTensors& t, hipStream_t s) {
   F32_FITS();
+  g_fake_one_launch++;
   dcp_status_t st = walk_group(g, t.q_rows, g_fake_kv_rows, 0, t.block_size, false);
   return st != DCP_OK ? st : mfma_bwd_dkv(gkv, t, s);
 }

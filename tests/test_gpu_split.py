@@ -98,3 +98,25 @@ def test_prepared_for_other_heads(d):
         out, lse = g.forward()
         dq, dk, dv = g.backward()
         H.check(w, dict(out=out, lse=lse, dq=dq, dk=dk, dv=dv), ref, ALL, f"prepared for {hq} D{d}")
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 32), ("bf16", 64), ("bf16", 128), ("f32", 32), ("f32", 64), ("f32", 128)])
+def test_gradients_over_the_inputs(dtype, d):
+    """dQ over O, dK over K and dV over V in a batch that is small enough for one backward launch takes two, which allow it."""
+    import paper_2510_10620_amd as P
+    w = W.custom_workload("inplace", [300, 77, 33], 128, 4, 2, d, dtype, W.MaskSpec("causal"), seed=88, input_scale=0.5)
+    tensors, table = W.make_tensors(w), H.oracle_table(w)
+    ref = H.oracle_full(w, tensors, table)
+    for dq_over, dkv_over in [(True, False), (False, True), (True, True)]:
+        g = H.GpuRun(w, tensors, table)
+        g.forward()
+        dq = g.out if dq_over else g.q.new_full(g.q.shape, float("nan"))
+        dk, dv = (g.k, g.v) if dkv_over else (g.k.new_full(g.k.shape, float("nan")), g.v.new_full(g.v.shape, float("nan")))
+        ws = g.torch.empty(max(256, P.dcp_bwd_workspace_bytes(g.plan, w.hq, w.hkv, d, P.DCP_BF16 if dtype == "bf16" else P.DCP_F32)),
+                           dtype=g.torch.uint8, device="cuda")
+        P.dcp_profile_enable(True)
+        P.dcp_block_attn_bwd(g.plan, g.q, g.k, g.v, g.out, g.lse, g.dout, dq, dk, dv, w.softmax_scale, ws, g.ranges)
+        own_dq = P.dcp_profile_read("dq")[1]
+        P.dcp_profile_enable(False)
+        assert own_dq == 1
+        H.check(w, dict(dq=H.from_torch(dq), dk=H.from_torch(dk), dv=H.from_torch(dv)), ref, ("dq", "dk", "dv"), f"in place {dtype} D{d}")
