@@ -105,7 +105,7 @@ __device__ __forceinline__ void fwd_scores64(const FwdState<NQ>& st, const char*
 // either (a skipped one has scores -inf, so P = 0 and its MFMAs add nothing; for tables with per-token ranges this form
 // replaced one with a section per kind of tile, 9 984 -> 9 814 us forward and backward in the case named at KvIter::next): one straight block, in which the P.V
 // MFMAs of the first 32 keys are issued between the exponentials of the second 32 (the scheduling groups below say
-// so; exponentials are their own instruction class there).  NQ = 1.  v0_lds, v1_lds: the V tile for its first and second 32 keys.
+// so; exponentials are their own instruction class there).  NQ = 1.  v0_lds, v1_lds: the V rows of the first and second 32 keys.
 template <int NQ>
 __device__ __forceinline__ void fwd_softmax_pv(FwdState<NQ>& st, f32x16 (&s)[2][NQ], const char* v0_lds, const char* v1_lds, float c_log2) {
   static_assert(NQ == 1, "one query per lane");
@@ -155,7 +155,7 @@ __device__ __forceinline__ void fwd_softmax_pv(FwdState<NQ>& st, f32x16 (&s)[2][
 #pragma unroll
   for (int dt = 0; dt < 4; dt++) st.o[0][dt] = mfma(va[dt], p00, st.o[0][dt]);
 #pragma unroll
-  for (int dt = 0; dt < 4; dt++) vc[dt] = frag_tr(v1_lds, st.fa, 32, dt);
+  for (int dt = 0; dt < 4; dt++) vc[dt] = frag_tr(v1_lds, st.fa, 0, dt);
 #pragma unroll
   for (int dt = 0; dt < 4; dt++) st.o[0][dt] = mfma(vb[dt], p01, st.o[0][dt]);
   float sum1 = 0.f;
@@ -176,7 +176,7 @@ __device__ __forceinline__ void fwd_softmax_pv(FwdState<NQ>& st, f32x16 (&s)[2][
   st.l[0] += sum0 + sum1;
   const bf16x8 p10 = pack_frag(s[1][0], 0), p11 = pack_frag(s[1][0], 1);
 #pragma unroll
-  for (int dt = 0; dt < 4; dt++) vb[dt] = frag_tr(v1_lds, st.fa, 48, dt);
+  for (int dt = 0; dt < 4; dt++) vb[dt] = frag_tr(v1_lds, st.fa, 16, dt);
 #pragma unroll
   for (int dt = 0; dt < 4; dt++) st.o[0][dt] = mfma(vc[dt], p10, st.o[0][dt]);
 #pragma unroll
@@ -192,6 +192,9 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void mfma_fwd_kernel(DevGroup g,
   __shared__ __attribute__((aligned(1024))) char stage0[2 * kTileBytes];
   __shared__ __attribute__((aligned(1024))) char stage1[2 * kTileBytes];
   __shared__ int wg_bounds[kFwdWaves][8];
+  __shared__ __attribute__((aligned(1024))) char zero_rows[RANGES ? 32 * kRowBytes : 16];   // V of the keys of an unseen half tile
+  if (RANGES)
+    for (int x = threadIdx.x; x < 32 * kRowBytes / 16; x += 64 * kFwdWaves) *(uint4*)(zero_rows + 16 * x) = make_uint4(0, 0, 0, 0);
 
   int item, head_x;
   const int G = t.hq / t.hkv;
@@ -283,7 +286,8 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void mfma_fwd_kernel(DevGroup g,
     // the score paths join in one softmax + PV section (4 % faster: no copies of the accumulators at the merge)
     f32x16 s[2][NQ];
     bool pv;
-    int v0 = 0, v1 = 0;   // where the V rows of the two halves lie, from their own place
+    const char* v0 = cur + kTileBytes;   // V of the first and the second 32 keys
+    const char* v1 = v0 + 32 * kRowBytes;
     const bool common = !RANGES || kind < 2 ? ks + 2 * kTN <= (kind ? min(c1, wq_lo + 1) : c1)
                                             : ks + 2 * kTN <= c1 && wrb.all_see(ks, ks + 2 * kTN);
     if (w_rows > 0 && common) {
@@ -307,9 +311,9 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void mfma_fwd_kernel(DevGroup g,
       const int cls0 = w_rows > 0 ? classify32(kind, ks, c1, wq_lo, wq_hi, wrb) : kSkip;
       const int cls1 = w_rows > 0 ? classify32(kind, ks + 32, c1, wq_lo, wq_hi, wrb) : kSkip;
       pv = cls0 != kSkip || cls1 != kSkip;
-      if (RANGES) {   // weight 0 meets the rows of the half that is seen: those of an unseen half need not be finite
-        v0 = cls0 == kSkip ? 32 * kRowBytes : 0;
-        v1 = cls1 == kSkip ? -32 * kRowBytes : 0;
+      if (RANGES) {   // the weights 0 of an unseen half meet zeros: neither its V rows nor those of the seen half need be finite
+        v0 = cls0 == kSkip ? zero_rows : v0;
+        v1 = cls1 == kSkip ? zero_rows : v1;
       }
       if (cls0 == kFull && cls1 == kFull) {
         fwd_scores64<NQ, false>(st, cur, s);
@@ -328,7 +332,7 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void mfma_fwd_kernel(DevGroup g,
         }
       }
     }
-    if (pv) fwd_softmax_pv<NQ>(st, s, cur + kTileBytes + v0, cur + kTileBytes + v1, c_log2);
+    if (pv) fwd_softmax_pv<NQ>(st, s, v0, v1, c_log2);
     DCP_WAIT_VMCNT(0);
     __syncthreads();  // the copy into `nxt` has landed and `cur` may be overwritten
   };

@@ -41,3 +41,23 @@ def test_values_in_an_unseen_half_of_a_tile():
     g.v[:32] = float("inf")
     poisoned, _ = g.forward()
     assert np.isfinite(clean).all() and np.array_equal(clean[64:], poisoned[64:])
+
+
+@pytest.mark.parametrize("window_rows", [False, True], ids=["ranges", "window"])
+def test_inf_in_the_seen_half_of_a_tile(window_rows):
+    """D = 128: V_63 = Inf in one column, and in another V_31.  Rows 64 to 95 all see key 63, in a tile whose other half none of them sees: Inf
+    there, and every other value as without it, bit for bit.  Rows 32 to 63 see key 31 among 32 (31 + 33 is past them) likewise."""
+    w = W.custom_workload("seen", [601, 129], 512, 128, 32, 128, "bf16", W.MaskSpec("window", window=33), seed=93, input_scale=0.5)
+    table = H.oracle_table(w)
+    if window_rows:
+        table[table[:, 2] == W.MASK_RANGES, 2] = W.MASK_WINDOW
+    g = H.GpuRun(w, W.make_tensors(w), table, window=(33, 0) if window_rows else None)
+    want, _ = g.forward()
+    g.v[63, :, 5] = float("inf")
+    g.v[31, :, 9] = float("inf")
+    got, _ = g.forward()
+    want[64:96, :, 5] = float("inf")
+    assert np.array_equal(got[64:], want[64:])
+    want[32:64, :, 9] = float("inf")
+    rows, cols = slice(32, 64), [c for c in range(128) if c != 5]   # (key 63 is masked for some of these rows, not unseen)
+    assert np.array_equal(got[rows][:, :, cols], want[rows][:, :, cols])
