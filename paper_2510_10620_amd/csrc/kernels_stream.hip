@@ -117,7 +117,8 @@ __global__ __launch_bounds__(256) void merge_kernel(const int32_t* __restrict__ 
 // run-time divisors, and arithmetic it does not need when a q block has no partial or only one): here lane t keeps chunk t % CH
 // and the (row, head) pairs of the workgroup's rows go round in steps of 256 / CH without a division, and there are three paths
 // chosen per q block: no partial (the rows are zero-filled), one partial (weight 1: the row is copied, or zero-filled where its
-// LSE is -inf), several (up to kMergePreload with every load issued before the arithmetic).
+// LSE is -inf), several (up to kMergePreload with every load issued before the arithmetic).  The results are the above kernel's for
+// every LSE: one that is NaN makes the row NaN beside a partial with a weight and counts for nothing alone; +inf makes it NaN.
 static constexpr int kMergePreload = 4;   // partial slots per q block up to which all of an item's loads are issued at once
 typedef __bf16 hbf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x8 __attribute__((ext_vector_type(8)));
@@ -157,11 +158,13 @@ __global__ __launch_bounds__(256) void merge_rows_kernel(const int32_t* __restri
   }
   if (n_p == 1) {
     const int slot = plan_load(merge_idx, p0);
+    const u32x4 nan = {0x7fc07fc0u, 0x7fc07fc0u, 0x7fc07fc0u, 0x7fc07fc0u};
     for (; pair < n_pairs; next()) {
       const float lp = lse_of(slot);
-      const u32x4 v = __builtin_nontemporal_load(part_at(slot));
+      u32x4 v = __builtin_nontemporal_load(part_at(slot));
+      v = lp < INFINITY ? v : nan;
       __builtin_nontemporal_store(lp > -INFINITY ? v : zero, out_at());
-      if (c == 0) lse[(int64_t)h * q_rows + mem0 + row] = lp;
+      if (c == 0) lse[(int64_t)h * q_rows + mem0 + row] = lp > -INFINITY ? lp + (lp - lp) : -INFINITY;
     }
     return;
   }
@@ -177,13 +180,13 @@ __global__ __launch_bounds__(256) void merge_rows_kernel(const int32_t* __restri
           const int slot = plan_load(merge_idx, p0 + k);
           lp[k] = lse_of(slot);
           raw[k] = __builtin_nontemporal_load(part_at(slot));
-          m = fmaxf(m, lp[k]);
+          m = fmaxf(m, lp[k]);   // of those that are not NaN
         }
 #pragma unroll
       for (int k = 0; k < kMergePreload; k++)
         if (k < n_p) {
-          const bool live = lp[k] > -INFINITY;
-          const float wgt = live ? expf(lp[k] - m) : 0.f;   // m = -inf only if every partial is dead
+          const bool live = m > -INFINITY && lp[k] != -INFINITY;
+          const float wgt = live ? expf(lp[k] - m) : 0.f;
           tot += wgt;
 #pragma unroll
           for (int i = 0; i < 4; i++) {
@@ -196,7 +199,7 @@ __global__ __launch_bounds__(256) void merge_rows_kernel(const int32_t* __restri
       for (int k = 0; k < n_p; k++) {
         const int slot = merge_idx[p0 + k];
         const float lpk = lse_of(slot);
-        if (lpk == -INFINITY) continue;
+        if (lpk == -INFINITY || m == -INFINITY) continue;
         const float wgt = expf(lpk - m);
         tot += wgt;
         const u32x4 rw = *part_at(slot);
@@ -207,11 +210,10 @@ __global__ __launch_bounds__(256) void merge_rows_kernel(const int32_t* __restri
         }
       }
     }
-    const float inv = tot > 0.f ? 1.f / tot : 0.f;
-    acc *= inv;
+    acc *= m > -INFINITY ? 1.f / tot : 0.f;
     const hbf16x8 ob = __builtin_convertvector(acc, hbf16x8);   // round to nearest even in hardware
     __builtin_nontemporal_store(__builtin_bit_cast(u32x4, ob), out_at());
-    if (c == 0) lse[(int64_t)h * q_rows + mem0 + row] = tot > 0.f ? m + logf(tot) : -INFINITY;
+    if (c == 0) lse[(int64_t)h * q_rows + mem0 + row] = m > -INFINITY ? m + logf(tot) : -INFINITY;
   }
 }
 

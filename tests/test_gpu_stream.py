@@ -89,6 +89,33 @@ def test_merge_of_none_to_six_partials(d, hq):
         assert ((l[:, a:a + n].double() - ref_l)[~dead].abs() <= 1e-5).all(), (b, len(s))
 
 
+@pytest.mark.parametrize("d,hq", [(128, 3), (128, 16), (64, 5), (32, 7)])
+def test_merge_of_partials_whose_lse_is_not_finite(d, hq):
+    """The bf16 merge gives NaN, zeros and -inf where the merge for any shape gives them (here on the same values in fp32), whichever of 1 to 6
+    partials has LSE NaN, Inf or -inf; the other rows to a bf16 rounding."""
+    B = 16
+    table = np.array([[i, j, 1 if i == j else 0] for i in range(6) for j in range(i + 1)], dtype=np.int32)
+    n_slots = len(table)
+    plan = P.dcp_plan_create(np.array([0, 6 * B], np.int32), B, table, np.arange(n_slots, dtype=np.int32), n_slots)
+    gen = torch.Generator(device="cuda").manual_seed(hq + d)
+    o = torch.randn((n_slots, B, hq, d), device="cuda", generator=gen).to(torch.bfloat16)
+    lse = torch.randn((n_slots, hq, B), device="cuda", generator=gen)
+    kind = torch.rand(lse.shape, device="cuda", generator=gen)
+    for at, value in ((0.5, "-inf"), (0.2, "nan"), (0.1, "inf")):
+        lse[kind < at] = float(value)
+    res = []
+    for x in (o, o.float()):
+        out, l = torch.full((6 * B, hq, d), 7.0, device="cuda", dtype=x.dtype), torch.full((hq, 6 * B), 7.0, device="cuda")
+        P.dcp_merge_partials(plan, x, lse, out, l)
+        res.append((out.double(), l.double()))
+    (out, l), (ref, ref_l) = res
+    assert torch.isnan(ref_l).any() and (ref_l == -float("inf")).any() and torch.isfinite(ref_l).any()
+    for a, b, tol in ((out, ref, 2.0 ** -8), (l, ref_l, 2.0 ** -23)):
+        assert torch.equal(torch.isnan(a), torch.isnan(b)) and torch.equal(torch.isinf(a), torch.isinf(b))
+        fin = torch.isfinite(b)
+        assert ((a - b).abs() <= tol * b.abs() + 2.0 ** -22)[fin].all()
+
+
 @pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 128), (torch.bfloat16, 8), (torch.float32, 64)])
 @pytest.mark.parametrize("T", [1, 7, 8, 9, 32 * 1024 - 1, 32 * 1024])
 def test_delta_tokens_per_workgroup(T, dtype, d):
