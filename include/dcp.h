@@ -148,8 +148,10 @@ dcp_status_t dcp_plan_destroy(dcp_plan_t* plan);
  * and waits for `stream` (the upload of the arrays); after it, dcp_block_attn_fwd, dcp_block_attn_bwd and
  * dcp_merge_partials with this plan and shape only enqueue kernels.  Without it the first of those calls does the same
  * work itself, once.  Call it after dcp_plan_set_block_buffers, if that is used.  Errors as for the launching calls.
- * The lists are the same for every kernel family, but for the cut dK/dV list of bf16 with D = 128: outside that shape a
- * prepared plan serves calls that their strides or their `impl` send to another family, and other head counts.
+ * The lists are the same for every kernel family, but for bf16 with D = 128, whose dK/dV list holds whole or cut items as hq,
+ * hkv and the batch ask for.  Outside that shape a prepared plan serves calls that their strides or their `impl` send to
+ * another family, and other head counts.  In it a call with another hq that asks for the other list creates that at its first use,
+ * or, under stream capture and in dcp_block_attn_bwd_static, runs on the list that is there.
  * A prepared plan's launches are kernel launches and nothing else (no memset or copy nodes, no events), so they may
  * be recorded into a HIP graph by stream capture and replayed. */
 dcp_status_t dcp_plan_prepare(dcp_plan_t* plan, int32_t hq, int32_t hkv, int32_t d, int32_t dtype, int32_t impl,

@@ -424,12 +424,12 @@ dcp_status_t dcp::bwd_launch(dcp_plan_t* plan, const dcp_tensors_t* t, void* wor
   DevGroup gq, gkv;
   const int n_seg = xcd_segments(t->hkv);
   if ((st = plan->group_for(1, s, &gq, t->hq / t->hkv, n_seg, may_alloc)) != DCP_OK) return st;
-  // Whole or cut dK/dV items: what the choice of kernels wants, unless the plan holds only the other list (made for another number
-  // of query heads); whole items serve every kernel, cut ones only the one that shares its tiles.
+  // Whole or cut dK/dV items: what the choice of kernels wants.  Where that list cannot be created now and the plan holds the
+  // other one, the other one: whole items serve every kernel, cut ones only the one that shares its tiles.
   const int cut = cut_heads(use_mfma, t->dtype, t->d, t->hkv);
   const bool one_launch = one_launch_is_safe(plan, t);
   int heads = dkv_heads(plan, t, use_mfma, n_seg, one_launch);
-  if (cut && !plan->has_items(2, heads, n_seg) && plan->has_items(2, cut - heads, n_seg)) heads = cut - heads;
+  if (cut && !plan->has_items(2, heads, n_seg) && plan->has_items(2, cut - heads, n_seg) && (!may_alloc || is_capturing(s))) heads = cut - heads;
   if ((st = plan->group_for(2, s, &gkv, heads, n_seg, may_alloc)) != DCP_OK) return st;
   use_mfma = use_mfma && mfma_launch_fits(gq, false, t->dtype, t->d, t->hq, t->hkv) && mfma_launch_fits(gkv, true, t->dtype, t->d, t->hq, t->hkv) &&
              !rows_are_faster(plan, t, true);

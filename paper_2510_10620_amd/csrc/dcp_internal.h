@@ -15,6 +15,7 @@ namespace dcp {
 
 void set_error(const std::string& msg);
 dcp_status_t fail(dcp_status_t code, const std::string& msg);
+bool is_capturing(hipStream_t stream);
 
 #define DCP_HIP_TRY(expr)                                                                     \
   do {                                                                                        \

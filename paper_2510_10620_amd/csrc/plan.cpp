@@ -829,7 +829,7 @@ static dcp_status_t upload(const std::vector<T>& v, T** dev, hipStream_t stream)
   return DCP_OK;
 }
 
-static bool is_capturing(hipStream_t stream) {
+bool dcp::is_capturing(hipStream_t stream) {
   hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &status) != hipSuccess) {   // the legacy stream beside a capture elsewhere
     (void)hipGetLastError();                                   // is not for the next launch to report

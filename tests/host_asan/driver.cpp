@@ -9,6 +9,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <random>
+#include <utility>
 #include <vector>
 
 #include "dcp.h"
@@ -18,6 +19,7 @@ extern int64_t g_fake_kv_rows;
 extern int32_t g_fake_n_slots;
 extern bool g_fake_capturing;
 extern long g_fake_one_launch;
+extern int g_fake_dkv_items, g_fake_dkv_reduce;
 long fake_rows_walked();
 }
 
@@ -308,12 +310,87 @@ static void in_place_backward(int32_t dtype, int32_t d) {
   EXPECT(dcp_plan_destroy(plan) == DCP_OK);
 }
 
+// One plan used with several shapes: which dK/dV list (cut or whole items) a backward takes does not depend on what the plan ran
+// before.  Where a list cannot be created (a stream under capture) the other one serves.
+struct HistoryBatch {
+  std::vector<int32_t> cu{0}, table;
+  static constexpr int B = 512, hkv = 4;
+  HistoryBatch(int first, int n300) {
+    cu.push_back(first);
+    for (int i = 0; i < n300; i++) cu.push_back(cu.back() + 300);
+    for (size_t s = 0, b0 = 0; s + 1 < cu.size(); s++) {
+      const int nb = (cu[s + 1] - cu[s] + B - 1) / B;
+      for (int i = 0; i < nb; i++)
+        for (int j = 0; j <= i; j++) table.insert(table.end(), {(int)b0 + i, (int)b0 + j, i == j ? DCP_MASK_CAUSAL : DCP_MASK_NONE});
+      b0 += nb;
+    }
+  }
+  dcp_plan_t* plan() const {
+    dcp_plan_t* p = nullptr;
+    EXPECT(dcp_plan_create(&p, cu.data(), (int)cu.size() - 1, B, table.data(), (int64_t)table.size() / 3, nullptr, 0) == DCP_OK);
+    return p;
+  }
+  // (items, cut items) of the dK/dV launch
+  std::pair<int, int> bwd(dcp_plan_t* plan, int hq, int d, int impl = DCP_IMPL_AUTO) const {
+    dcp::g_fake_kv_rows = cu.back(); dcp::g_fake_n_slots = 0;
+    auto tensor = [](int i) { return (void*)((uintptr_t)(i + 1) << 40); };   // the stand-in kernels touch no tensor
+    dcp_tensors_t t{};
+    t.hq = hq; t.hkv = hkv; t.d = d; t.dtype = DCP_BF16; t.impl = impl; t.softmax_scale = 0.1f;
+    t.q = tensor(0); t.k = tensor(1); t.v = tensor(2); t.out = tensor(3); t.dout = tensor(4);
+    t.dq = tensor(5); t.dk = tensor(6); t.dv = tensor(7); t.lse = (float*)tensor(8);
+    t.q_stride_t = t.o_stride_t = t.do_stride_t = t.dq_stride_t = hq * d;
+    t.k_stride_t = t.v_stride_t = t.dk_stride_t = t.dv_stride_t = hkv * d;
+    t.q_stride_h = t.k_stride_h = t.v_stride_h = t.o_stride_h = t.do_stride_h = t.dq_stride_h = t.dk_stride_h = t.dv_stride_h = d;
+    const size_t wsb = dcp_bwd_workspace_bytes(plan, hq, hkv, d, DCP_BF16);
+    void* ws = nullptr;
+    EXPECT(posix_memalign(&ws, 256, wsb) == 0);
+    EXPECT(dcp_block_attn_bwd(plan, &t, ws, wsb, nullptr) == DCP_OK);
+    std::free(ws);
+    return {dcp::g_fake_dkv_items, dcp::g_fake_dkv_reduce};
+  }
+};
+
+static void lists_do_not_depend_on_history() {
+  typedef std::pair<int, int> Pair;
+  {   // one long sequence beside short ones: D = 128 takes cut items, after whatever call
+    const HistoryBatch b(16000, 40);
+    dcp_plan_t* fresh = b.plan();
+    const Pair cut = b.bwd(fresh, 32, 128), whole = b.bwd(fresh, 32, 64);
+    EXPECT(cut.second > 0 && whole.second == 0 && whole.first < cut.first);
+    EXPECT(dcp_plan_destroy(fresh) == DCP_OK);
+    for (int first = 0; first < 2; first++) {
+      dcp_plan_t* plan = b.plan();
+      if (first == 0) b.bwd(plan, 32, 64);
+      else b.bwd(plan, 32, 128, DCP_IMPL_SCALAR);
+      dcp::g_fake_capturing = true;
+      EXPECT(b.bwd(plan, 32, 128) == whole);
+      dcp::g_fake_capturing = false;
+      EXPECT(b.bwd(plan, 32, 128) == cut);
+      EXPECT(dcp_plan_destroy(plan) == DCP_OK);
+    }
+  }
+  {   // 16 query heads take cut items, 32 whole ones (waves that split the other side)
+    const HistoryBatch b(2000, 10);
+    dcp_plan_t *f16 = b.plan(), *f32 = b.plan(), *plan = b.plan();
+    const Pair cut = b.bwd(f16, 16, 128), whole = b.bwd(f32, 32, 128);
+    EXPECT(cut.second > 0 && whole.second == 0);
+    EXPECT(b.bwd(f16, 32, 128) == whole && b.bwd(f32, 16, 128) == cut);
+    EXPECT(dcp_plan_prepare(plan, 16, HistoryBatch::hkv, 128, DCP_BF16, DCP_IMPL_AUTO, nullptr) == DCP_OK);
+    dcp::g_fake_capturing = true;
+    EXPECT(b.bwd(plan, 32, 128) == cut);
+    dcp::g_fake_capturing = false;
+    EXPECT(b.bwd(plan, 32, 128) == whole);
+    for (dcp_plan_t* p : {f16, f32, plan}) EXPECT(dcp_plan_destroy(p) == DCP_OK);
+  }
+}
+
 int main(int argc, char** argv) {
   const int iters = argc > 1 ? std::atoi(argv[1]) : 150;
   Rng r(20251028);
   for (int i = 0; i < iters && g_fail == 0; i++) one_case(r, i);
   if (g_fail == 0) largest_batch();
   for (int d = 32; d <= 128; d *= 2) { in_place_backward(DCP_BF16, d); in_place_backward(DCP_F32, d); }
+  if (g_fail == 0) lists_do_not_depend_on_history();
   // the empty plan and NULL arguments
   dcp_plan_t* plan = nullptr;
   int32_t cu0 = 0;

@@ -111,8 +111,10 @@ dcp_status_t mfma_bwd_dq(const DevGroup& g, const KTensors& t, hipStream_t) {
   if (g.n_items > 0) { t.delta_w[(int64_t)t.hq * t.q_rows - 1] = 0.f; t.lse2_w[(int64_t)t.hq * t.q_rows - 1] = 0.f; }
   return walk_group(g, t.q_rows, g_fake_kv_rows, 0, t.block_size, false);
 }
+int g_fake_dkv_items = 0, g_fake_dkv_reduce = 0;   // the list of the last dK/dV launch
 dcp_status_t mfma_bwd_dkv(const DevGroup& g, const KTensors& t, hipStream_t) {
   FITS(true);
+  g_fake_dkv_items = g.n_items; g_fake_dkv_reduce = g.n_reduce;
   dcp_status_t st = walk_group(g, g_fake_kv_rows, t.q_rows, 0, t.block_size, true);
   if (st != DCP_OK) return st;
   // every part slot of a cut item lies inside the partial-sum area of the workspace: touch its last float

@@ -87,7 +87,8 @@ def test_slots_strides_and_a_row_without_keys(d):
 
 @pytest.mark.parametrize("d", [64, 128])
 def test_prepared_for_other_heads(d):
-    """A plan made ready for 128 query heads (D = 128: cut dK/dV items, which the split kernels do not take) serves two."""
+    """A plan made ready for 128 query heads (D = 128: cut dK/dV items, which the split kernels do not take) serves two: on that list where
+    none may be created (the entry point that allocates nothing), else on their own."""
     import paper_2510_10620_amd as P
     w = W.custom_workload("prep", [1300, 200], 128, 2, 2, d, "bf16", W.MaskSpec("causal"), seed=84, input_scale=0.5)
     tensors, table = W.make_tensors(w), H.oracle_table(w)
@@ -96,8 +97,11 @@ def test_prepared_for_other_heads(d):
         g = H.GpuRun(w, tensors, table)
         P.dcp_plan_prepare(g.plan, hq, 2, d, P.DCP_BF16)
         out, lse = g.forward()
-        dq, dk, dv = g.backward()
-        H.check(w, dict(out=out, lse=lse, dq=dq, dk=dk, dv=dv), ref, ALL, f"prepared for {hq} D{d}")
+        grads = [g.torch.full_like(x, float("nan")) for x in (g.q, g.k, g.v)]
+        P.dcp_block_attn_bwd_static(g.plan, g.q, g.k, g.v, g.out, g.lse, g.dout, *grads, w.softmax_scale, g.ranges)
+        g.torch.cuda.synchronize()
+        for dq, dk, dv in ([H.from_torch(x) for x in grads], g.backward()):
+            H.check(w, dict(out=out, lse=lse, dq=dq, dk=dk, dv=dv), ref, ALL, f"prepared for {hq} D{d}")
 
 
 @pytest.mark.parametrize("dtype,d", [("bf16", 32), ("bf16", 64), ("bf16", 128), ("f32", 32), ("f32", 64), ("f32", 128)])
