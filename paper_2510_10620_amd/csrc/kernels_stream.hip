@@ -325,10 +325,15 @@ dcp_status_t stream_delta(const void* o, int64_t o_st, int64_t o_sh, const void*
                           float* delta, const float* lse, float* lse2, int64_t total_tokens, int32_t hq, int32_t d,
                           int32_t dtype, hipStream_t s) {
   if (total_tokens == 0) return DCP_OK;
-  // 32 tokens a workgroup make less than four workgroups a CU of a short batch, each with a chain of loads: in bf16 with D 128, 32 and
-  // 8 tokens: 9 706 tokens, 16 heads 26.1 and 14.0 us; 8 192, 4 heads 8.6 and 5.5; 24 724, 24 heads 51.1 and 51.7; 65 536, 32
-  // heads 170 and 186.
-  const int tok = total_tokens < 32 * 1024 ? 8 : 32;
+  // 32 tokens a workgroup make less than four workgroups a CU of a short batch, each with a chain of loads; 8 make four times the
+  // starts, and with few chunks to a token threads without a load.  8 and 32 tokens, bf16, D 128: 16 384 tokens, 4 / 16 / 128 heads
+  // 7.2 / 23.1 / 181 and 10.3 / 32.0 / 226 us; 24 576 tokens 9.4 / 33.7 / 281 and 11.1 / 35.5 / 255; 32 768 tokens 11.7 / 45.0 / 379
+  // and 12.6 / 44.3 / 334; one head of 64, 4 096 / 16 384 tokens 3.8 / 5.0 and 3.6 / 3.8.  fp32, whose chunk is two loads: 32 heads of
+  // 64, 8 192 / 12 288 tokens 21.7 / 31.9 and 23.1 / 30.2; one head 4.0 and 3.5 at 8 192.
+  const int64_t chunks8 = 8 * (int64_t)hq * (d / 8);   // of 8 tokens
+  const bool few = dtype == DCP_BF16 ? total_tokens < (hq <= 16 ? 32 * 1024 : 22 * 1024) && total_tokens <= 96 * chunks8
+                                     : total_tokens < 10 * 1024 && total_tokens <= 32 * chunks8;
+  const int tok = few ? 8 : 32;
   dim3 grid((unsigned)((total_tokens + tok - 1) / tok)), block(256);
   const size_t sm = (size_t)hq * (tok + 1) * sizeof(float);
 #define DCP_DELTA(T, TOK)                                                                                                  \

@@ -127,3 +127,16 @@ def test_delta_tokens_per_workgroup(T, dtype, d):
     P.dcp_bwd_delta(o, do, delta)
     t = o.double() * do.double()
     assert ((delta.double() - t.sum(-1).T).abs() <= d * 2.0 ** -24 * t.abs().sum(-1).T).all()
+
+
+@pytest.mark.parametrize("dtype,d,h,last", [(torch.bfloat16, 128, 17, 22 * 1024 - 1), (torch.bfloat16, 8, 3, 96 * 24), (torch.float32, 64, 3, 32 * 192),
+                                            (torch.float32, 128, 5, 10 * 1024 - 1)])
+def test_delta_tokens_per_workgroup_by_work(dtype, d, h, last):
+    """The same where many heads, few chunks to a token or fp32 take 8 tokens a workgroup up to `last` tokens only."""
+    for T in (last, last + 1):
+        gen = torch.Generator(device="cuda").manual_seed(T)
+        o, do = (torch.randn((T, h, d), device="cuda", generator=gen).to(dtype) for _ in range(2))
+        delta = torch.full((h, T), float("nan"), device="cuda")
+        P.dcp_bwd_delta(o, do, delta)
+        t = o.double() * do.double()
+        assert ((delta.double() - t.sum(-1).T).abs() <= d * 2.0 ** -24 * t.abs().sum(-1).T).all(), T
