@@ -14,6 +14,7 @@ DCP_ERR_UNSUPPORTED, DCP_ERR_WORKSPACE, DCP_ERR_HIP = -4, -5, -6
 DCP_MASK_NONE, DCP_MASK_CAUSAL, DCP_MASK_RANGES, DCP_MASK_SKIP, DCP_MASK_WINDOW = 0, 1, 2, 3, 4
 DCP_BF16, DCP_F32 = 0, 1
 DCP_IMPL_AUTO, DCP_IMPL_SCALAR, DCP_IMPL_MFMA = 0, 1, 2
+DCP_FORM_ROWS, DCP_FORM_SHARED, DCP_FORM_SPLIT, DCP_FORM_SPLIT8 = -1, 0, 1, 2
 EXPORTS = dict(BLK_START=0, BLK_LEN=1, BLK_SEQ=2, FWD_PTR=3, FWD_IDX=4, BWDQ_PTR=5, BWDQ_IDX=6,
                BWDKV_PTR=7, BWDKV_IDX=8, SLOT_QBLK=9, MERGE_PTR=10, MERGE_IDX=11)
 
@@ -182,6 +183,13 @@ def dcp_plan_export_dkv_segments(plan, hkv):
     seg = np.zeros(9, dtype=np.int32)
     _check(lib.dcp_plan_export_dkv_segments(plan.handle, int(hkv), ctypes.byref(n), seg.ctypes.data_as(_lib.i32p)))
     return int(n.value), seg
+
+
+def dcp_plan_export_forms(plan, hq, hkv, d, dtype_code):
+    """Kernel forms (DCP_FORM_*) that calls of this shape take: dict(fwd, dq, dkv, bwd); bwd SHARED: dQ and dK/dV are two launches."""
+    forms = (ctypes.c_int32 * 4)()
+    _check(_lib.load().dcp_plan_export_forms(plan.handle, hq, hkv, d, dtype_code, forms))
+    return dict(zip(("fwd", "dq", "dkv", "bwd"), forms))
 
 
 # ------------------------------------------------------------------ launching calls (torch)

@@ -139,7 +139,8 @@ static bool rows_are_faster(const dcp_plan_t* plan, const dcp_tensors_t* t, bool
 // the first or less: over those batches no call was slower than with the first kind alone by more than 2 %, on average it took 0.87 /
 // 0.64 / 0.71 of the time in the forward and 0.79 / 0.52 / 0.47 in the backward (fp32 0.78 / 0.88 / 0.92 and 0.66 / 0.71 / 0.66).
 struct LaunchFit { double start, chain, share, item; };
-enum { kShared = 0, kSplit, kSplit8, kForms };   // bf16: shared tiles, four waves, eight waves; fp32: 32 rows, 16 rows
+// bf16: shared tiles, four waves, eight waves; fp32: 32 rows, 16 rows; kRows: the thread-per-row kernels
+enum { kRows = DCP_FORM_ROWS, kShared = DCP_FORM_SHARED, kSplit = DCP_FORM_SPLIT, kSplit8 = DCP_FORM_SPLIT8, kForms };
 struct LaunchFits { int32_t dtype, d; double sure; LaunchFit fwd[kForms], dq[kForms], dkv[kForms], bwd[kForms]; };   // bwd: dQ and dK/dV in one launch
 static const LaunchFits kFits[] = {
     {DCP_BF16, 128, 0.9, {{7.0, 128, 253, 5.7}, {5.0, 53.5, 373, 18.9}, {5.3, 30.1, 380, 41.1}}, {{7.3, 167, 335, 7.5}, {6.6, 50.4, 428, 29.6}, {7.8, 28.9, 433, 62.8}},
@@ -229,6 +230,27 @@ static bool one_launch_is_safe(const dcp_plan_t* plan, const dcp_tensors_t* t) {
 }
 static int waves_of(int form) { return form == kSplit ? 4 : 8; }
 
+// The form of a forward over the list g.
+static int fwd_form(dcp_plan_t* plan, const dcp_tensors_t* t, bool use_mfma, const DevGroup& g) {
+  if (!use_mfma || !mfma_launch_fits(g, false, t->dtype, t->d, t->hq, t->hkv) || rows_are_faster(plan, t, false)) return kRows;
+  const LaunchSize& z = plan->host_items(0, t->hq / t->hkv, xcd_segments(t->hkv)).size;
+  const LaunchFits* f = fits_of(t, z);
+  double us = 0;
+  return f ? pick_q(*f, f->fwd, t, z, &us) : kShared;
+}
+
+// The forms of a backward over the lists gq and gkv, the latter of items cut for `heads` KV heads (0: whole items).
+static BwdChoice bwd_forms(dcp_plan_t* plan, const dcp_tensors_t* t, bool use_mfma, const DevGroup& gq, const DevGroup& gkv, int cut, int heads,
+                           bool one_launch) {
+  if (!use_mfma || !mfma_launch_fits(gq, false, t->dtype, t->d, t->hq, t->hkv) ||
+      !mfma_launch_fits(gkv, true, t->dtype, t->d, t->hq, t->hkv) || rows_are_faster(plan, t, true))
+    return {kRows, kRows, kShared};
+  const int n_seg = xcd_segments(t->hkv);
+  BwdChoice c = pick_bwd(t, plan->host_items(1, t->hq / t->hkv, n_seg).size, plan->host_items(2, cut, n_seg).size, one_launch);
+  if (heads != 0) c.dkv = c.both = kShared;
+  return c;
+}
+
 // KV heads the dK/dV list is cut for (0: whole items).  All other lists are the same for every kernel family, so a plan
 // made ready for a shape serves it whichever family a call's strides or its `impl` choose.
 static int cut_heads(bool use_mfma, int32_t dtype, int32_t d, int32_t hkv) { return use_mfma && mfma_splits_dkv(dtype, d) ? hkv : 0; }
@@ -301,16 +323,12 @@ extern "C" dcp_status_t dcp_block_attn_fwd(dcp_plan_t* plan, const dcp_tensors_t
   hipStream_t s = (hipStream_t)stream;
   DevGroup g;
   if ((st = plan->group_for(0, s, &g, t->hq / t->hkv, xcd_segments(t->hkv))) != DCP_OK) return st;
-  use_mfma = use_mfma && mfma_launch_fits(g, false, t->dtype, t->d, t->hq, t->hkv) && !rows_are_faster(plan, t, false);
+  const int form = fwd_form(plan, t, use_mfma, g);
   KTensors k = pack(plan, t);
   ProfScope ps(DCP_K_FWD, s);
-  const LaunchSize& z = plan->host_items(0, t->hq / t->hkv, xcd_segments(t->hkv)).size;
-  if (const LaunchFits* f = use_mfma ? fits_of(t, z) : nullptr) {
-    double us = 0;
-    const int form = pick_q(*f, f->fwd, t, z, &us);
-    if (form != kShared) return t->dtype == DCP_F32 ? mfma_f32_fwd(g, k, 16, s) : mfma_split_fwd(g, k, waves_of(form), s);
-  }
-  return use_mfma ? mfma_fwd(g, k, s) : scalar_fwd(g, k, t->dtype, s);
+  if (form == kRows) return scalar_fwd(g, k, t->dtype, s);
+  if (form == kShared) return mfma_fwd(g, k, s);
+  return t->dtype == DCP_F32 ? mfma_f32_fwd(g, k, 16, s) : mfma_split_fwd(g, k, waves_of(form), s);
 }
 
 extern "C" dcp_status_t dcp_merge_partials(dcp_plan_t* plan, const void* o_part, const float* lse_part, void* out,
@@ -390,6 +408,29 @@ extern "C" dcp_status_t dcp_plan_export_dkv_segments(dcp_plan_t* plan, int32_t h
   return DCP_OK;
 }
 
+extern "C" dcp_status_t dcp_plan_export_forms(dcp_plan_t* plan, int32_t hq, int32_t hkv, int32_t d, int32_t dtype, int32_t* forms) {
+  if (!plan || !forms) return fail(DCP_ERR_INVALID_ARG, "plan or forms is NULL");
+  dcp_tensors_t t{};
+  t.hq = hq; t.hkv = hkv; t.d = d; t.dtype = dtype; t.softmax_scale = 1.f;
+  dcp_status_t st = check_shape(&t);
+  bool use_mfma = false;
+  if (st == DCP_OK) st = pick_impl(&t, &use_mfma);
+  if (st != DCP_OK) return st;
+  const int n_seg = xcd_segments(hkv), cut = cut_heads(use_mfma, dtype, d, hkv), heads = dkv_heads(plan, &t, use_mfma, n_seg, true);
+  auto list = [&](int gid, int h) {
+    const HostItems& hi = plan->host_items(gid, h, n_seg);
+    DevGroup g{};
+    g.n_items = (int32_t)hi.items.size();
+    g.n_seg = hi.n_seg;
+    for (int k = 0; k <= 8; k++) g.seg[k] = hi.seg[k];
+    return g;
+  };
+  forms[0] = fwd_form(plan, &t, use_mfma, list(0, hq / hkv));
+  const BwdChoice c = bwd_forms(plan, &t, use_mfma, list(1, hq / hkv), list(2, heads), cut, heads, true);
+  forms[1] = c.dq; forms[2] = c.dkv; forms[3] = c.both;
+  return DCP_OK;
+}
+
 extern "C" size_t dcp_bwd_workspace_bytes(const dcp_plan_t* plan, int32_t hq, int32_t hkv, int32_t d, int32_t dtype) {
   if (!plan || hq <= 0) return 0;
   // the work lists are cached in the plan the first time a size or a launch asks for them
@@ -431,8 +472,8 @@ dcp_status_t dcp::bwd_launch(dcp_plan_t* plan, const dcp_tensors_t* t, void* wor
   int heads = dkv_heads(plan, t, use_mfma, n_seg, one_launch);
   if (cut && !plan->has_items(2, heads, n_seg) && plan->has_items(2, cut - heads, n_seg) && (!may_alloc || is_capturing(s))) heads = cut - heads;
   if ((st = plan->group_for(2, s, &gkv, heads, n_seg, may_alloc)) != DCP_OK) return st;
-  use_mfma = use_mfma && mfma_launch_fits(gq, false, t->dtype, t->d, t->hq, t->hkv) && mfma_launch_fits(gkv, true, t->dtype, t->d, t->hq, t->hkv) &&
-             !rows_are_faster(plan, t, true);
+  const BwdChoice form = bwd_forms(plan, t, use_mfma, gq, gkv, cut, heads, one_launch);
+  use_mfma = form.dq != kRows;
   KTensors k = pack(plan, t);
   const size_t n_hT = wsz.n_hT;
   k.part = (float*)((char*)workspace + 2 * wsz.n_hT + wsz.n_bounds);
@@ -445,9 +486,6 @@ dcp_status_t dcp::bwd_launch(dcp_plan_t* plan, const dcp_tensors_t* t, void* wor
     k.qbounds = qb;
     if ((st = mfma_range_bounds(gkv, k, plan->d_blk_t32, plan->n_blocks, plan->longest_block, qb, s)) != DCP_OK) return st;
   }
-  BwdChoice form{kShared, kShared, kShared};
-  if (use_mfma) form = pick_bwd(t, plan->host_items(1, t->hq / t->hkv, n_seg).size, plan->host_items(2, cut, n_seg).size, one_launch);
-  if (heads != 0) form.dkv = form.both = kShared;
   if (form.both != kShared) {
     ProfScope ps(DCP_K_DKV, s, may_alloc);
     return t->dtype == DCP_F32 ? mfma_f32_bwd(gq, gkv, k, s) : mfma_split_bwd(gq, gkv, k, waves_of(form.both), s);
@@ -463,13 +501,15 @@ dcp_status_t dcp::bwd_launch(dcp_plan_t* plan, const dcp_tensors_t* t, void* wor
   }
   {
     ProfScope ps(DCP_K_DQ, s, may_alloc);
-    if (form.dq != kShared) st = t->dtype == DCP_F32 ? mfma_f32_dq(gq, k, 16, s) : mfma_split_dq(gq, k, waves_of(form.dq), s);
-    else st = use_mfma ? mfma_bwd_dq(gq, k, s) : scalar_bwd_dq(gq, k, t->dtype, s);
+    if (form.dq == kRows) st = scalar_bwd_dq(gq, k, t->dtype, s);
+    else if (form.dq == kShared) st = mfma_bwd_dq(gq, k, s);
+    else st = t->dtype == DCP_F32 ? mfma_f32_dq(gq, k, 16, s) : mfma_split_dq(gq, k, waves_of(form.dq), s);
     if (st != DCP_OK) return st;
   }
   ProfScope ps(DCP_K_DKV, s, may_alloc);
-  if (form.dkv != kShared) return t->dtype == DCP_F32 ? mfma_f32_dkv(gkv, k, 16, s) : mfma_split_dkv(gkv, k, waves_of(form.dkv), s);
-  return use_mfma ? mfma_bwd_dkv(gkv, k, s) : scalar_bwd_dkv(gkv, k, t->dtype, s);
+  if (form.dkv == kRows) return scalar_bwd_dkv(gkv, k, t->dtype, s);
+  if (form.dkv == kShared) return mfma_bwd_dkv(gkv, k, s);
+  return t->dtype == DCP_F32 ? mfma_f32_dkv(gkv, k, 16, s) : mfma_split_dkv(gkv, k, waves_of(form.dkv), s);
 }
 
 extern "C" dcp_status_t dcp_block_attn_bwd(dcp_plan_t* plan, const dcp_tensors_t* t, void* workspace,

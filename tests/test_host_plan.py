@@ -243,6 +243,24 @@ def test_dkv_work_list_segments_balance_the_xcds(hkv):
             assert len(set(seg_of_item[seq_of == q])) == 1, f"sequence {q} is spread over several segments"
 
 
+@pytest.mark.parametrize("dtype,d", [(P.DCP_BF16, 32), (P.DCP_BF16, 64), (P.DCP_BF16, 128), (P.DCP_F32, 32), (P.DCP_F32, 64), (P.DCP_F32, 128)])
+def test_forms_of_small_and_large_batches(dtype, d):
+    """A few tokens go to the kernels that split the other side, in one backward launch; a large batch to those that share their tiles; a
+    great many short blocks to the thread-per-row kernels where there is that choice."""
+    def forms(lens, B, hq, hkv):
+        cu = W.cu_from_lengths(lens)
+        plan = P.dcp_plan_create(cu, B, P.dcp_build_block_table(cu, B, W.attn_ranges(W.MaskSpec("causal"), cu)))
+        return P.dcp_plan_export_forms(plan, hq, hkv, d, dtype)
+    small, large, short = forms([300], 128, 4, 2), forms([2048] * 16, 1024, 32, 8), forms([2] * 4000, 64, 4, 2)
+    last = P.DCP_FORM_SPLIT8 if dtype == P.DCP_BF16 else P.DCP_FORM_SPLIT
+    assert P.DCP_FORM_SPLIT <= small["bwd"] <= last and (dtype == P.DCP_F32 or P.DCP_FORM_SPLIT <= small["fwd"] <= last)
+    assert large["fwd"] == large["dq"] == large["bwd"] == P.DCP_FORM_SHARED
+    rows = dtype == P.DCP_F32 or d == 32
+    assert (short["fwd"] == short["dq"] == short["dkv"] == P.DCP_FORM_ROWS) == rows
+    with pytest.raises(P.DcpError):
+        forms([300], 128, 3, 2)
+
+
 @pytest.mark.parametrize("window,sink", [(50, 0), (40, 7), (16, 16), (1, 0), (300, 3), (5, 400)])
 def test_window_table_and_pair_counts_bit_exact_vs_oracle(window, sink):
     rng = np.random.default_rng(29)
