@@ -138,6 +138,13 @@ static bool rows_are_faster(const dcp_plan_t* plan, const dcp_tensors_t* t, bool
 // to 4 096.  The estimates are 12 to 27 % off, so the second kind is taken only where it is estimated at 0.9 (fp32: 0.85 to 0.87) of
 // the first or less: over those batches no call was slower than with the first kind alone by more than 2 %, on average it took 0.87 /
 // 0.64 / 0.71 of the time in the forward and 0.79 / 0.52 / 0.47 in the backward (fp32 0.78 / 0.88 / 0.92 and 0.66 / 0.71 / 0.66).
+// bf16 with D 128 where no block has more than 64 rows: the pairs are those that are walked (LaunchSize), since a split workgroup has 32
+// rows and walks such an item as long as one of 128 rows.  Counted as visible pairs, its dK/dV was estimated at 0.6 of its time: 5 765
+// tokens, 8/2 heads, blocks of 64, backward 177 us with shared tiles and 329 in the form that was taken.  Shared tiles take 0.85 of
+// their estimate there (the waves without rows leave their issue slots to the CU's other workgroup), hence
+// kSureShort.  149 batches with blocks of 16 to 64: 34 were slower than with shared tiles alone by more than 3 %, up to 1.81 times; now 8 are, up to 1.13 (blocks of 64: 1.07).
+// Per-token ranges, whose pairs are a guess (windows of 32 to 4 096, sinks, mask blocks, shared questions; blocks of 64 to 4 096), measured over
+// 251 batches of all types: forward 0.63 to 0.96, backward 0.58 to 0.75 of the time of the first kind alone, single calls up to 1.05 of it.
 struct LaunchFit { double start, chain, share, item; };
 // bf16: shared tiles, four waves, eight waves; fp32: 32 rows, 16 rows; kRows: the thread-per-row kernels
 enum { kRows = DCP_FORM_ROWS, kShared = DCP_FORM_SHARED, kSplit = DCP_FORM_SPLIT, kSplit8 = DCP_FORM_SPLIT8, kForms };
@@ -156,6 +163,8 @@ static const LaunchFits kFits[] = {
     {DCP_F32, 32, 0.86, {{5.1, 70.8, 573, 21.1}, {4.8, 42.8, 748, 23.3}}, {{5.8, 97.3, 789, 24.6}, {4.8, 71.1, 1130, 27.4}},
      {{6.6, 152, 1120, 52.6}, {5.9, 94.8, 1390, 26.6}}, {{}, {4.5, 109, 2975, 41.0}}}};
 static constexpr double kLaunchGap = 1.0;   // between two launches
+static constexpr double kSureShort = 0.8, kSureShort8 = 0.7;   // `sure` of dK/dV over short blocks with four and eight waves
+static bool short_blocks(const dcp_tensors_t* t, const LaunchSize& z) { return t->dtype == DCP_BF16 && t->d == 128 && z.rows <= 64; }
 
 static double launch_us(const LaunchFit& f, double longest, double total, double items) {
   return f.start + std::hypot(f.chain * longest * 1e-6, f.share * total / 512e6) + f.item * items / 512;
@@ -170,20 +179,22 @@ static const LaunchFits* fits_of(const dcp_tensors_t* t, const LaunchSize& z) {
 }
 static int last_form(const dcp_tensors_t* t) { return t->dtype == DCP_BF16 ? kSplit8 : kSplit; }
 
-// The form of a launch whose estimates are us[kShared ..], and its estimate.
-static int least_form(const LaunchFits& f, const dcp_tensors_t* t, const double* us, double* out) {
+// The form of a launch whose estimates are us[kShared ..], and its estimate.  sure, sure8: for kSplit and kSplit8.
+static int least_form(double sure, double sure8, const dcp_tensors_t* t, const double* us, double* out) {
   int best = kShared;
-  double least = f.sure * us[kShared];
+  double least = HUGE_VAL;
   for (int v = kSplit; v <= last_form(t); v++)
-    if (us[v] < least) { best = v; least = us[v]; }
+    if (us[v] < least && us[v] < (v == kSplit ? sure : sure8) * us[kShared]) { best = v; least = us[v]; }
   *out = us[best];
   return best;
 }
 
 static int pick_q(const LaunchFits& fits, const LaunchFit* f, const dcp_tensors_t* t, const LaunchSize& z, double* us) {
   double x[kForms];
-  for (int v = kShared; v <= last_form(t); v++) x[v] = launch_us(f[v], (double)z.longest, (double)z.total * t->hq, (double)z.items * t->hq);
-  return least_form(fits, t, x, us);
+  const bool walked = short_blocks(t, z);
+  const double longest = (double)(walked ? z.walk : z.longest), total = (double)(walked ? z.walk_total : z.total) * t->hq;
+  for (int v = kShared; v <= last_form(t); v++) x[v] = launch_us(f[v], longest, total, (double)z.items * t->hq);
+  return least_form(fits.sure, fits.sure, t, x, us);
 }
 
 struct BwdChoice { int dq, dkv, both; };   // both: the form of the one launch, or kShared (two launches)
@@ -191,13 +202,15 @@ static BwdChoice pick_bwd(const dcp_tensors_t* t, const LaunchSize& zq, const La
   BwdChoice c{kShared, kShared, kShared};
   const LaunchFits* f = fits_of(t, zq);
   if (!f || !fits_of(t, zk)) return c;
-  const double longest = (double)zk.longest * (t->hq / t->hkv), total = (double)zk.total * t->hq, items = (double)zk.items * t->hkv;
+  const bool walked = short_blocks(t, zk);
+  const double group = t->hq / t->hkv, longest = (double)(walked ? zk.walk : zk.longest) * group,
+               total = (double)(walked ? zk.walk_total : zk.total) * t->hq, items = (double)zk.items * t->hkv;
   double us_q = 0, us_k = 0, x[kForms];
   c.dq = pick_q(*f, f->dq, t, zq, &us_q);
   for (int v = kShared; v <= last_form(t); v++) x[v] = launch_us(f->dkv[v], longest, total, items);
   if (mfma_splits_dkv(t->dtype, t->d))   // shared tiles go over a list of cut items
-    x[kShared] = launch_us(f->dkv[kShared], (double)zk.longest_part * (t->hq / t->hkv), total, (double)zk.parts * t->hkv);
-  c.dkv = least_form(*f, t, x, &us_k);
+    x[kShared] = launch_us(f->dkv[kShared], (double)(walked ? zk.walk_part : zk.longest_part) * group, total, (double)zk.parts * t->hkv);
+  c.dkv = least_form(walked ? kSureShort : f->sure, walked ? kSureShort8 : f->sure, t, x, &us_k);
   double least = f->sure * (us_q + us_k + kLaunchGap);
   for (int v = kSplit; one_launch && v <= last_form(t); v++) {
     const double us = launch_us(f->bwd[v], longest, total, items + (double)zq.items * t->hq);

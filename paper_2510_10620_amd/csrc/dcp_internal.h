@@ -98,6 +98,15 @@ struct GroupSize {
 struct LaunchSize {
   int64_t items = 0, longest = 0, total = 0;   // whole items, the costliest, all of them
   int64_t parts = 0, longest_part = 0;         // of the list as it is, which may hold cut items
+  // The same in pairs that are walked: the longest item and part (as if they had all 128 rows) and all items (rows in 32s), at least
+  // 32 rows of the other side for a table row.
+  int64_t walk = 0, walk_part = 0, walk_total = 0;
+  int32_t rows = 0;   // most own rows of an item
+};
+
+// Cost of an item in pairs, and rows of the other side that it walks, at least 32 for a table row.
+struct ItemCost {
+  int64_t pairs = 0, walk = 0;
 };
 
 struct HostItems {
@@ -145,7 +154,7 @@ struct dcp_plan {
   typedef std::tuple<int, int, int> ItemKey;
   static ItemKey item_key(int group_id, int heads, int n_seg) { return ItemKey(group_id, group_id == 2 ? heads : 0, n_seg); }
   std::map<ItemKey, dcp::HostItems> h_items;
-  std::vector<int64_t> item_cost[3];   // of every group's whole items, in unit order, once a list has been made
+  std::vector<dcp::ItemCost> item_cost[3];   // of every group's whole items, in unit order, once a list has been made
   std::map<ItemKey, dcp::DevItems> items;
 
   // may_alloc = false: fail (DCP_ERR_INVALID_ARG) instead of creating a device copy that does not exist yet

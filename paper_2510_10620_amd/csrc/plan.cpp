@@ -621,9 +621,10 @@ const HostItems& dcp_plan::host_items(int gid, int heads, int n_seg) {
   auto hit = h_items.find(key);
   if (hit != h_items.end()) return hit->second;
   HostGroup* hg = gid == 0 ? &fwd : (gid == 1 ? &bwdq : &bwdkv);
-  struct Scored { WorkItem w; int64_t cost; };
+  struct Scored { WorkItem w; int64_t cost, walk; };
   std::vector<Scored> sc;
   std::vector<int64_t> ecost;   // per-entry costs of the item being built
+  auto walked = [](int64_t pairs, int64_t rows) { return pairs > 0 ? std::max<int64_t>(32, pairs / rows) : 0; };
   // first pass: whole items and the total cost
   int64_t total = 0;
   const bool known = !item_cost[gid].empty();
@@ -635,20 +636,29 @@ const HostItems& dcp_plan::host_items(int gid, int heads, int n_seg) {
     for (int32_t t = 0; t < nt; t++) {
       int64_t r0 = blk_start[b] + (int64_t)t * kItemRows;
       int64_t r1 = std::min<int64_t>(r0 + kItemRows, blk_start[b] + blk_len[b]);
-      int64_t cost = 0;
+      ItemCost cost;
       if (known) cost = item_cost[gid][sc.size()];
-      else for (int32_t e = hg->ptr[u]; e < hg->ptr[u + 1]; e++)
-        cost += tile_cost(hg->ent_kind[e], r0, r1, hg->ent_start[e], hg->ent_start[e] + hg->ent_len[e], gid == 2);
-      sc.push_back({{u, t, hg->ptr[u], hg->ptr[u + 1], -1, blk_start[b], blk_len[b], (gid == 2 ? kv_moff : q_moff)[b]}, cost});
-      total += cost;
+      else for (int32_t e = hg->ptr[u]; e < hg->ptr[u + 1]; e++) {
+        const int64_t pairs = tile_cost(hg->ent_kind[e], r0, r1, hg->ent_start[e], hg->ent_start[e] + hg->ent_len[e], gid == 2);
+        cost.pairs += pairs;
+        cost.walk += walked(pairs, r1 - r0);
+      }
+      sc.push_back({{u, t, hg->ptr[u], hg->ptr[u + 1], -1, blk_start[b], blk_len[b], (gid == 2 ? kv_moff : q_moff)[b]}, cost.pairs, cost.walk});
+      total += cost.pairs;
     }
   }
   if (!known)
-    for (const Scored& x : sc) item_cost[gid].push_back(x.cost);
+    for (const Scored& x : sc) item_cost[gid].push_back({x.cost, x.walk});
   HostItems hi;
   hi.size.items = (int64_t)sc.size();
   hi.size.total = total;
-  for (const Scored& x : sc) hi.size.longest = std::max(hi.size.longest, x.cost);
+  for (const Scored& x : sc) {
+    const int32_t rows = std::min(kItemRows, x.w.blk_len - x.w.tile * kItemRows);
+    hi.size.longest = std::max(hi.size.longest, x.cost);
+    hi.size.walk = std::max(hi.size.walk, kItemRows * x.walk);
+    hi.size.walk_total += (rows + 31) / 32 * 32 * x.walk;
+    hi.size.rows = std::max(hi.size.rows, rows);
+  }
   if (gid == 2 && heads > 0) {
     // Long items are cut, along their table rows, into parts (each with a slot of fp32 partial sums that a reduce
     // kernel adds up): one key tile under a sink, or the first keys of the one long sequence of a small batch, can
@@ -696,10 +706,11 @@ const HostItems& dcp_plan::host_items(int gid, int heads, int n_seg) {
           const int32_t left_parts = n_parts - p - 1;
           const int64_t goal = it.cost * (p + 1) / n_parts;
           int32_t e_hi = e + 1;
-          int64_t c = ecost[e - w.e0];
+          int64_t c = ecost[e - w.e0], walk = 0;
           while (e_hi < w.e1 - left_parts && done + c < goal) { c += ecost[e_hi - w.e0]; e_hi++; }
           if (p == n_parts - 1) { while (e_hi < w.e1) { c += ecost[e_hi - w.e0]; e_hi++; } }
-          cut.push_back({{w.unit, w.tile, e, e_hi, out->n_pslots + p, w.blk_start, w.blk_len, w.moff}, c});
+          for (int32_t x = e; x < e_hi; x++) walk += walked(ecost[x - w.e0], r1 - r0);
+          cut.push_back({{w.unit, w.tile, e, e_hi, out->n_pslots + p, w.blk_start, w.blk_len, w.moff}, c, walk});
           done += c;
           e = e_hi;
         }
@@ -719,6 +730,7 @@ const HostItems& dcp_plan::host_items(int gid, int heads, int n_seg) {
   std::stable_sort(sc.begin(), sc.end(), [](const Scored& a, const Scored& b) { return a.cost > b.cost; });
   hi.size.parts = (int64_t)sc.size();
   hi.size.longest_part = sc.empty() ? 0 : sc[0].cost;
+  for (const Scored& x : sc) hi.size.walk_part = std::max(hi.size.walk_part, kItemRows * x.walk);
   if (heads > 0 && !sc.empty() && (gid == 2 || (!has_ranges && (int64_t)sc.size() * heads > kResidentWorkgroups / 8 * n_seg))) {
     // Sequence by sequence (the costliest sequence first, longest item first inside it) when that balances as well as
     // strict longest-first does.  Items of one sequence that run at the same time read the same rows of the other

@@ -261,6 +261,21 @@ def test_forms_of_small_and_large_batches(dtype, d):
         forms([300], 128, 3, 2)
 
 
+def test_forms_of_short_blocks():
+    """bf16, D 128, blocks of up to 64 rows: a workgroup of 32 rows walks such a block's table rows as long as a block of 128's, so that long
+    walks stay with the shared tiles, whose items are cut (measured, backward, shared tiles and split dK/dV: 177 and 329 us, 451 and
+    477), and short walks of few workgroups do not (one launch: 49 and 27 us, 31 and 20)."""
+    def forms(lens, B, hq, hkv, spec=W.MaskSpec("causal")):
+        cu = W.cu_from_lengths(lens)
+        plan = P.dcp_plan_create(cu, B, P.dcp_build_block_table(cu, B, W.attn_ranges(spec, cu)))
+        return P.dcp_plan_export_forms(plan, hq, hkv, 128, P.DCP_BF16)
+    for lens, hq, hkv, spec in [([5765], 8, 2, W.MaskSpec("lambda", window=635, sink=15)), ([1288] * 5, 32, 8, W.MaskSpec("causal"))]:
+        f = forms(lens, 64, hq, hkv, spec)
+        assert f["dkv"] == f["bwd"] == P.DCP_FORM_SHARED, (lens, f)
+    for lens, hq, hkv in [([256, 300, 250], 8, 8), ([391], 4, 1)]:
+        assert forms(lens, 64, hq, hkv)["bwd"] >= P.DCP_FORM_SPLIT, lens
+
+
 @pytest.mark.parametrize("window,sink", [(50, 0), (40, 7), (16, 16), (1, 0), (300, 3), (5, 400)])
 def test_window_table_and_pair_counts_bit_exact_vs_oracle(window, sink):
     rng = np.random.default_rng(29)
