@@ -17,8 +17,9 @@ static constexpr float kLazy = 8.f;  // rescale threshold, log2 units
 static constexpr int kFwdWaves = 4;   // waves per workgroup; the step's inline tile copies and QSplit are written for four
 
 // NQ: 32-query tiles per wave, which is 1 (QSplit).  It stays a parameter for the instruction schedule alone: with plain
-// members in place of arrays of one, the variant for per-token ranges spilled scalars and took 8.59 instead of 7.94 ms
-// (a 4 096-token window over 131 072 tokens; causal blockwise 2.66 and 2.75, the other variant the same).
+// members in place of arrays of one, the variant for per-token ranges took 8.59 instead of 7.94 ms when this was measured
+// (a 4 096-token window over 131 072 tokens; causal blockwise 2.66 and 2.75, the other variant the same).  Scalars that the two
+// variants park in vector lanes: 14 with ranges, 24 without.
 template <int NQ>
 struct FwdState {
   bf16x8 qf[NQ][8];
@@ -101,13 +102,17 @@ __device__ __forceinline__ void fwd_scores64(const FwdState<NQ>& st, const char*
 // Online softmax over the 64 keys of a tile and O^T += V^T P^T.  This is the only code that touches the output
 // accumulators: every kind of tile (fully visible, mask edge, half skipped) computes its scores on its own path and
 // joins here, so the accumulators never meet at a control-flow merge with different register assignments (which
-// costs a copy of all 64 of them, there and back, per tile).  There is no branch on which sub-tiles are active
-// either (a skipped one has scores -inf, so P = 0 and its MFMAs add nothing; for tables with per-token ranges this form
-// replaced one with a section per kind of tile, 9 984 -> 9 814 us forward and backward in the case named at KvIter::next): one straight block, in which the P.V
+// costs a copy of all 64 of them, there and back, per tile).  For tables with per-token ranges this form
+// replaced one with a section per kind of tile, 9 984 -> 9 814 us forward and backward in the case named at KvIter::next.
+// One straight block, in which the P.V
 // MFMAs of the first 32 keys are issued between the exponentials of the second 32 (the scheduling groups below say
 // so; exponentials are their own instruction class there).  NQ = 1.  v0_lds, v1_lds: the V rows of the first and second 32 keys.
+// two: the second 32 keys have weights other than 0.  A skipped half has scores -inf, so P = 0; without ranges (two = true) its MFMAs
+// run all the same and add nothing, with ranges the seen half comes first and the other's are left out: 0 x V would make NaN of
+// an Inf in rows that nothing sees, and blocks of 16 and 32 keys are half a tile each (6 174 tokens, 32/8 heads, blocks of 16, a window of
+// 812: 1 409 -> 1 332 us, 1 243 with a section per kind of tile).
 template <int NQ>
-__device__ __forceinline__ void fwd_softmax_pv(FwdState<NQ>& st, f32x16 (&s)[2][NQ], const char* v0_lds, const char* v1_lds, float c_log2) {
+__device__ __forceinline__ void fwd_softmax_pv(FwdState<NQ>& st, f32x16 (&s)[2][NQ], const char* v0_lds, const char* v1_lds, float c_log2, bool two) {
   static_assert(NQ == 1, "one query per lane");
   bf16x8 va[4];
 #pragma unroll
@@ -174,6 +179,7 @@ __device__ __forceinline__ void fwd_softmax_pv(FwdState<NQ>& st, f32x16 (&s)[2][
   }
   __builtin_amdgcn_sched_barrier(0);
   st.l[0] += sum0 + sum1;
+  if (!two) return;
   const bf16x8 p10 = pack_frag(s[1][0], 0), p11 = pack_frag(s[1][0], 1);
 #pragma unroll
   for (int dt = 0; dt < 4; dt++) vb[dt] = frag_tr(v1_lds, st.fa, 16, dt);
@@ -192,9 +198,6 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void mfma_fwd_kernel(DevGroup g,
   __shared__ __attribute__((aligned(1024))) char stage0[2 * kTileBytes];
   __shared__ __attribute__((aligned(1024))) char stage1[2 * kTileBytes];
   __shared__ int wg_bounds[kFwdWaves][8];
-  __shared__ __attribute__((aligned(1024))) char zero_rows[RANGES ? 32 * kRowBytes : 16];   // V of the keys of an unseen half tile
-  if (RANGES)
-    for (int x = threadIdx.x; x < 32 * kRowBytes / 16; x += 64 * kFwdWaves) *(uint4*)(zero_rows + 16 * x) = make_uint4(0, 0, 0, 0);
 
   int item, head_x;
   const int G = t.hq / t.hkv;
@@ -288,6 +291,7 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void mfma_fwd_kernel(DevGroup g,
     bool pv;
     const char* v0 = cur + kTileBytes;   // V of the first and the second 32 keys
     const char* v1 = v0 + 32 * kRowBytes;
+    bool two = true;
     const bool common = !RANGES || kind < 2 ? ks + 2 * kTN <= (kind ? min(c1, wq_lo + 1) : c1)
                                             : ks + 2 * kTN <= c1 && wrb.all_see(ks, ks + 2 * kTN);
     if (w_rows > 0 && common) {
@@ -311,28 +315,37 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void mfma_fwd_kernel(DevGroup g,
       const int cls0 = w_rows > 0 ? classify32(kind, ks, c1, wq_lo, wq_hi, wrb) : kSkip;
       const int cls1 = w_rows > 0 ? classify32(kind, ks + 32, c1, wq_lo, wq_hi, wrb) : kSkip;
       pv = cls0 != kSkip || cls1 != kSkip;
-      if (RANGES) {   // the weights 0 of an unseen half meet zeros: neither its V rows nor those of the seen half need be finite
-        v0 = cls0 == kSkip ? zero_rows : v0;
-        v1 = cls1 == kSkip ? zero_rows : v1;
-      }
       if (cls0 == kFull && cls1 == kFull) {
         fwd_scores64<NQ, false>(st, cur, s);
       } else if (pv) {
-#pragma unroll
-        for (int kt = 0; kt < 2; kt++) {
-          const int cls = kt ? cls1 : cls0;
-          if (cls != kSkip) {
-            fwd_scores32<NQ>(st, cur, kt, ks + 32 * kt, kind, c0, c1, lane, cls == kPartial, s[kt]);
+        if constexpr (RANGES) {   // the half that is seen comes first, and the other one's V rows meet nothing
+          const int first = cls0 != kSkip ? 0 : 1;
+          two = cls0 != kSkip && cls1 != kSkip;
+          v0 += first * 32 * kRowBytes;
+          fwd_scores32<NQ>(st, cur + first * 32 * kRowBytes, 0, ks + 32 * first, kind, c0, c1, lane, (first ? cls1 : cls0) == kPartial, s[0]);
+          if (two) {
+            fwd_scores32<NQ>(st, cur, 1, ks + 32, kind, c0, c1, lane, cls1 == kPartial, s[1]);
           } else {
 #pragma unroll
-            for (int nq = 0; nq < NQ; nq++)
+            for (int r = 0; r < 16; r++) s[1][0][r] = -INFINITY;
+          }
+        } else {
 #pragma unroll
-              for (int r = 0; r < 16; r++) s[kt][nq][r] = -INFINITY;
+          for (int kt = 0; kt < 2; kt++) {
+            const int cls = kt ? cls1 : cls0;
+            if (cls != kSkip) {
+              fwd_scores32<NQ>(st, cur, kt, ks + 32 * kt, kind, c0, c1, lane, cls == kPartial, s[kt]);
+            } else {
+#pragma unroll
+              for (int nq = 0; nq < NQ; nq++)
+#pragma unroll
+                for (int r = 0; r < 16; r++) s[kt][nq][r] = -INFINITY;
+            }
           }
         }
       }
     }
-    if (pv) fwd_softmax_pv<NQ>(st, s, v0, v1, c_log2);
+    if (pv) fwd_softmax_pv<NQ>(st, s, v0, v1, c_log2, !RANGES || two);
     DCP_WAIT_VMCNT(0);
     __syncthreads();  // the copy into `nxt` has landed and `cur` may be overwritten
   };

@@ -32,6 +32,23 @@ def test_unseen_tiles(d, heads, spec, window_rows):
     H.check(w, dict(out=out, lse=lse, dq=dq, dk=dk, dv=dv), ref, ("out", "lse", "dq", "dk", "dv"), f"walk D{d} {heads} {spec.kind}", by_row=("dv",))
 
 
+@pytest.mark.parametrize("B", [16, 32, 33])
+@pytest.mark.parametrize("spec,window_rows", [(W.MaskSpec("lambda", window=40, sink=9), False), (W.MaskSpec("window", window=24), True)], ids=["ranges", "window"])
+def test_half_tiles(B, spec, window_rows):
+    """D = 128, blocks of at most 33 rows: tiles of which a half has no key, or one."""
+    import paper_2510_10620_amd as P
+    w = W.custom_workload("half", [150, 97, 1], B, 64, 32, 128, "bf16", spec, seed=94, input_scale=0.5)
+    tensors, table = W.make_tensors(w), H.oracle_table(w)
+    ref = H.oracle_full(w, tensors, table)
+    t = table.copy()
+    if window_rows:
+        t[t[:, 2] == W.MASK_RANGES, 2] = W.MASK_WINDOW
+    g = H.GpuRun(w, tensors, t, window=(spec.window, spec.sink) if window_rows else None)
+    assert P.dcp_plan_export_forms(g.plan, 64, 32, 128, P.DCP_BF16)["fwd"] == P.DCP_FORM_SHARED
+    out, lse = g.forward()
+    H.check(w, dict(out=out, lse=lse), ref, ("out", "lse"), f"half tiles B{B} {spec.kind}")
+
+
 def test_values_in_an_unseen_half_of_a_tile():
     """D = 128: V rows that are not finite in 32 keys of a 64-key tile which a workgroup's 32 rows see nothing of, beside 32 that they see in part:
     the rows come out as without them, bit for bit (64 query rows and their keys at most 33 back: the first 32 keys are unseen)."""
