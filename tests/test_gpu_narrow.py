@@ -50,14 +50,15 @@ def test_narrow_slots_strides_and_empty_rows():
 
 
 @pytest.mark.parametrize("d", [32, 64])
-@pytest.mark.parametrize("n_items", [64, 65])
+@pytest.mark.parametrize("n_items,heads,form", [(64, (32, 16), 1), (65, (32, 16), 1), (65, (128, 128), 0)], ids=["split-64", "split-65", "shared"])
 @pytest.mark.parametrize("spec,window_rows", [(W.MaskSpec("causal"), False), (W.MaskSpec("lambda", window=50, sink=9), False),
                                               (W.MaskSpec("lambda", window=50, sink=9), True)], ids=["causal", "ranges", "window"])
-def test_narrow_dkv_on_both_sides_of_its_rule(d, n_items, spec, window_rows):
-    """Up to 1 024 (work item, KV head) pairs the dK/dV kernel takes 64 keys per workgroup in four groups of waves, above
-    that 128 keys in two: 64 and 65 items with 16 KV heads.  Sequences of 1 to 128 tokens beside one of 700."""
+def test_narrow_dkv_on_both_sides_of_the_choice(d, n_items, heads, form, spec, window_rows):
+    """dK/dV whose four waves split the other side, and the kernel that shares a tile among them (which takes launches of a great many items):
+    sequences of 1 to 128 tokens beside one of 700."""
+    import paper_2510_10620_amd as P
     lens = [700, 129, 128, 127, 65, 64, 33, 1] + [1 + 7 * i % 128 for i in range(n_items - 14)]
-    w = W.custom_workload("narrow_rule", lens, 128, 32, 16, d, "bf16", spec, seed=72, input_scale=0.5)
+    w = W.custom_workload("narrow_rule", lens, 128, heads[0], heads[1], d, "bf16", spec, seed=72, input_scale=0.5)
     assert sum(-(-n // 128) for n in lens) == n_items
     tensors, table = W.make_tensors(w), H.oracle_table(w)
     ref = H.oracle_full(w, tensors, table)
@@ -65,6 +66,8 @@ def test_narrow_dkv_on_both_sides_of_its_rule(d, n_items, spec, window_rows):
     if window_rows:
         t[t[:, 2] == W.MASK_RANGES, 2] = W.MASK_WINDOW
     g = H.GpuRun(w, tensors, t, window=(spec.window, spec.sink) if window_rows else None)
+    forms = P.dcp_plan_export_forms(g.plan, *heads, d, P.DCP_BF16)
+    assert forms["dkv"] == form and forms["bwd"] == P.DCP_FORM_SHARED
     out, lse = g.forward()
     dq, dk, dv = g.backward()
     H.check(w, dict(out=out, lse=lse, dq=dq, dk=dk, dv=dv), ref, ALL, f"narrow D{d} {n_items} items {spec.kind}")

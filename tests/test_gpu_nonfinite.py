@@ -93,12 +93,14 @@ def test_values_near_the_largest(dtype, d):
 
 
 @pytest.mark.parametrize("d", [32, 64])
-def test_inf_and_nan_in_a_large_narrow_batch(d):
-    """More than 1 024 (work item, KV head) pairs: the other form of the narrow dK/dV kernel."""
+@pytest.mark.parametrize("heads,form", [(16, 1), (128, 0)], ids=["split", "shared"])
+def test_inf_and_nan_in_a_large_narrow_batch(d, heads, form):
+    """dK/dV whose waves split the other side, and the kernel that shares a tile among them."""
     import torch
     import paper_2510_10620_amd as P
-    w = W.custom_workload("nonfinite_l", [700, 129] + [40] * 57, 128, 16, 16, d, "bf16", W.MaskSpec("causal"), seed=73, input_scale=0.5)
+    w = W.custom_workload("nonfinite_l", [700, 129] + [40] * 57, 128, heads, heads, d, "bf16", W.MaskSpec("causal"), seed=73, input_scale=0.5)
     tensors, table = W.make_tensors(w), H.oracle_table(w)
+    assert P.dcp_plan_export_forms(H.GpuRun(w, tensors, table).plan, heads, heads, d, P.DCP_BF16)["dkv"] == form
     fast, slow = H.GpuRun(w, tensors, table), H.GpuRun(w, tensors, table, impl=P.DCP_IMPL_SCALAR)
     for g in (fast, slow):
         g.v[40, 3, 1], g.v[650, 5], g.q[300, 7, 2], g.dout[820, 15, 9] = float("inf"), float("nan"), float("inf"), float("nan")

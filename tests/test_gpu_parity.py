@@ -41,6 +41,9 @@ SPECS = [W.MaskSpec("causal"), W.MaskSpec("window", window=200), W.MaskSpec("lam
          W.MaskSpec("causal_blockwise", window=2, sink=1, mblock=96), W.MaskSpec("shared_question")]
 
 
+CUT_DKV = {"causal": True, "window": False, "lambda": True, "causal_blockwise": False, "shared_question": True}
+
+
 @pytest.mark.parametrize("impl", list(IMPLS), ids=list(IMPLS))
 @pytest.mark.parametrize("spec", SPECS, ids=lambda s: s.kind)
 def test_small_bf16_all_masks(spec, impl):
@@ -49,9 +52,11 @@ def test_small_bf16_all_masks(spec, impl):
     g, _, _ = run_case(w, table, IMPLS[impl], label=f"{spec.kind}/{impl}")
     if impl == "auto":
         # the 1000-token sequence's key tiles are long items for so small a launch: the run above went through split
-        # dK/dV items, their fp32 partial sums and the reduce kernel
+        # dK/dV items, their fp32 partial sums and the reduce kernel, unless it took the waves that split the other side instead
         import paper_2510_10620_amd as P
         assert (P.dcp_plan_export_dkv_items(g.plan, w.hkv)[:, 4] >= 0).any()
+        forms = P.dcp_plan_export_forms(g.plan, w.hq, w.hkv, w.d, P.DCP_BF16)
+        assert (forms["dkv"] == forms["bwd"] == P.DCP_FORM_SHARED) == CUT_DKV[spec.kind]
 
 
 @pytest.mark.parametrize("impl", list(IMPLS), ids=list(IMPLS))
@@ -130,6 +135,20 @@ def test_items_around_64_rows_for_every_head_split(hq, hkv, d):
         w = W.custom_workload("items", [1, 63, 64, 65, 96, 97, 128, 129, 192, 193, 400], B, hq, hkv, d, "bf16", W.MaskSpec("causal"), seed=39,
                               input_scale=0.5)
         run_case(w, H.oracle_table(w), IMPLS["auto"], label=f"{hq}/{hkv} D{d} B{B}")
+
+
+@pytest.mark.parametrize("d", [128, 64, 32])
+@pytest.mark.parametrize("hq,hkv", [(64, 64), (64, 32), (96, 32), (128, 32)])
+def test_items_around_64_rows_with_many_heads(hq, hkv, d):
+    """The same with heads enough for the forward and dQ kernels that share their tiles, which divide an item among their waves so (the fewer
+    heads above mostly go to the kernels whose waves split the other side)."""
+    import paper_2510_10620_amd as P
+    for B in (64, 200):
+        w = W.custom_workload("items", [1, 63, 64, 65, 96, 97, 128, 129, 192, 193, 400], B, hq, hkv, d, "bf16", W.MaskSpec("causal"), seed=39,
+                              input_scale=0.5)
+        g, _, _ = run_case(w, H.oracle_table(w), IMPLS["auto"], label=f"{hq}/{hkv} D{d} B{B}")
+        forms = P.dcp_plan_export_forms(g.plan, hq, hkv, d, P.DCP_BF16)
+        assert forms["fwd"] == forms["dq"] == forms["bwd"] == P.DCP_FORM_SHARED
 
 
 def test_library_loaded_before_torch_touches_the_gpu():
