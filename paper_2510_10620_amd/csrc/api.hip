@@ -164,7 +164,7 @@ static const LaunchFits kFits[] = {
      {{6.6, 152, 1120, 52.6}, {5.9, 94.8, 1390, 26.6}}, {{}, {4.5, 109, 2975, 41.0}}}};
 static constexpr double kLaunchGap = 1.0;   // between two launches
 static constexpr double kSureShort = 0.8, kSureShort8 = 0.7;   // `sure` of dK/dV over short blocks with four and eight waves
-static bool short_blocks(const dcp_tensors_t* t, const LaunchSize& z) { return t->dtype == DCP_BF16 && t->d == 128 && z.rows <= 64; }
+static bool short_blocks(const dcp_tensors_t* t, const LaunchSize& z) { return t->dtype == DCP_BF16 && t->d == 128 && z.walk > 0; }
 
 static double launch_us(const LaunchFit& f, double longest, double total, double items) {
   return f.start + std::hypot(f.chain * longest * 1e-6, f.share * total / 512e6) + f.item * items / 512;

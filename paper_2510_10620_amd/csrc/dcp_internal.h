@@ -26,6 +26,7 @@ bool is_capturing(hipStream_t stream);
 
 // Rows of a work item, the same in every kernel family, so that they share the lists.
 static constexpr int kItemRows = 128;
+static constexpr int kShortBlock = 64;   // see LaunchSize
 
 // One piece of work: `unit` indexes a Group's units, `tile` is the tile number inside the unit's own block
 // (tile * kItemRows is the first row), [e0, e1) the table rows of the unit this piece covers (all of them, unless
@@ -98,10 +99,9 @@ struct GroupSize {
 struct LaunchSize {
   int64_t items = 0, longest = 0, total = 0;   // whole items, the costliest, all of them
   int64_t parts = 0, longest_part = 0;         // of the list as it is, which may hold cut items
-  // The same in pairs that are walked: the longest item and part (as if they had all 128 rows) and all items (rows in 32s), at least
-  // 32 rows of the other side for a table row.
+  // The same in pairs that are walked, where no block has more than kShortBlock rows (else 0): the longest item and part (as if they
+  // had all 128 rows) and all items (rows in 32s), at least 32 rows of the other side for a table row.
   int64_t walk = 0, walk_part = 0, walk_total = 0;
-  int32_t rows = 0;   // most own rows of an item
 };
 
 // Cost of an item in pairs, and rows of the other side that it walks, at least 32 for a table row.

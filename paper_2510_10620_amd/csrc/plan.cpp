@@ -624,7 +624,8 @@ const HostItems& dcp_plan::host_items(int gid, int heads, int n_seg) {
   struct Scored { WorkItem w; int64_t cost, walk; };
   std::vector<Scored> sc;
   std::vector<int64_t> ecost;   // per-entry costs of the item being built
-  auto walked = [](int64_t pairs, int64_t rows) { return pairs > 0 ? std::max<int64_t>(32, pairs / rows) : 0; };
+  const bool short_blocks = longest_block <= kShortBlock;   // only these are chosen by what they walk
+  auto walked = [&](int64_t pairs, int64_t rows) { return short_blocks && pairs > 0 ? std::max<int64_t>(32, pairs / rows) : 0; };
   // first pass: whole items and the total cost
   int64_t total = 0;
   const bool known = !item_cost[gid].empty();
@@ -653,11 +654,9 @@ const HostItems& dcp_plan::host_items(int gid, int heads, int n_seg) {
   hi.size.items = (int64_t)sc.size();
   hi.size.total = total;
   for (const Scored& x : sc) {
-    const int32_t rows = std::min(kItemRows, x.w.blk_len - x.w.tile * kItemRows);
     hi.size.longest = std::max(hi.size.longest, x.cost);
     hi.size.walk = std::max(hi.size.walk, kItemRows * x.walk);
-    hi.size.walk_total += (rows + 31) / 32 * 32 * x.walk;
-    hi.size.rows = std::max(hi.size.rows, rows);
+    hi.size.walk_total += (x.w.blk_len + 31) / 32 * 32 * x.walk;   // (short blocks are one item)
   }
   if (gid == 2 && heads > 0) {
     // Long items are cut, along their table rows, into parts (each with a slot of fp32 partial sums that a reduce
@@ -709,7 +708,7 @@ const HostItems& dcp_plan::host_items(int gid, int heads, int n_seg) {
           int64_t c = ecost[e - w.e0], walk = 0;
           while (e_hi < w.e1 - left_parts && done + c < goal) { c += ecost[e_hi - w.e0]; e_hi++; }
           if (p == n_parts - 1) { while (e_hi < w.e1) { c += ecost[e_hi - w.e0]; e_hi++; } }
-          for (int32_t x = e; x < e_hi; x++) walk += walked(ecost[x - w.e0], r1 - r0);
+          for (int32_t x = e; short_blocks && x < e_hi; x++) walk += walked(ecost[x - w.e0], r1 - r0);
           cut.push_back({{w.unit, w.tile, e, e_hi, out->n_pslots + p, w.blk_start, w.blk_len, w.moff}, c, walk});
           done += c;
           e = e_hi;
