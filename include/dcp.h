@@ -182,7 +182,8 @@ typedef enum {
 dcp_status_t dcp_plan_export(const dcp_plan_t* plan, dcp_export_t which, int32_t* dst_host,
                              int64_t capacity, int64_t* n_out);
 
-/* The dK/dV work list of the bf16 MFMA kernels for `hkv` KV heads, for bit-exact host checks: rows
+/* The cut dK/dV work list for `hkv` KV heads, for bit-exact host checks (bf16 with D = 128 uses it where dcp_plan_export_forms
+ * says SHARED for dK/dV; every other launch takes whole items): rows
  * (unit = kv_blk position in the BWDKV CSR, tile = 128-key tile of that block, e0, e1 = the CSR entries
  * [e0, e1) the piece covers, pslot).  An item that would keep one workgroup busy much longer than its
  * share of the launch is cut along its table rows into parts; each part has its own pslot >= 0 (a slot
@@ -387,7 +388,8 @@ dcp_status_t dcp_comm_volume(const int32_t* cu_seqlens_host, int32_t n_seq, int3
 
 /* Per-kernel timing for benchmarks.  While enabled, every kernel the library launches is
  * bracketed by hipEvents recorded on the launch stream (the kernels of one backward call are timed
- * one by one).  dcp_profile_read synchronises on the recorded events, returns the summed duration
+ * one by one; the one launch that small batches take for dQ and dK/dV together counts as DCP_K_DKV, and
+ * DCP_K_DQ has no launch then).  dcp_profile_read synchronises on the recorded events, returns the summed duration
  * and the number of launches of one kernel since the last enable, and leaves the records in place;
  * dcp_profile_enable(1) clears them.  Not thread-safe; meant for a single benchmarking thread. */
 typedef enum { DCP_K_FWD = 0, DCP_K_MERGE = 1, DCP_K_DELTA = 2, DCP_K_DQ = 3, DCP_K_DKV = 4, DCP_K_SUM = 5, DCP_K_COPY = 6 } dcp_kernel_id_t;

@@ -103,7 +103,8 @@ dcp_status_t mfma_f32_fwd(const DevGroup& g, const KTensors& t, int rows, hipStr
 dcp_status_t mfma_f32_dq(const DevGroup& g, const KTensors& t, int rows, hipStream_t s);
 dcp_status_t mfma_f32_dkv(const DevGroup& g, const KTensors& t, int rows, hipStream_t s);
 dcp_status_t mfma_f32_bwd(const DevGroup& gq, const DevGroup& gkv, const KTensors& t, hipStream_t s);
-dcp_status_t mfma_narrow_fwd(const DevGroup& g, const KTensors& t, hipStream_t s);   // the part of the three above for D < 128
+// the part of mfma_fwd, mfma_bwd_dq and mfma_bwd_dkv for bf16 with D < 128
+dcp_status_t mfma_narrow_fwd(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_narrow_dq(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_narrow_dkv(const DevGroup& g, const KTensors& t, hipStream_t s);
 // bf16 (any of these D), for launches that the others leave uneven or the chip half empty (kernels_mfma_split.hip): 4 or 8 waves

@@ -11,8 +11,9 @@
 // eight waves have room for with D = 128: an operand's next tile is requested as soon as its last product has read the current one
 // (K before the softmax, V before the next scores, ..); dK/dV with D < 128 has two stages (16 384 tokens, 16/4 heads, D 64:
 // 1 180 -> 1 110 us).  The partial results meet once, in fp32, in LDS.
-// Measured, shared kernels -> these: 1 508 tokens, 4/2 heads, D 128, forward / dQ / dK/dV 26 / 30 / 27 us -> 12 / 15 / 18; 4 528 tokens,
-// 4/1 heads, 31 / 39 / 83 -> 20 / 26 / 28; 7 866 tokens, 8/1 heads, D 64, 159 / 164 / 783 -> 94 / 110 / 377.
+// Measured, shared kernels -> these: 1 508 tokens, 4/2 heads, D 128, forward / dQ / dK/dV 26 / 30 / 27 us -> 12 / 15 / 18 (here
+// dK/dV stays with the first, see api.hip); 4 528 tokens, 4/1 heads, 31 / 39 / 83 -> 20 / 26 / 28; 7 866 tokens, 8/1 heads, D 64,
+// 159 / 164 / 783 -> 94 / 110 / 377.
 // dQ and dK/dV are one launch where both fit the chip at once, which spares a launch and its start (the dK/dV workgroups work
 // delta out for themselves, from O): 620 tokens, 4/2 heads, forward and backward 51 -> 28 us with two launches, 23 with one.
 #include "mfma_dkv_kernel.h"

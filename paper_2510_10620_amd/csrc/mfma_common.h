@@ -398,7 +398,7 @@ struct KvIter {
   // RANGES = false: the table has no RANGES row (nothing of the range machinery is compiled in).
   // rb has to be uniform for the compiler too (RangeBounds::wave_reduce, and no path on which it is still a lane's): one value of
   // it that could be a lane's, and every branch of the walk and of the steps runs on the vector unit under an execution mask.
-  // 131 072 tokens, mask blocks of 256 with a window of two and a sink, forward and backward: 10 537 -> 9 622 us with that, the
+  // 131 072 tokens, mask blocks of 256 with a window of two and a sink, forward and backward: 10 543 -> 9 608 us with that, the
   // jump over unseen tiles and the joined forward step.
   template <bool RANGES>
   __device__ bool next(int q_hi, const RangeBounds& rb) {

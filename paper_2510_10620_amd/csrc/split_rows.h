@@ -1,5 +1,6 @@
 // Workgroups that split the other side: their waves own the SAME 32 rows (queries in the forward and dQ, keys in dK/dV), take
-// every eighth 32-row tile of the other side and meet once, in LDS, at the end (kernels_mfma_f32.hip, kernels_mfma_split.hip).
+// every NW-th 32-row tile of the other side (NW = 4 or 8 waves) and meet once, in LDS, at the end (kernels_mfma_f32.hip, eight waves and
+// 32 or 16 rows; kernels_mfma_split.hip).
 #pragma once
 #include "device_utils.h"
 #include "mfma_common.h"
