@@ -142,7 +142,8 @@ static bool rows_are_faster(const dcp_plan_t* plan, const dcp_tensors_t* t, bool
 // rows and walks such an item as long as one of 128 rows.  Counted as visible pairs, its dK/dV was estimated at 0.6 of its time: 5 765
 // tokens, 8/2 heads, blocks of 64, backward 177 us with shared tiles and 329 in the form that was taken.  Shared tiles take 0.85 of
 // their estimate there (the waves without rows leave their issue slots to the CU's other workgroup), hence
-// kSureShort.  149 batches with blocks of 16 to 64: 34 were slower than with shared tiles alone by more than 3 %, up to 1.81 times; now 8 are, up to 1.13 (blocks of 64: 1.07).
+// kSureShort.  149 batches with blocks of 16 to 64: 34 were slower than with shared tiles alone by more than 3 %, up to 1.81 times; now
+// 8 are, up to 1.13 (blocks of 64: 1.07).
 // Per-token ranges, whose pairs are a guess (windows of 32 to 4 096, sinks, mask blocks, shared questions; blocks of 64 to 4 096), measured over
 // 251 batches of all types: forward 0.63 to 0.96, backward 0.58 to 0.75 of the time of the first kind alone, single calls up to 1.05 of it.
 struct LaunchFit { double start, chain, share, item; };
