@@ -192,6 +192,13 @@ def dcp_plan_export_forms(plan, hq, hkv, d, dtype_code):
     return dict(zip(("fwd", "dq", "dkv", "bwd"), forms))
 
 
+def dcp_plan_export_part_groups(plan, hq, hkv, d):
+    """(forward, dQ): groups of waves, 1 or 2 (several), of the fp32 kernels of form SHARED with D < 128."""
+    groups = (ctypes.c_int32 * 2)()
+    _check(_lib.load().dcp_plan_export_part_groups(plan.handle, hq, hkv, d, groups))
+    return tuple(groups)
+
+
 # ------------------------------------------------------------------ launching calls (torch)
 def _dtype_code(t):
     import torch

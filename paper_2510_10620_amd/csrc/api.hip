@@ -126,7 +126,8 @@ static bool rows_are_faster(const dcp_plan_t* plan, const dcp_tensors_t* t, bool
 }
 
 // Which of the MFMA kernels a launch takes.  bf16: those that share a tile among the waves of a workgroup, or those whose four or
-// eight waves split the other side (kernels_mfma_split.hip); fp32: 32 or 16 rows a workgroup.  The first kind streams least from the
+// eight waves split the other side (kernels_mfma_split.hip); fp32: 32 rows a wave in bf16 parts
+// (D 128: 32 rows a workgroup) or 16 rows a workgroup on the fp32 pipe.  The first kind streams least from the
 // L2 and wins where the chip is full of equal work; the second finishes a long walk several times sooner and wins where a launch
 // has few items or waits for its longest: bf16, 5 196 tokens, 16/4 heads, blocks of 4 096, dK/dV 374 and 130 us; 4 528 tokens, 4/1
 // heads, forward 31 and 20; 65 536 tokens, 32/8 heads, forward 2.6 and 5.3 ms; fp32, 1 723 tokens, one head of 64, dK/dV 70 and 44 us,
@@ -146,9 +147,13 @@ static bool rows_are_faster(const dcp_plan_t* plan, const dcp_tensors_t* t, bool
 // 8 are, up to 1.13 (blocks of 64: 1.07).
 // Per-token ranges, whose pairs are a guess (windows of 32 to 4 096, sinks, mask blocks, shared questions; blocks of 64 to 4 096), measured over
 // 251 batches of all types: forward 0.63 to 0.96, backward 0.58 to 0.75 of the time of the first kind alone, single calls up to 1.05 of it.
+// fp32 with D 32 and 64: fitted to 297 batches of 100 to 16 384 tokens (148 with D 32), blocks of 64 to 2 048, and then moved within what the
+// times allow until the choices cost least; against the choice between 32 and 16 rows on the fp32 pipe that was there before: 0.91 and
+// 0.92 of the time on average (forward and backward), 2 and 5 batches slower by more than 3 %, up to 1.05 and 1.14 (the least that any
+// choice could reach: 0.90 and 0.89).
 struct LaunchFit { double start, chain, share, item; };
-// bf16: shared tiles, four waves, eight waves; fp32: 32 rows, 16 rows; kRows: the thread-per-row kernels
-enum { kRows = DCP_FORM_ROWS, kShared = DCP_FORM_SHARED, kSplit = DCP_FORM_SPLIT, kSplit8 = DCP_FORM_SPLIT8, kForms };
+// bf16: shared tiles, four waves, eight waves; fp32: 32 rows, 16 rows and, with D < 128, 32 rows with one group of waves (kFull); kRows: the thread-per-row kernels
+enum { kRows = DCP_FORM_ROWS, kShared = DCP_FORM_SHARED, kSplit = DCP_FORM_SPLIT, kSplit8 = DCP_FORM_SPLIT8, kForms, kFull = kSplit8 };
 struct LaunchFits { int32_t dtype, d; double sure; LaunchFit fwd[kForms], dq[kForms], dkv[kForms], bwd[kForms]; };   // bwd: dQ and dK/dV in one launch
 static const LaunchFits kFits[] = {
     {DCP_BF16, 128, 0.9, {{7.0, 128, 253, 5.7}, {5.0, 53.5, 373, 18.9}, {5.3, 30.1, 380, 41.1}}, {{7.3, 167, 335, 7.5}, {6.6, 50.4, 428, 29.6}, {7.8, 28.9, 433, 62.8}},
@@ -159,10 +164,10 @@ static const LaunchFits kFits[] = {
      {{10.7, 180, 394, 11.3}, {6.1, 70.2, 341, 10.9}, {6.2, 43.3, 358, 19.8}}, {{}, {6.1, 80.7, 655, 11.7}, {4.5, 42.0, 779, 33.2}}},
     {DCP_F32, 128, 0.85, {{9.6, 223, 2220, 82.9}, {7.6, 151, 2810, 32.9}}, {{13.9, 314, 3240, 120}, {9.9, 248, 4860, 40.2}},
      {{15.9, 448, 3710, 183}, {10.8, 274, 4960, 89.9}}, {{}, {11.4, 364, 11050, 76.4}}},
-    {DCP_F32, 64, 0.87, {{6.9, 125, 1180, 41.4}, {5.4, 88.9, 1300, 31.5}}, {{8.7, 174, 1640, 54.4}, {6.3, 144, 2160, 38.8}},
-     {{12.5, 252, 1990, 61.7}, {8.1, 164, 2310, 31.5}}, {{}, {8.6, 170, 5574, 51.4}}},
-    {DCP_F32, 32, 0.86, {{5.1, 70.8, 573, 21.1}, {4.8, 42.8, 748, 23.3}}, {{5.8, 97.3, 789, 24.6}, {4.8, 71.1, 1130, 27.4}},
-     {{6.6, 152, 1120, 52.6}, {5.9, 94.8, 1390, 26.6}}, {{}, {4.5, 109, 2975, 41.0}}}};
+    {DCP_F32, 64, 0.9, {{11.3, 271, 524, 16.7}, {7.47, 111, 1800, 25.7}, {12.2, 422, 499, 9.18}}, {{16.1, 418, 1040, 8.69}, {6.34, 240, 3130, 28.1}, {12.1, 523, 850, 7.12}},
+     {{12.1, 224, 1610, 54.8}, {10.4, 197, 2070, 21.2}}, {{}, {7.35, 215, 7090, 45.4}}},
+    {DCP_F32, 32, 0.9, {{8.42, 161, 537, 11.8}, {6.36, 66.3, 846, 23.7}, {10.3, 315, 367, 4.61}}, {{10.6, 146, 553, 24.7}, {7.79, 81.5, 1350, 17.2}, {10.7, 422, 447, 5.48}},
+     {{9.67, 134, 729, 17.1}, {7.82, 119, 2620, 17.3}}, {{}, {9.23, 141, 2920, 33}}}};
 static constexpr double kLaunchGap = 1.0;   // between two launches
 static constexpr double kSureShort = 0.8, kSureShort8 = 0.7;   // `sure` of dK/dV over short blocks with four and eight waves
 static bool short_blocks(const dcp_tensors_t* t, const LaunchSize& z) { return t->dtype == DCP_BF16 && t->d == 128 && z.walk > 0; }
@@ -190,11 +195,26 @@ static int least_form(double sure, double sure8, const dcp_tensors_t* t, const d
   return best;
 }
 
+// fp32 with D < 128: kShared are the kernels that multiply in bf16 parts; forward and dQ have one group of waves a workgroup (kFull) or
+// several, whichever is estimated faster.
+static bool in_parts(const dcp_tensors_t* t) { return t->dtype == DCP_F32 && t->d < 128; }
+static int part_groups(const LaunchFit* f, const dcp_tensors_t* t, const LaunchSize& z) {
+  const double longest = (double)z.longest, total = (double)z.total * t->hq, items = (double)z.items * t->hq;
+  return launch_us(f[kFull], longest, total, items) < launch_us(f[kShared], longest, total, items) ? 1 : 2;
+}
+// of a forward (gid 0) or dQ (1) of form kShared
+static int part_groups(dcp_plan_t* plan, const dcp_tensors_t* t, int gid) {
+  const LaunchSize& z = plan->host_items(gid, t->hq / t->hkv, xcd_segments(t->hkv)).size;
+  const LaunchFits* f = fits_of(t, z);
+  return f ? part_groups(gid ? f->dq : f->fwd, t, z) : 1;
+}
+
 static int pick_q(const LaunchFits& fits, const LaunchFit* f, const dcp_tensors_t* t, const LaunchSize& z, double* us) {
   double x[kForms];
   const bool walked = short_blocks(t, z);
   const double longest = (double)(walked ? z.walk : z.longest), total = (double)(walked ? z.walk_total : z.total) * t->hq;
   for (int v = kShared; v <= last_form(t); v++) x[v] = launch_us(f[v], longest, total, (double)z.items * t->hq);
+  if (in_parts(t)) x[kShared] = std::min(x[kShared], launch_us(f[kFull], longest, total, (double)z.items * t->hq));
   return least_form(fits.sure, fits.sure, t, x, us);
 }
 
@@ -341,7 +361,10 @@ extern "C" dcp_status_t dcp_block_attn_fwd(dcp_plan_t* plan, const dcp_tensors_t
   KTensors k = pack(plan, t);
   ProfScope ps(DCP_K_FWD, s);
   if (form == kRows) return scalar_fwd(g, k, t->dtype, s);
-  if (form == kShared) return mfma_fwd(g, k, s);
+  if (form == kShared) {
+    if (in_parts(t)) k.part_groups = part_groups(plan, t, 0);
+    return mfma_fwd(g, k, s);
+  }
   return t->dtype == DCP_F32 ? mfma_f32_fwd(g, k, 16, s) : mfma_split_fwd(g, k, waves_of(form), s);
 }
 
@@ -445,6 +468,16 @@ extern "C" dcp_status_t dcp_plan_export_forms(dcp_plan_t* plan, int32_t hq, int3
   return DCP_OK;
 }
 
+extern "C" dcp_status_t dcp_plan_export_part_groups(dcp_plan_t* plan, int32_t hq, int32_t hkv, int32_t d, int32_t* groups) {
+  if (!plan || !groups) return fail(DCP_ERR_INVALID_ARG, "plan or groups is NULL");
+  dcp_tensors_t t{};
+  t.hq = hq; t.hkv = hkv; t.d = d; t.dtype = DCP_F32; t.softmax_scale = 1.f;
+  const dcp_status_t st = check_shape(&t);
+  if (st != DCP_OK) return st;
+  for (int gid = 0; gid < 2; gid++) groups[gid] = in_parts(&t) ? part_groups(plan, &t, gid) : 0;
+  return DCP_OK;
+}
+
 extern "C" size_t dcp_bwd_workspace_bytes(const dcp_plan_t* plan, int32_t hq, int32_t hkv, int32_t d, int32_t dtype) {
   if (!plan || hq <= 0) return 0;
   // the work lists are cached in the plan the first time a size or a launch asks for them
@@ -516,7 +549,10 @@ dcp_status_t dcp::bwd_launch(dcp_plan_t* plan, const dcp_tensors_t* t, void* wor
   {
     ProfScope ps(DCP_K_DQ, s, may_alloc);
     if (form.dq == kRows) st = scalar_bwd_dq(gq, k, t->dtype, s);
-    else if (form.dq == kShared) st = mfma_bwd_dq(gq, k, s);
+    else if (form.dq == kShared) {
+      if (in_parts(t)) k.part_groups = part_groups(plan, t, 1);
+      st = mfma_bwd_dq(gq, k, s);
+    }
     else st = t->dtype == DCP_F32 ? mfma_f32_dq(gq, k, 16, s) : mfma_split_dq(gq, k, waves_of(form.dq), s);
     if (st != DCP_OK) return st;
   }

@@ -24,6 +24,7 @@ struct KTensors {
   int32_t dtype;           // dcp_dtype_t
   float scale;
   int32_t use_slots;
+  int32_t part_groups;     // forward and dQ in fp32 with D < 128, 32 rows a wave: groups of waves a workgroup, 1 or 2 (several)
 };
 
 #ifdef __HIPCC__
@@ -90,7 +91,7 @@ dcp_status_t scalar_bwd_dq(const DevGroup& g, const KTensors& t, int32_t dtype, 
 dcp_status_t scalar_bwd_dkv(const DevGroup& g, const KTensors& t, int32_t dtype, hipStream_t s);
 
 // MFMA family: bf16 with D = 128 (kernels_mfma_fwd / dq / dkv) and D in {32, 64} (kernels_mfma_narrow), fp32 with D in
-// {32, 64, 128} (kernels_mfma_f32)
+// {32, 64, 128} (kernels_mfma_f32, kernels_mfma_f32_parts)
 bool mfma_supports(int32_t dtype, int32_t d);
 // the dK/dV kernel takes cut work items (KTensors::part)
 inline bool mfma_splits_dkv(int32_t dtype, int32_t d) { return dtype == DCP_BF16 && d == 128; }
@@ -98,11 +99,15 @@ size_t mfma_dkv_part_bytes(int32_t n_pslots, int32_t hkv);   // size of KTensors
 dcp_status_t mfma_fwd(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_bwd_dq(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_bwd_dkv(const DevGroup& g, const KTensors& t, hipStream_t s);
-// fp32, 32 or 16 rows per workgroup; f32_bwd is dQ and dK/dV in one launch (16 rows)
+// fp32, 32 (D = 128) or 16 rows per workgroup; f32_bwd is dQ and dK/dV in one launch (16 rows)
 dcp_status_t mfma_f32_fwd(const DevGroup& g, const KTensors& t, int rows, hipStream_t s);
 dcp_status_t mfma_f32_dq(const DevGroup& g, const KTensors& t, int rows, hipStream_t s);
 dcp_status_t mfma_f32_dkv(const DevGroup& g, const KTensors& t, int rows, hipStream_t s);
 dcp_status_t mfma_f32_bwd(const DevGroup& gq, const DevGroup& gkv, const KTensors& t, hipStream_t s);
+// the part of mfma_fwd, mfma_bwd_dq and mfma_bwd_dkv for fp32 with D < 128
+dcp_status_t mfma_f32_parts_fwd(const DevGroup& g, const KTensors& t, hipStream_t s);
+dcp_status_t mfma_f32_parts_dq(const DevGroup& g, const KTensors& t, hipStream_t s);
+dcp_status_t mfma_f32_parts_dkv(const DevGroup& g, const KTensors& t, hipStream_t s);
 // the part of mfma_fwd, mfma_bwd_dq and mfma_bwd_dkv for bf16 with D < 128
 dcp_status_t mfma_narrow_fwd(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_narrow_dq(const DevGroup& g, const KTensors& t, hipStream_t s);

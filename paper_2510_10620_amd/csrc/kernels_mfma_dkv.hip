@@ -78,7 +78,7 @@ dcp_status_t mfma_range_bounds(const DevGroup& g, const KTensors& t, const int32
 
 dcp_status_t mfma_bwd_dkv(const DevGroup& g, const KTensors& t, hipStream_t s) {
   if (g.n_items == 0) return DCP_OK;
-  if (t.dtype == DCP_F32) return mfma_f32_dkv(g, t, 32, s);
+  if (t.dtype == DCP_F32) return t.d < 128 ? mfma_f32_parts_dkv(g, t, s) : mfma_f32_dkv(g, t, 32, s);
   if (t.d != kD) return mfma_narrow_dkv(g, t, s);
   const int grid = xcd_grid(g, t.hkv, 1);
   if (t.masked) hipLaunchKernelGGL(mfma_dkv_kernel<true>, dim3(grid), dim3(256), 0, s, g, t);

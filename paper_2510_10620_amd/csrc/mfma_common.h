@@ -479,16 +479,20 @@ __device__ __forceinline__ bool decode_wg(const DevGroup& g, int heads_outer, in
 // lengths (median 2 048) 2 605 -> 2 583, 3 537 -> 3 503.  Items of at most 64 rows keep 128 rows of one head: with HP = 4 half
 // or three quarters of their workgroups would have no row and cost their launch all the same (32/8 heads, HP = 4 -> 1: 1 000
 // sequences of 20 tokens, forward 390 -> 340 us; 4 096 tokens in blocks of 32, 919 -> 816).
-struct QSplit {
+// RG: waves that have different rows (or heads), four; two take gcd(G, 2) heads x 64 / HP rows, twice the workgroups.
+template <int RG>
+struct QSplitT {
   int head, row0, rows, wrow0;   // the wave's head; the workgroup's first row and row count inside the block; the wave's first of them
-  __device__ __forceinline__ QSplit(int item_tile, int blk_len, int head_x, int G, int wave) {
-    const int sh = blk_len - item_tile * 128 <= 64 || (G & 1) ? 0 : (G & 3) ? 1 : 2, hp = 1 << sh;
-    const int hk = head_x / G, x = head_x - hk * G;
-    rows = 128 >> sh;
-    row0 = item_tile * 128 + (x & (hp - 1)) * rows;
-    head = hk * G + (x & ~(hp - 1)) + (wave & (hp - 1));
+  static constexpr int PARTS = 4 / RG;   // workgroups per item and query head
+  __device__ __forceinline__ QSplitT(int item_tile, int blk_len, int head_x, int G, int wave) {
+    const int sh = blk_len - item_tile * 128 <= 64 || (G & 1) ? 0 : (G & 3) || RG == 2 ? 1 : 2, hp = 1 << sh, n = hp * PARTS;
+    const int hk = head_x / (G * PARTS), x = head_x - hk * (G * PARTS);
+    rows = 32 * RG >> sh;
+    row0 = item_tile * 128 + (x & (n - 1)) * rows;
+    head = hk * G + x / n * hp + (wave & (hp - 1));
     wrow0 = (wave >> sh) * 32;
   }
 };
+typedef QSplitT<4> QSplit;
 
 }  // namespace dcp

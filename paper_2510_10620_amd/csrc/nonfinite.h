@@ -137,6 +137,47 @@ __device__ void fix_out(const DevGroup& g, const KTensors& t, const FixRow& f, i
   put_row<T, D>(dst, acc, 1.f, lane);
 }
 
+// The same for a row whose scores were not all worked out from what the inputs are (fp32 in parts: an Inf leaves NaN in the parts of its
+// number): its maximum, its sum and its LSE too.  Exponents are differences of scores, as in the kernel, so that scores of any size do.
+template <typename T, int D>
+__device__ void fix_scores_and_out(const DevGroup& g, const KTensors& t, const FixRow& f, int hk, const T* q, T* dst, float* lse) {
+  const int lane = threadIdx.x & 63;
+  const float c_log2 = t.scale * 1.44269504088896340736f;
+  const T* kb = (const T*)t.k + (int64_t)hk * t.k_sh;
+  const T* vb = (const T*)t.v + (int64_t)hk * t.v_sh;
+  float mx = -INFINITY, l = 0.f, m_use = 0.f, inv = 0.f, acc[(D + 63) / 64] = {};
+  for (int pass = 0; pass < 3; pass++) {   // maximum, sum, weights times V
+    for (int e = f.e0; e < f.e1; e++) {
+      const int c0 = uni(g.ent_start[e]), c1 = c0 + uni(g.ent_len[e]), kind = uni(g.ent_kind[e]), moff = uni(g.ent_moff[e]);
+      for (int j0 = c0; j0 < c1; j0 += 64) {
+        const int j = j0 + lane;
+        const bool vis = j < c1 && key_visible(kind, f.qi, j, f.qr);
+        const uint64_t on = __ballot(vis);
+        if (!on) continue;
+        const float s = vis ? dot_row<T, D>(q, kb + (int64_t)(j + moff) * t.k_st) : -INFINITY;
+        const float p = vis ? __builtin_amdgcn_exp2f((s - m_use) * c_log2) : 0.f;
+        if (pass == 0) mx = fmaxf(mx, s);
+        else if (pass == 1) l += p;
+        else add_rows<T, D>(acc, p * inv, on, vb + (int64_t)(j0 + moff) * t.v_st, t.v_st, lane);
+      }
+    }
+#pragma unroll
+    for (int x = 32; x > 0; x >>= 1) {
+      if (pass == 0) mx = fmaxf(mx, __shfl_xor(mx, x));
+      else if (pass == 1) l += __shfl_xor(l, x);
+    }
+    if (pass == 0) m_use = mx == -INFINITY ? 0.f : mx;
+    if (pass == 1) inv = l > 0.f ? 1.f / l : 0.f;
+    if (pass == 1 && l != l) {   // a NaN score
+#pragma unroll
+      for (int k = 0; k < (D + 63) / 64; k++) acc[k] = l;
+      break;
+    }
+  }
+  if (lane == 0) *lse = l > 0.f ? (mx * c_log2 + __builtin_amdgcn_logf(l)) * 0.69314718055994530942f : -INFINITY;
+  put_row<T, D>(dst, acc, 1.f, lane);
+}
+
 // dQ of the row, which is 0 for a row that is off (lse2 = +inf)
 template <typename T, int D>
 __device__ void fix_dq(const DevGroup& g, const KTensors& t, const FixRow& f, int hk, const T* q, const T* dout, float lse2, float delta, T* dst) {

@@ -23,6 +23,29 @@ struct TileLayout {
   }
 };
 
+// Fragment addresses from two registers: every other one is an XOR of these with a constant.
+template <int D>
+struct Frags {
+  typedef TileLayout<D> L;
+  int rm, tr;
+  __device__ __forceinline__ void init(int lane) {
+    rm = L::off(lane & 31, lane >> 5);
+    const int j = lane & 15, blk = lane >> 4, col = 16 * (blk & 1) + 4 * (j & 3);
+    tr = L::off(4 * (blk >> 1) + (j >> 2), col >> 3) + (col & 7) * 2;
+  }
+  __device__ __forceinline__ bf16x8 rows(const char* tile, int ks) const { return as_frag(*(const uint4*)(tile + (rm ^ (ks << 5)))); }
+  // rows 16 c + 8a + 4h + b, columns 32 dt + lane % 32
+  __device__ __forceinline__ bf16x8 cols(const char* tile, int c, int dt) const {
+    typedef __attribute__((address_space(3))) s16x4* lds_p;
+    const int a0 = tr ^ (dt << 6), a1 = a0 ^ (8 / L::RPL * 256 + 0x20);
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_p)(tile + c * 16 * L::kRow + a0));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_p)(tile + c * 16 * L::kRow + a1));
+    s16x8 v;
+    v[0] = lo[0]; v[1] = lo[1]; v[2] = lo[2]; v[3] = lo[3]; v[4] = hi[0]; v[5] = hi[1]; v[6] = hi[2]; v[7] = hi[3];
+    return __builtin_bit_cast(bf16x8, v);
+  }
+};
+
 // Registers 8c .. 8c + 7 of a C tile as three bf16 operands that add up to the values exactly: 8 significant bits each, cut
 // off (not rounded: a finite value has finite parts), the remainders being exact in fp32.
 __device__ __forceinline__ void pack_split(const f32x16& s, int c, bf16x8 (&part)[3]) {
