@@ -315,6 +315,7 @@ static KTensors pack(const dcp_plan_t* plan, const dcp_tensors_t* t) {
   k.hq = t->hq; k.hkv = t->hkv; k.d = t->d; k.dtype = t->dtype; k.block_size = plan->block_size;
   k.scale = t->softmax_scale;
   k.use_slots = plan->use_slots ? 1 : 0;
+  k.by_head = plan->kv_by_head ? 1 : 0;
   return k;
 }
 

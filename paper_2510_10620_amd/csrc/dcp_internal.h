@@ -130,6 +130,7 @@ struct dcp_plan {
   int32_t n_seq = 0, block_size = 0, n_blocks = 0, n_slots = 0, longest_block = 0;
   int64_t total_tokens = 0, n_kept = 0;
   bool use_slots = false, has_ranges = false, has_window = false;
+  bool kv_by_head = false;   // most dK/dV rows are in units that rotate_units has put in order and that have more than three
   int32_t window = 0, sink = 0;   // parameters of the WINDOW rows (window 0: not set)
   // block buffers: slot of every block in the Q-type and the KV-type buffer (-1: absent), rows per buffer
   bool buffers = false;

@@ -81,8 +81,9 @@ dcp_status_t mfma_bwd_dkv(const DevGroup& g, const KTensors& t, hipStream_t s) {
   if (t.dtype == DCP_F32) return t.d < 128 ? mfma_f32_parts_dkv(g, t, s) : mfma_f32_dkv(g, t, 32, s);
   if (t.d != kD) return mfma_narrow_dkv(g, t, s);
   const int grid = xcd_grid(g, t.hkv, 1);
-  if (t.masked) hipLaunchKernelGGL(mfma_dkv_kernel<true>, dim3(grid), dim3(256), 0, s, g, t);
-  else hipLaunchKernelGGL(mfma_dkv_kernel<false>, dim3(grid), dim3(256), 0, s, g, t);
+  if (t.masked && t.by_head) hipLaunchKernelGGL((mfma_dkv_kernel<true, true>), dim3(grid), dim3(256), 0, s, g, t);
+  else if (t.masked) hipLaunchKernelGGL((mfma_dkv_kernel<true, false>), dim3(grid), dim3(256), 0, s, g, t);
+  else hipLaunchKernelGGL((mfma_dkv_kernel<false, false>), dim3(grid), dim3(256), 0, s, g, t);
   DCP_HIP_TRY(hipGetLastError());
   if (g.n_reduce > 0) {
     hipLaunchKernelGGL(dkv_reduce_kernel, dim3(g.n_reduce, t.hkv, 16), dim3(256), 0, s, g, t);

@@ -15,12 +15,12 @@ static constexpr int kStageRanges = kStageDelta + 256;
 static constexpr int kStageBounds = kStageRanges + 1024;   // range bounds of the tile's two 32-row halves (2 x 8 ints; 1 KB reserved)
 static constexpr int kStageBytes = kStageBounds + 1024;
 
-// Walks (table row, query head of the group, 64-query tile) for one KV tile.
-template <bool RANGES>
+// Walks (table row, query head of the group, 64-query tile) for one KV tile; BY_HEAD: (query head, table row, tile).
+template <bool RANGES, bool BY_HEAD = false>
 struct QIter {
   const int4* rec;       // per table row: {first query, length, mask kind, memory offset of the Q block}, {first 32-row tile, ..}
   const int4* qbounds;   // RANGES: range-bound summaries per 32-row tile
-  int e, e_end, hh, G, jt, n_t, jt0;
+  int e, e_end, e_top, hh, G, jt, n_t, jt0;
   int q0, q1, kind;
   int moff;  // the Q block's rows sit at (packed index + moff) in the Q-type buffers
   int t32;   // index of the Q block's first 32-row tile in qbounds
@@ -31,7 +31,7 @@ struct QIter {
   // start at its own diagonal, two steps behind its neighbour, which is as far apart as the L2 is large.
   __device__ QIter(const DevGroup& g, int e0, int e1, int G_, const int32_t* qb)
       : rec((const int4*)g.ent_rec), qbounds((const int4*)qb) {
-    e = e1; e_end = e0; hh = G_ - 1; G = G_; jt = 0; n_t = 0; jt0 = 0; q0 = q1 = kind = 0; moff = 0; t32 = 0; qs = 0;
+    e = e_top = e1; e_end = e0; hh = BY_HEAD ? 0 : G_ - 1; G = G_; jt = 0; n_t = 0; jt0 = 0; q0 = q1 = kind = 0; moff = 0; t32 = 0; qs = 0;
   }
   // Which of the (at most 64) 64-query tiles of the current RANGES row may see a key of [k_lo, k_end): lane l merges
   // the bounds of the two 32-row halves of tile l.  Returns the ballot (wave-uniform).
@@ -57,11 +57,17 @@ struct QIter {
     for (;;) {
       jt--;
       if (jt < jt0) {
-        hh++;
-        if (hh >= G) {
-          e--;
-          if (e < e_end) return false;
+        bool row = true;   // a new row
+        if (BY_HEAD) {
+          if (--e < e_end) {
+            if (++hh >= G || e_top == e_end) return false;
+            e = e_top - 1;
+          }
+        } else if ((row = ++hh >= G)) {
+          if (--e < e_end) return false;
           hh = 0;
+        }
+        if (row) {
           const int4 r = plan_load(rec, 2 * e);
           q0 = uni(r.x); q1 = q0 + uni(r.y); kind = uni(r.z); moff = uni(r.w); t32 = uni(plan_load(rec, 2 * e + 1).x);
           n_t = (q1 - q0 + kTN - 1) / kTN;
@@ -226,7 +232,12 @@ __device__ __forceinline__ void dkv_subtile(DkvState& st, const char* stage, int
 
 // RANGES = false: the table has no row with per-token ranges (RANGES or WINDOW); everything that serves them is
 // compiled out.  Two workgroups per CU: at most 256 registers.
-template <bool RANGES>
+// BY_HEAD (tables with per-token ranges whose key blocks see several neighbouring query blocks, as under a window): the heads are the outer
+// loop, so that workgroups that run together, walking the rows in the order of rotate_units (plan.cpp), are a few steps apart at any time
+// and not a few steps times the heads.  A 4 096-token window over 131 072 tokens, 32/8 heads: the order of the rows alone 17.3 -> 15.9 ms,
+// with the heads outside 15.5, and 63.6 -> 35.4 (in units of the same counter) fetched.  Tables whose key blocks see two or three query
+// blocks keep the rows outside: the look at a row's bounds for every head costs what this gains (mask blocks of 256, 4.25 and 4.39 ms).
+template <bool RANGES, bool BY_HEAD>
 __global__ __launch_bounds__(256, 2) void mfma_dkv_kernel(DevGroup g, KTensors t) {
   constexpr int TK = 128;
   __shared__ __attribute__((aligned(1024))) char stages[2 * kStageBytes];   // double buffer
@@ -266,7 +277,7 @@ __global__ __launch_bounds__(256, 2) void mfma_dkv_kernel(DevGroup g, KTensors t
   }
   const float c_log2 = t.scale * kLog2e;
 
-  QIter<RANGES> it(g, w.e0, w.e1, G, t.qbounds);
+  QIter<RANGES, BY_HEAD> it(g, w.e0, w.e1, G, t.qbounds);
   auto issue = [&](char* stage) {
     const int head = hk * G + it.hh;
     const int last = it.q1 - 1;

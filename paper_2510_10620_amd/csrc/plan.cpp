@@ -288,6 +288,26 @@ static void build_group(const dcp_plan& pl, const std::vector<int64_t>& kept, in
   }
 }
 
+// The walk order of units under per-token ranges.  The key blocks of a window see n neighbouring query blocks each (and the other way
+// round), and walked in the table's order neighbours are a block apart at any time.  Rotated to ascending (other block mod n), the units
+// that run together walk the same block at the same time wherever they share it, and their XCD's L2 serves its rows once (the export keeps
+// the table's order).  A 4 096-token window over 131 072 tokens, blocks of 1 024, 32/8 heads: dK/dV 17.3 -> 15.9 ms (15.5 with the
+// heads outside, see mfma_dkv_kernel.h), forward 7.74 -> 7.61, dQ 10.53 -> 10.43.
+// Returns whether most rows are in such units of more than three.
+static bool rotate_units(HostGroup* g) {
+  int64_t rows = 0;
+  for (size_t u = 0; u + 1 < g->ptr.size(); u++) {
+    const int32_t e0 = g->ptr[u], e1 = g->ptr[u + 1], n = e1 - e0;
+    if (n < 2 || g->ent_blk[e1 - 1] - g->ent_blk[e0] != n - 1) continue;   // not neighbours
+    if (std::none_of(g->ent_kind.begin() + e0, g->ent_kind.begin() + e1, [](int32_t k) { return k == DCP_MASK_RANGES || k == DCP_MASK_WINDOW; })) continue;
+    const int32_t first = (n - g->ent_blk[e0] % n) % n;   // of the entries, that with block mod n = 0
+    for (std::vector<int32_t>* v : {&g->ent_blk, &g->ent_start, &g->ent_len, &g->ent_kind})
+      std::rotate(v->begin() + e0, v->begin() + e0 + first, v->begin() + e1);
+    if (n > 3) rows += n;
+  }
+  return 2 * rows > (int64_t)g->ent_blk.size();
+}
+
 static void measure_groups(dcp_plan* plan) {
   const HostGroup* gs[3] = {&plan->fwd, &plan->bwdq, &plan->bwdkv};
   for (int i = 0; i < 3; i++) {
@@ -381,6 +401,9 @@ extern "C" dcp_status_t dcp_plan_create(dcp_plan_t** out, const int32_t* cu, int
   }
   build_group(*pl, kept, pl->n_blocks, qb_of, kb_of, &pl->bwdq);
   build_group(*pl, kept, pl->n_blocks, kb_of, qb_of, &pl->bwdkv);
+  pl->kv_by_head = rotate_units(&pl->bwdkv);
+  rotate_units(&pl->bwdq);
+  rotate_units(&pl->fwd);
   for (HostGroup* g : {&pl->bwdq, &pl->bwdkv}) {
     g->unit_blk.resize(pl->n_blocks);
     std::iota(g->unit_blk.begin(), g->unit_blk.end(), 0);

@@ -78,3 +78,25 @@ def test_inf_in_the_seen_half_of_a_tile(window_rows):
     want[32:64, :, 9] = float("inf")
     rows, cols = slice(32, 64), [c for c in range(128) if c != 5]   # (key 63 is masked for some of these rows, not unseen)
     assert np.array_equal(got[rows][:, :, cols], want[rows][:, :, cols])
+
+
+@pytest.mark.parametrize("lens,B,heads,spec,window_rows", [
+    ([700, 333, 1], 64, (128, 64), W.MaskSpec("window", window=260), True), ([700, 333, 1], 64, (128, 64), W.MaskSpec("window", window=260), False),
+    ([600] * 6 + [65], 96, (96, 32), W.MaskSpec("window", window=330), True), ([1100] * 4 + [97], 128, (64, 64), W.MaskSpec("window", window=500), False)],
+    ids=["window64", "ranges64", "window96", "ranges128"])
+def test_key_blocks_that_see_many_query_blocks(lens, B, heads, spec, window_rows):
+    """D = 128: most table rows are in units of more than three neighbouring blocks, which are walked in another order than the table's, in
+    dK/dV with the heads outside; cut items, ragged last blocks, units of one and two rows at the ends of the sequences."""
+    import paper_2510_10620_amd as P
+    w = W.custom_workload("many", lens, B, heads[0], heads[1], 128, "bf16", spec, seed=97, input_scale=0.5)
+    tensors, table = W.make_tensors(w), H.oracle_table(w)
+    rows = np.bincount(table[:, 1])
+    assert 2 * rows[rows > 3].sum() > len(table)
+    t = table.copy()
+    if window_rows:
+        t[t[:, 2] == W.MASK_RANGES, 2] = W.MASK_WINDOW
+    g = H.GpuRun(w, tensors, t, window=(spec.window, spec.sink) if window_rows else None)
+    assert P.dcp_plan_export_forms(g.plan, *heads, 128, P.DCP_BF16)["dkv"] == P.DCP_FORM_SHARED
+    out, lse = g.forward()
+    dq, dk, dv = g.backward()
+    H.check(w, dict(out=out, lse=lse, dq=dq, dk=dk, dv=dv), H.oracle_full(w, tensors, table), ("out", "lse", "dq", "dk", "dv"), f"many {B} {heads}", by_row=("dv",))
