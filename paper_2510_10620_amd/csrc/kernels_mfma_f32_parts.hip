@@ -21,7 +21,7 @@
 // halves of a step fall beside one another); elsewhere it is two groups of four waves (D 64) or four of two (D 32) that take the tiles in
 // turn, half a step apart, and meet at the end.  16 384 tokens in 8 sequences, 16/4 heads, D 64, one group / two: forward 362 / 401 us, dQ 490 /
 // 587; 8 192 tokens of which 5 582 in one sequence, 8/2 heads: 303 / 227, 380 / 324.
-// Against fp32 MFMA with 32 rows a workgroup, the last batch: forward / dQ / dK/dV 357 / 500 / 723 (16 rows) -> 227 / 324 / 540 us.
+// Against fp32 MFMA with 32 rows a workgroup, the last batch: forward / dQ / dK/dV 357 / 500 / 723 (16 rows) -> 227 / 324 / 466 us.
 #include "mfma_dkv_kernel.h"
 #include "query_rows.h"
 #include "split_rows.h"
@@ -97,14 +97,12 @@ __device__ __forceinline__ void put_own(char* lds, const Frags<D>& fa, const Own
     for (int k = 0; k < 3; k++) *(uint4*)(lds + k * kPlane<D> + (fa.rm ^ (ks << 5))) = __builtin_bit_cast(uint4, o.s[ks].p[k]);
 }
 
-// N MFMAs with V vector instructions behind each: a wave issues in order, so what is to run beside a chain has to stand in it.
-template <int N, int V>
-__device__ __forceinline__ void interleave() {
+template <int D>
+__device__ __forceinline__ Parts get_own(const char* lds, const Frags<D>& fa, int ks) {
+  Parts a;
 #pragma unroll
-  for (int i = 0; i < N; i++) {
-    __builtin_amdgcn_sched_group_barrier(8, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(2, V, 0);
-  }
+  for (int k = 0; k < 3; k++) a.p[k] = fa.rows(lds + k * kPlane<D>, ks);
+  return a;
 }
 
 // A tile of the other side on its way: memory -> registers -> three planes in LDS, by the 64 RG threads of a group, eight floats at a
@@ -146,12 +144,7 @@ struct Fetch {
 template <int D>
 __device__ __forceinline__ f32x16 dot_parts(const Frags<D>& fa, const char* tile, const OwnParts<D>& b, f32x16 s) {
 #pragma unroll
-  for (int x = 0; x < D / 16; x++) {
-    Parts a;
-#pragma unroll
-    for (int k = 0; k < 3; k++) a.p[k] = fa.rows(tile + k * kPlane<D>, x);
-    s = mul6(a, b.s[x], s);
-  }
+  for (int x = 0; x < D / 16; x++) s = mul6(get_own<D>(tile, fa, x), b.s[x], s);
   return s;
 }
 // (columns 32 dt .. of the tile) x p, p the parts of a score tile as the accumulator holds it
@@ -482,14 +475,20 @@ __global__ __launch_bounds__(64 * RG * NG, 2) void f32p_dq_kernel(DevGroup g, KT
   }
 }
 
-// dK / dV of 32 keys of one KV head: four waves take the (query head, 32-query tile) pairs in turn.  A wave has a SIMD to itself (512
-// registers): it holds its keys' parts and the parts of the tile it multiplies, as they come from memory (the rows of a tile are an A
-// operand already), and puts them into LDS of its own for the transposed reads alone, so that the loop has no barrier.
-template <int D, bool RANGES>
-__global__ __launch_bounds__(kNarrowThreads, 1) void f32p_dkv_kernel(DevGroup g, KTensors t) {
-  constexpr int NG = 4, KS = D / 16, SUB = kItemRows / 32;
-  constexpr int kWave = 2 * kOperand<D> > 2 * kSlabP<D> * 4 ? 2 * kOperand<D> : 2 * kSlabP<D> * 4;   // Q and dO; later dK and dV
-  __shared__ __attribute__((aligned(1024))) char lds[NG * kWave];
+// dK / dV of 32 keys of one KV head: eight waves take the (query head, 32-query tile) pairs in turn, two on a SIMD.  The rows of a tile
+// are an A operand as they come from memory: a wave cuts them in registers, multiplies them from there, and puts them into LDS of its own
+// for the transposed reads alone, dO first and Q after it into the same place, so that the loop has no barrier.  The keys' parts are in
+// LDS for all waves.  What is live then fits 256 registers: the sums (64), the parts of one operand (48), the next tile's rows as they come
+// (32, 64 during the last products) and one score tile or its parts; the two fences keep the compiler from holding more.  A wave that
+// multiplies goes before one that cuts, or both would cut and then both multiply.  8 192 tokens of which 5 582 in one sequence, 8/2 heads,
+// D 64 (the longest chain decides) and 16 384 in 8 equal ones, 16/4 heads: four waves that hold their keys' parts, one on a SIMD, 543 and
+// 914 us; four that read them from LDS, two on a SIMD, 659 and 816; eight 507 and 862, with priorities 483 and 844, with two fences of
+// four 466 and 815.
+template <int D, int NG, bool RANGES>
+__global__ __launch_bounds__(64 * NG, 2) void f32p_dkv_kernel(DevGroup g, KTensors t) {
+  constexpr int KS = D / 16, SUB = kItemRows / 32;
+  constexpr int kSums = NG * 2 * kSlabP<D> * 4;
+  __shared__ __attribute__((aligned(1024))) char lds[(NG + 2) * kOperand<D> > kSums ? (NG + 2) * kOperand<D> : kSums];   // a tile of every wave, K, V
   __shared__ float row_vals[NG][64];   // lse2 and -delta of the tile's rows
   const int lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6), li = lane & 31, lh = lane >> 5;
   touch_args<sizeof(DevGroup) + sizeof(KTensors)>();
@@ -501,90 +500,94 @@ __global__ __launch_bounds__(kNarrowThreads, 1) void f32p_dkv_kernel(DevGroup g,
   if (n_rows <= 0) return;
   const int seq0 = RANGES ? uni(plan_load(g.blk_s0, plan_load(g.unit_blk, uni(w.unit)))) : 0;
   const int k_lo = uni(w.blk_start) + row0, k_end = k_lo + n_rows;
-  char* q_lds = lds + wave * kWave;
-  char* do_lds = q_lds + kOperand<D>;
+  char* mine = lds + wave * kOperand<D>;
+  char* k_lds = lds + NG * kOperand<D>;
+  char* v_lds = k_lds + kOperand<D>;
   float* vals = row_vals[wave];
   QWalk<NG, RANGES> it(g, uni(w.e0), uni(w.e1), G, wave, t.qbounds);
   float rq[KS][8], rd[KS][8], rv = 0.f;   // the next tile as it comes
-  int head = 0, r0 = 0, lim = 0;        // its head, first row in memory and last row of it
-  auto load = [&]() {
-    const int row = min(li, lim);
+  int head = 0, r0 = 0, lim = 0;          // its head, first row in memory and last row of it
+  auto fetch = [&](float (&r)[KS][8], const void* base, int64_t st, int64_t sh) {
+    const int ln = fresh_lane();
     typedef const __attribute__((address_space(1))) char* gp;
-    const gp qb = (gp)(uint64_t)uni_ptr((const float*)t.q + (int64_t)r0 * t.q_st + (int64_t)head * t.q_sh);
-    const gp db = (gp)(uint64_t)uni_ptr((const float*)t.dout + (int64_t)r0 * t.do_st + (int64_t)head * t.do_sh);
-    const unsigned qo = (unsigned)row * (unsigned)t.q_st * 4u + 32u * lh, dd = (unsigned)row * (unsigned)t.do_st * 4u + 32u * lh;
+    const gp b = (gp)(uint64_t)uni_ptr((const float*)base + (int64_t)r0 * st + (int64_t)head * sh);
+    const unsigned off = (unsigned)min(ln & 31, lim) * (unsigned)st * 4u + 32u * (ln >> 5);
 #pragma unroll
     for (int ks = 0; ks < KS; ks++)
 #pragma unroll
       for (int y = 0; y < 2; y++) {
-        const pf32x4 a = *(const __attribute__((address_space(1))) pf32x4*)(db + dd + 64 * ks + 16 * y);
-        const pf32x4 b = *(const __attribute__((address_space(1))) pf32x4*)(qb + qo + 64 * ks + 16 * y);
+        const pf32x4 a = *(const __attribute__((address_space(1))) pf32x4*)(b + off + 64 * ks + 16 * y);
 #pragma unroll
-        for (int e = 0; e < 4; e++) { rd[ks][4 * y + e] = a[e]; rq[ks][4 * y + e] = b[e]; }
+        for (int e = 0; e < 4; e++) r[ks][4 * y + e] = a[e];
       }
-    rv = ((lh ? t.delta : t.lse2) + (int64_t)head * t.q_rows)[r0 + row];
   };
+  auto load_do = [&]() {
+    fetch(rd, t.dout, t.do_st, t.do_sh);
+    const int ln = fresh_lane();
+    rv = ((ln < 32 ? t.lse2 : t.delta) + (int64_t)head * t.q_rows)[r0 + min(ln & 31, lim)];
+  };
+  auto load_q = [&]() { fetch(rq, t.q, t.q_st, t.q_sh); };
   auto at_next = [&]() { head = hk * G + it.hh; r0 = it.qs() + it.moff; lim = it.q1 - 1 - it.qs(); };
   bool have = it.next(k_lo, k_end);
-  if (have) { at_next(); load(); }
-  OwnParts<D> kf, vf, qp, dop;
-  {
-    float y[KS][8];
-    const int kl = min(k_lo + li, k_end - 1) + koff;
-    read_own<D>(y, t.k, kl, t.k_st, (int64_t)hk * t.k_sh, lane);
-    cut_own<D>(kf, y);
-    read_own<D>(y, t.v, kl, t.v_st, (int64_t)hk * t.v_sh, lane);
-    cut_own<D>(vf, y);
-  }
+  if (have) { at_next(); load_do(); load_q(); }
   Frags<D> fa;
   fa.init(lane);
+  if (wave < 2) {
+    float y[KS][8];
+    const int kl = min(k_lo + li, k_end - 1) + koff;
+    if (wave == 0) read_own<D>(y, t.k, kl, t.k_st, (int64_t)hk * t.k_sh, lane);
+    else read_own<D>(y, t.v, kl, t.v_st, (int64_t)hk * t.v_sh, lane);
+    OwnParts<D> o;
+    cut_own<D>(o, y);
+    put_own<D>(wave ? v_lds : k_lds, fa, o);
+  }
+  __syncthreads();
   f32x16 dk[D / 32], dv[D / 32];
   clear(dk);
   clear(dv);
   const float c_log2 = t.scale * kLog2e;
-  if (have) cut_own<D>(dop, rd);
+  OwnParts<D> rows;   // dO, then Q, then the next dO
+  if (have) cut_own<D>(rows, rd);
   while (have) {
     const int qs = it.qs(), q1 = it.q1, kind = it.kind;
     const bool full = n_rows == 32 && it.full(k_end - 1);
-    vals[lane] = rv;
+    vals[fresh_lane()] = rv;
     f32x16 s, dp;
 #pragma unroll
     for (int a = 0; a < 4; a++) {
       const float4 d4 = *(const float4*)(vals + 32 + 8 * a + 4 * lh);
       dp[4 * a] = d4.x; dp[4 * a + 1] = d4.y; dp[4 * a + 2] = d4.z; dp[4 * a + 3] = d4.w;
     }
+    put_own<D>(mine, fa, rows);
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) dp = mul6(rows.s[ks], get_own<D>(v_lds, fa, ks), dp);
+    cut_own<D>(rows, rq);
 #pragma unroll
     for (int r = 0; r < 16; r++) s[r] = 0.f;
-    put_own<D>(do_lds, fa, dop);
 #pragma unroll
-    for (int ks = 0; ks < KS; ks++) dp = mul6(dop.s[ks], vf.s[ks], dp);
-    cut_own<D>(qp, rq);
-    put_own<D>(q_lds, fa, qp);
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) s = mul6(qp.s[ks], kf.s[ks], s);
-    interleave<6 * KS, 7>();
+    for (int ks = 0; ks < KS; ks++) s = mul6(rows.s[ks], get_own<D>(k_lds, fa, ks), s);
+    __builtin_amdgcn_s_setprio(0);
     have = it.next(k_lo, k_end);
     if (have) at_next();   // past the last tile it is that one again, unused
-    load();
-    uint32_t vis = 0xffffffffu;
+    load_do();
+    __builtin_amdgcn_sched_barrier(0);
     if (!full) {
-      // which of the wave's 32 keys query row (l & 31) sees, as a bit mask of lane l (see mfma_dkv_kernel.h)
+      // which of the 32 keys query row (l & 31) sees, as a bit mask of lane l (see mfma_dkv_kernel.h)
       const int i = qs + li;
       int lo1 = 0, hi1 = kind == 1 ? i + 1 : INT32_MAX, lo2 = 0, hi2 = 0;
       if (RANGES && kind == 2) {
         const int4 r = range_row(t, min(i, q1 - 1), seq0);
         lo1 = r.x; hi1 = r.y; lo2 = r.z; hi2 = r.w;
       }
-      vis = (keys_below(hi1, k_lo) & ~keys_below(lo1, k_lo)) | (keys_below(hi2, k_lo) & ~keys_below(lo2, k_lo));
+      uint32_t vis = (keys_below(hi1, k_lo) & ~keys_below(lo1, k_lo)) | (keys_below(hi2, k_lo) & ~keys_below(lo2, k_lo));
       vis &= keys_below(k_end, k_lo);
       vis = i < q1 ? vis : 0u;
-    }
-    if (!full) {
 #pragma unroll
       for (int r = 0; r < 16; r++) {
-        const int r0 = acc_row(r);
-        const uint64_t cond = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)vis, r0) |
-                              ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)vis, r0 + 4) << 32);
+        const int m0 = acc_row(r);
+        const uint64_t cond = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)vis, m0) |
+                              ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)vis, m0 + 4) << 32);
         s[r] = __builtin_amdgcn_inverse_ballot_w64(cond) ? s[r] : -INFINITY;
       }
     }
@@ -599,33 +602,42 @@ __global__ __launch_bounds__(kNarrowThreads, 1) void f32p_dkv_kernel(DevGroup g,
         dp[r] *= s[r];
       }
     }
-    const Parts ps[2] = {split_acc(s, 0), split_acc(s, 1)};
-    const Parts ds[2] = {split_acc(dp, 0), split_acc(dp, 1)};
+    __builtin_amdgcn_s_setprio(1);
+    {
+      const Parts p[2] = {split_acc(s, 0), split_acc(s, 1)};
 #pragma unroll
-    for (int dt = 0; dt < D / 32; dt++) {
-      const f32x16 a = cols_parts<D>(fa, do_lds, ps, dt);
+      for (int dt = 0; dt < D / 32; dt++) {
+        const f32x16 a = cols_parts<D>(fa, mine, p, dt);
 #pragma unroll
-      for (int r = 0; r < 16; r++) dv[dt][r] += a[r];
+        for (int r = 0; r < 16; r++) dv[dt][r] += a[r];
+      }
     }
+    put_own<D>(mine, fa, rows);   // Q takes dO's place, behind the reads (one wave's LDS operations are done in order)
+    load_q();
+    {
+      const Parts p[2] = {split_acc(dp, 0), split_acc(dp, 1)};
 #pragma unroll
-    for (int dt = 0; dt < D / 32; dt++) {
-      const f32x16 b = cols_parts<D>(fa, q_lds, ds, dt);
+      for (int dt = 0; dt < D / 32; dt++) {
+        const f32x16 b = cols_parts<D>(fa, mine, p, dt);
 #pragma unroll
-      for (int r = 0; r < 16; r++) dk[dt][r] += b[r];
+        for (int r = 0; r < 16; r++) dk[dt][r] += b[r];
+      }
     }
-    cut_own<D>(dop, rd);   // nothing uses it if there is no next tile
-    __builtin_amdgcn_sched_group_barrier(2, 130, 0);
-    interleave<24 * (D / 32), 7>();
+    __builtin_amdgcn_s_setprio(0);
+    cut_own<D>(rows, rd);   // nothing uses it if there is no next tile
+    __builtin_amdgcn_sched_barrier(0);
   }
-  // the waves' sums meet: a wave stores a quarter of the rows
-  constexpr int kPitch = kWave / 4;
+  // the waves' sums meet, and a wave stores some of the rows
+  constexpr int kPitch = 2 * kSlabP<D>;
   float* slabs = (float*)lds;
+  __syncthreads();   // K and V have been read
   stage_slab<D>(slabs + wave * kPitch, dk, lane);
   stage_slab<D>(slabs + wave * kPitch + kSlabP<D>, dv, lane);
   __syncthreads();
   float* dkp = (float*)t.dk + (int64_t)(k_lo + koff) * t.dk_st + (int64_t)hk * t.dk_sh;
   float* dvp = (float*)t.dv + (int64_t)(k_lo + koff) * t.dv_st + (int64_t)hk * t.dv_sh;
-  constexpr int MINE = 32 / NG;
+  constexpr int MINE = 32 / NG > 256 / D ? 32 / NG : 256 / D;   // no fewer than an instruction stores
+  if (MINE * wave >= 32) return;
   uint32_t again = store_slabs<D, NG, MINE>(slabs, kPitch, MINE * wave, t.scale, n_rows, dkp, t.dk_st, lane) |
                    store_slabs<D, NG, MINE>(slabs + kSlabP<D>, kPitch, MINE * wave, 1.f, n_rows, dvp, t.dv_st, lane);
   if (again) {
@@ -667,10 +679,10 @@ dcp_status_t mfma_f32_parts_dq(const DevGroup& g, const KTensors& t, hipStream_t
 dcp_status_t mfma_f32_parts_dkv(const DevGroup& g, const KTensors& t, hipStream_t s) {
   if (g.n_items == 0) return DCP_OK;
   const dim3 grid(xcd_grid(g, t.hkv, kSplitSub));
-  if (t.d == 32 && t.masked) DCP_F32P_ONE(f32p_dkv_kernel, kNarrowThreads, 32, true);
-  else if (t.d == 32) DCP_F32P_ONE(f32p_dkv_kernel, kNarrowThreads, 32, false);
-  else if (t.masked) DCP_F32P_ONE(f32p_dkv_kernel, kNarrowThreads, 64, true);
-  else DCP_F32P_ONE(f32p_dkv_kernel, kNarrowThreads, 64, false);
+  if (t.d == 32 && t.masked) DCP_F32P_ONE(f32p_dkv_kernel, 512, 32, 8, true);
+  else if (t.d == 32) DCP_F32P_ONE(f32p_dkv_kernel, 512, 32, 8, false);
+  else if (t.masked) DCP_F32P_ONE(f32p_dkv_kernel, 512, 64, 8, true);
+  else DCP_F32P_ONE(f32p_dkv_kernel, 512, 64, 8, false);
   DCP_HIP_TRY(hipGetLastError());
   return DCP_OK;
 }
