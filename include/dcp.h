@@ -210,8 +210,8 @@ dcp_status_t dcp_plan_export_dkv_segments(dcp_plan_t* plan, int32_t hkv, int32_t
 typedef enum { DCP_FORM_ROWS = -1, DCP_FORM_SHARED = 0, DCP_FORM_SPLIT = 1, DCP_FORM_SPLIT8 = 2 } dcp_form_t;
 dcp_status_t dcp_plan_export_forms(dcp_plan_t* plan, int32_t hq, int32_t hkv, int32_t d, int32_t dtype, int32_t* forms_out);
 
-/* The same for the fp32 kernels of form SHARED with D < 128: groups_out[2] = forward, dQ: 1 (a workgroup's waves are one group that
- * shares its tiles) or 2 (several groups take the tiles in turn).  0 with D 128.  Host only. */
+/* The same for the fp32 kernels of form SHARED with D < 128: groups_out[3] = forward, dQ, dK/dV: 1 (a workgroup has four waves) or
+ * 2 (eight; forward and dQ: in groups that take the tiles in turn).  0 with D 128.  Host only. */
 dcp_status_t dcp_plan_export_part_groups(dcp_plan_t* plan, int32_t hq, int32_t hkv, int32_t d, int32_t* groups_out);
 
 /* ---------------------------------------------------------------------------------------------

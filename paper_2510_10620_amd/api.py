@@ -193,8 +193,8 @@ def dcp_plan_export_forms(plan, hq, hkv, d, dtype_code):
 
 
 def dcp_plan_export_part_groups(plan, hq, hkv, d):
-    """(forward, dQ): groups of waves, 1 or 2 (several), of the fp32 kernels of form SHARED with D < 128."""
-    groups = (ctypes.c_int32 * 2)()
+    """(forward, dQ, dK/dV): 1 (four waves a workgroup) or 2 (eight, in several groups) of the fp32 kernels of form SHARED with D < 128."""
+    groups = (ctypes.c_int32 * 3)()
     _check(_lib.load().dcp_plan_export_part_groups(plan.handle, hq, hkv, d, groups))
     return tuple(groups)
 

@@ -147,12 +147,12 @@ static bool rows_are_faster(const dcp_plan_t* plan, const dcp_tensors_t* t, bool
 // 8 are, up to 1.13 (blocks of 64: 1.07).
 // Per-token ranges, whose pairs are a guess (windows of 32 to 4 096, sinks, mask blocks, shared questions; blocks of 64 to 4 096), measured over
 // 251 batches of all types: forward 0.63 to 0.96, backward 0.58 to 0.75 of the time of the first kind alone, single calls up to 1.05 of it.
-// fp32 with D 32 and 64: fitted to 297 batches of 100 to 16 384 tokens (148 with D 32), blocks of 64 to 2 048, and then moved within what the
-// times allow until the choices cost least; against the choice between 32 and 16 rows on the fp32 pipe that was there before: 0.91 and
-// 0.92 of the time on average (forward and backward), 2 and 5 batches slower by more than 3 %, up to 1.05 and 1.14 (the least that any
-// choice could reach: 0.90 and 0.89).
+// fp32 with D 32 and 64: fitted to 587 batches of 100 to 16 384 tokens (278 with D 32), blocks of 64 to 2 048, and then moved within what
+// the times allow until the choices cost least.  dK/dV with four waves or eight: four take 0.66 (D 32: 0.68) to 1.6 of the time of eight,
+// less than 0.97 in a quarter of the batches.  Of the time that the constants for eight waves alone took (forward and backward): 0.984 and
+// 0.990 on average, 4 and 13 batches slower by more than 3 %, up to 1.05 and 1.21; the least that any choice could reach is 0.95 and 0.97.
 struct LaunchFit { double start, chain, share, item; };
-// bf16: shared tiles, four waves, eight waves; fp32: 32 rows, 16 rows and, with D < 128, 32 rows with one group of waves (kFull); kRows: the thread-per-row kernels
+// bf16: shared tiles, four waves, eight waves; fp32: 32 rows, 16 rows and, with D < 128, 32 rows with fewer waves (kFull); kRows: the thread-per-row kernels
 enum { kRows = DCP_FORM_ROWS, kShared = DCP_FORM_SHARED, kSplit = DCP_FORM_SPLIT, kSplit8 = DCP_FORM_SPLIT8, kForms, kFull = kSplit8 };
 struct LaunchFits { int32_t dtype, d; double sure; LaunchFit fwd[kForms], dq[kForms], dkv[kForms], bwd[kForms]; };   // bwd: dQ and dK/dV in one launch
 static const LaunchFits kFits[] = {
@@ -164,10 +164,10 @@ static const LaunchFits kFits[] = {
      {{10.7, 180, 394, 11.3}, {6.1, 70.2, 341, 10.9}, {6.2, 43.3, 358, 19.8}}, {{}, {6.1, 80.7, 655, 11.7}, {4.5, 42.0, 779, 33.2}}},
     {DCP_F32, 128, 0.85, {{9.6, 223, 2220, 82.9}, {7.6, 151, 2810, 32.9}}, {{13.9, 314, 3240, 120}, {9.9, 248, 4860, 40.2}},
      {{15.9, 448, 3710, 183}, {10.8, 274, 4960, 89.9}}, {{}, {11.4, 364, 11050, 76.4}}},
-    {DCP_F32, 64, 0.9, {{11.3, 271, 524, 16.7}, {7.47, 111, 1800, 25.7}, {12.2, 422, 499, 9.18}}, {{16.1, 418, 1040, 8.69}, {6.34, 240, 3130, 28.1}, {12.1, 523, 850, 7.12}},
-     {{12.1, 224, 1610, 54.8}, {10.4, 197, 2070, 21.2}}, {{}, {7.35, 215, 7090, 45.4}}},
-    {DCP_F32, 32, 0.9, {{8.42, 161, 537, 11.8}, {6.36, 66.3, 846, 23.7}, {10.3, 315, 367, 4.61}}, {{10.6, 146, 553, 24.7}, {7.79, 81.5, 1350, 17.2}, {10.7, 422, 447, 5.48}},
-     {{9.67, 134, 729, 17.1}, {7.82, 119, 2620, 17.3}}, {{}, {9.23, 141, 2920, 33}}}};
+    {DCP_F32, 64, 0.9, {{11.3, 271, 609, 17.7}, {7.25, 125, 1800, 25.6}, {12.2, 386, 394, 9.45}}, {{16.0, 399, 1130, 8.43}, {6.22, 225, 2860, 29.9}, {12.1, 519, 820, 6.74}},
+     {{14.2, 159, 1350, 56.9}, {10.2, 142, 1880, 25.3}, {12.8, 207, 1360, 25.7}}, {{}, {9.09, 131, 6610, 44.6}}},
+    {DCP_F32, 32, 0.9, {{8.31, 129, 554, 12.8}, {6.41, 64.8, 973, 22.4}, {9.42, 326, 420, 4.15}}, {{10.4, 159, 696, 21.4}, {7.08, 97.6, 1340, 22.9}, {10.4, 471, 462, 6.75}},
+     {{10.1, 89.3, 1010, 16.8}, {6.24, 85.9, 2830, 23.2}, {9.24, 126, 913, 15.2}}, {{}, {8.83, 110, 2470, 38.4}}}};
 static constexpr double kLaunchGap = 1.0;   // between two launches
 static constexpr double kSureShort = 0.8, kSureShort8 = 0.7;   // `sure` of dK/dV over short blocks with four and eight waves
 static bool short_blocks(const dcp_tensors_t* t, const LaunchSize& z) { return t->dtype == DCP_BF16 && t->d == 128 && z.walk > 0; }
@@ -196,17 +196,19 @@ static int least_form(double sure, double sure8, const dcp_tensors_t* t, const d
 }
 
 // fp32 with D < 128: kShared are the kernels that multiply in bf16 parts; forward and dQ have one group of waves a workgroup (kFull) or
-// several, whichever is estimated faster.
+// several, dK/dV four waves (kFull) or eight, whichever is estimated faster.
 static bool in_parts(const dcp_tensors_t* t) { return t->dtype == DCP_F32 && t->d < 128; }
-static int part_groups(const LaunchFit* f, const dcp_tensors_t* t, const LaunchSize& z) {
-  const double longest = (double)z.longest, total = (double)z.total * t->hq, items = (double)z.items * t->hq;
+static int part_groups(const LaunchFit* f, double longest, double total, double items) {
   return launch_us(f[kFull], longest, total, items) < launch_us(f[kShared], longest, total, items) ? 1 : 2;
 }
-// of a forward (gid 0) or dQ (1) of form kShared
+// of a forward (gid 0), dQ (1) or dK/dV (2) of form kShared
 static int part_groups(dcp_plan_t* plan, const dcp_tensors_t* t, int gid) {
-  const LaunchSize& z = plan->host_items(gid, t->hq / t->hkv, xcd_segments(t->hkv)).size;
+  const int group = t->hq / t->hkv;
+  const LaunchSize& z = plan->host_items(gid, gid < 2 ? group : 0, xcd_segments(t->hkv)).size;
   const LaunchFits* f = fits_of(t, z);
-  return f ? part_groups(gid ? f->dq : f->fwd, t, z) : 1;
+  if (!f) return 1;
+  if (gid == 2) return part_groups(f->dkv, (double)z.longest * group, (double)z.total * t->hq, (double)z.items * t->hkv);
+  return part_groups(gid ? f->dq : f->fwd, (double)z.longest, (double)z.total * t->hq, (double)z.items * t->hq);
 }
 
 static int pick_q(const LaunchFits& fits, const LaunchFit* f, const dcp_tensors_t* t, const LaunchSize& z, double* us) {
@@ -231,6 +233,7 @@ static BwdChoice pick_bwd(const dcp_tensors_t* t, const LaunchSize& zq, const La
   for (int v = kShared; v <= last_form(t); v++) x[v] = launch_us(f->dkv[v], longest, total, items);
   if (mfma_splits_dkv(t->dtype, t->d))   // shared tiles go over a list of cut items
     x[kShared] = launch_us(f->dkv[kShared], (double)(walked ? zk.walk_part : zk.longest_part) * group, total, (double)zk.parts * t->hkv);
+  if (in_parts(t)) x[kShared] = std::min(x[kShared], launch_us(f->dkv[kFull], longest, total, items));
   c.dkv = least_form(walked ? kSureShort : f->sure, walked ? kSureShort8 : f->sure, t, x, &us_k);
   double least = f->sure * (us_q + us_k + kLaunchGap);
   for (int v = kSplit; one_launch && v <= last_form(t); v++) {
@@ -475,7 +478,7 @@ extern "C" dcp_status_t dcp_plan_export_part_groups(dcp_plan_t* plan, int32_t hq
   t.hq = hq; t.hkv = hkv; t.d = d; t.dtype = DCP_F32; t.softmax_scale = 1.f;
   const dcp_status_t st = check_shape(&t);
   if (st != DCP_OK) return st;
-  for (int gid = 0; gid < 2; gid++) groups[gid] = in_parts(&t) ? part_groups(plan, &t, gid) : 0;
+  for (int gid = 0; gid < 3; gid++) groups[gid] = in_parts(&t) ? part_groups(plan, &t, gid) : 0;
   return DCP_OK;
 }
 
@@ -559,7 +562,10 @@ dcp_status_t dcp::bwd_launch(dcp_plan_t* plan, const dcp_tensors_t* t, void* wor
   }
   ProfScope ps(DCP_K_DKV, s, may_alloc);
   if (form.dkv == kRows) return scalar_bwd_dkv(gkv, k, t->dtype, s);
-  if (form.dkv == kShared) return mfma_bwd_dkv(gkv, k, s);
+  if (form.dkv == kShared) {
+    if (in_parts(t)) k.part_groups = part_groups(plan, t, 2);
+    return mfma_bwd_dkv(gkv, k, s);
+  }
   return t->dtype == DCP_F32 ? mfma_f32_dkv(gkv, k, 16, s) : mfma_split_dkv(gkv, k, waves_of(form.dkv), s);
 }
 

@@ -25,7 +25,7 @@ struct KTensors {
   float scale;
   int32_t use_slots;
   int32_t by_head;         // dK/dV, bf16 with D = 128, masked: the query heads are the outer loop (dcp_plan::kv_by_head)
-  int32_t part_groups;     // forward and dQ in fp32 with D < 128, 32 rows a wave: groups of waves a workgroup, 1 or 2 (several)
+  int32_t part_groups;     // fp32 with D < 128, 32 rows a wave: 1 (four waves a workgroup) or 2 (eight)
 };
 
 #ifdef __HIPCC__

@@ -475,7 +475,8 @@ __global__ __launch_bounds__(64 * RG * NG, 2) void f32p_dq_kernel(DevGroup g, KT
   }
 }
 
-// dK / dV of 32 keys of one KV head: eight waves take the (query head, 32-query tile) pairs in turn, two on a SIMD.  The rows of a tile
+// dK / dV of 32 keys of one KV head: NG waves take the (query head, 32-query tile) pairs in turn, two on a SIMD: eight, or where the chip
+// is full of equal work four, whose start and end fall beside another workgroup's loop (see part_groups in api.hip).  The rows of a tile
 // are an A operand as they come from memory: a wave cuts them in registers, multiplies them from there, and puts them into LDS of its own
 // for the transposed reads alone, dO first and Q after it into the same place, so that the loop has no barrier.  The keys' parts are in
 // LDS for all waves.  What is live then fits 256 registers: the sums (64), the parts of one operand (48), the next tile's rows as they come
@@ -483,7 +484,7 @@ __global__ __launch_bounds__(64 * RG * NG, 2) void f32p_dq_kernel(DevGroup g, KT
 // multiplies goes before one that cuts, or both would cut and then both multiply.  8 192 tokens of which 5 582 in one sequence, 8/2 heads,
 // D 64 (the longest chain decides) and 16 384 in 8 equal ones, 16/4 heads: four waves that hold their keys' parts, one on a SIMD, 543 and
 // 914 us; four that read them from LDS, two on a SIMD, 659 and 816; eight 507 and 862, with priorities 483 and 844, with two fences of
-// four 466 and 815.
+// four 466 and 815; four with both 647 and 782.
 template <int D, int NG, bool RANGES>
 __global__ __launch_bounds__(64 * NG, 2) void f32p_dkv_kernel(DevGroup g, KTensors t) {
   constexpr int KS = D / 16, SUB = kItemRows / 32;
@@ -679,10 +680,17 @@ dcp_status_t mfma_f32_parts_dq(const DevGroup& g, const KTensors& t, hipStream_t
 dcp_status_t mfma_f32_parts_dkv(const DevGroup& g, const KTensors& t, hipStream_t s) {
   if (g.n_items == 0) return DCP_OK;
   const dim3 grid(xcd_grid(g, t.hkv, kSplitSub));
-  if (t.d == 32 && t.masked) DCP_F32P_ONE(f32p_dkv_kernel, 512, 32, 8, true);
-  else if (t.d == 32) DCP_F32P_ONE(f32p_dkv_kernel, 512, 32, 8, false);
-  else if (t.masked) DCP_F32P_ONE(f32p_dkv_kernel, 512, 64, 8, true);
-  else DCP_F32P_ONE(f32p_dkv_kernel, 512, 64, 8, false);
+  if (t.part_groups == 1) {
+    if (t.d == 32 && t.masked) DCP_F32P_ONE(f32p_dkv_kernel, 256, 32, 4, true);
+    else if (t.d == 32) DCP_F32P_ONE(f32p_dkv_kernel, 256, 32, 4, false);
+    else if (t.masked) DCP_F32P_ONE(f32p_dkv_kernel, 256, 64, 4, true);
+    else DCP_F32P_ONE(f32p_dkv_kernel, 256, 64, 4, false);
+  } else {
+    if (t.d == 32 && t.masked) DCP_F32P_ONE(f32p_dkv_kernel, 512, 32, 8, true);
+    else if (t.d == 32) DCP_F32P_ONE(f32p_dkv_kernel, 512, 32, 8, false);
+    else if (t.masked) DCP_F32P_ONE(f32p_dkv_kernel, 512, 64, 8, true);
+    else DCP_F32P_ONE(f32p_dkv_kernel, 512, 64, 8, false);
+  }
   DCP_HIP_TRY(hipGetLastError());
   return DCP_OK;
 }

@@ -12,9 +12,10 @@ pytestmark = pytest.mark.gpu
 
 EQ, MIXED = [161] * 10 + [1, 33], [1100, 127, 65, 31]
 SPECS = {"causal": W.MaskSpec("causal"), "lambda": W.MaskSpec("lambda", window=70, sink=9)}
-# D, lengths, block size, heads, groups of (forward, dQ)
+# D, lengths, block size, heads, groups of every kernel
 CASES = [(32, EQ, 512, (15, 5), 1), (32, MIXED, 512, (18, 6), 2), (32, [900, 257, 129, 65, 33, 1], 512, (16, 4), 2),
-         (64, EQ, 512, (15, 5), 1), (64, MIXED, 512, (18, 6), 2), (64, [1500], 512, (16, 4), 2)]
+         (64, EQ, 512, (15, 5), 1), (64, MIXED, 512, (18, 6), 2), (64, [1500], 512, (16, 4), 2),
+         (64, EQ + EQ, 512, (15, 5), 1)]
 NAMES = ("out", "lse", "dq", "dk", "dv")
 
 
@@ -29,12 +30,13 @@ def _run(case, mask, spread=False, scale=0.5):
     g = H.GpuRun(w, tensors, table)
     forms = P.dcp_plan_export_forms(g.plan, hq, hkv, d, P.DCP_F32)
     assert (forms["fwd"], forms["dq"]) == (P.DCP_FORM_SHARED, P.DCP_FORM_SHARED)
-    assert P.dcp_plan_export_part_groups(g.plan, hq, hkv, d) == (groups, groups)
+    assert case is CASES[3] or forms["dkv"] == P.DCP_FORM_SHARED
+    assert P.dcp_plan_export_part_groups(g.plan, hq, hkv, d) == (groups,) * 3
     return w, tensors, table, g
 
 
 @pytest.mark.parametrize("mask", list(SPECS))
-@pytest.mark.parametrize("case", CASES, ids=lambda c: f"D{c[0]}-{c[3][0]}x{c[3][1]}-g{c[4]}")
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"D{c[0]}-{len(c[1])}-{c[3][0]}x{c[3][1]}-g{c[4]}")
 def test_results(case, mask):
     w, tensors, table, g = _run(case, mask)
     out, lse = g.forward()
