@@ -6,7 +6,9 @@
 // and of the nine products of two such sums the six largest are kept: h h, h m, m h, m m, h l, l h.  What is left out is below 2^-24 of
 // the product, and the sums over a tile start at zero and are added to the running ones by one rounded addition, where a chain of fp32
 // MFMAs rounds the running sum once per two products.  Relative errors against 64 bits (norms; 8 192 tokens, 8/2 heads, D 64), fp32 MFMA ->
-// these: out 1.23e-7 -> 0.82e-7, LSE 6.08e-8 -> 6.08e-8, dQ 3.78e-7 -> 3.52e-7, dK 8.30e-7 -> 4.06e-7, dV 8.04e-7 -> 3.46e-7.
+// these: out 1.23e-7 -> 0.82e-7, LSE 6.08e-8 -> 6.08e-8, dQ 3.78e-7 -> 3.52e-7, dK 8.30e-7 -> 3.87e-7, dV 8.04e-7 -> 3.24e-7.  The third part
+// ends at the smallest bf16, 2^-133: a factor is kept to 2^-134 where that is more than 2^-25 of it, below 2^-109 (dO times 2^-90 changes no
+// result beyond its scale by more than 3e-9, times 2^-105: dQ and dK by 8e-7, times 2^-115: 8e-4; fp32 MFMA 1e-7).
 //
 // What bounds it: matrix and vector pipe together.  Cutting a value takes 5.5 vector instructions, a 32 x 32 tile 48 MFMAs (forward, D 64)
 // to 96 (dK/dV), so a wave that cuts its own tiles works as long on that as on the products; the chip runs the full launches at 1.0 to
