@@ -65,7 +65,7 @@ struct DevGroup {
   const int32_t* unit_moff;  // [n_units] offset of the unit's own block (Q side for fwd / dQ, KV side for dK/dV)
   const int32_t* ent_moff;   // [nnz]     offset of each row's other block
   const int32_t* ent_t32;    // [nnz]     index of the other block's first 32-row tile (range-bound summaries)
-  const int32_t* ent_rec;    // [nnz][8]  the same per row in one record: start, len, kind, moff, t32, 0, 0, 0 (32-byte aligned)
+  const int32_t* ent_rec;    // [nnz][8]  the same per row in one record: start, len, kind, moff, t32, number of the other block in its sequence, 0, 0 (32-byte aligned)
   const WorkItem* items;     // [n_items] longest first inside each segment
   const ReduceItem* reduce;  // [n_reduce] split (unit, tile)s, or null
   int32_t n_items;
@@ -130,7 +130,7 @@ struct dcp_plan {
   int32_t n_seq = 0, block_size = 0, n_blocks = 0, n_slots = 0, longest_block = 0;
   int64_t total_tokens = 0, n_kept = 0;
   bool use_slots = false, has_ranges = false, has_window = false;
-  bool kv_by_head = false;   // most dK/dV rows are in units that rotate_units has put in order and that have more than three
+  bool kv_by_head = false;   // most dK/dV rows are in units of more than three neighbouring query blocks, with per-token ranges
   int32_t window = 0, sink = 0;   // parameters of the WINDOW rows (window 0: not set)
   // block buffers: slot of every block in the Q-type and the KV-type buffer (-1: absent), rows per buffer
   bool buffers = false;

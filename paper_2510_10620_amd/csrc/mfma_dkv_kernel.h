@@ -18,9 +18,9 @@ static constexpr int kStageBytes = kStageBounds + 1024;
 // Walks (table row, query head of the group, 64-query tile) for one KV tile; BY_HEAD: (query head, table row, tile).
 template <bool RANGES, bool BY_HEAD = false>
 struct QIter {
-  const int4* rec;       // per table row: {first query, length, mask kind, memory offset of the Q block}, {first 32-row tile, ..}
+  const int4* rec;       // per table row: {first query, length, mask kind, memory offset of the Q block}, {first 32-row tile, number in the sequence, ..}
   const int4* qbounds;   // RANGES: range-bound summaries per 32-row tile
-  int e, e_end, e_top, hh, G, jt, n_t, jt0;
+  int e, e_end, n_e, left, hh, G, jt, n_t, jt0;   // BY_HEAD: of n_e rows, `left` are to come for this head
   int q0, q1, kind;
   int moff;  // the Q block's rows sit at (packed index + moff) in the Q-type buffers
   int t32;   // index of the Q block's first 32-row tile in qbounds
@@ -31,7 +31,11 @@ struct QIter {
   // start at its own diagonal, two steps behind its neighbour, which is as far apart as the L2 is large.
   __device__ QIter(const DevGroup& g, int e0, int e1, int G_, const int32_t* qb)
       : rec((const int4*)g.ent_rec), qbounds((const int4*)qb) {
-    e = e_top = e1; e_end = e0; hh = BY_HEAD ? 0 : G_ - 1; G = G_; jt = 0; n_t = 0; jt0 = 0; q0 = q1 = kind = 0; moff = 0; t32 = 0; qs = 0;
+    e = e1; e_end = e0; n_e = left = e1 - e0; hh = BY_HEAD ? 0 : G_ - 1; G = G_; jt = 0; n_t = 0; jt0 = 0; q0 = q1 = kind = 0; moff = 0; t32 = 0; qs = 0;
+    if (BY_HEAD && n_e > 1) {   // neighbouring query blocks: the first is that whose number is n_e - 1 mod n_e
+      const int b0 = uni(plan_load(rec, 2 * e0 + 1).y), b1 = uni(plan_load(rec, 2 * (e1 - 1) + 1).y);
+      if (b1 - b0 == n_e - 1) e = e1 - b0 % n_e;
+    }
   }
   // Which of the (at most 64) 64-query tiles of the current RANGES row may see a key of [k_lo, k_end): lane l merges
   // the bounds of the two 32-row halves of tile l.  Returns the ballot (wave-uniform).
@@ -59,10 +63,12 @@ struct QIter {
       if (jt < jt0) {
         bool row = true;   // a new row
         if (BY_HEAD) {
-          if (--e < e_end) {
-            if (++hh >= G || e_top == e_end) return false;
-            e = e_top - 1;
+          if (left == 0) {
+            if (++hh >= G || n_e == 0) return false;
+            left = n_e;
           }
+          left--;
+          e = e == e_end ? e_end + n_e - 1 : e - 1;
         } else if ((row = ++hh >= G)) {
           if (--e < e_end) return false;
           hh = 0;
@@ -233,10 +239,15 @@ __device__ __forceinline__ void dkv_subtile(DkvState& st, const char* stage, int
 // RANGES = false: the table has no row with per-token ranges (RANGES or WINDOW); everything that serves them is
 // compiled out.  Two workgroups per CU: at most 256 registers.
 // BY_HEAD (tables with per-token ranges whose key blocks see several neighbouring query blocks, as under a window): the heads are the outer
-// loop, so that workgroups that run together, walking the rows in the order of rotate_units (plan.cpp), are a few steps apart at any time
-// and not a few steps times the heads.  A 4 096-token window over 131 072 tokens, 32/8 heads: the order of the rows alone 17.3 -> 15.9 ms,
-// with the heads outside 15.5, and 63.6 -> 35.4 (in units of the same counter) fetched.  Tables whose key blocks see two or three query
-// blocks keep the rows outside: the look at a row's bounds for every head costs what this gains (mask blocks of 256, 4.25 and 4.39 ms).
+// loop, and a piece starts at the block whose number in its sequence is n - 1 mod n, n being its rows, and goes round.  Key blocks of a window
+// see n neighbouring query blocks each; from the table's last row on, neighbours are a block times the heads apart at any time, which is as
+// much as an XCD's L2 holds; like this the workgroups that run together walk the same block wherever they share it.  65 536 tokens, 32/8 heads
+// (131 072 in the first), every column a whole dK/dV launch in ms: rows outside from the last | heads outside from the last | as here
+//   window 4 096, blocks of 1 024   16.90 | 16.31 | 15.11        window 8 192, blocks of 1 024   11.60 | 11.27 | 10.96
+//   window 2 048, blocks of 512      4.34 |  4.03 |  3.92        window 2 000 + 64 sinks, 512     4.75 |  4.69 |  4.60
+//   4 096 as range arrays, 1 024     7.52 |  7.38 |  7.01        window 4 096, 1 024, 8/2 heads   1.85 |  1.85 |  1.86
+// Key blocks that see two or three query blocks keep the rows outside: the look at a row's bounds for every head costs what this gains (mask
+// blocks of 256, 4.25 and 4.39 ms).
 template <bool RANGES, bool BY_HEAD>
 __global__ __launch_bounds__(256, 2) void mfma_dkv_kernel(DevGroup g, KTensors t) {
   constexpr int TK = 128;

@@ -288,24 +288,15 @@ static void build_group(const dcp_plan& pl, const std::vector<int64_t>& kept, in
   }
 }
 
-// The walk order of units under per-token ranges.  The key blocks of a window see n neighbouring query blocks each (and the other way
-// round), and walked in the table's order neighbours are a block apart at any time.  Rotated to ascending (other block mod n), the units
-// that run together walk the same block at the same time wherever they share it, and their XCD's L2 serves its rows once (the export keeps
-// the table's order).  A 4 096-token window over 131 072 tokens, blocks of 1 024, 32/8 heads: dK/dV 17.3 -> 15.9 ms (15.5 with the
-// heads outside, see mfma_dkv_kernel.h), forward 7.74 -> 7.61, dQ 10.53 -> 10.43.
-// Returns whether most rows are in such units of more than three.
-static bool rotate_units(HostGroup* g) {
+// Whether most rows are in units of more than three neighbouring blocks, with per-token ranges in some of them (dcp_plan::kv_by_head).
+static bool many_neighbours(const HostGroup& g) {
   int64_t rows = 0;
-  for (size_t u = 0; u + 1 < g->ptr.size(); u++) {
-    const int32_t e0 = g->ptr[u], e1 = g->ptr[u + 1], n = e1 - e0;
-    if (n < 2 || g->ent_blk[e1 - 1] - g->ent_blk[e0] != n - 1) continue;   // not neighbours
-    if (std::none_of(g->ent_kind.begin() + e0, g->ent_kind.begin() + e1, [](int32_t k) { return k == DCP_MASK_RANGES || k == DCP_MASK_WINDOW; })) continue;
-    const int32_t first = (n - g->ent_blk[e0] % n) % n;   // of the entries, that with block mod n = 0
-    for (std::vector<int32_t>* v : {&g->ent_blk, &g->ent_start, &g->ent_len, &g->ent_kind})
-      std::rotate(v->begin() + e0, v->begin() + e0 + first, v->begin() + e1);
-    if (n > 3) rows += n;
+  for (size_t u = 0; u + 1 < g.ptr.size(); u++) {
+    const int32_t e0 = g.ptr[u], e1 = g.ptr[u + 1], n = e1 - e0;
+    if (n < 4 || g.ent_blk[e1 - 1] - g.ent_blk[e0] != n - 1) continue;
+    if (std::any_of(g.ent_kind.begin() + e0, g.ent_kind.begin() + e1, [](int32_t k) { return k == DCP_MASK_RANGES || k == DCP_MASK_WINDOW; })) rows += n;
   }
-  return 2 * rows > (int64_t)g->ent_blk.size();
+  return 2 * rows > (int64_t)g.ent_blk.size();
 }
 
 static void measure_groups(dcp_plan* plan) {
@@ -401,9 +392,7 @@ extern "C" dcp_status_t dcp_plan_create(dcp_plan_t** out, const int32_t* cu, int
   }
   build_group(*pl, kept, pl->n_blocks, qb_of, kb_of, &pl->bwdq);
   build_group(*pl, kept, pl->n_blocks, kb_of, qb_of, &pl->bwdkv);
-  pl->kv_by_head = rotate_units(&pl->bwdkv);
-  rotate_units(&pl->bwdq);
-  rotate_units(&pl->fwd);
+  pl->kv_by_head = many_neighbours(pl->bwdkv);
   for (HostGroup* g : {&pl->bwdq, &pl->bwdkv}) {
     g->unit_blk.resize(pl->n_blocks);
     std::iota(g->unit_blk.begin(), g->unit_blk.end(), 0);
@@ -570,6 +559,8 @@ dcp_status_t dcp_plan::ensure_device(hipStream_t stream, bool may_alloc) {
       for (size_t e = 0; e < em.size(); e++) {
         rec[8 * e] = gs[i]->ent_start[e]; rec[8 * e + 1] = gs[i]->ent_len[e]; rec[8 * e + 2] = dk[e];
         rec[8 * e + 3] = em[e]; rec[8 * e + 4] = et[e];
+        const int32_t b = gs[i]->ent_blk[e];
+        rec[8 * e + 5] = (blk_start[b] - cu[blk_seq[b]]) / block_size;
       }
       while (host.size() % 8) host.push_back(0);   // records are read as 16-byte vectors
       go[i].er = put(rec);

@@ -100,3 +100,34 @@ def test_key_blocks_that_see_many_query_blocks(lens, B, heads, spec, window_rows
     out, lse = g.forward()
     dq, dk, dv = g.backward()
     H.check(w, dict(out=out, lse=lse, dq=dq, dk=dk, dv=dv), H.oracle_full(w, tensors, table), ("out", "lse", "dq", "dk", "dv"), f"many {B} {heads}", by_row=("dv",))
+
+
+@pytest.mark.parametrize("spec,B,window_rows", [(W.MaskSpec("window", window=260), 64, True), (W.MaskSpec("lambda", window=260, sink=20), 64, False),
+                                                (W.MaskSpec("causal_blockwise", window=2, sink=1, mblock=64), 128, False)], ids=["window", "lambda", "blockwise"])
+def test_a_sequence_gives_the_same_bits_wherever_it_lies(spec, B, window_rows):
+    """The same two sequences in either order, by kernels that share tiles: no sum may depend on the number of a block in the batch (items are
+    cut alike in both orders).  With B = 64 key blocks see five or six query blocks, with 128 two or three."""
+    import torch
+    import paper_2510_10620_amd as P
+    hq, hkv, lens = 256, 128, (1300, 733)
+    got = []
+    for order in (lens, lens[::-1]):
+        w = W.custom_workload("order", list(order), B, hq, hkv, 128, "bf16", spec, seed=98, input_scale=0.5)
+        t = H.oracle_table(w).copy()
+        if window_rows:
+            t[t[:, 2] == W.MASK_RANGES, 2] = W.MASK_WINDOW
+        g = H.GpuRun(w, W.make_tensors(w), t, window=(spec.window, spec.sink) if window_rows else None)
+        forms = P.dcp_plan_export_forms(g.plan, hq, hkv, 128, P.DCP_BF16)
+        assert set(forms.values()) == {P.DCP_FORM_SHARED}
+        gen = torch.Generator(device="cuda").manual_seed(5)
+        seqs = {n: [torch.randn((n, h, 128), device="cuda", generator=gen).to(torch.bfloat16) for h in (hq, hkv, hkv, hq)] for n in lens}
+        for i, x in enumerate((g.q, g.k, g.v, g.dout)):
+            x.copy_(torch.cat([seqs[n][i] for n in order]))
+        g.forward()
+        g.backward()
+        at = dict(zip(order, (0, order[0])))
+        got.append({n: {"out": g.out[at[n]:at[n] + n].clone(), "lse": g.lse[:, at[n]:at[n] + n].clone(),
+                        **{k: getattr(g, k)[at[n]:at[n] + n].clone() for k in ("dq", "dk", "dv")}} for n in lens})
+    for n in lens:
+        for k in got[0][n]:
+            assert torch.equal(got[0][n][k], got[1][n][k]), (n, k)

@@ -202,6 +202,38 @@ def test_dkv_work_list_is_an_exact_partition(spec, lens, B, hkv):
     assert full - base == len(slots) * hkv * 2 * 128 * 128 * 4
 
 
+@pytest.mark.parametrize("lens,B,hkv,window,sink", [([6000, 300], 64, 8, 2000, 0), ([4096, 3000], 64, 4, 1000, 0), ([8192, 300], 64, 8, 3000, 64)])
+def test_cut_dkv_items_under_a_window_cover_the_rows_that_they_name(lens, B, hkv, window, sink):
+    """A cut item's pieces, looked up through BWDKV_IDX, end where the sum of their rows' estimated costs reaches its share of the item's
+    (RANGES / WINDOW rows count half their area), as far as every later piece keeps a row."""
+    cu = W.cu_from_lengths(lens)
+    table = P.dcp_build_block_table_window(cu, B, window, sink)
+    plan = P.dcp_plan_create(cu, B, table)
+    ptr, idx, start, length = (plan.export(n) for n in ("BWDKV_PTR", "BWDKV_IDX", "BLK_START", "BLK_LEN"))
+    by_tile = {}
+    for u, t, e0, e1, ps in P.dcp_plan_export_dkv_items(plan, hkv).tolist():
+        by_tile.setdefault((u, t), []).append((e0, e1))
+    uneven = 0
+    for (u, t), parts in by_tile.items():
+        parts.sort()
+        n, keys = len(parts), np.arange(start[u] + 128 * t, min(start[u] + 128 * (t + 1), start[u] + length[u]))
+        cost = {}
+        for e in range(ptr[u], ptr[u + 1]):
+            qb, _, kind = table[idx[e]]
+            q0, q1 = start[qb], start[qb] + length[qb]
+            area = len(keys) * int(q1 - q0)
+            cost[e] = area if kind == P.DCP_MASK_NONE else int(np.maximum(0, q1 - np.maximum(keys, q0)).sum()) if kind == P.DCP_MASK_CAUSAL else area // 2
+        total, done = sum(cost.values()), 0
+        for p, (e0, e1) in enumerate(parts[:-1]):
+            c = sum(cost[e] for e in range(e0, e1))
+            goal = total * (p + 1) // n
+            assert done + c >= goal or ptr[u + 1] - e1 == n - p - 1, (u, t, parts)
+            assert e1 == e0 + 1 or done + c - cost[e1 - 1] < goal, (u, t, parts)
+            done += c
+            uneven += len(set(cost.values())) > 1 and e1 > e0 + 1
+    assert uneven > 0
+
+
 @pytest.mark.parametrize("hkv", [1, 2, 3, 4, 6, 8, 12, 16])
 def test_dkv_work_list_segments_balance_the_xcds(hkv):
     """With KV heads that are no multiple of 8 an XCD takes (KV head, segment) pairs: the segments must cover the work
