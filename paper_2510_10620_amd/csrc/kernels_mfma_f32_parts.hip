@@ -347,11 +347,11 @@ __global__ __launch_bounds__(64 * RG * NG, 2) void f32p_fwd_kernel(DevGroup g, K
   for (int w = 0; w < NG; w++) f[w] *= inv;
   const int brow0 = q.row0 + q.wrow0;
   float* lp = slot < 0 ? t.lse + (int64_t)q.head * t.q_rows + q.wq_lo + q.qoff : t.lse + ((int64_t)slot * t.hq + q.head) * t.block_size + brow0;
-  if (group == 0 && q.qv && lh == 0) lp[li] = lt > 0.f ? (mt * c_log2 + __builtin_amdgcn_logf(lt)) * kLn2P : -INFINITY;
+  constexpr int MINE = 32 / NG;   // rows of a wave here: it stores and repairs both O and LSE of them, in this order
+  if (li / MINE == group && q.qv && lh == 0) lp[li] = lt > 0.f ? (mt * c_log2 + __builtin_amdgcn_logf(lt)) * kLn2P : -INFINITY;
   float* op = slot < 0 ? (float*)t.out + (int64_t)(q.wq_lo + q.qoff) * t.o_st + (int64_t)q.head * t.o_sh
                        : (float*)t.out + (((int64_t)slot * t.block_size + brow0) * t.hq + q.head) * D;
   const int64_t op_st = slot < 0 ? t.o_st : (int64_t)t.hq * D;
-  constexpr int MINE = 32 / NG;
   uint32_t again = store_slabs<D, NG, MINE>(slabs + rg * kSlabP<D>, RG * kSlabP<D>, MINE * group, f, q.w_rows, op, op_st, lane);
   if (again) {
     DCP_WAIT_VMCNT(0);   // the stores above come first

@@ -70,3 +70,22 @@ def test_inf_in_k(case, mask):
     for a, b, n in zip(fast.forward(), slow.forward(), ("out", "lse")):
         _same(a, b, w, n)
     assert np.isfinite(H.from_torch(slow.out)).any() and not np.isfinite(H.from_torch(slow.out)).all()
+
+
+@pytest.mark.parametrize("case", [CASES[1], CASES[4]], ids=lambda c: f"D{c[0]}-g{c[4]}")
+def test_lse_of_repaired_rows(case):
+    """Several groups of waves, and every row but the first of a sequence is worked out again: the second key of each sequence is Inf where q is
+    negative, so its weight is 0.  A row's LSE is that of its other keys, whichever group repairs it."""
+    import torch
+    from tests.test_gpu_nonfinite import _same
+    w, tensors, table, fast = _run(case, "causal")
+    slow = H.GpuRun(w, tensors, table, impl=P.DCP_IMPL_SCALAR)
+    second = torch.as_tensor(w.cu_seqlens[:-1].astype(np.int64) + 1).cuda()
+    for g in (fast, slow):
+        g.q[:, :, 5] = -g.q[:, :, 5].abs() - 0.1
+        g.k[second, :, 5] = float("inf")
+    out, lse = slow.forward()
+    assert np.isfinite(lse).all()
+    for _ in range(4):
+        for a, b, n in zip(fast.forward(), (out, lse), ("out", "lse")):
+            _same(a, b, w, n)
