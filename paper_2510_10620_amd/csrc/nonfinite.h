@@ -6,11 +6,14 @@
 // A row whose result is not finite is therefore worked out once more from the pairs it really sees, one wave per row
 // (lane = key of a 64-key step for the scores, lane = column for the sums, in table order): Inf and NaN then stand where the
 // pairs' own arithmetic puts them.  Finite inputs pay one fused multiply-add per accumulator register at the end (nothing
-// measurable: fp32, 8 192 tokens, 8/2 heads of 64, 351 / 490 / 776 us before and 349 / 489 / 777 with it; bf16, 16 384 tokens,
-// 16/4 heads of 64, 576 / 640 / 1 339 and 577 / 641 / 1 319).  Bound by latency where it runs: that bf16 batch forward and
+// measurable: bf16, 16 384 tokens, 16/4 heads of 64, 576 / 640 / 1 339 us before and 577 / 641 / 1 319 with it).  Bound by latency where it runs: that bf16 batch forward and
 // backward takes 2.9 ms finite, 10 with q, k, v all NaN (a row that is NaN in every column ends at once), 48 with V_5 NaN,
 // 210 with one query in the middle NaN in every head (its keys' gradients are all worked out again, and are finite); the
-// thread-per-row kernels took 133 in each case but the second.
+// thread-per-row kernels took 133 in each case but the second.  fp32 in parts (8 192 tokens, longest 5 582, 8/2 heads of 64; forward, then
+// forward and backward, ms): finite 0.27, 1.13; q, k, v all NaN 0.44, 1.52; in the longest sequence one K element NaN at its start 0.34,
+// 1.27, in its middle 3.3, 6.2, Inf there 11.3, 22.7; one query NaN in every head 0.27, 22.4; V_5 NaN 10.6, 34.5.  The fp32 MFMA kernels,
+// which work with Inf and NaN as they come and give a row of these to more waves, took 0.36, 1.61 | 0.36, 1.68 | 0.36, 1.63 | 0.35, 2.4 |
+// 0.35, 8.5 | 0.39, 14.6 | 7.5, 22.5.
 #pragma once
 #include "mfma_common.h"
 
@@ -138,43 +141,56 @@ __device__ void fix_out(const DevGroup& g, const KTensors& t, const FixRow& f, i
 }
 
 // The same for a row whose scores were not all worked out from what the inputs are (fp32 in parts: an Inf leaves NaN in the parts of its
-// number): its maximum, its sum and its LSE too.  Exponents are differences of scores, as in the kernel, so that scores of any size do.
+// number): its maximum, its sum and its LSE too, in a walk before that of fix_out.  Exponents are differences of scores, as in the
+// kernel, so that scores of any size do.  A score that is NaN or +Inf makes the whole row NaN, and ends the walk.
 template <typename T, int D>
 __device__ void fix_scores_and_out(const DevGroup& g, const KTensors& t, const FixRow& f, int hk, const T* q, T* dst, float* lse) {
   const int lane = threadIdx.x & 63;
   const float c_log2 = t.scale * 1.44269504088896340736f;
   const T* kb = (const T*)t.k + (int64_t)hk * t.k_sh;
   const T* vb = (const T*)t.v + (int64_t)hk * t.v_sh;
-  float mx = -INFINITY, l = 0.f, m_use = 0.f, inv = 0.f, acc[(D + 63) / 64] = {};
-  for (int pass = 0; pass < 3; pass++) {   // maximum, sum, weights times V
-    for (int e = f.e0; e < f.e1; e++) {
-      const int c0 = uni(g.ent_start[e]), c1 = c0 + uni(g.ent_len[e]), kind = uni(g.ent_kind[e]), moff = uni(g.ent_moff[e]);
-      for (int j0 = c0; j0 < c1; j0 += 64) {
-        const int j = j0 + lane;
-        const bool vis = j < c1 && key_visible(kind, f.qi, j, f.qr);
-        const uint64_t on = __ballot(vis);
-        if (!on) continue;
-        const float s = vis ? dot_row<T, D>(q, kb + (int64_t)(j + moff) * t.k_st) : -INFINITY;
-        const float p = vis ? __builtin_amdgcn_exp2f((s - m_use) * c_log2) : 0.f;
-        if (pass == 0) mx = fmaxf(mx, s);
-        else if (pass == 1) l += p;
-        else add_rows<T, D>(acc, p * inv, on, vb + (int64_t)(j0 + moff) * t.v_st, t.v_st, lane);
-      }
-    }
-#pragma unroll
-    for (int x = 32; x > 0; x >>= 1) {
-      if (pass == 0) mx = fmaxf(mx, __shfl_xor(mx, x));
-      else if (pass == 1) l += __shfl_xor(l, x);
-    }
-    if (pass == 0) m_use = mx == -INFINITY ? 0.f : mx;
-    if (pass == 1) inv = l > 0.f ? 1.f / l : 0.f;
-    if (pass == 1 && l != l) {   // a NaN score
-#pragma unroll
-      for (int k = 0; k < (D + 63) / 64; k++) acc[k] = l;
-      break;
+  float mx = -INFINITY, l = 0.f, acc[(D + 63) / 64] = {};   // the lane's maximum and its sum against that
+  bool nan = false;
+  for (int e = f.e0; e < f.e1 && !nan; e++) {
+    const int c0 = uni(g.ent_start[e]), c1 = c0 + uni(g.ent_len[e]), kind = uni(g.ent_kind[e]), moff = uni(g.ent_moff[e]);
+    for (int j0 = c0; j0 < c1 && !nan; j0 += 64) {
+      const int j = j0 + lane;
+      const bool vis = j < c1 && key_visible(kind, f.qi, j, f.qr);
+      if (!__any(vis)) continue;
+      const float s = vis ? dot_row<T, D>(q, kb + (int64_t)(j + moff) * t.k_st) : -INFINITY;
+      nan = __any(!(s < INFINITY));
+      const float m = fmaxf(mx, s);
+      if (m > -INFINITY) l = fmaf(l, __builtin_amdgcn_exp2f((mx - m) * c_log2), __builtin_amdgcn_exp2f((s - m) * c_log2));
+      mx = m;
     }
   }
-  if (lane == 0) *lse = l > 0.f ? (mx * c_log2 + __builtin_amdgcn_logf(l)) * 0.69314718055994530942f : -INFINITY;
+  if (nan) {
+    if (lane == 0) *lse = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < (D + 63) / 64; k++) acc[k] = __builtin_nanf("");
+    put_row<T, D>(dst, acc, 1.f, lane);
+    return;
+  }
+  float m = mx;
+#pragma unroll
+  for (int x = 32; x > 0; x >>= 1) m = fmaxf(m, __shfl_xor(m, x));
+  l = mx > -INFINITY ? l * __builtin_amdgcn_exp2f((mx - m) * c_log2) : 0.f;
+#pragma unroll
+  for (int x = 32; x > 0; x >>= 1) l += __shfl_xor(l, x);
+  const float inv = l > 0.f ? 1.f / l : 0.f;
+  if (lane == 0) *lse = l > 0.f ? (m * c_log2 + __builtin_amdgcn_logf(l)) * 0.69314718055994530942f : -INFINITY;
+  for (int e = l > 0.f ? f.e0 : f.e1; e < f.e1; e++) {
+    const int c0 = uni(g.ent_start[e]), c1 = c0 + uni(g.ent_len[e]), kind = uni(g.ent_kind[e]), moff = uni(g.ent_moff[e]);
+    for (int j0 = c0; j0 < c1; j0 += 64) {
+      const int j = j0 + lane;
+      const bool vis = j < c1 && key_visible(kind, f.qi, j, f.qr);
+      const uint64_t on = __ballot(vis);
+      if (!on) continue;
+      const float p = vis ? __builtin_amdgcn_exp2f((dot_row<T, D>(q, kb + (int64_t)(j + moff) * t.k_st) - m) * c_log2) * inv : 0.f;
+      add_rows<T, D>(acc, p, on, vb + (int64_t)(j0 + moff) * t.v_st, t.v_st, lane);
+      if (all_nan(acc, lane < D)) { e = f.e1; break; }
+    }
+  }
   put_row<T, D>(dst, acc, 1.f, lane);
 }
 
