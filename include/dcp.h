@@ -278,7 +278,7 @@ size_t dcp_bwd_workspace_bytes(const dcp_plan_t* plan, int32_t hq, int32_t hkv, 
  * are that share's partial sums.  workspace: device, >= dcp_bwd_workspace_bytes, 256-byte aligned.
  * Gradients may lie over inputs only so, at the same address and strides: dq over out, dk over k, dv over v (each row is read
  * before it is replaced; fp32 and bf16 with D < 128 work out keys whose gradients are not finite once more, from k and v, and
- * then need them elsewhere).  Such a call takes a launch for dQ and one for dK/dV where small batches otherwise take one for both. */
+ * then need them elsewhere; so does fp32 with D < 128 for keys that meet an operand of 2^112 or have a gradient of 2^80 or beyond).  Such a call takes a launch for dQ and one for dK/dV where small batches otherwise take one for both. */
 dcp_status_t dcp_block_attn_bwd(dcp_plan_t* plan, const dcp_tensors_t* t, void* workspace,
                                 size_t workspace_bytes, void* stream);
 

@@ -6,9 +6,7 @@
 // and of the nine products of two such sums the six largest are kept: h h, h m, m h, m m, h l, l h.  What is left out is below 2^-24 of
 // the product, and the sums over a tile start at zero and are added to the running ones by one rounded addition, where a chain of fp32
 // MFMAs rounds the running sum once per two products.  Relative errors against 64 bits (norms; 8 192 tokens, 8/2 heads, D 64), fp32 MFMA ->
-// these: out 1.23e-7 -> 0.82e-7, LSE 6.08e-8 -> 6.08e-8, dQ 3.78e-7 -> 3.52e-7, dK 8.30e-7 -> 3.87e-7, dV 8.04e-7 -> 3.24e-7.  The third part
-// ends at the smallest bf16, 2^-133: a factor is kept to 2^-134 where that is more than 2^-25 of it, below 2^-109 (dO times 2^-90 changes no
-// result beyond its scale by more than 3e-9, times 2^-105: dQ and dK by 8e-7, times 2^-115: 8e-4; fp32 MFMA 1e-7).
+// these: out 1.23e-7 -> 0.82e-7, LSE 6.08e-8 -> 6.08e-8, dQ 3.78e-7 -> 3.52e-7, dK 8.30e-7 -> 3.87e-7, dV 8.04e-7 -> 3.24e-7.
 //
 // What bounds it: matrix and vector pipe together.  Cutting a value takes 5.5 vector instructions, a 32 x 32 tile 48 MFMAs (forward, D 64)
 // to 96 (dK/dV), so a wave that cuts its own tiles works as long on that as on the products; the chip runs the full launches at 1.0 to
@@ -33,6 +31,13 @@ namespace dcp {
 
 namespace {
 
+// A bf16 ends at 2^-133, an fp32 number at 2^-149: times 2^16 every one has three parts that add up to it.  So the operands that a result is
+// linear in are cut times 2^16 (V in the forward; K, V and dO in dQ; Q, dO and V in dK/dV, and dS is 2^32 times itself through dP), and the
+// sums are put right before they are stored.  What overflows for it, operands of 2^112 and gradients of 2^80, is not finite in the parts and
+// worked out again.  64 more multiplications a tile in dK/dV (96 values are cut), 8 and 16 in the others: 8 192 tokens, 8/2 heads, forward / dQ /
+// dK/dV 234 / 331 / 475 -> 236 / 332 / 489 us.  Not so P, and Q and K in the forward's scores: their last bits, at 2^-134, count in a weight
+// below 2^-117 (which has lost as many to the rounding of its exponent, and is 0 below 2^-126) and in a score against a factor beyond 2^108.
+constexpr float kUp = 0x1p16f, kDown = 0x1p-16f;
 constexpr float kLn2P = 0.69314718055994530942f;
 constexpr float kRaiseP = 8.f;   // the running maximum is raised when a tile exceeds it by more than 2^8
 constexpr int kTR = 32;          // rows of a tile of the other side
@@ -52,10 +57,10 @@ __device__ __forceinline__ void split2(float a, float b, uint32_t& h, uint32_t& 
   l = pack_bf16x2(a, b);
 }
 struct Parts { bf16x8 p[3]; };
-__device__ __forceinline__ Parts split8(const float (&x)[8]) {
+__device__ __forceinline__ Parts split8(const float (&x)[8], float mul = 1.f) {
   uint32_t w[3][4];
 #pragma unroll
-  for (int e = 0; e < 4; e++) split2(x[2 * e], x[2 * e + 1], w[0][e], w[1][e], w[2][e]);
+  for (int e = 0; e < 4; e++) split2(x[2 * e] * mul, x[2 * e + 1] * mul, w[0][e], w[1][e], w[2][e]);
   Parts r;
 #pragma unroll
   for (int k = 0; k < 3; k++) r.p[k] = as_frag(make_uint4(w[k][0], w[k][1], w[k][2], w[k][3]));
@@ -85,10 +90,24 @@ __device__ __forceinline__ void read_own(float (&x)[D / 16][8], const void* base
   for (int ks = 0; ks < D / 16; ks++) load8<float>(p + 16 * ks, x[ks]);
 }
 template <int D>
-__device__ __forceinline__ void cut_own(OwnParts<D>& o, const float (&x)[D / 16][8]) {
+__device__ __forceinline__ void cut_own(OwnParts<D>& o, const float (&x)[D / 16][8], float mul = 1.f) {
 #pragma unroll
-  for (int ks = 0; ks < D / 16; ks++) o.s[ks] = split8(x[ks]);
+  for (int ks = 0; ks < D / 16; ks++) o.s[ks] = split8(x[ks], mul);
 }
+
+// Own rows that meet a tile times kUp in the scores are cut times kDown, so that the products are the scores and overflow no sooner; small
+// ones, whose last bits that would take, times 2^32, and the scores' factor makes up for it.
+template <int D>
+__device__ __forceinline__ bool are_small(const float (&x)[D / 16][8]) {
+  float m = 0.f;
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ks++)
+#pragma unroll
+    for (int e = 0; e < 8; e++) m = fmaxf(m, fabsf(x[ks][e]));
+  return !__any(m >= 0x1p-40f);
+}
+__device__ __forceinline__ float own_mul(bool small) { return small ? 0x1p32f : kDown; }
+__device__ __forceinline__ float score_factor(float scale, bool small) { return scale * kLog2e * (small ? 0x1p-48f : 1.f); }
 
 // ... and into LDS, as a tile of 32 rows
 template <int D>
@@ -128,13 +147,13 @@ struct Fetch {
       v[i][1] = *(const __attribute__((address_space(1))) pf32x4*)(b + off + 16);
     }
   }
-  __device__ __forceinline__ void put(char* lds) const {
+  __device__ __forceinline__ void put(char* lds, float mul = 1.f) const {
     if (idle()) return;
     const int x = tid();
 #pragma unroll
     for (int i = 0; i < PER; i++) {
       const float f[8] = {v[i][0][0], v[i][0][1], v[i][0][2], v[i][0][3], v[i][1][0], v[i][1][1], v[i][1][2], v[i][1][3]};
-      const Parts q = split8(f);
+      const Parts q = split8(f, mul);
       char* at = lds + TileLayout<D>::off((x + T * i) / CPR, (x + T * i) % CPR);
 #pragma unroll
       for (int k = 0; k < 3; k++) *(uint4*)(at + k * kPlane<D>) = __builtin_bit_cast(uint4, q.p[k]);
@@ -173,15 +192,15 @@ __device__ __forceinline__ void clear(f32x16 (&acc)[N]) {
     for (int r = 0; r < 16; r++) acc[i][r] = 0.f;
 }
 
-// A wave's D x 32 accumulator tile (lane = row of the result) into its slab, rows of D + 4 floats.
+// A wave's D x 32 accumulator tile (lane = row of the result), times mul, into its slab, rows of D + 4 floats.
 template <int D>
-__device__ __forceinline__ void stage_slab(float* slab, const f32x16 (&acc)[D / 32], int lane) {
+__device__ __forceinline__ void stage_slab(float* slab, const f32x16 (&acc)[D / 32], float mul, int lane) {
   float* row = slab + (lane & 31) * (D + 4) + 4 * (lane >> 5);
 #pragma unroll
   for (int dt = 0; dt < D / 32; dt++)
 #pragma unroll
     for (int a = 0; a < 4; a++)
-      *(float4*)(row + 32 * dt + 8 * a) = make_float4(acc[dt][4 * a], acc[dt][4 * a + 1], acc[dt][4 * a + 2], acc[dt][4 * a + 3]);
+      *(float4*)(row + 32 * dt + 8 * a) = make_float4(acc[dt][4 * a] * mul, acc[dt][4 * a + 1] * mul, acc[dt][4 * a + 2] * mul, acc[dt][4 * a + 3] * mul);
 }
 
 // Rows r0 .. r0 + ROWS - 1 of NG slabs (`pitch` floats apart) added up in order, each times its factor (one for all, or lane r of an
@@ -286,7 +305,7 @@ __global__ __launch_bounds__(64 * RG * NG, 2) void f32p_fwd_kernel(DevGroup g, K
 #pragma unroll
       for (int r = 0; r < 16; r++) s[r] = 0.f;
       s = dot_parts<D>(fa, k_lds, qf, s);
-      fv.put(v_lds);
+      fv.put(v_lds, kUp);
     }
     more.put(par, group, rg == 0, have);
     __syncthreads();
@@ -328,7 +347,7 @@ __global__ __launch_bounds__(64 * RG * NG, 2) void f32p_fwd_kernel(DevGroup g, K
   f[0] = 1.f;
   if (NG > 1 && lh == 0) { sm[group][rg][li] = m; sl[group][rg][li] = lt; }
   float* slabs = (float*)lds;
-  stage_slab<D>(slabs + wave * kSlabP<D>, o, lane);
+  stage_slab<D>(slabs + wave * kSlabP<D>, o, kDown, lane);
   __syncthreads();
   if (NG > 1) {
     mt = -INFINITY;
@@ -392,6 +411,7 @@ __global__ __launch_bounds__(64 * RG * NG, 2) void f32p_dq_kernel(DevGroup g, KT
   const float lse = t.lse[at];
   OwnParts<D> qf, dof;
   float delta = 0.f;
+  bool small;
   {
     // the backward preprocess, fused: delta = sum_d dO * O of the lane's row, left (negated) with the rescaled LSE in the
     // workspace for the dK/dV kernel
@@ -402,19 +422,20 @@ __global__ __launch_bounds__(64 * RG * NG, 2) void f32p_dq_kernel(DevGroup g, KT
     for (int ks = 0; ks < D / 16; ks++)
 #pragma unroll
       for (int e = 0; e < 8; e++) delta = fmaf(y[ks][e], x[ks][e], delta);
-    cut_own<D>(dof, x);
+    cut_own<D>(dof, x, kUp);
     read_own<D>(x, t.q, mem, t.q_st, (int64_t)q.head * t.q_sh, lane);
-    cut_own<D>(qf, x);
+    small = are_small<D>(x);
+    cut_own<D>(qf, x, own_mul(small));
   }
   delta = xhalf_sum(delta);
-  const float lse2 = row_lse2(lse, &delta);
+  const float lse2 = row_lse2(lse, &delta), delta_up = delta * (kUp * kUp);
   if (group == 0 && q.qv && lh == 0) { t.delta_w[at] = -delta; t.lse2_w[at] = lse2; }
   Frags<D> fa;
   fa.init(lane);
-  const float c_log2 = t.scale * kLog2e;
+  const float c_log2 = score_factor(t.scale, small);
   f32x16 dq[D / 32];
   clear(dq);
-  if (have) fv.put(v_lds);
+  if (have) fv.put(v_lds, kUp);
   more.put(1, group, rg == 0, have);
   __syncthreads();
   bool alive = more.any(1, have);
@@ -429,9 +450,9 @@ __global__ __launch_bounds__(64 * RG * NG, 2) void f32p_dq_kernel(DevGroup g, KT
       have = it.template next<RANGES>(q.q_hi, q.rb);
       if (have) fv.load(vb, t.v_st, it.ks() + it.moff, it.c1 - 1 + it.moff);
 #pragma unroll
-      for (int r = 0; r < 16; r++) dp[r] = -delta;
+      for (int r = 0; r < 16; r++) dp[r] = -delta_up;
       dp = dot_parts<D>(fa, v_lds, dof, dp);
-      fk.put(k_lds);
+      fk.put(k_lds, kUp);
     }
     more.put(par, group, rg == 0, have);
     __syncthreads();
@@ -451,7 +472,7 @@ __global__ __launch_bounds__(64 * RG * NG, 2) void f32p_dq_kernel(DevGroup g, KT
 #pragma unroll
         for (int r = 0; r < 16; r++) dq[dt][r] += x[r];
       }
-      fv.put(v_lds);   // nothing reads it if there is no next tile
+      fv.put(v_lds, kUp);   // nothing reads it if there is no next tile
     }
     __syncthreads();
     alive = more.any(par, have);
@@ -459,7 +480,7 @@ __global__ __launch_bounds__(64 * RG * NG, 2) void f32p_dq_kernel(DevGroup g, KT
   }
   if (NG > 1 && !late) __syncthreads();
   float* slabs = (float*)lds;
-  stage_slab<D>(slabs + wave * kSlabP<D>, dq, lane);
+  stage_slab<D>(slabs + wave * kSlabP<D>, dq, kDown * kDown * kDown, lane);
   __syncthreads();
   float* dqp = (float*)t.dq + (int64_t)(q.wq_lo + q.qoff) * t.dq_st + (int64_t)q.head * t.dq_sh;
   constexpr int MINE = 32 / NG;
@@ -493,6 +514,7 @@ __global__ __launch_bounds__(64 * NG, 2) void f32p_dkv_kernel(DevGroup g, KTenso
   constexpr int kSums = NG * 2 * kSlabP<D> * 4;
   __shared__ __attribute__((aligned(1024))) char lds[(NG + 2) * kOperand<D> > kSums ? (NG + 2) * kOperand<D> : kSums];   // a tile of every wave, K, V
   __shared__ float row_vals[NG][64];   // lse2 and -delta of the tile's rows
+  __shared__ int k_small;
   const int lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6), li = lane & 31, lh = lane >> 5;
   touch_args<sizeof(DevGroup) + sizeof(KTensors)>();
   int item, x;
@@ -541,20 +563,22 @@ __global__ __launch_bounds__(64 * NG, 2) void f32p_dkv_kernel(DevGroup g, KTenso
     if (wave == 0) read_own<D>(y, t.k, kl, t.k_st, (int64_t)hk * t.k_sh, lane);
     else read_own<D>(y, t.v, kl, t.v_st, (int64_t)hk * t.v_sh, lane);
     OwnParts<D> o;
-    cut_own<D>(o, y);
+    const bool small = are_small<D>(y);
+    cut_own<D>(o, y, wave ? kUp : own_mul(small));
     put_own<D>(wave ? v_lds : k_lds, fa, o);
+    if (wave == 0 && lane == 0) k_small = small;
   }
   __syncthreads();
   f32x16 dk[D / 32], dv[D / 32];
   clear(dk);
   clear(dv);
-  const float c_log2 = t.scale * kLog2e;
+  const float c_log2 = score_factor(t.scale, uni(k_small) != 0);
   OwnParts<D> rows;   // dO, then Q, then the next dO
-  if (have) cut_own<D>(rows, rd);
+  if (have) cut_own<D>(rows, rd, kUp);
   while (have) {
     const int qs = it.qs(), q1 = it.q1, kind = it.kind;
     const bool full = n_rows == 32 && it.full(k_end - 1);
-    vals[fresh_lane()] = rv;
+    vals[fresh_lane()] = rv * (fresh_lane() < 32 ? 1.f : kUp * kUp);
     f32x16 s, dp;
 #pragma unroll
     for (int a = 0; a < 4; a++) {
@@ -565,7 +589,7 @@ __global__ __launch_bounds__(64 * NG, 2) void f32p_dkv_kernel(DevGroup g, KTenso
     __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) dp = mul6(rows.s[ks], get_own<D>(v_lds, fa, ks), dp);
-    cut_own<D>(rows, rq);
+    cut_own<D>(rows, rq, kUp);
 #pragma unroll
     for (int r = 0; r < 16; r++) s[r] = 0.f;
 #pragma unroll
@@ -627,15 +651,15 @@ __global__ __launch_bounds__(64 * NG, 2) void f32p_dkv_kernel(DevGroup g, KTenso
       }
     }
     __builtin_amdgcn_s_setprio(0);
-    cut_own<D>(rows, rd);   // nothing uses it if there is no next tile
+    cut_own<D>(rows, rd, kUp);   // nothing uses it if there is no next tile
     __builtin_amdgcn_sched_barrier(0);
   }
   // the waves' sums meet, and a wave stores some of the rows
   constexpr int kPitch = 2 * kSlabP<D>;
   float* slabs = (float*)lds;
   __syncthreads();   // K and V have been read
-  stage_slab<D>(slabs + wave * kPitch, dk, lane);
-  stage_slab<D>(slabs + wave * kPitch + kSlabP<D>, dv, lane);
+  stage_slab<D>(slabs + wave * kPitch, dk, kDown * kDown * kDown, lane);
+  stage_slab<D>(slabs + wave * kPitch + kSlabP<D>, dv, kDown, lane);
   __syncthreads();
   float* dkp = (float*)t.dk + (int64_t)(k_lo + koff) * t.dk_st + (int64_t)hk * t.dk_sh;
   float* dvp = (float*)t.dv + (int64_t)(k_lo + koff) * t.dv_st + (int64_t)hk * t.dv_sh;

@@ -19,7 +19,7 @@ CASES = [(32, EQ, 512, (15, 5), 1), (32, MIXED, 512, (18, 6), 2), (32, [900, 257
 NAMES = ("out", "lse", "dq", "dk", "dv")
 
 
-def _run(case, mask, spread=False, scale=0.5):
+def _run(case, mask, spread=False, scale=0.5, exponents=()):
     d, lens, B, (hq, hkv), groups = case
     w = W.custom_workload("parts", lens, B, hq, hkv, d, "f32", SPECS[mask], seed=96, input_scale=scale)
     tensors, table = W.make_tensors(w), H.oracle_table(w)
@@ -27,6 +27,8 @@ def _run(case, mask, spread=False, scale=0.5):
         rng = np.random.default_rng(7)
         tensors = {k: (v * np.exp2(-20 * rng.random(v.shape))).astype(v.dtype) if isinstance(v, np.ndarray) and v.dtype == np.float32 else v
                    for k, v in tensors.items()}
+    for n, e in exponents:
+        tensors[n] = np.ldexp(tensors[n], e)
     g = H.GpuRun(w, tensors, table)
     forms = P.dcp_plan_export_forms(g.plan, hq, hkv, d, P.DCP_F32)
     assert (forms["fwd"], forms["dq"]) == (P.DCP_FORM_SHARED, P.DCP_FORM_SHARED)
@@ -55,6 +57,22 @@ def test_all_bits_of_the_inputs_count(case):
     for n in NAMES:
         a, b = got[n].astype(np.float64), np.asarray(ref[n])
         assert np.linalg.norm(a - b) <= (2.0 ** -20 if n[0] == "d" else 2.0 ** -21) * np.linalg.norm(b), n
+
+
+@pytest.mark.parametrize("exponents", [(("dout", -112),), (("v", -118),), (("k", -118),), (("q", -118),), (("q", 60), ("k", -60), ("dout", -100)),
+                                       (("q", 100), ("k", -100)), (("q", -100), ("k", 100)), (("v", 114),), (("dout", 100),)],
+                         ids=lambda x: "-".join(f"{n}{e}" for n, e in x))
+@pytest.mark.parametrize("case", [CASES[0], CASES[1], CASES[3], CASES[4]], ids=lambda c: f"D{c[0]}-g{c[4]}")
+def test_numbers_of_any_size_keep_their_bits(case, exponents):
+    """An operand, or the dS that comes of it, down to 2^-140: parts that ended at bf16's smallest number would leave it fewer than 10 bits; or up
+    to 2^116, which overflows in the parts and is worked out again.  The bounds are those of test_all_bits_of_the_inputs_count; what is new is that results of 2^-126 and less are rounded to 2^-149."""
+    w, tensors, table, g = _run(case, "causal", exponents=exponents)
+    got = dict(zip(NAMES, g.forward() + g.backward()))
+    ref = H.oracle_full(w, tensors, table)
+    for n in NAMES:
+        a, b = got[n].astype(np.float64), np.asarray(ref[n])
+        bound = (2.0 ** -20 if n[0] == "d" else 2.0 ** -21) * np.linalg.norm(b) + 2.0 ** -149 * np.sqrt(b.size)
+        assert np.linalg.norm(a - b) <= bound, (n, np.linalg.norm(a - b) / np.linalg.norm(b))
 
 
 @pytest.mark.parametrize("mask", list(SPECS))
