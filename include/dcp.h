@@ -204,14 +204,16 @@ dcp_status_t dcp_plan_export_dkv_segments(dcp_plan_t* plan, int32_t hkv, int32_t
 
 /* Which kernels the calls of a shape take, for checks: forms_out[4] = forward, dQ, dK/dV, and the launch that holds dQ and
  * dK/dV together (DCP_FORM_SHARED: there are two).  For impl AUTO, token strides of at most 2^24 elements and gradients
- * apart from the inputs.  SHARED: a tile is shared among a workgroup's waves (fp32: 32 rows a wave, D 128: 32 rows a workgroup); SPLIT, SPLIT8: four or
+ * apart from the inputs.  SHARED: a tile is shared among a workgroup's waves (fp32: 32 rows a workgroup, or with D < 128 the kernels of
+ * dcp_plan_export_part_groups: 32 rows a wave, 32 keys a workgroup); SPLIT, SPLIT8: four or
  * eight waves of 32 rows split the other side (fp32: SPLIT, 16 rows a workgroup); ROWS: a thread per row.  Chosen by
  * estimated time: see dcp_impl_t.  Host only. */
 typedef enum { DCP_FORM_ROWS = -1, DCP_FORM_SHARED = 0, DCP_FORM_SPLIT = 1, DCP_FORM_SPLIT8 = 2 } dcp_form_t;
 dcp_status_t dcp_plan_export_forms(dcp_plan_t* plan, int32_t hq, int32_t hkv, int32_t d, int32_t dtype, int32_t* forms_out);
 
-/* The same for the fp32 kernels of form SHARED with D < 128: groups_out[3] = forward, dQ, dK/dV: 1 (a workgroup has four waves) or
- * 2 (eight; forward and dQ: in groups that take the tiles in turn).  0 with D 128.  Host only. */
+/* The same for the fp32 kernels of form SHARED with D < 128: groups_out[3] = forward, dQ, dK/dV: 0, 32 rows a workgroup on the fp32 matrix pipe;
+ * bf16 parts: 1 (a workgroup has four waves) or 2 (eight; forward and dQ: in groups that take the tiles in turn), also where the
+ * launch's form is SPLIT: what those in parts would be.  0 with D 128.  Host only. */
 dcp_status_t dcp_plan_export_part_groups(dcp_plan_t* plan, int32_t hq, int32_t hkv, int32_t d, int32_t* groups_out);
 
 /* ---------------------------------------------------------------------------------------------

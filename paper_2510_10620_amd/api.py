@@ -193,7 +193,8 @@ def dcp_plan_export_forms(plan, hq, hkv, d, dtype_code):
 
 
 def dcp_plan_export_part_groups(plan, hq, hkv, d):
-    """(forward, dQ, dK/dV): 1 (four waves a workgroup) or 2 (eight, in several groups) of the fp32 kernels of form SHARED with D < 128."""
+    """(forward, dQ, dK/dV) of the fp32 kernels of form SHARED with D < 128: 0 (32 rows on the fp32 matrix pipe), in bf16 parts 1 (four waves a
+    workgroup) or 2 (eight, in several groups)."""
     groups = (ctypes.c_int32 * 3)()
     _check(_lib.load().dcp_plan_export_part_groups(plan.handle, hq, hkv, d, groups))
     return tuple(groups)

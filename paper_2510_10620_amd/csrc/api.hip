@@ -126,8 +126,8 @@ static bool rows_are_faster(const dcp_plan_t* plan, const dcp_tensors_t* t, bool
 }
 
 // Which of the MFMA kernels a launch takes.  bf16: those that share a tile among the waves of a workgroup, or those whose four or
-// eight waves split the other side (kernels_mfma_split.hip); fp32: 32 rows a wave in bf16 parts
-// (D 128: 32 rows a workgroup) or 16 rows a workgroup on the fp32 pipe.  The first kind streams least from the
+// eight waves split the other side (kernels_mfma_split.hip); fp32: 32 rows a workgroup or 16
+// on the fp32 pipe (D < 128: and 32 rows a wave in bf16 parts, see kWalkFits).  The first kind streams least from the
 // L2 and wins where the chip is full of equal work; the second finishes a long walk several times sooner and wins where a launch
 // has few items or waits for its longest: bf16, 5 196 tokens, 16/4 heads, blocks of 4 096, dK/dV 374 and 130 us; 4 528 tokens, 4/1
 // heads, forward 31 and 20; 65 536 tokens, 32/8 heads, forward 2.6 and 5.3 ms; fp32, 1 723 tokens, one head of 64, dK/dV 70 and 44 us,
@@ -135,10 +135,10 @@ static bool rows_are_faster(const dcp_plan_t* plan, const dcp_tensors_t* t, bool
 //     start + sqrt((chain x pairs of the longest item)^2 + (share x all pairs / 512)^2) + item x items / 512
 // (a pair per query head for `share`; for dK/dV an item walks its KV head's whole group; 512 workgroups are resident) with
 // constants (us; chain and share per million pairs) fitted to the times of 230 batches in bf16, 121 / 69 / 40 of them with D 128 /
-// 64 / 32, and 105 in fp32, 32 / 47 / 26: 1 to 1 000 sequences of 1 to 65 536 tokens, 1 to 16 KV heads, groups of 1 to 8, blocks of 64
-// to 4 096.  The estimates are 12 to 27 % off, so the second kind is taken only where it is estimated at 0.9 (fp32: 0.85 to 0.87) of
+// 64 / 32, and 32 in fp32 with D 128 (D 64 and 32 without parts, kPipeFits: 47 / 26): 1 to 1 000 sequences of 1 to 65 536 tokens, 1 to 16 KV heads, groups of 1 to 8, blocks of 64
+// to 4 096.  The estimates are 12 to 27 % off, so the second kind is taken only where it is estimated at 0.9 (fp32: 0.85, D 32 and 64 0.9) of
 // the first or less: over those batches no call was slower than with the first kind alone by more than 2 %, on average it took 0.87 /
-// 0.64 / 0.71 of the time in the forward and 0.79 / 0.52 / 0.47 in the backward (fp32 0.78 / 0.88 / 0.92 and 0.66 / 0.71 / 0.66).
+// 0.64 / 0.71 of the time in the forward and 0.79 / 0.52 / 0.47 in the backward (fp32 without parts 0.78 / 0.88 / 0.92 and 0.66 / 0.71 / 0.66).
 // bf16 with D 128 where no block has more than 64 rows: the pairs are those that are walked (LaunchSize), since a split workgroup has 32
 // rows and walks such an item as long as one of 128 rows.  Counted as visible pairs, its dK/dV was estimated at 0.6 of its time: 5 765
 // tokens, 8/2 heads, blocks of 64, backward 177 us with shared tiles and 329 in the form that was taken.  Shared tiles take 0.85 of
@@ -147,12 +147,10 @@ static bool rows_are_faster(const dcp_plan_t* plan, const dcp_tensors_t* t, bool
 // 8 are, up to 1.13 (blocks of 64: 1.07).
 // Per-token ranges, whose pairs are a guess (windows of 32 to 4 096, sinks, mask blocks, shared questions; blocks of 64 to 4 096), measured over
 // 251 batches of all types: forward 0.63 to 0.96, backward 0.58 to 0.75 of the time of the first kind alone, single calls up to 1.05 of it.
-// fp32 with D 32 and 64: fitted to 587 batches of 100 to 16 384 tokens (278 with D 32), blocks of 64 to 2 048, and then moved within what
-// the times allow until the choices cost least.  dK/dV with four waves or eight: four take 0.66 (D 32: 0.68) to 1.6 of the time of eight,
-// less than 0.97 in a quarter of the batches.  Of the time that the constants for eight waves alone took (forward and backward): 0.984 and
-// 0.990 on average, 4 and 13 batches slower by more than 3 %, up to 1.05 and 1.21; the least that any choice could reach is 0.95 and 0.97.
+// fp32 with D 32 and 64 (the kernels in parts beside 16 rows): 587 batches of 100 to 16 384 tokens, and what the second choice below makes of it.
 struct LaunchFit { double start, chain, share, item; };
-// bf16: shared tiles, four waves, eight waves; fp32: 32 rows, 16 rows and, with D < 128, 32 rows with fewer waves (kFull); kRows: the thread-per-row kernels
+// bf16: shared tiles, four waves, eight waves; fp32: 32 rows and 16, with D < 128 in parts with several groups (dK/dV: eight waves), 16 rows, and
+// in parts with one (kFull); kRows: the thread-per-row kernels
 enum { kRows = DCP_FORM_ROWS, kShared = DCP_FORM_SHARED, kSplit = DCP_FORM_SPLIT, kSplit8 = DCP_FORM_SPLIT8, kForms, kFull = kSplit8 };
 struct LaunchFits { int32_t dtype, d; double sure; LaunchFit fwd[kForms], dq[kForms], dkv[kForms], bwd[kForms]; };   // bwd: dQ and dK/dV in one launch
 static const LaunchFits kFits[] = {
@@ -195,28 +193,118 @@ static int least_form(double sure, double sure8, const dcp_tensors_t* t, const d
   return best;
 }
 
-// fp32 with D < 128: kShared are the kernels that multiply in bf16 parts; forward and dQ have one group of waves a workgroup (kFull) or
-// several, dK/dV four waves (kFull) or eight, whichever is estimated faster.
+// fp32 with D < 128 has four kernels for the forward and for dQ: on the fp32 pipe with 32 rows a workgroup or 16, in bf16 parts
+// with one group of waves or several; dK/dV has 16 rows, and parts with four waves or eight (with 32 rows it was never the best).  By pairs two of them come into question: the faster of those in parts
+// and 16 rows (kFits: kFull, kShared, kSplit), or what the choice between 32 and 16 rows would be without parts (kPipeFits).  Where the
+// second is estimated at 0.9 of the first or less by what the workgroups walk (WalkSize, kWalkFits), it is taken.  Pairs alone
+// misjudge few long walks and short blocks, where workgroups of 128 rows in parts walk far longer than the pairs say: 4 407 tokens, 2/1
+// heads of 64, blocks of 64, forward / dQ 191 / 253 us in parts, 107 / 145 and 81 / 130 on the fp32 pipe; 9 839 tokens under mask blocks of
+// 256, 4/4 heads, 444 / 575 and 181 / 251, 136 / 216.  What is walked alone misjudges ranges, of which neither knows the widths.
+// 1 294 batches each of D 32 and 64 (100 to 16 384 tokens, 1 to 40 sequences, blocks of 64 to 2 048, a third with ranges; the constants of
+// kWalkFits fitted to the times of 905 of them, then moved within what those allow until the choices cost least): against kPipeFits
+// alone 0.90 of the time on average, 20 (D 32) and 17 batches more than 3 % slower, 3 and 4 more than 10 %, up to 1.38 and 1.37 (with kFits
+// alone 87 and 68, 39 and 37, up to 1.42 and 1.79); against kFits alone 0.99, 16 and 19 more than 3 % slower, none and 4 more than 10 %,
+// up to 1.08 and 1.21.  The best kernel each time would take 0.97 of it.
 static bool in_parts(const dcp_tensors_t* t) { return t->dtype == DCP_F32 && t->d < 128; }
-static int part_groups(const LaunchFit* f, double longest, double total, double items) {
-  return launch_us(f[kFull], longest, total, items) < launch_us(f[kShared], longest, total, items) ? 1 : 2;
-}
-// of a forward (gid 0), dQ (1) or dK/dV (2) of form kShared
-static int part_groups(dcp_plan_t* plan, const dcp_tensors_t* t, int gid) {
+struct PipeFits { int32_t d; double sure; LaunchFit f[3][2], bwd; };   // forward, dQ, dK/dV: 32 rows, 16 rows
+static const PipeFits kPipeFits[] = {
+    {64, 0.87, {{{6.9, 125, 1180, 41.4}, {5.4, 88.9, 1300, 31.5}}, {{8.7, 174, 1640, 54.4}, {6.3, 144, 2160, 38.8}}, {{12.5, 252, 1990, 61.7}, {8.1, 164, 2310, 31.5}}},
+     {8.6, 170, 5574, 51.4}},
+    {32, 0.86, {{{5.1, 70.8, 573, 21.1}, {4.8, 42.8, 748, 23.3}}, {{5.8, 97.3, 789, 24.6}, {4.8, 71.1, 1130, 27.4}}, {{6.6, 152, 1120, 52.6}, {5.9, 94.8, 1390, 26.6}}},
+     {4.5, 109, 2975, 41.0}}};
+enum { kPipe32, kPipe16, kParts1, kParts2, kF32Kernels };
+struct WalkFits { int32_t d; LaunchFit f[3][kF32Kernels], bwd; };   // of WalkSize in place of pairs
+static const WalkFits kWalkFits[] = {
+    {64, {{{6.09, 115, 1420, 58.8}, {8.11, 90.4, 1450, 17.7}, {8.19, 437, 573, 3.12}, {10.5, 374, 506, 4.41}},
+          {{5.24, 255, 1730, 42.1}, {7.15, 142, 1710, 26.6}, {14, 402, 869, 1.54}, {12.8, 396, 1570, 6.21}},
+          {{}, {10.4, 208, 2210, 24.9}, {11.7, 195, 1280, 16.3}, {13.4, 159, 1340, 42.8}}}, {9.35, 190, 6200, 47.1}},
+    {32, {{{5.13, 54.3, 725, 19.9}, {5.21, 38.9, 806, 33}, {5.52, 212, 351, 1.85}, {7.3, 101, 823, 8.82}},
+          {{4.65, 71.1, 1350, 19.9}, {4.15, 69, 1020, 28.1}, {8.27, 374, 497, 1.38}, {10.7, 133, 706, 19.9}},
+          {{}, {12.3, 152, 1380, 17}, {9.31, 119, 816, 12.6}, {12, 135, 656, 33.5}}}, {8.63, 85.3, 4180, 37.1}}};
+static constexpr double kSecond = 0.9;   // the other choice is taken where it is estimated at this much of the first or less
+
+struct F32Launch { double longest, total, items; };   // as launch_us takes them
+// Of forward (gid 0), dQ (1), dK/dV (2), by pairs: the kernel with those in parts to choose from, that without, their estimates; the faster in parts.
+struct F32Pick { int first, second, parts; double first_us, second_us; };
+static F32Launch f32_pairs(dcp_plan_t* plan, const dcp_tensors_t* t, int gid) {
   const int group = t->hq / t->hkv;
   const LaunchSize& z = plan->host_items(gid, gid < 2 ? group : 0, xcd_segments(t->hkv)).size;
-  const LaunchFits* f = fits_of(t, z);
-  if (!f) return 1;
-  if (gid == 2) return part_groups(f->dkv, (double)z.longest * group, (double)z.total * t->hq, (double)z.items * t->hkv);
-  return part_groups(gid ? f->dq : f->fwd, (double)z.longest, (double)z.total * t->hq, (double)z.items * t->hq);
+  return {(double)z.longest * (gid == 2 ? group : 1), (double)z.total * t->hq, (double)z.items * (gid == 2 ? t->hkv : t->hq)};
 }
+template <class F> static const F& f32_row(const F (&rows)[2], int32_t d) { return rows[rows[0].d == d ? 0 : 1]; }
+static double launch_us(const LaunchFit& f, const F32Launch& x) { return launch_us(f, x.longest, x.total, x.items); }
+static F32Pick f32_pick(const LaunchFits& fits, const dcp_tensors_t* t, int gid, const F32Launch& x) {
+  const LaunchFit* f = gid == 0 ? fits.fwd : gid == 1 ? fits.dq : fits.dkv;
+  const PipeFits& pf = f32_row(kPipeFits, t->d);
+  const double p1 = launch_us(f[kFull], x), p2 = launch_us(f[kShared], x), r16 = launch_us(f[kSplit], x), parts = std::min(p1, p2);
+  const double a = launch_us(pf.f[gid][0], x), b = launch_us(pf.f[gid][1], x);
+  F32Pick c;
+  const bool rows16 = r16 < fits.sure * parts, pipe16 = b < pf.sure * a;
+  c.parts = p1 < p2 ? kParts1 : kParts2;
+  c.first = rows16 ? kPipe16 : c.parts;
+  c.first_us = rows16 ? r16 : parts;
+  c.second = pipe16 ? kPipe16 : kPipe32;
+  c.second_us = pipe16 ? b : a;
+  return c;
+}
+// by what is walked
+static F32Launch f32_walked(dcp_plan_t* plan, const dcp_tensors_t* t, int gid, int kernel, double items) {
+  const WalkSize& w = plan->walk_size(gid);
+  const int rows = kernel == kPipe16 ? 0 : kernel == kPipe32 || gid == 2 ? 1 : t->d == 32 && kernel == kParts2 ? 2 : 3;
+  return {(double)w.longest * (gid == 2 ? t->hq / t->hkv : 1), (double)w.total[rows] * t->hq, items};
+}
+// The kernel of a launch, and its estimate by what is walked.
+static int f32_kernel(dcp_plan_t* plan, const dcp_tensors_t* t, int gid, const F32Launch& x, const F32Pick& c, double* us) {
+  const LaunchFit* f = f32_row(kWalkFits, t->d).f[gid];
+  const double first = launch_us(f[c.first], f32_walked(plan, t, gid, c.first, x.items)), second = launch_us(f[c.second], f32_walked(plan, t, gid, c.second, x.items));
+  const bool other = (gid < 2 || c.second == kPipe16) && second < kSecond * first;
+  *us = other ? second : first;
+  return other ? c.second : c.first;
+}
+static F32Choice f32_choose(dcp_plan_t* plan, const dcp_tensors_t* t) {
+  F32Choice c{{kParts1, kParts1, kParts1}, {kParts1, kParts1, kParts1}, false};
+  const int group = t->hq / t->hkv, n_seg = xcd_segments(t->hkv);
+  F32Launch x[3];
+  F32Pick p[3];
+  double us[3];
+  for (int gid = 0; gid < 3; gid++) {
+    const LaunchFits* f = fits_of(t, plan->host_items(gid, gid < 2 ? group : 0, n_seg).size);
+    if (!f) return c;
+    x[gid] = f32_pairs(plan, t, gid);
+    p[gid] = f32_pick(*f, t, gid, x[gid]);
+    c.kernel[gid] = f32_kernel(plan, t, gid, x[gid], p[gid], &us[gid]);
+    c.parts[gid] = p[gid].parts;
+  }
+  // one launch for dQ and dK/dV or two: the same way, each choice with its own two launches by pairs
+  const LaunchFits* f = fits_of(t, plan->host_items(1, group, n_seg).size);
+  const PipeFits& pf = f32_row(kPipeFits, t->d);
+  const F32Launch xb{x[2].longest, x[2].total, x[2].items + x[1].items};
+  const bool first = launch_us(f->bwd[kSplit], xb) < f->sure * (p[1].first_us + p[2].first_us + kLaunchGap);
+  const bool second = launch_us(pf.bwd, xb) < pf.sure * (p[1].second_us + p[2].second_us + kLaunchGap);
+  const double one = launch_us(f32_row(kWalkFits, t->d).bwd, f32_walked(plan, t, 2, kPipe16, xb.items)), two = us[1] + us[2] + kLaunchGap;
+  c.one_launch = first == second ? first : first ? !(two < kSecond * one) : one < kSecond * two;
+  return c;
+}
+// ... once for a plan and shape
+static F32Choice f32_choice(dcp_plan_t* plan, const dcp_tensors_t* t) {
+  const std::tuple<int, int, int> key(t->hq, t->hkv, t->d);
+  {
+    std::lock_guard<std::mutex> lock(plan->mu);
+    const auto hit = plan->f32_choices.find(key);
+    if (hit != plan->f32_choices.end()) return hit->second;
+  }
+  const F32Choice c = f32_choose(plan, t);
+  std::lock_guard<std::mutex> lock(plan->mu);
+  return plan->f32_choices.emplace(key, c).first->second;
+}
+static int f32_form(int kernel) { return kernel == kPipe16 ? kSplit : kShared; }
+static int f32_groups(int kernel) { return kernel == kParts1 ? 1 : kernel == kParts2 ? 2 : 0; }
 
 static int pick_q(const LaunchFits& fits, const LaunchFit* f, const dcp_tensors_t* t, const LaunchSize& z, double* us) {
   double x[kForms];
   const bool walked = short_blocks(t, z);
   const double longest = (double)(walked ? z.walk : z.longest), total = (double)(walked ? z.walk_total : z.total) * t->hq;
   for (int v = kShared; v <= last_form(t); v++) x[v] = launch_us(f[v], longest, total, (double)z.items * t->hq);
-  if (in_parts(t)) x[kShared] = std::min(x[kShared], launch_us(f[kFull], longest, total, (double)z.items * t->hq));
   return least_form(fits.sure, fits.sure, t, x, us);
 }
 
@@ -233,7 +321,6 @@ static BwdChoice pick_bwd(const dcp_tensors_t* t, const LaunchSize& zq, const La
   for (int v = kShared; v <= last_form(t); v++) x[v] = launch_us(f->dkv[v], longest, total, items);
   if (mfma_splits_dkv(t->dtype, t->d))   // shared tiles go over a list of cut items
     x[kShared] = launch_us(f->dkv[kShared], (double)(walked ? zk.walk_part : zk.longest_part) * group, total, (double)zk.parts * t->hkv);
-  if (in_parts(t)) x[kShared] = std::min(x[kShared], launch_us(f->dkv[kFull], longest, total, items));
   c.dkv = least_form(walked ? kSureShort : f->sure, walked ? kSureShort8 : f->sure, t, x, &us_k);
   double least = f->sure * (us_q + us_k + kLaunchGap);
   for (int v = kSplit; one_launch && v <= last_form(t); v++) {
@@ -270,6 +357,7 @@ static int waves_of(int form) { return form == kSplit ? 4 : 8; }
 // The form of a forward over the list g.
 static int fwd_form(dcp_plan_t* plan, const dcp_tensors_t* t, bool use_mfma, const DevGroup& g) {
   if (!use_mfma || !mfma_launch_fits(g, false, t->dtype, t->d, t->hq, t->hkv) || rows_are_faster(plan, t, false)) return kRows;
+  if (in_parts(t)) return f32_form(f32_choice(plan, t).kernel[0]);
   const LaunchSize& z = plan->host_items(0, t->hq / t->hkv, xcd_segments(t->hkv)).size;
   const LaunchFits* f = fits_of(t, z);
   double us = 0;
@@ -282,6 +370,10 @@ static BwdChoice bwd_forms(dcp_plan_t* plan, const dcp_tensors_t* t, bool use_mf
   if (!use_mfma || !mfma_launch_fits(gq, false, t->dtype, t->d, t->hq, t->hkv) ||
       !mfma_launch_fits(gkv, true, t->dtype, t->d, t->hq, t->hkv) || rows_are_faster(plan, t, true))
     return {kRows, kRows, kShared};
+  if (in_parts(t)) {
+    const F32Choice f = f32_choice(plan, t);
+    return {f32_form(f.kernel[1]), f32_form(f.kernel[2]), one_launch && f.one_launch ? kSplit : kShared};
+  }
   const int n_seg = xcd_segments(t->hkv);
   BwdChoice c = pick_bwd(t, plan->host_items(1, t->hq / t->hkv, n_seg).size, plan->host_items(2, cut, n_seg).size, one_launch);
   if (heads != 0) c.dkv = c.both = kShared;
@@ -366,7 +458,7 @@ extern "C" dcp_status_t dcp_block_attn_fwd(dcp_plan_t* plan, const dcp_tensors_t
   ProfScope ps(DCP_K_FWD, s);
   if (form == kRows) return scalar_fwd(g, k, t->dtype, s);
   if (form == kShared) {
-    if (in_parts(t)) k.part_groups = part_groups(plan, t, 0);
+    if (in_parts(t)) k.part_groups = f32_groups(f32_choice(plan, t).kernel[0]);
     return mfma_fwd(g, k, s);
   }
   return t->dtype == DCP_F32 ? mfma_f32_fwd(g, k, 16, s) : mfma_split_fwd(g, k, waves_of(form), s);
@@ -478,7 +570,8 @@ extern "C" dcp_status_t dcp_plan_export_part_groups(dcp_plan_t* plan, int32_t hq
   t.hq = hq; t.hkv = hkv; t.d = d; t.dtype = DCP_F32; t.softmax_scale = 1.f;
   const dcp_status_t st = check_shape(&t);
   if (st != DCP_OK) return st;
-  for (int gid = 0; gid < 3; gid++) groups[gid] = in_parts(&t) ? part_groups(plan, &t, gid) : 0;
+  const F32Choice c = in_parts(&t) ? f32_choice(plan, &t) : F32Choice{};
+  for (int gid = 0; gid < 3; gid++) groups[gid] = in_parts(&t) ? f32_groups(c.kernel[gid] == kPipe16 ? c.parts[gid] : c.kernel[gid]) : 0;
   return DCP_OK;
 }
 
@@ -554,7 +647,7 @@ dcp_status_t dcp::bwd_launch(dcp_plan_t* plan, const dcp_tensors_t* t, void* wor
     ProfScope ps(DCP_K_DQ, s, may_alloc);
     if (form.dq == kRows) st = scalar_bwd_dq(gq, k, t->dtype, s);
     else if (form.dq == kShared) {
-      if (in_parts(t)) k.part_groups = part_groups(plan, t, 1);
+      if (in_parts(t)) k.part_groups = f32_groups(f32_choice(plan, t).kernel[1]);
       st = mfma_bwd_dq(gq, k, s);
     }
     else st = t->dtype == DCP_F32 ? mfma_f32_dq(gq, k, 16, s) : mfma_split_dq(gq, k, waves_of(form.dq), s);
@@ -563,7 +656,7 @@ dcp_status_t dcp::bwd_launch(dcp_plan_t* plan, const dcp_tensors_t* t, void* wor
   ProfScope ps(DCP_K_DKV, s, may_alloc);
   if (form.dkv == kRows) return scalar_bwd_dkv(gkv, k, t->dtype, s);
   if (form.dkv == kShared) {
-    if (in_parts(t)) k.part_groups = part_groups(plan, t, 2);
+    if (in_parts(t)) k.part_groups = f32_groups(f32_choice(plan, t).kernel[2]);
     return mfma_bwd_dkv(gkv, k, s);
   }
   return t->dtype == DCP_F32 ? mfma_f32_dkv(gkv, k, 16, s) : mfma_split_dkv(gkv, k, waves_of(form.dkv), s);

@@ -4,6 +4,7 @@
 
 #include <cstdint>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <tuple>
@@ -104,6 +105,19 @@ struct LaunchSize {
   int64_t walk = 0, walk_part = 0, walk_total = 0;
 };
 
+// What the whole items of a launch walk, counted by workgroups of 16, 32, 64 and 128 rows (total[0] .. [3]): their rows, filled up, times
+// the rows of the other side that they walk, at least 32 for a table row that they see; the longest item as if it had 128 rows.  Rows with
+// per-token ranges count half the other block (dK/dV: three quarters).
+struct WalkSize {
+  int64_t longest = 0, total[4] = {0, 0, 0, 0};
+};
+
+// The kernels of fp32 calls with D < 128 (api.hip): forward, dQ, dK/dV, the faster in parts of each, and whether dQ and dK/dV are one launch.
+struct F32Choice {
+  int kernel[3], parts[3];
+  bool one_launch;
+};
+
 // Cost of an item in pairs, and rows of the other side that it walks, at least 32 for a table row.
 struct ItemCost {
   int64_t pairs = 0, walk = 0;
@@ -156,6 +170,8 @@ struct dcp_plan {
   static ItemKey item_key(int group_id, int heads, int n_seg) { return ItemKey(group_id, group_id == 2 ? heads : 0, n_seg); }
   std::map<ItemKey, dcp::HostItems> h_items;
   std::vector<dcp::ItemCost> item_cost[3];   // of every group's whole items, in unit order, once a list has been made
+  std::unique_ptr<dcp::WalkSize> walks[3];
+  std::map<std::tuple<int, int, int>, dcp::F32Choice> f32_choices;   // by hq, hkv, d
   std::map<ItemKey, dcp::DevItems> items;
 
   // may_alloc = false: fail (DCP_ERR_INVALID_ARG) instead of creating a device copy that does not exist yet
@@ -163,6 +179,8 @@ struct dcp_plan {
   // group id: 0 fwd, 1 bwdq, 2 bwdkv.  heads: for dK/dV see ItemKey; for the others the query heads per KV head, which
   // weigh the order of the list where the call creates it.  Host only; takes the plan's lock.
   const dcp::HostItems& host_items(int group_id, int heads, int n_seg);
+  // Counted at the first call, which takes the plan's lock; host only.
+  const dcp::WalkSize& walk_size(int group_id);
   // The list is on the device.
   bool has_items(int group_id, int heads, int n_seg);
   // Where the list is missing and must not be created (may_alloc false, or `stream` is being captured), a list of whole

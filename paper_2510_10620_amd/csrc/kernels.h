@@ -25,7 +25,7 @@ struct KTensors {
   float scale;
   int32_t use_slots;
   int32_t by_head;         // dK/dV, bf16 with D = 128, masked: the query heads are the outer loop (dcp_plan::kv_by_head)
-  int32_t part_groups;     // fp32 with D < 128, 32 rows a wave: 1 (four waves a workgroup) or 2 (eight)
+  int32_t part_groups;     // fp32, not 16 rows: 0 (32 rows a workgroup, fp32 pipe) or, with D < 128, in parts: 1 (four waves a workgroup) or 2 (eight)
 };
 
 #ifdef __HIPCC__
@@ -100,12 +100,12 @@ size_t mfma_dkv_part_bytes(int32_t n_pslots, int32_t hkv);   // size of KTensors
 dcp_status_t mfma_fwd(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_bwd_dq(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_bwd_dkv(const DevGroup& g, const KTensors& t, hipStream_t s);
-// fp32, 32 (D = 128) or 16 rows per workgroup; f32_bwd is dQ and dK/dV in one launch (16 rows)
+// fp32 on the fp32 pipe, 32 or 16 rows per workgroup; f32_bwd is dQ and dK/dV in one launch (16 rows)
 dcp_status_t mfma_f32_fwd(const DevGroup& g, const KTensors& t, int rows, hipStream_t s);
 dcp_status_t mfma_f32_dq(const DevGroup& g, const KTensors& t, int rows, hipStream_t s);
 dcp_status_t mfma_f32_dkv(const DevGroup& g, const KTensors& t, int rows, hipStream_t s);
 dcp_status_t mfma_f32_bwd(const DevGroup& gq, const DevGroup& gkv, const KTensors& t, hipStream_t s);
-// the part of mfma_fwd, mfma_bwd_dq and mfma_bwd_dkv for fp32 with D < 128
+// the part of mfma_fwd, mfma_bwd_dq and mfma_bwd_dkv for fp32 with D < 128 in bf16 parts
 dcp_status_t mfma_f32_parts_fwd(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_f32_parts_dq(const DevGroup& g, const KTensors& t, hipStream_t s);
 dcp_status_t mfma_f32_parts_dkv(const DevGroup& g, const KTensors& t, hipStream_t s);

@@ -209,7 +209,7 @@ __global__ __launch_bounds__(256, 2) void mfma_dq_kernel(DevGroup g, KTensors t)
 
 dcp_status_t mfma_bwd_dq(const DevGroup& g, const KTensors& t, hipStream_t s) {
   if (g.n_items == 0) return DCP_OK;
-  if (t.dtype == DCP_F32) return t.d < 128 ? mfma_f32_parts_dq(g, t, s) : mfma_f32_dq(g, t, 32, s);
+  if (t.dtype == DCP_F32) return t.part_groups ? mfma_f32_parts_dq(g, t, s) : mfma_f32_dq(g, t, 32, s);
   if (t.d != kD) return mfma_narrow_dq(g, t, s);
   const int grid = xcd_grid(g, t.hkv, t.hq / t.hkv);
   if (t.masked) hipLaunchKernelGGL(mfma_dq_kernel<true>, dim3(grid), dim3(256), 0, s, g, t);

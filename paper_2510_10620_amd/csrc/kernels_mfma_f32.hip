@@ -6,7 +6,8 @@
 // independently.  That freedom is used to split the contraction inside the workgroup: its eight waves own the SAME 32 or 16
 // rows (kept in LDS, operand B) and take every eighth 32-row tile of the other side, and their partial results meet
 // once, in LDS, at the end -- a small batch has eight times the parallel work it would have with a wave per 32 rows.
-// With D = 32 and 64 full launches go to kernels_mfma_f32_parts.hip, which has 32 rows of its own; 32 rows here are for D = 128.
+// With D = 32 and 64 full launches go to kernels_mfma_f32_parts.hip; 32 rows here are for D = 128, and for the forward and dQ of few long walks
+// (3 950 tokens in one sequence, 4/2 heads, D 64: 95 and 131 us, in parts 167 and 233, 16 rows 100 and 154).
 // 16 rows (16 x 16 x 4 MFMAs, the same rate) serve launches that leave most of the chip idle or wait for their longest item: a
 // small batch is a few dozen workgroups whose CUs' matrix pipes are what its time is made of, and half the rows are twice the
 // workgroups (512 tokens, one head, D 64: forward / dQ / dK/dV 12.7 / 16.5 / 21.9 -> 8.9 / 11.6 / 14.5 us; 8 192, 8/2 heads 358 / 503 / 804
@@ -645,48 +646,42 @@ __global__ __launch_bounds__(kThreads, 2) void f32_bwd_kernel(DevGroup gq, DevGr
   else f32_dq<D, R, RANGES, true>(gq, t, slabs, blockIdx.x - n_dkv);
 }
 
-#define DCP_F32_LAUNCH(KERNEL, GRID, ...)                                                                                  \
+#define DCP_F32_LAUNCH(KERNEL, R, GRID, ...)                                                                               \
   {                                                                                                                       \
     const dim3 grid(GRID), block(kThreads);                                                                               \
     if (t.masked) {                                                                                                       \
-      if (t.d == 32) hipLaunchKernelGGL((KERNEL<32, 16, true>), grid, block, 0, s, __VA_ARGS__);                          \
-      else if (t.d == 64) hipLaunchKernelGGL((KERNEL<64, 16, true>), grid, block, 0, s, __VA_ARGS__);                     \
-      else hipLaunchKernelGGL((KERNEL<128, 16, true>), grid, block, 0, s, __VA_ARGS__);                                   \
+      if (t.d == 32) hipLaunchKernelGGL((KERNEL<32, R, true>), grid, block, 0, s, __VA_ARGS__);                           \
+      else if (t.d == 64) hipLaunchKernelGGL((KERNEL<64, R, true>), grid, block, 0, s, __VA_ARGS__);                      \
+      else hipLaunchKernelGGL((KERNEL<128, R, true>), grid, block, 0, s, __VA_ARGS__);                                    \
     } else {                                                                                                              \
-      if (t.d == 32) hipLaunchKernelGGL((KERNEL<32, 16, false>), grid, block, 0, s, __VA_ARGS__);                         \
-      else if (t.d == 64) hipLaunchKernelGGL((KERNEL<64, 16, false>), grid, block, 0, s, __VA_ARGS__);                    \
-      else hipLaunchKernelGGL((KERNEL<128, 16, false>), grid, block, 0, s, __VA_ARGS__);                                  \
+      if (t.d == 32) hipLaunchKernelGGL((KERNEL<32, R, false>), grid, block, 0, s, __VA_ARGS__);                          \
+      else if (t.d == 64) hipLaunchKernelGGL((KERNEL<64, R, false>), grid, block, 0, s, __VA_ARGS__);                     \
+      else hipLaunchKernelGGL((KERNEL<128, R, false>), grid, block, 0, s, __VA_ARGS__);                                   \
     }                                                                                                                     \
   }
-#define DCP_F32_LAUNCH32(KERNEL, GRID, ...)                                                                                \
-  {                                                                                                                       \
-    const dim3 grid(GRID), block(kThreads);                                                                               \
-    if (t.masked) hipLaunchKernelGGL((KERNEL<128, 32, true>), grid, block, 0, s, __VA_ARGS__);                            \
-    else hipLaunchKernelGGL((KERNEL<128, 32, false>), grid, block, 0, s, __VA_ARGS__);                                    \
-  }
 
-// rows: 16, or (D = 128) 32
 dcp_status_t mfma_f32_fwd(const DevGroup& g, const KTensors& t, int rows, hipStream_t s) {
   if (g.n_items == 0) return DCP_OK;
   const int64_t n = xcd_grid(g, t.hkv, t.hq / t.hkv * (kItemRows / rows));
-  if (rows == 16) DCP_F32_LAUNCH(f32_fwd_kernel, n, g, t)
-  else DCP_F32_LAUNCH32(f32_fwd_kernel, n, g, t)
+  if (rows == 16) DCP_F32_LAUNCH(f32_fwd_kernel, 16, n, g, t)
+  else DCP_F32_LAUNCH(f32_fwd_kernel, 32, n, g, t)
   DCP_HIP_TRY(hipGetLastError());
   return DCP_OK;
 }
 dcp_status_t mfma_f32_dq(const DevGroup& g, const KTensors& t, int rows, hipStream_t s) {
   if (g.n_items == 0) return DCP_OK;
   const int64_t n = xcd_grid(g, t.hkv, t.hq / t.hkv * (kItemRows / rows));
-  if (rows == 16) DCP_F32_LAUNCH(f32_dq_kernel, n, g, t)
-  else DCP_F32_LAUNCH32(f32_dq_kernel, n, g, t)
+  if (rows == 16) DCP_F32_LAUNCH(f32_dq_kernel, 16, n, g, t)
+  else DCP_F32_LAUNCH(f32_dq_kernel, 32, n, g, t)
   DCP_HIP_TRY(hipGetLastError());
   return DCP_OK;
 }
 dcp_status_t mfma_f32_dkv(const DevGroup& g, const KTensors& t, int rows, hipStream_t s) {
   if (g.n_items == 0) return DCP_OK;
   const int64_t n = xcd_grid(g, t.hkv, kItemRows / rows);
-  if (rows == 16) DCP_F32_LAUNCH(f32_dkv_kernel, n, g, t)
-  else DCP_F32_LAUNCH32(f32_dkv_kernel, n, g, t)
+  if (rows == 16) DCP_F32_LAUNCH(f32_dkv_kernel, 16, n, g, t)
+  else if (t.masked) hipLaunchKernelGGL((f32_dkv_kernel<128, 32, true>), dim3(n), dim3(kThreads), 0, s, g, t);   // D = 128 alone
+  else hipLaunchKernelGGL((f32_dkv_kernel<128, 32, false>), dim3(n), dim3(kThreads), 0, s, g, t);
   DCP_HIP_TRY(hipGetLastError());
   return DCP_OK;
 }
@@ -694,7 +689,7 @@ dcp_status_t mfma_f32_dkv(const DevGroup& g, const KTensors& t, int rows, hipStr
 dcp_status_t mfma_f32_bwd(const DevGroup& gq, const DevGroup& gkv, const KTensors& t, hipStream_t s) {
   if (gq.n_items + gkv.n_items == 0) return DCP_OK;
   const int64_t n_dkv = xcd_grid(gkv, t.hkv, kItemRows / 16), n = n_dkv + xcd_grid(gq, t.hkv, t.hq / t.hkv * (kItemRows / 16));
-  DCP_F32_LAUNCH(f32_bwd_kernel, n, gq, gkv, t, (int)n_dkv)
+  DCP_F32_LAUNCH(f32_bwd_kernel, 16, n, gq, gkv, t, (int)n_dkv)
   DCP_HIP_TRY(hipGetLastError());
   return DCP_OK;
 }

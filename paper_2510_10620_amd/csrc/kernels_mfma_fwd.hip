@@ -380,7 +380,7 @@ bool mfma_supports(int32_t dtype, int32_t d) { return (dtype == DCP_BF16 || dtyp
 
 dcp_status_t mfma_fwd(const DevGroup& g, const KTensors& t, hipStream_t s) {
   if (g.n_items == 0) return DCP_OK;
-  if (t.dtype == DCP_F32) return t.d < 128 ? mfma_f32_parts_fwd(g, t, s) : mfma_f32_fwd(g, t, 32, s);
+  if (t.dtype == DCP_F32) return t.part_groups ? mfma_f32_parts_fwd(g, t, s) : mfma_f32_fwd(g, t, 32, s);
   if (t.d != kD) return mfma_narrow_fwd(g, t, s);
   const int grid = xcd_grid(g, t.hkv, t.hq / t.hkv);
   if (t.masked) hipLaunchKernelGGL((mfma_fwd_kernel<1, true>), dim3(grid), dim3(64 * kFwdWaves), 0, s, g, t);

@@ -450,6 +450,8 @@ extern "C" dcp_status_t dcp_plan_set_block_buffers(dcp_plan_t* plan, const int32
   plan->buffers = true;
   plan->h_items.clear();   // work lists leave out absent blocks
   for (auto& c : plan->item_cost) c.clear();
+  for (auto& w : plan->walks) w.reset();
+  plan->f32_choices.clear();
   plan->q_slot.assign(q_slot, q_slot + plan->n_blocks);
   plan->kv_slot.assign(kv_slot, kv_slot + plan->n_blocks);
   for (int32_t b = 0; b < plan->n_blocks; b++) {
@@ -623,6 +625,34 @@ static int64_t tile_cost(int32_t kind, int64_t r0, int64_t r1, int64_t c0, int64
     return n;
   }
   return (r1 - r0) * (c1 - c0) / 2;  // RANGES: unknown without the arrays; half is the estimate
+}
+
+const WalkSize& dcp_plan::walk_size(int gid) {
+  std::lock_guard<std::mutex> lock(mu);
+  if (walks[gid]) return *walks[gid];
+  const HostGroup& g = gid == 0 ? fwd : (gid == 1 ? bwdq : bwdkv);
+  std::unique_ptr<WalkSize> z(new WalkSize);
+  for (size_t u = 0; u < g.unit_blk.size(); u++) {
+    const int32_t b = g.unit_blk[u];
+    if (b < 0 || (buffers && (gid == 2 ? kv_slot : q_slot)[b] < 0)) continue;
+    for (int64_t r0 = blk_start[b], end = r0 + blk_len[b]; r0 < end; r0 += kItemRows) {
+      const int64_t rows = std::min<int64_t>(kItemRows, end - r0);
+      int64_t walk = 0;
+      for (int32_t e = g.ptr[u]; e < g.ptr[u + 1]; e++) {
+        const int32_t kind = g.ent_kind[e], len = g.ent_len[e];
+        if (kind == DCP_MASK_NONE || kind == DCP_MASK_CAUSAL) {
+          const int64_t pairs = tile_cost(kind, r0, r0 + rows, g.ent_start[e], g.ent_start[e] + len, gid == 2);
+          if (pairs > 0) walk += std::max<int64_t>(32, pairs / rows);
+        } else {
+          walk += std::max(32, gid == 2 ? len / 4 * 3 : len / 2);
+        }
+      }
+      z->longest = std::max(z->longest, kItemRows * walk);
+      for (int k = 0; k < 4; k++) z->total[k] += (rows + (16 << k) - 1) / (16 << k) * (16 << k) * walk;
+    }
+  }
+  walks[gid] = std::move(z);
+  return *walks[gid];
 }
 
 // Workgroups the chip holds at once in the kernels that split their items (2 per CU, 256 CUs).

@@ -107,3 +107,17 @@ def test_lse_of_repaired_rows(case):
     for _ in range(4):
         for a, b, n in zip(fast.forward(), (out, lse), ("out", "lse")):
             _same(a, b, w, n)
+
+
+@pytest.mark.parametrize("d,mask,lens,B,heads", [(32, "causal", [1500], 64, (6, 3)), (32, "lambda", [1030, 7], 1024, (8, 8)), (64, "causal", [2050, 33], 64, (4, 4)),
+                                                 (64, "lambda", [2050, 33], 1024, (6, 3))], ids=["D32-causal", "D32-ranges", "D64-causal", "D64-ranges"])
+def test_dkv_in_parts_behind_32_rows_on_the_fp32_pipe(d, mask, lens, B, heads):
+    """Few long walks: forward and dQ by 32 rows a workgroup on the fp32 pipe, which leaves delta and lse2 for dK/dV in parts."""
+    w = W.custom_workload("pipe", lens, B, heads[0], heads[1], d, "f32", SPECS[mask], seed=99, input_scale=0.5)
+    tensors, table = W.make_tensors(w), H.oracle_table(w)
+    g = H.GpuRun(w, tensors, table)
+    assert set(P.dcp_plan_export_forms(g.plan, *heads, d, P.DCP_F32).values()) == {P.DCP_FORM_SHARED}
+    groups = P.dcp_plan_export_part_groups(g.plan, *heads, d)
+    assert groups[:2] == (0, 0) and groups[2] > 0
+    got = dict(zip(NAMES, g.forward() + g.backward()))
+    H.check(w, got, H.oracle_full(w, tensors, table), NAMES, f"D{d} {mask}")

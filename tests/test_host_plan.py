@@ -293,6 +293,26 @@ def test_forms_of_small_and_large_batches(dtype, d):
         forms([300], 128, 3, 2)
 
 
+def test_fp32_kernels_of_few_long_walks_and_short_blocks():
+    """fp32, D 64 and 32: batches whose forward and dQ the kernels in bf16 parts work on longer than those on the fp32 pipe (measured, us, in
+    parts / 32 rows / 16 rows): the visible pairs of an item do not show that its workgroup of 128 rows walks them alone."""
+    def kernels(lens, B, hq, hkv, d, spec=W.MaskSpec("causal")):
+        cu = W.cu_from_lengths(lens)
+        plan = P.dcp_plan_create(cu, B, P.dcp_build_block_table(cu, B, W.attn_ranges(spec, cu)))
+        f, g = P.dcp_plan_export_forms(plan, hq, hkv, d, P.DCP_F32), P.dcp_plan_export_part_groups(plan, hq, hkv, d)
+        return ["16" if f[n] == P.DCP_FORM_SPLIT else g[i] for i, n in enumerate(("fwd", "dq", "dkv"))]
+    blockwise = W.MaskSpec("causal_blockwise", window=2, sink=1)
+    pipe = (0, "16")
+    assert all(k in pipe for k in kernels([3950], 1024, 4, 2, 64)[:2])              # 167 / 95 / 100, dQ 233 / 131 / 154
+    assert all(k in pipe for k in kernels([4407], 64, 2, 1, 64)[:2])                # 191 / 107 / 81, dQ 253 / 145 / 130
+    assert all(k in pipe for k in kernels([1021], 64, 8, 8, 64)[:2])                # 50 / - / 25, dQ 66 / 41 / -
+    assert all(k in pipe for k in kernels([9839], 1024, 4, 4, 64, blockwise)[:2])   # 444 / 181 / 136, dQ 575 / 251 / 216
+    assert kernels([8841], 2048, 2, 1, 32, blockwise)[0] in pipe                    # 208 / 115 / 93
+    # full launches stay in parts (16 384 tokens, 16/4 heads, forward 362 / 570 / -)
+    assert kernels([2048] * 8, 512, 16, 4, 64) == [1, 1, 1]
+    assert all(k in (1, 2) for k in kernels([5582, 1000, 700, 500, 410], 512, 8, 2, 64))
+
+
 def test_forms_of_short_blocks():
     """bf16, D 128, blocks of up to 64 rows: a workgroup of 32 rows walks such a block's table rows as long as a block of 128's, so that long
     walks stay with the shared tiles, whose items are cut (measured, backward, shared tiles and split dK/dV: 177 and 329 us, 451 and
