@@ -1,6 +1,6 @@
 """The fp32 kernels that multiply in bf16 parts (D 32 and 64): one group of waves and several, odd head groups, ragged and one-token
-sequences, against the fp64 oracle; values of every size, whose last bits are in the third part; an Inf in K, which leaves NaN in the parts
-of a score that is -Inf."""
+sequences, against the fp64 oracle; values of every size, whose last bits are in the third part; Inf and NaN, which have no parts; block
+buffers, partial slots, strides, gradients over the inputs and rows that are off."""
 import numpy as np
 import pytest
 
@@ -121,3 +121,150 @@ def test_dkv_in_parts_behind_32_rows_on_the_fp32_pipe(d, mask, lens, B, heads):
     assert groups[:2] == (0, 0) and groups[2] > 0
     got = dict(zip(NAMES, g.forward() + g.backward()))
     H.check(w, got, H.oracle_full(w, tensors, table), NAMES, f"D{d} {mask}")
+
+
+LAYOUTS = [CASES[0], CASES[2], CASES[4], CASES[6]]   # D 32 and 64, one group of waves and several
+
+
+def _in_parts(plan, case, dkv=True):
+    d, _, _, heads, _ = case
+    forms, groups = P.dcp_plan_export_forms(plan, *heads, d, P.DCP_F32), P.dcp_plan_export_part_groups(plan, *heads, d)
+    return all(forms[n] == P.DCP_FORM_SHARED and g > 0 for n, g in zip(("fwd", "dq", "dkv") if dkv else ("fwd", "dq"), groups)) and forms["bwd"] == P.DCP_FORM_SHARED
+
+
+@pytest.mark.parametrize("slots", [False, True], ids=["whole", "slots"])
+@pytest.mark.parametrize("case", LAYOUTS, ids=lambda c: f"D{c[0]}-g{c[4]}")
+def test_block_buffers(case, slots):
+    """Permuted blocks with free ones between them; with slots, each query block in up to three partial results and their merge."""
+    from tests.test_gpu_parity import _buffer_case
+    d, lens, B, heads, _ = case
+    w = W.custom_workload("buffers", lens, B, *heads, d, "f32", SPECS["lambda"], seed=100, input_scale=0.5)
+    table = H.oracle_table(w)
+    slot, n_slots = W.deal_divisions(table[:, 0], 3, 5)[:2] if slots else (None, 0)
+    assert _in_parts(P.dcp_plan_create(w.cu_seqlens, B, table, slot, n_slots), case)
+    _buffer_case(w, table, 0, np.random.default_rng(11), out_slot=slot, n_slots=n_slots)
+
+
+@pytest.mark.parametrize("case", LAYOUTS, ids=lambda c: f"D{c[0]}-g{c[4]}")
+def test_strides_and_gradients_over_the_inputs(case):
+    """Inputs as views of one projection, outputs in padded rows; then dQ over O, dK over K and dV over V: the same bits."""
+    import torch
+    d, lens, B, (hq, hkv), _ = case
+    w, tensors, table, g = _run(case, "causal")
+    ref = H.oracle_full(w, tensors, table)
+    fused = torch.cat([g.q, g.k, g.v], dim=1).contiguous()
+    q, k, v = fused[:, :hq], fused[:, hq:hq + hkv], fused[:, hq + hkv:]
+    pad = lambda h: torch.full((w.total_tokens, h + 1, d + 8), float("nan"), device="cuda")
+    full = [pad(h) for h in (hq, hq, hq, hkv, hkv)]
+    do, out, dq, dk, dv = (x[:, :-1, :d] for x in full)
+    do.copy_(g.dout)
+    lse = torch.empty((hq, w.total_tokens), device="cuda")
+    ws = torch.empty(max(256, P.dcp_bwd_workspace_bytes(g.plan, hq, hkv, d, P.DCP_F32)), dtype=torch.uint8, device="cuda")
+    P.dcp_block_attn_fwd(g.plan, q, k, v, out, lse, w.softmax_scale)
+    P.dcp_block_attn_bwd(g.plan, q, k, v, out, lse, do, dq, dk, dv, w.softmax_scale, ws)
+    torch.cuda.synchronize()
+    got = dict(zip(NAMES, (H.from_torch(x.contiguous()) for x in (out, lse, dq, dk, dv))))
+    H.check(w, got, ref, NAMES, "strided")
+    for x in full[1:]:
+        assert torch.isnan(x[:, -1]).all() and torch.isnan(x[:, :, d:]).all(), "a row's padding was written"
+    want = [x.contiguous() for x in (dq, dk, dv)]
+    P.dcp_block_attn_bwd(g.plan, q, k, v, out, lse, do, out, k, v, w.softmax_scale, ws)
+    torch.cuda.synchronize()
+    for a, b, n in zip((out, k, v), want, NAMES[2:]):
+        assert torch.equal(a, b), n
+
+
+@pytest.mark.parametrize("mask", list(SPECS))
+@pytest.mark.parametrize("case", LAYOUTS, ids=lambda c: f"D{c[0]}-g{c[4]}")
+def test_rows_switched_off_by_their_lse(case, mask):
+    """Query rows whose LSE is -inf or NaN contribute nothing: the gradients are those of dO = 0 in these rows, to the bit."""
+    w, _, _, g = _run(case, mask)
+    g.forward_only()
+    off = [0, 31, 32, 160, 161, 500, 1285]
+    lse, dout = g.lse, g.dout
+    lse_off = lse.clone()
+    lse_off[:, off[:-2]] = float("-inf")
+    lse_off[1, off[-2:]] = float("nan")
+    g.dout = dout.clone()
+    g.dout[off[:-2]] = 0
+    g.dout[off[-2:], 1] = 0
+    want = g.backward(lse=lse)
+    g.dout = dout
+    for name, a, b in zip(NAMES[2:], g.backward(lse=lse_off), want):
+        assert (a == b).all(), name
+
+
+@pytest.mark.parametrize("mask", list(SPECS))
+@pytest.mark.parametrize("case", LAYOUTS, ids=lambda c: f"D{c[0]}-g{c[4]}")
+def test_inf_and_nan_reach_visible_pairs_only(case, mask):
+    """Forward and backward against the thread-per-row kernels, one tensor at a time, with what test_gpu_nonfinite.py plants."""
+    import torch
+    from tests.test_gpu_nonfinite import PLANT, _same
+    w, tensors, table, _ = _run(case, mask)
+    for name, plants in PLANT.items():
+        fast, slow = H.GpuRun(w, tensors, table), H.GpuRun(w, tensors, table, impl=P.DCP_IMPL_SCALAR)
+
+        def plant(x):
+            for tok, head, col, value in plants:
+                x[tok, head, slice(None) if col is None else col] = float(value)
+        if name != "out":
+            for g in (fast, slow):
+                plant(getattr(g, name))
+        for a, b, n in zip(fast.forward(), slow.forward(), ("out", "lse")):
+            _same(a, b, w, f"{name} planted, {n}")
+        out, lse = slow.out.clone(), slow.lse.clone()
+        if name == "out":
+            plant(out)
+        lse[~torch.isfinite(lse)] = 1.0
+        for a, b, n in zip(fast.backward(out, lse), slow.backward(out, lse), NAMES[2:]):
+            _same(a, b, w, f"{name} planted, {n}")
+
+
+@pytest.mark.parametrize("case", [CASES[0], CASES[4]], ids=lambda c: f"D{c[0]}-g{c[4]}")
+def test_static_workspace(case):
+    """dcp_block_attn_bwd_static: the same bits."""
+    import torch
+    w, _, _, g = _run(case, "lambda")
+    P.dcp_plan_prepare(g.plan, w.hq, w.hkv, w.d, P.DCP_F32)
+    g.forward_only()
+    g.backward_only(g.out, g.lse)
+    got = [torch.full_like(x, float("nan")) for x in (g.dq, g.dk, g.dv)]
+    P.dcp_block_attn_bwd_static(g.plan, g.q, g.k, g.v, g.out, g.lse, g.dout, *got, w.softmax_scale, g.ranges)
+    torch.cuda.synchronize()
+    for a, b, n in zip(got, (g.dq, g.dk, g.dv), NAMES[2:]):
+        assert torch.equal(a, b), n
+
+
+@pytest.mark.parametrize("d", [32, 64])
+def test_ranges_past_four_gigabytes(d):
+    """The last sequence of a batch of more than 2^28 packed tokens, whose blocks are in block buffers, gives the bits of the same sequence by
+    itself: byte offsets into the range array pass 2^32 there."""
+    import torch
+    B, far, n, (hq, hkv) = 2048, 1 << 28, 1500, (16, 4)
+    case = (d, [n], B, (hq, hkv), 0)
+    w = W.custom_workload("near", [n], B, hq, hkv, d, "f32", SPECS["lambda"], seed=101, input_scale=0.5)
+    g = H.GpuRun(w, W.make_tensors(w), np.array([[0, 0, W.MASK_RANGES]], np.int32))
+    assert _in_parts(g.plan, case)
+    g.forward_only()
+    g.backward_only(g.out, g.lse)
+    nb = far // B + 1
+    plan = P.dcp_plan_create(np.array([0, far, far + n], np.int32), B, np.array([[nb - 1, nb - 1, W.MASK_RANGES]], np.int32))
+    slot = np.full(nb, -1, np.int32)
+    slot[-1] = 0
+    P.dcp_plan_set_block_buffers(plan, slot, 1, slot, 1)
+    assert _in_parts(plan, case)
+    ranges = torch.zeros((far + n, 4), dtype=torch.int32, device="cuda")
+    near = torch.from_numpy(w.ranges).cuda()
+    for c in (0, 2):
+        near[near[:, c + 1] > near[:, c], c:c + 2] += far
+    ranges[far:] = near
+    rows = lambda x: torch.cat([x, torch.zeros((B - n,) + tuple(x.shape[1:]), device="cuda")])
+    q, k, v, do = (rows(x) for x in (g.q, g.k, g.v, g.dout))
+    out, dq, dk, dv = (torch.zeros_like(x) for x in (q, q, k, v))
+    lse = torch.zeros((hq, B), device="cuda")
+    P.dcp_block_attn_fwd(plan, q, k, v, out, lse, w.softmax_scale, ranges)
+    ws = torch.empty(P.dcp_bwd_workspace_bytes(plan, hq, hkv, d, P.DCP_F32), dtype=torch.uint8, device="cuda")
+    P.dcp_block_attn_bwd(plan, q, k, v, out, lse, do, dq, dk, dv, w.softmax_scale, ws, ranges)
+    torch.cuda.synchronize()
+    for name, a, b in zip(NAMES, (out[:n], lse[:, :n], dq[:n], dk[:n], dv[:n]), (g.out, g.lse, g.dq, g.dk, g.dv)):
+        assert torch.equal(a, b), name
