@@ -10,8 +10,8 @@
 // (3 950 tokens in one sequence, 4/2 heads, D 64: 95 and 131 us, in parts 167 and 233, 16 rows 100 and 154).
 // 16 rows (16 x 16 x 4 MFMAs, the same rate) serve launches that leave most of the chip idle or wait for their longest item: a
 // small batch is a few dozen workgroups whose CUs' matrix pipes are what its time is made of, and half the rows are twice the
-// workgroups (512 tokens, one head, D 64: forward / dQ / dK/dV 12.7 / 16.5 / 21.9 -> 8.9 / 11.6 / 14.5 us; 8 192, 8/2 heads 358 / 503 / 804
-// -> 377 / 608 / 748: twice the streamed bytes a product), and their backward is one launch where both halves fit the chip (26.1 ->
+// workgroups (512 tokens, one head, D 64: forward / dQ / dK/dV 12.7 / 16.5 / 21.9 -> 8.9 / 11.6 / 14.5 us; 8 192, 8/2 heads, where the parts are
+// faster than both, 358 / 503 / 804 -> 377 / 608 / 748: twice the streamed bytes a product), and their backward is one launch where both halves fit the chip (26.1 ->
 // 16.9; the dK/dV workgroups work delta out for themselves, from O).
 // Streamed operands come in chunks of at most 32 registers (16 with 16 rows: four waves on a SIMD then), the next one on its way
 // under the MFMAs of the current, so that two waves fit on a SIMD at every D.  Operand layouts: Fp below;

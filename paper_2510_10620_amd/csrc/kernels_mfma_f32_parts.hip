@@ -21,7 +21,8 @@
 // halves of a step fall beside one another); elsewhere it is two groups of four waves (D 64) or four of two (D 32) that take the tiles in
 // turn, half a step apart, and meet at the end.  16 384 tokens in 8 sequences, 16/4 heads, D 64, one group / two: forward 362 / 401 us, dQ 490 /
 // 587; 8 192 tokens of which 5 582 in one sequence, 8/2 heads: 303 / 227, 380 / 324.
-// Against fp32 MFMA with 32 rows a workgroup, the last batch: forward / dQ / dK/dV 357 / 500 / 723 (16 rows) -> 227 / 324 / 466 us.
+// Against fp32 MFMA with 32 rows a workgroup, the last batch: forward / dQ / dK/dV 357 / 500 / 723 (16 rows) -> 227 / 324 / 466 us, and 1 to 3 %
+// more with the factors of kUp below.
 #include "mfma_dkv_kernel.h"
 #include "query_rows.h"
 #include "split_rows.h"
@@ -35,7 +36,7 @@ namespace {
 // linear in are cut times 2^16 (V in the forward; K, V and dO in dQ; Q, dO and V in dK/dV, and dS is 2^32 times itself through dP), and the
 // sums are put right before they are stored.  What overflows for it, operands of 2^112 and gradients of 2^80, is not finite in the parts and
 // worked out again.  64 more multiplications a tile in dK/dV (96 values are cut), 8 and 16 in the others: 8 192 tokens, 8/2 heads, forward / dQ /
-// dK/dV 234 / 331 / 475 -> 236 / 332 / 489 us.  Not so P, and Q and K in the forward's scores: their last bits, at 2^-134, count in a weight
+// dK/dV 237 / 336 / 484 -> 240 / 337 / 496 us.  Not so P, and Q and K in the forward's scores: their last bits, at 2^-134, count in a weight
 // below 2^-117 (which has lost as many to the rounding of its exponent, and is 0 below 2^-126) and in a score against a factor beyond 2^108.
 constexpr float kUp = 0x1p16f, kDown = 0x1p-16f;
 constexpr float kLn2P = 0.69314718055994530942f;
@@ -503,7 +504,8 @@ __global__ __launch_bounds__(64 * RG * NG, 2) void f32p_dq_kernel(DevGroup g, KT
 // are an A operand as they come from memory: a wave cuts them in registers, multiplies them from there, and puts them into LDS of its own
 // for the transposed reads alone, dO first and Q after it into the same place, so that the loop has no barrier.  The keys' parts are in
 // LDS for all waves.  What is live then fits 256 registers: the sums (64), the parts of one operand (48), the next tile's rows as they come
-// (32, 64 during the last products) and one score tile or its parts; the two fences keep the compiler from holding more.  A wave that
+// (32, 64 during the last products) and one score tile or its parts; the two fences keep the compiler from holding more (with D 64 one
+// register is spilled, three under ranges).  A wave that
 // multiplies goes before one that cuts, or both would cut and then both multiply.  8 192 tokens of which 5 582 in one sequence, 8/2 heads,
 // D 64 (the longest chain decides) and 16 384 in 8 equal ones, 16/4 heads: four waves that hold their keys' parts, one on a SIMD, 543 and
 // 914 us; four that read them from LDS, two on a SIMD, 659 and 816; eight 507 and 862, with priorities 483 and 844, with two fences of
