@@ -194,8 +194,8 @@ static int least_form(double sure, double sure8, const dcp_tensors_t* t, const d
 }
 
 // fp32 with D < 128 has four kernels for the forward and for dQ: on the fp32 pipe with 32 rows a workgroup or 16, in bf16 parts
-// with one group of waves or several; dK/dV has 16 rows, and parts with four waves or eight (with 32 rows it was never the best).  By pairs two of them come into question: the faster of those in parts
-// and 16 rows (kFits: kFull, kShared, kSplit), or what the choice between 32 and 16 rows would be without parts (kPipeFits).  Where the
+// with one group of waves or several; dK/dV has 16 rows, and parts with four waves or eight (with 32 rows it was never the best).
+// By pairs two of them come into question: the faster of those in parts and 16 rows (kFits: kFull, kShared, kSplit), or what the choice between 32 and 16 rows would be without parts (kPipeFits).  Where the
 // second is estimated at 0.9 of the first or less by what the workgroups walk (WalkSize, kWalkFits), it is taken.  Pairs alone
 // misjudge few long walks and short blocks, where workgroups of 128 rows in parts walk far longer than the pairs say: 4 407 tokens, 2/1
 // heads of 64, blocks of 64, forward / dQ 191 / 253 us in parts, 107 / 145 and 81 / 130 on the fp32 pipe; 9 839 tokens under mask blocks of
@@ -432,6 +432,7 @@ extern "C" dcp_status_t dcp_plan_prepare(dcp_plan_t* plan, int32_t hq, int32_t h
   const int n_seg = xcd_segments(hkv);
   if ((st = plan->group_for(0, s, &g, hq / hkv, n_seg)) != DCP_OK) return st;
   if ((st = plan->group_for(1, s, &g, hq / hkv, n_seg)) != DCP_OK) return st;
+  if (use_mfma && in_parts(&t)) (void)f32_choice(plan, &t);
   return plan->group_for(2, s, &g, dkv_heads(plan, &t, use_mfma, n_seg, true), n_seg);
 }
 
